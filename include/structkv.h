@@ -45,7 +45,7 @@ enum { STRUCTKV_DTYPE_F32 = 0, STRUCTKV_DTYPE_BF16 = 1 };
 typedef struct {
   int32_t n_q_heads;  /* H_q >= 1 */
   int32_t n_kv_heads; /* G >= 1, divides H_q */
-  int32_t head_dim;   /* d: 1..256; the bf16 MFMA path needs d in {64,128}, other shapes take a SIMT path */
+  int32_t head_dim;   /* d: 1..256; the bf16 MFMA path needs d in {64,128}, other shapes take an fp32 matrix path */
   int32_t window;     /* w >= 1 */
   int32_t dtype;      /* STRUCTKV_DTYPE_F32 or STRUCTKV_DTYPE_BF16: element type of q_win and k */
   int32_t causal;     /* 0 (Eq. 1 as written): each window query sees all n keys;

@@ -16,7 +16,7 @@ extern "C" {
  * The attention rows themselves (paper Eq. 1) for ONE sequence of n tokens, probs_out [H_q][w][n] fp32,
  * computed by the same kernels as structkv_score_layer.  H_q*w*n must not exceed 2^26.
  * workspace: structkv_workspace_bytes(shape, 1, n) + 4 n + 512 bytes.
- * force_simt != 0 takes the SIMT kernels even where the bf16 MFMA kernels apply.
+ * force_simt != 0 takes the fp32 matrix kernels even where the bf16 ones apply.
  */
 structkv_status structkv_debug_probs(const structkv_shape* shape, const void* q_win, const void* k,
                                      int64_t k_stride_head, int64_t k_stride_tok, int64_t n,

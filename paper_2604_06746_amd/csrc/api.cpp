@@ -63,6 +63,7 @@ structkv_status check_cu(int32_t batch, const int64_t* cu, SeqTable* seq) {
 void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t total, bool mfma_ok,
                ScorePlan* p, bool planes = false) {
   const int gs = s.n_q_heads / s.n_kv_heads;
+  int64_t chunk_bound = total / 256;   // bf16 kernels: KC is at least 256
   p->R = gs * s.window;
   p->kshare = 1;
   p->path = mfma_ok ? 0 : 1;
@@ -107,16 +108,25 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     p->KC = (int)kc;
     p->CP = p->planes ? p->RC * p->planes : (int)ceil_div(p->RC, p->NW);
   } else {
-    p->RPC = 16; p->RB = 0; p->NW = 0; p->WK = 1;
+    // fp32 matrix kernels: waves of 32 rows, four to a workgroup: NW row-chunks that take the same keys, 4/NW waves
+    // per row-chunk that take turns at its 32-key tiles
+    p->RPC = 32; p->RB = 1; p->WK = 1;
     p->RC = (int)ceil_div(p->R, p->RPC);
-    p->KC = 256;
-    p->CP = p->RC;
+    p->NW = p->RC > 2 ? 4 : p->RC;
+    p->CP = (int)ceil_div(p->RC, p->NW);
+    // keys per workgroup: one round of workgroups (256 CUs x 2), but at least one tile per wave, at most the 1024
+    // whose column sums the kernels hold in LDS
+    const int64_t chunks_per_round = ceil_div(512, (int64_t)s.n_kv_heads * p->CP);
+    const int64_t step = 32 * (4 / p->NW);
+    int64_t kc = ceil_div(ceil_div(total > 0 ? total : 1, chunks_per_round), step) * step;
+    p->KC = (int)(kc > 1024 ? 1024 : kc);
+    chunk_bound = chunks_per_round > total / 1024 ? chunks_per_round : total / 1024;
   }
   if (seq) {
     p->n_chunks = 0;
     for (int b = 0; b < batch; ++b) p->n_chunks += ceil_div(seq->cu[b + 1] - seq->cu[b], p->KC);
   } else {
-    p->n_chunks = total / 256 + batch;   // KC is at least 256 on either path
+    p->n_chunks = chunk_bound + batch;
   }
   p->grid_chunks = p->n_chunks;
   const size_t GRC = (size_t)s.n_kv_heads * p->RC;
@@ -149,7 +159,7 @@ struct ScoreOpts {
   float lambda = 0.f, inv_w = 0.f;
   float* groups = nullptr;     // per-KV-head in-degree [G][total]
   int kshare = 1;              // consecutive groups that read one K head (per-head scoring)
-  bool force_simt = false;     // test hook: SIMT kernels even where the MFMA kernels apply
+  bool force_simt = false;     // test hook: the fp32 kernels even where the bf16 ones apply
   bool cache_groups = false;   // measurement hook: score a batch in cache-sized groups of sequences
   bool flip_stream_k = false;  // test hook: the other cache policy for the K tiles than the size rule picks
   float* probs = nullptr;      // test hook: the attention rows themselves

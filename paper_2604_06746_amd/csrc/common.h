@@ -82,14 +82,14 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 
 // ---- scoring plan: how one structkv_score_layer call is cut into workgroups ----------------
 struct ScorePlan {
-  int path;          // 0 = bf16 MFMA kernels, 1 = SIMT kernels
+  int path;          // 0 = bf16 kernels, 1 = fp32 kernels (inputs widened)
   int R;             // query rows per KV head: (H_q/G) * w
   int RPC;           // rows per row-chunk (a workgroup's share of R)
   int RC;            // row-chunks per KV head
   int KC;            // keys per key-chunk (one workgroup)
   int WK;            // partial statistics written per (row-chunk, key-chunk)
-  int RB;            // MFMA path: 32-row blocks per wave (1, 2 or 4)
-  int NW;            // MFMA path: waves (row-chunks) per workgroup sharing the key tiles (1, 2 or 4)
+  int RB;            // 32-row blocks per wave (1 or 2)
+  int NW;            // waves (row-chunks) per workgroup sharing the key tiles (bf16: 1 or 4; fp32: 1, 2 or 4)
   int CP;            // pass-2 column-sum planes per KV head (the waves of a workgroup add theirs up first)
   int planes;        // MFMA path, pass 2: 0, or column-sum planes per WAVE (1: a wave's rows are one query head's
                      // window; 2: each of its two 32-row blocks is) instead of one per workgroup: CP = RC * planes =
