@@ -142,7 +142,6 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
 bool mfma_eligible(const structkv_shape& s, const void* q, const void* k, int64_t ksh, int64_t kst) {
   if (s.dtype != STRUCTKV_DTYPE_BF16) return false;
   if (s.head_dim != 64 && s.head_dim != 128) return false;
-  if (s.causal && (s.window % 32) != 0) return false;   // the MFMA kernels' causal masks assume whole 32-row blocks per head
   if ((((uintptr_t)q | (uintptr_t)k) & 15) != 0) return false;
   if ((ksh % 8) != 0 || (kst % 8) != 0) return false;
   return true;

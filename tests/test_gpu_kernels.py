@@ -60,3 +60,9 @@ def test_fp32_matrix_scoring_kernels(sweep_mod, oracle, Hq, G, d, w, lens, pad, 
         lens = [max(n, w) for n in lens]
     _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens, pad)
 
+
+# causal windows that are no multiple of the 32-row blocks: heads straddle row blocks and waves
+@pytest.mark.parametrize("Hq,G,d,w", [(8, 2, 128, 1), (8, 2, 128, 7), (32, 8, 128, 8), (4, 4, 64, 33), (10, 2, 64, 24), (8, 2, 128, 40),
+                                      (2, 1, 128, 100)])
+def test_causal_windows_on_the_bf16_kernels(sweep_mod, oracle, Hq, G, d, w):
+    _check_scores(sweep_mod, oracle, Hq, G, d, w, torch.bfloat16, True, [w, w + 1, 257, 64 + w, 1111])
