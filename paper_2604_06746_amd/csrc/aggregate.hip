@@ -9,7 +9,8 @@ namespace skv {
 namespace {
 
 // one thread per cache block, left-to-right fp32 sum (deterministic); seq.out_off holds the block offsets
-__global__ __launch_bounds__(256) void block_scores_kernel(const float* __restrict__ scores, SeqTable seq,
+template <class TAB>
+__global__ __launch_bounds__(256) void block_scores_kernel(const float* __restrict__ scores, TAB seq,
                                                            int block, float* __restrict__ out) {
   const int64_t gb = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (gb >= seq.out_off[seq.batch]) return;
@@ -25,7 +26,8 @@ __global__ __launch_bounds__(256) void block_scores_kernel(const float* __restri
 }
 
 // pos_dst[row] = pos_src ? pos_src[cu[b] + idx[row]] : idx[row]; out-of-range indices read position 0
-__global__ __launch_bounds__(256) void positions_kernel(const int64_t* __restrict__ pos_src, SeqTable seq,
+template <class TAB>
+__global__ __launch_bounds__(256) void positions_kernel(const int64_t* __restrict__ pos_src, TAB seq,
                                                         const int32_t* __restrict__ idx,
                                                         int64_t* __restrict__ pos_dst) {
   const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -43,8 +45,10 @@ __global__ __launch_bounds__(256) void positions_kernel(const int64_t* __restric
 hipError_t launch_block_scores(const float* scores, const SeqTable& seq, int block, float* out, hipStream_t st) {
   const int64_t nb = seq.out_off[seq.batch];
   if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL(block_scores_kernel, dim3((unsigned)ceil_div(nb, 256)), dim3(256), 0, st, scores, seq, block,
-                     out);
+  with_table(seq, [&](const auto& tab) {
+    hipLaunchKernelGGL((block_scores_kernel<std::decay_t<decltype(tab)>>), dim3((unsigned)ceil_div(nb, 256)), dim3(256), 0, st, scores,
+                       tab, block, out);
+  });
   return hipGetLastError();
 }
 
@@ -52,8 +56,10 @@ hipError_t launch_positions(const int64_t* pos_src, const SeqTable& seq, const i
                             hipStream_t st) {
   const int64_t rows = seq.out_off[seq.batch];
   if (rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(positions_kernel, dim3((unsigned)ceil_div(rows, 256)), dim3(256), 0, st, pos_src, seq, idx,
-                     pos_dst);
+  with_table(seq, [&](const auto& tab) {
+    hipLaunchKernelGGL((positions_kernel<std::decay_t<decltype(tab)>>), dim3((unsigned)ceil_div(rows, 256)), dim3(256), 0, st, pos_src,
+                       tab, idx, pos_dst);
+  });
   return hipGetLastError();
 }
 

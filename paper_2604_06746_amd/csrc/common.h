@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <type_traits>
 
 #include "../../include/structkv.h"
 
@@ -22,13 +23,29 @@ void clear_error();
 constexpr int kMaxBatch = STRUCTKV_MAX_BATCH;
 
 // Per-sequence table passed by value in kernel arguments (host arrays never touch the device heap).
-struct SeqTable {
-  int64_t cu[kMaxBatch + 1];        // token offsets
-  int64_t out_off[kMaxBatch + 1];   // output-row offsets (top-k / gather)
-  int32_t k[kMaxBatch];             // top-k budget
-  int32_t chunk_start[kMaxBatch + 1]; // cumulative key-chunk counts (scoring) / block counts (top-k)
+template <int N>
+struct SeqTab {
+  int64_t cu[N + 1];          // token offsets
+  int64_t out_off[N + 1];     // output-row offsets (top-k / gather)
+  int32_t k[N];               // top-k budget
+  int32_t chunk_start[N + 1]; // cumulative key-chunk counts (scoring) / block counts (top-k)
   int32_t batch;
 };
+using SeqTable = SeqTab<kMaxBatch>;
+
+// Kernels take the table in one of two sizes: the 1.6 KB of a full one are copied into the launch's argument buffer
+// on every launch, which costs the host 4.3 us per launch against 2.75 us with a few words (back-to-back launches of a
+// trivial kernel), and short layers are bound by the host's launches.
+using SmallTable = SeqTab<8>;
+template <class F>
+void with_table(const SeqTable& s, F f) {
+  if (s.batch > 8) { f(s); return; }
+  SmallTable t;
+  for (int i = 0; i <= 8; ++i) { t.cu[i] = s.cu[i]; t.out_off[i] = s.out_off[i]; t.chunk_start[i] = s.chunk_start[i]; }
+  for (int i = 0; i < 8; ++i) t.k[i] = s.k[i];
+  t.batch = s.batch;
+  f(t);
+}
 
 // The short, latency-bound kernels of a layer (combine, reduce, accumulate, top-k, gather) call this first.  When
 // layers run as chains on several streams such a kernel shares a SIMD with waves of another layer's scoring

@@ -34,11 +34,11 @@ template <typename V> __device__ inline void store_once(uint8_t* p, V v) {
   }
 }
 
-template <typename V, bool POW2>
+template <class TAB, typename V, bool POW2>
 __global__ __launch_bounds__(kThreads) void gather_rows_kernel(
     const uint8_t* __restrict__ src0, const uint8_t* __restrict__ src1, uint8_t* __restrict__ dst0,
     uint8_t* __restrict__ dst1, int64_t ssh, int64_t sst, int64_t dsh, int64_t dst_tok, uint32_t units_per_row,
-    uint32_t upr_shift, uint32_t total_units, SeqTable seq, const int32_t* __restrict__ idx) {
+    uint32_t upr_shift, uint32_t total_units, TAB seq, const int32_t* __restrict__ idx) {
   short_kernel_priority();
   const int g = blockIdx.y;
   const uint8_t* src = (blockIdx.z == 0 ? src0 : src1) + (int64_t)g * ssh;
@@ -95,11 +95,14 @@ hipError_t launch_gather(const void* k_src, const void* v_src, int64_t ssh, int6
   while ((1 << sh) < upr) ++sh;
   dim3 grid((unsigned)ceil_div(total_units, kThreads * kUnroll), (unsigned)G, (unsigned)nz), blk(kThreads);
 #define SKV_GATHER(V, P)                                                                              \
-  hipLaunchKernelGGL((gather_rows_kernel<V, P>), grid, blk, 0, st, s0, s1, d0, d1, ssh, sst, dsh, dst_tok, \
-                     (uint32_t)upr, sh, (uint32_t)total_units, seq, idx)
-  if (vec == 16) { if (pow2) SKV_GATHER(uint4, true); else SKV_GATHER(uint4, false); }
-  else if (vec == 4) { if (pow2) SKV_GATHER(uint32_t, true); else SKV_GATHER(uint32_t, false); }
-  else { if (pow2) SKV_GATHER(uint16_t, true); else SKV_GATHER(uint16_t, false); }
+  hipLaunchKernelGGL((gather_rows_kernel<T, V, P>), grid, blk, 0, st, s0, s1, d0, d1, ssh, sst, dsh, dst_tok, \
+                     (uint32_t)upr, sh, (uint32_t)total_units, tab, idx)
+  with_table(seq, [&](const auto& tab) {
+    using T = std::decay_t<decltype(tab)>;
+    if (vec == 16) { if (pow2) SKV_GATHER(uint4, true); else SKV_GATHER(uint4, false); }
+    else if (vec == 4) { if (pow2) SKV_GATHER(uint32_t, true); else SKV_GATHER(uint32_t, false); }
+    else { if (pow2) SKV_GATHER(uint16_t, true); else SKV_GATHER(uint16_t, false); }
+  });
 #undef SKV_GATHER
   return hipGetLastError();
 }

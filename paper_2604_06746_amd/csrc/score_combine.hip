@@ -18,8 +18,9 @@ constexpr float kLn2 = 0.6931471805599453f;
 // the contiguous direction of the partials), then merge in a fixed order: lane pairs, then waves
 constexpr int kCombRows = 32, kCombSlots = 32;
 
+template <class TAB>
 __global__ __launch_bounds__(kCombRows* kCombSlots) void score_combine_kernel(
-    SeqTable seq, int G, int R, int RPC, int RC, int WK, int64_t n_chunks, int row_blocks,
+    TAB seq, int G, int R, int RPC, int RC, int WK, int64_t n_chunks, int row_blocks,
     const float* __restrict__ stats, float* __restrict__ lse2, float* __restrict__ row_ent,
     uint32_t* __restrict__ zero_ptr, int64_t zero_words) {
   short_kernel_priority();
@@ -83,11 +84,11 @@ __global__ __launch_bounds__(kCombRows* kCombSlots) void score_combine_kernel(
 // FUSED (a fused layer step, Eq. 13 follows Eq. 2 directly): the kernel also starts the selection on the
 // scores it has just formed -- the histogram of their first radix digit (what topk_hist0_kernel builds
 // from memory) and the kept window's indices.
-template <int V, bool FUSED>
+template <class TAB, int V, bool FUSED>
 __global__ __launch_bounds__(256) void score_reduce_kernel(
     const float* __restrict__ colsum, int GRC, int64_t total, float* __restrict__ indeg,
     const float* __restrict__ row_ent, float* __restrict__ ent_head, float* __restrict__ entropy, int B,
-    int Hq, int w, float* __restrict__ cen, float lambda, float inv_w, SeqTable seq, SelectFusion fs) {
+    int Hq, int w, float* __restrict__ cen, float lambda, float inv_w, TAB seq, SelectFusion fs) {
   short_kernel_priority();
   __shared__ float hsum[256];
   __shared__ uint32_t h0[FUSED ? kTopkBins : 1];
@@ -241,8 +242,10 @@ hipError_t launch_score_combine(const structkv_shape& s, const ScorePlan& p, con
   const int row_blocks = (int)ceil_div(p.R, kCombRows);
   const int64_t blocks = (int64_t)seq.batch * s.n_kv_heads * row_blocks;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(score_combine_kernel, dim3((unsigned)blocks), dim3(kCombRows * kCombSlots), 0, st, seq, s.n_kv_heads, p.R,
-                     p.RPC, p.RC, p.WK, p.n_chunks, row_blocks, stats, lse2, row_ent, zero_ptr, zero_words);
+  with_table(seq, [&](const auto& tab) {
+    hipLaunchKernelGGL((score_combine_kernel<std::decay_t<decltype(tab)>>), dim3((unsigned)blocks), dim3(kCombRows * kCombSlots), 0, st,
+                       tab, s.n_kv_heads, p.R, p.RPC, p.RC, p.WK, p.n_chunks, row_blocks, stats, lse2, row_ent, zero_ptr, zero_words);
+  });
   return hipGetLastError();
 }
 
@@ -257,11 +260,14 @@ hipError_t launch_score_reduce(const structkv_shape& s, const ScorePlan& p, cons
   const bool fused = fuse != nullptr && fuse->hist != nullptr;
   const SelectFusion fs = fused ? *fuse : SelectFusion{};
 #define SKV_REDUCE(V, F)                                                                                       \
-  hipLaunchKernelGGL((score_reduce_kernel<V, F>), dim3((unsigned)blocks), dim3(256), 0, st, colsum,            \
+  hipLaunchKernelGGL((score_reduce_kernel<T, V, F>), dim3((unsigned)blocks), dim3(256), 0, st, colsum,            \
                      s.n_kv_heads * p.CP, total, indeg, row_ent, ent_head, entropy, seq.batch, s.n_q_heads,    \
-                     s.window, centrality, lambda, inv_w, seq, fs)
-  if (vec) { if (fused) SKV_REDUCE(4, true); else SKV_REDUCE(4, false); }
-  else     { if (fused) SKV_REDUCE(1, true); else SKV_REDUCE(1, false); }
+                     s.window, centrality, lambda, inv_w, tab, fs)
+  with_table(seq, [&](const auto& tab) {
+    using T = std::decay_t<decltype(tab)>;
+    if (vec) { if (fused) SKV_REDUCE(4, true); else SKV_REDUCE(4, false); }
+    else     { if (fused) SKV_REDUCE(1, true); else SKV_REDUCE(1, false); }
+  });
 #undef SKV_REDUCE
   return hipGetLastError();
 }

@@ -55,9 +55,9 @@ __device__ __forceinline__ void load4(const T* __restrict__ row, int c, int d, f
 }
 
 // DP: head_dim rounded up to 64, 128 or 256
-template <typename T, int DP, bool VEC, int PASS>
+template <class TAB, typename T, int DP, bool VEC, int PASS>
 __global__ __launch_bounds__(256, DP == 256 ? 1 : 2) void score_f32_kernel(
-    const T* __restrict__ q, const T* __restrict__ k, int64_t ksh, int64_t kst, int kshare, SeqTable seq, int Hq,
+    const T* __restrict__ q, const T* __restrict__ k, int64_t ksh, int64_t kst, int kshare, TAB seq, int Hq,
     int G, int d, int w, uint32_t w_recip, int causal, float c2, int R, int RC, int NW, int KC, int64_t n_chunks,
     float* __restrict__ stats, const float* __restrict__ lse2, float* __restrict__ colsum, int64_t total,
     float* __restrict__ probs) {
@@ -206,10 +206,13 @@ hipError_t launch_cfg(const structkv_shape& s, const ScorePlan& p, const SeqTabl
   const uint32_t w_recip = s.window > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint64_t)s.window) + 1u : 0u;
   const dim3 g((unsigned)(s.n_kv_heads * p.CP * p.grid_chunks)), blk(256);
 #define SKV_ARGS                                                                                                    \
-  g, blk, 0, st, (const T*)q, (const T*)k, ksh, kst, p.kshare, seq, s.n_q_heads, s.n_kv_heads, s.head_dim, s.window, \
+  g, blk, 0, st, (const T*)q, (const T*)k, ksh, kst, p.kshare, tab, s.n_q_heads, s.n_kv_heads, s.head_dim, s.window, \
       w_recip, causal, c2, p.R, p.RC, p.NW, p.KC, p.n_chunks, stats, lse2, colsum, total, probs
-  if (pass == 1) hipLaunchKernelGGL((score_f32_kernel<T, DP, VEC, 1>), SKV_ARGS);
-  else hipLaunchKernelGGL((score_f32_kernel<T, DP, VEC, 2>), SKV_ARGS);
+  with_table(seq, [&](const auto& tab) {
+    using TAB = std::decay_t<decltype(tab)>;
+    if (pass == 1) hipLaunchKernelGGL((score_f32_kernel<TAB, T, DP, VEC, 1>), SKV_ARGS);
+    else hipLaunchKernelGGL((score_f32_kernel<TAB, T, DP, VEC, 2>), SKV_ARGS);
+  });
 #undef SKV_ARGS
   return hipGetLastError();
 }

@@ -86,10 +86,10 @@ template <int NW, int PPW> constexpr int kPlanesLdsKeys = kPlanesKeyCap<NW, PPW>
 // NT: the key tiles are fetched with the non-temporal cache policy -- for a K larger than the 256 MB memory-side
 // cache, whose lines no later pass would find there anyway (measured: 4-8 % off both passes on a 1.1 GB K,
 // ~1 % on 256 MiB, and 3-6 % SLOWER on 64 MiB, where pass 2 and the gather do find pass 1's lines)
-template <int D, int NRB, int NW, int NBUF, int PASS, bool DUMP, int PPW = 0, bool NT = false>
+template <class TAB, int D, int NRB, int NW, int NBUF, int PASS, bool DUMP, int PPW = 0, bool NT = false>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int64_t ksh, int64_t kst, int kshare,
-    SeqTable seq, int Hq, int G, int w, uint32_t w_recip, int causal, float c2, int R, int RC, int KC, int64_t n_chunks,
+    TAB seq, int Hq, int G, int w, uint32_t w_recip, int causal, float c2, int R, int RC, int KC, int64_t n_chunks,
     float* __restrict__ stats, const float* __restrict__ lse2, float* __restrict__ colsum,
     int64_t total, float* __restrict__ probs) {
   constexpr int KS = D / 16;        // MFMA k-steps over the head dimension
@@ -619,19 +619,19 @@ hipError_t launch_ring_cfg(const structkv_shape& s, const ScorePlan& p, const Se
   const int causal = s.causal && s.window > 1;
   const uint32_t w_recip = s.window > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint64_t)s.window) + 1u : 0u;
 #define SKV_ARGS                                                                                        \
-  g, blk, dyn, st, (const uint16_t*)q, (const uint16_t*)k, ksh, kst, p.kshare, seq, s.n_q_heads, s.n_kv_heads, \
+  g, blk, dyn, st, (const uint16_t*)q, (const uint16_t*)k, ksh, kst, p.kshare, tab, s.n_q_heads, s.n_kv_heads, \
       s.window, w_recip, causal, c2, p.R, p.RC, p.KC, p.n_chunks, stats, lse2, colsum, total, probs
-  if (pass == 1 && p.stream_k) hipLaunchKernelGGL((score_mfma_ring_kernel<D, NRB, NW, NBUF, 1, false, 0, true>), SKV_ARGS);
-  else if (pass == 1) hipLaunchKernelGGL((score_mfma_ring_kernel<D, NRB, NW, NBUF, 1, false>), SKV_ARGS);
-  else if (ppw == 1) hipLaunchKernelGGL((score_mfma_ring_kernel<D, NRB, NW, NBUF, 2, false, 1>), SKV_ARGS);
-  else if (ppw == 2) {
-    if constexpr (NRB == 2) hipLaunchKernelGGL((score_mfma_ring_kernel<D, NRB, NW, NBUF, 2, false, 2>), SKV_ARGS);
-    else return hipErrorInvalidValue;
-  }
-  else if (probs == nullptr && p.stream_k)
-    hipLaunchKernelGGL((score_mfma_ring_kernel<D, NRB, NW, NBUF, 2, false, 0, true>), SKV_ARGS);
-  else if (probs == nullptr) hipLaunchKernelGGL((score_mfma_ring_kernel<D, NRB, NW, NBUF, 2, false>), SKV_ARGS);
-  else hipLaunchKernelGGL((score_mfma_ring_kernel<D, NRB, NW, NBUF, 2, true>), SKV_ARGS);
+  if (ppw == 2 && NRB != 2) return hipErrorInvalidValue;
+  with_table(seq, [&](const auto& tab) {
+    using T = std::decay_t<decltype(tab)>;
+    if (pass == 1 && p.stream_k) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 1, false, 0, true>), SKV_ARGS);
+    else if (pass == 1) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 1, false>), SKV_ARGS);
+    else if (ppw == 1) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, false, 1>), SKV_ARGS);
+    else if (ppw == 2) { if constexpr (NRB == 2) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, false, 2>), SKV_ARGS); }
+    else if (probs == nullptr && p.stream_k) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, false, 0, true>), SKV_ARGS);
+    else if (probs == nullptr) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, false>), SKV_ARGS);
+    else hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, true>), SKV_ARGS);
+  });
 #undef SKV_ARGS
   return hipGetLastError();
 }

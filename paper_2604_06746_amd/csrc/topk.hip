@@ -44,7 +44,8 @@ struct Share {
   const float* sc;
 };
 
-__device__ inline Share my_share(const float* scores, const SeqTable& seq, int keep_tail) {
+template <class TAB>
+__device__ inline Share my_share(const float* scores, const TAB& seq, int keep_tail) {
   Share s;
   int b = 0;
   while (b + 1 < seq.batch && (int)blockIdx.x >= seq.chunk_start[b + 1]) ++b;
@@ -60,7 +61,8 @@ __device__ inline Share my_share(const float* scores, const SeqTable& seq, int k
   return s;
 }
 
-__global__ __launch_bounds__(kThreads) void topk_init_kernel(SeqTable seq, int keep_tail, TopkWs ws,
+template <class TAB>
+__global__ __launch_bounds__(kThreads) void topk_init_kernel(TAB seq, int keep_tail, TopkWs ws,
                                                              int32_t* __restrict__ idx_out) {
   short_kernel_priority();
   const int b = blockIdx.y;
@@ -166,7 +168,8 @@ __device__ inline void for_each_strided(const Share& s, const float (&v)[kPerThr
   }
 }
 
-__global__ __launch_bounds__(kThreads) void topk_hist0_kernel(const float* __restrict__ scores, SeqTable seq,
+template <class TAB>
+__global__ __launch_bounds__(kThreads) void topk_hist0_kernel(const float* __restrict__ scores, TAB seq,
                                                               int keep_tail, TopkWs ws) {
   short_kernel_priority();
   __shared__ uint32_t h[kBins];
@@ -181,7 +184,8 @@ __global__ __launch_bounds__(kThreads) void topk_hist0_kernel(const float* __res
   merge_hist(h, kBins, ws.hist + (size_t)s.b * 3 * kBins);
 }
 
-__global__ __launch_bounds__(kThreads) void topk_hist1_kernel(const float* __restrict__ scores, SeqTable seq,
+template <class TAB>
+__global__ __launch_bounds__(kThreads) void topk_hist1_kernel(const float* __restrict__ scores, TAB seq,
                                                               int keep_tail, TopkWs ws) {
   short_kernel_priority();
   __shared__ uint32_t h[kBins];
@@ -206,7 +210,8 @@ __global__ __launch_bounds__(kThreads) void topk_hist1_kernel(const float* __res
   merge_hist(h, kBins, gh + kBins);
 }
 
-__global__ __launch_bounds__(kThreads) void topk_hist2_kernel(const float* __restrict__ scores, SeqTable seq,
+template <class TAB>
+__global__ __launch_bounds__(kThreads) void topk_hist2_kernel(const float* __restrict__ scores, TAB seq,
                                                               int keep_tail, TopkWs ws) {
   short_kernel_priority();
   __shared__ uint32_t h[kLowBins];
@@ -255,7 +260,8 @@ __global__ __launch_bounds__(kThreads) void topk_hist2_kernel(const float* __res
   }
 }
 
-__global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* __restrict__ scores, SeqTable seq,
+template <class TAB>
+__global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* __restrict__ scores, TAB seq,
                                                               int keep_tail, TopkWs ws,
                                                               int32_t* __restrict__ idx_out) {
   short_kernel_priority();
@@ -560,9 +566,12 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
 hipError_t launch_topk_rest(const float* scores, const SeqTable& plan, int keep_tail, const TopkWs& ws,
                             unsigned blocks, int32_t* idx_out, hipStream_t st) {
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(topk_hist1_kernel, dim3(blocks), dim3(kThreads), 0, st, scores, plan, keep_tail, ws);
-  hipLaunchKernelGGL(topk_hist2_kernel, dim3(blocks), dim3(kThreads), 0, st, scores, plan, keep_tail, ws);
-  hipLaunchKernelGGL(topk_write_kernel, dim3(blocks), dim3(kThreads), 0, st, scores, plan, keep_tail, ws, idx_out);
+  with_table(plan, [&](const auto& tab) {
+    using T = std::decay_t<decltype(tab)>;
+    hipLaunchKernelGGL((topk_hist1_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+    hipLaunchKernelGGL((topk_hist2_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+    hipLaunchKernelGGL((topk_write_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws, idx_out);
+  });
   return hipGetLastError();
 }
 
@@ -587,9 +596,11 @@ hipError_t launch_topk(const float* scores, const SeqTable& seq_in, int keep_tai
   TopkWs ws;
   unsigned blocks = 0;
   topk_plan(seq_in, keep_tail, wsp, &seq, &ws, &blocks);
-  hipLaunchKernelGGL(topk_init_kernel, dim3(4, seq.batch), dim3(kThreads), 0, st, seq, keep_tail, ws, idx_out);
-  if (blocks > 0)
-    hipLaunchKernelGGL(topk_hist0_kernel, dim3(blocks), dim3(kThreads), 0, st, scores, seq, keep_tail, ws);
+  with_table(seq, [&](const auto& tab) {
+    using T = std::decay_t<decltype(tab)>;
+    hipLaunchKernelGGL((topk_init_kernel<T>), dim3(4, seq.batch), dim3(kThreads), 0, st, tab, keep_tail, ws, idx_out);
+    if (blocks > 0) hipLaunchKernelGGL((topk_hist0_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_topk_rest(scores, seq, keep_tail, ws, blocks, idx_out, st);
