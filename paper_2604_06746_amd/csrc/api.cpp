@@ -3,6 +3,7 @@
 #include "common.h"
 #include "../../include/structkv_debug.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -120,7 +121,7 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     const int64_t step = 32 * (4 / p->NW);
     int64_t kc = ceil_div(ceil_div(total > 0 ? total : 1, chunks_per_round), step) * step;
     p->KC = (int)(kc > 1024 ? 1024 : kc);
-    chunk_bound = chunks_per_round > total / 1024 ? chunks_per_round : total / 1024;
+    chunk_bound = std::max(std::min(chunks_per_round, ceil_div(total, step)), total / 1024);   // (grows with total)
   }
   if (seq) {
     p->n_chunks = 0;
@@ -586,7 +587,7 @@ struct LayerStepPlan {
   SeqTable sel;          // cu, budgets, output offsets
   SeqTable blocks;       // the selection's workgroups per sequence
   SeqTable gseq;         // the row gather's table (fallback path)
-  TopkWs tws;
+  TopkWs tws{};
   unsigned n_blocks = 0;
   int64_t rows = 0;      // output entries in all
   bool no_rows = true;
@@ -627,6 +628,8 @@ structkv_status plan_layer_step(const structkv_shape* shape, const void* k, cons
     return fail(STRUCTKV_ERR_WORKSPACE, "workspace has %zu bytes, a layer step needs %zu", workspace_bytes,
                 p->score_bytes + topk_bytes);
   topk_plan(p->sel, keep_tail, (uint8_t*)workspace + p->score_bytes, &p->blocks, &p->tws, &p->n_blocks);
+  p->tws.mass = (float)shape->window * (float)shape->n_q_heads;   // what a sequence's in-degrees add up to
+  p->fuse.mode = p->tws.mode;
   p->fuse.hist = p->tws.hist;
   p->fuse.idx_out = idx_out;
   p->fuse.keep_tail = keep_tail;
@@ -670,7 +673,7 @@ structkv_status structkv_layer_begin(const structkv_shape* shape, const void* q_
   if (st != STRUCTKV_OK || done) return st;
   ScoreOpts o;
   o.centrality = centrality; o.lambda = lambda; o.inv_w = inv_w;
-  o.fuse = p.rows > 0 ? &p.fuse : nullptr;
+  o.fuse = p.rows > 0 && p.tws.mode != kSelShort ? &p.fuse : nullptr;   // (the short form needs nothing from the scoring)
   return score_layer_impl(shape, q_win, k, kv_stride_head, kv_stride_tok, batch, cu_seqlens, indeg_out, entropy_out,
                           entropy_per_head_out, workspace, p.score_bytes, stream, o, &p.sel);
 }

@@ -78,11 +78,46 @@ __device__ inline uint32_t score_key(float f) {
 }
 #endif
 
+// How one selection call runs, by its longest searched prefix (n_b - keep_tail):
+//   short  up to kShortSeq scores: one workgroup per sequence does everything in one launch.  At 8192 scores 7.8 us
+//          against 15.3 us for the mid form's four launches (in a layer step, where two of those fall away, about
+//          even); at 16384 one workgroup needs 13.2 us.
+//   mid    up to kMidSeq: a histogram whose fine bins lie around the scores that matter, so that the k-th largest's bin
+//          holds few scores (the candidates); one launch lists them, one resolves them and places the indices.
+//          131072 scores: 18.0 us, long form 22.6; in a layer step 12.5 us after the reduce kernel, long form 20.6.
+//   long   beyond: three radix digits (11/11/10 bits), one launch each, then the placement.  Every workgroup of the mid
+//          form reads all candidates of its sequence and all counts before it, a thread each: 256 workgroups at most.
+//          At the limit 21.8 us (mid) and 24.4 us (long).
+enum { kSelShort = 0, kSelMid = 1, kSelLong = 2 };
+constexpr int kShortSeq = 8192;
+constexpr int kMidSeq = 262144;
+constexpr int kFineBins = 4096, kFineShift = 16;   // fine bins: 1/128 of an octave wide, 32 octaves of them
+constexpr int kCandCap = 16384;                    // most candidates of a sequence that are listed (beyond: the scores are
+constexpr int kCandTotal = 262144;                 // read again), and of a call
+
+#ifdef __HIPCC__
+// first key of the fine bins for the in-degrees of a sequence: they add up to `mass` over n keys, so no more than n/64 of
+// them lie above 64 times their mean; 26 octaves below it and 6 above
+__device__ inline uint32_t fine_base(float mass, int64_t n) {
+  return score_key(mass / (float)(n > 0 ? n : 1)) - (26u << 23);
+}
+// bin of a key; the first and the last bin also take what lies beyond them
+__device__ inline uint32_t fine_bin(uint32_t key, uint32_t base) {
+  return key < base ? 0u : min((key - base) >> kFineShift, (uint32_t)(kFineBins - 1));
+}
+#endif
+
 struct TopkWs {
-  uint32_t* hist;    // [B][3][kTopkBins]
-  uint32_t* state;   // [B][4]: digit 0, k left after it, 22-bit prefix, k left after it
-  uint32_t* suf;     // [blocks][1024]: suffix sums of the workgroup's last-digit histogram
-  uint32_t* meta;    // [blocks][2]: keys above the 22-bit prefix, keys equal to it
+  uint32_t* hist;    // [B][3][kTopkBins]; mid: the fine histogram in the first kFineBins words, then the candidate counter
+  uint32_t* state;   // [B][8]; long: digit 0, k left after it, 22-bit prefix, k left after it
+                     //         mid: first and last key of the k-th largest's bin, its width in bits, k left inside it,
+                     //              keys in it, first key of the fine bins
+  uint32_t* suf;     // long: [blocks][1024] suffix sums of the workgroup's last-digit histogram
+  uint2* cand;       // mid: candidates (key, workgroup) of sequence b from min(cu[b], b*cand_cap) on
+  uint32_t* meta;    // long: [blocks][2] keys above the 22-bit prefix, keys equal to it; mid: [blocks] keys above the bin
+  int cand_cap;      // mid: most candidates listed per sequence
+  int mode;          // kSelShort / kSelMid / kSelLong
+  float mass;        // > 0: the scores are in-degrees with this sum per sequence (fused layer step)
 };
 
 // What the scoring call's small kernels do for the selection that follows it in a fused layer step: the
@@ -92,6 +127,7 @@ struct SelectFusion {
   uint32_t* hist;        // [B][3][kTopkBins]; NULL = no fusion
   int32_t* idx_out;
   int keep_tail;
+  int mode;              // kSelMid: fine bins; kSelLong: the top 11 bits
 };
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

@@ -81,21 +81,28 @@ __global__ __launch_bounds__(kCombRows* kCombSlots) void score_combine_kernel(
 // exist to use every CU); planes are added in ascending order, eight loads in flight.
 // Workgroups b < B also finish Eq. 4 for sequence b.  With `cen` != NULL the kernel also applies
 // C <- lambda C + inv_w D with the arithmetic of accumulate_kernel (one fma on the rounded product).
-// FUSED (a fused layer step, Eq. 13 follows Eq. 2 directly): the kernel also starts the selection on the
-// scores it has just formed -- the histogram of their first radix digit (what topk_hist0_kernel builds
-// from memory) and the kept window's indices.
-template <class TAB, int V, bool FUSED>
-__global__ __launch_bounds__(256) void score_reduce_kernel(
+// FUSE > 0 (a fused layer step, Eq. 13 follows Eq. 2 directly): the kernel also starts the selection on the scores it has
+// just formed -- their histogram (kSelMid: fine bins around their mean, kSelLong: the top 11 bits of their keys) and the
+// kept window's indices; workgroups of 1024 threads then, so that there are fewer histograms to merge.
+template <class TAB, int V, int FUSE>
+__global__ __launch_bounds__(FUSE ? 1024 : 256) void score_reduce_kernel(
     const float* __restrict__ colsum, int GRC, int64_t total, float* __restrict__ indeg,
     const float* __restrict__ row_ent, float* __restrict__ ent_head, float* __restrict__ entropy, int B,
     int Hq, int w, float* __restrict__ cen, float lambda, float inv_w, TAB seq, SelectFusion fs) {
   short_kernel_priority();
   __shared__ float hsum[256];
-  __shared__ uint32_t h0[FUSED ? kTopkBins : 1];
+  constexpr bool FUSED = FUSE != 0;
+  constexpr int NT = FUSED ? 1024 : 256;
+  constexpr int BINS = FUSE == kSelMid ? kFineBins : kTopkBins;
+  __shared__ uint32_t h0[FUSED ? BINS : 1];
+  const float mass = (float)w * (float)Hq;
+  auto bin_of = [&](uint32_t key, int b) {
+    return FUSE == kSelMid ? fine_bin(key, fine_base(mass, seq.cu[b + 1] - seq.cu[b])) : key >> 21;
+  };
   const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
   int b_wg = 0;   // FUSED: the sequence of the workgroup's first token; its digits are counted in LDS
   if constexpr (FUSED) {
-    for (int i = threadIdx.x; i < kTopkBins; i += 256) h0[i] = 0u;
+    for (int i = threadIdx.x; i < BINS; i += NT) h0[i] = 0u;
     const int64_t first = min((int64_t)blockIdx.x * blockDim.x * V, total > 0 ? total - 1 : 0);
     while (b_wg + 1 < B && first >= seq.cu[b_wg + 1]) ++b_wg;
     __syncthreads();
@@ -149,7 +156,7 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(
         while (b + 1 < B && i >= seq.cu[b + 1]) ++b;
         // only the prefix [0, n_b - keep_tail) of a sequence with a budget is searched
         if (seq.k[b] > 0 && i - seq.cu[b] < seq.cu[b + 1] - seq.cu[b] - fs.keep_tail) {
-          const uint32_t digit = score_key(a[j]) >> 21;
+          const uint32_t digit = bin_of(score_key(a[j]), b);
           if (b == b_wg) atomicAdd(&h0[digit], 1u);
           else atomicAdd(&fs.hist[(size_t)b * 3 * kTopkBins + digit], 1u);
         }
@@ -159,7 +166,7 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(
   if constexpr (FUSED) {
     __syncthreads();
     uint32_t* gh = fs.hist + (size_t)b_wg * 3 * kTopkBins;
-    for (int i = threadIdx.x; i < kTopkBins; i += 256)
+    for (int i = threadIdx.x; i < BINS; i += NT)
       if (h0[i]) atomicAdd(&gh[i], h0[i]);
     // the kept window: indices n_b - keep_tail .. n_b - 1 behind the k_b selected ones
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gsz = (int64_t)gridDim.x * blockDim.x;
@@ -173,7 +180,7 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(
   for (int b = blockIdx.x; b < B; b += gridDim.x) {   // uniform per workgroup
     // eight lanes share a head: each sums every eighth window row, then a fixed shuffle tree
     float part = 0.f;
-    for (int h0i = 0; h0i < Hq; h0i += 32) {
+    for (int h0i = 0; h0i < Hq && threadIdx.x < 256; h0i += 32) {   // (whole waves)
       const int h = h0i + (threadIdx.x >> 3);
       float s = 0.f;
       if (h < Hq) {
@@ -189,7 +196,7 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(
         part += s;
       }
     }
-    hsum[threadIdx.x] = part;
+    if (threadIdx.x < 256) hsum[threadIdx.x] = part;
     __syncthreads();
     if (threadIdx.x == 0) {
       float s = 0.f;
@@ -255,18 +262,19 @@ hipError_t launch_score_reduce(const structkv_shape& s, const ScorePlan& p, cons
                                const SelectFusion* fuse, hipStream_t st) {
   const bool vec = (total % 4 == 0) && (((uintptr_t)indeg | (uintptr_t)colsum | (uintptr_t)centrality) & 15) == 0 &&
                    total >= (int64_t)4 * 256 * 1024;
-  int64_t blocks = ceil_div(ceil_div(total, vec ? 4 : 1), 256);
-  if (blocks == 0) blocks = 1;
   const bool fused = fuse != nullptr && fuse->hist != nullptr;
+  const int threads = fused ? 1024 : 256;
+  int64_t blocks = ceil_div(ceil_div(total, vec ? 4 : 1), threads);
+  if (blocks == 0) blocks = 1;
   const SelectFusion fs = fused ? *fuse : SelectFusion{};
 #define SKV_REDUCE(V, F)                                                                                       \
-  hipLaunchKernelGGL((score_reduce_kernel<T, V, F>), dim3((unsigned)blocks), dim3(256), 0, st, colsum,            \
+  hipLaunchKernelGGL((score_reduce_kernel<T, V, F>), dim3((unsigned)blocks), dim3(threads), 0, st, colsum,        \
                      s.n_kv_heads * p.CP, total, indeg, row_ent, ent_head, entropy, seq.batch, s.n_q_heads,    \
                      s.window, centrality, lambda, inv_w, tab, fs)
   with_table(seq, [&](const auto& tab) {
     using T = std::decay_t<decltype(tab)>;
-    if (vec) { if (fused) SKV_REDUCE(4, true); else SKV_REDUCE(4, false); }
-    else     { if (fused) SKV_REDUCE(1, true); else SKV_REDUCE(1, false); }
+    if (vec) { if (!fused) SKV_REDUCE(4, 0); else if (fs.mode == kSelMid) SKV_REDUCE(4, kSelMid); else SKV_REDUCE(4, kSelLong); }
+    else     { if (!fused) SKV_REDUCE(1, 0); else if (fs.mode == kSelMid) SKV_REDUCE(1, kSelMid); else SKV_REDUCE(1, kSelLong); }
   });
 #undef SKV_REDUCE
   return hipGetLastError();

@@ -1,21 +1,24 @@
-// Exact, deterministic top-k selection (paper Eq. 10 / Eq. 13): radix select on order-preserving
-// 32-bit keys (three digit passes, 11/11/10 bits from the top), then an index-ordered compaction.
+// Exact, deterministic top-k selection (paper Eq. 10 / Eq. 13) on order-preserving 32-bit keys, then an index-ordered
+// compaction.  Ties at the threshold go to the lowest indices; no floating-point atomics anywhere; stream order is the
+// only synchronisation between launches (no workgroup ever waits for another one).
 //
-// Five short launches per call; the stream order between them is the only synchronisation (no
-// workgroup ever waits for another one, so there is no residency requirement and nothing can hang):
-//   init   : zero the three digit histograms, write the kept window
-//   hist0  : histogram of the top 11 key bits (LDS, merged into global memory with integer atomics)
-//   hist1  : every workgroup scans histogram 0 from the top to find the digit of the k-th key, then
-//            histograms the next 11 bits of the keys that carry that digit
-//   hist2  : same for digit 1; then one sweep that counts the keys above the 22-bit prefix and
-//            histograms the last 10 bits of the keys equal to it.  Each workgroup also publishes the
-//            suffix sums of its own last-digit histogram, so that once the last digit T is known
-//            anyone can read "keys of workgroup w above T" and "equal to T" with two loads
-//   write  : find the last digit, add up the counts of the workgroups before this one, and write the
-//            selected indices in ascending order.
-// Ties at the threshold go to the lowest indices; no floating-point atomics anywhere.
+// These kernels move a few bytes per score; launches, dependent memory round trips and barriers are what they cost.
+// So there are three forms, by the longest sequence (topk_plan):
+//   short (one launch): a workgroup of 1024 threads per sequence, keys in registers; the range between the smallest and
+//     the largest key is cut into 2048 bins, then the k-th largest's bin again, until it is one key.
+//   mid (fused into the scoring kernels: two launches; alone: four):
+//     [init]    zero the histogram, write the kept window, find from a sample where the k-th largest lies (alone only)
+//     [hist]    histogram over 4096 fine bins around it (in a layer step the reduce kernel does this)
+//     compact   find the k-th largest's bin; every workgroup lists its scores in that bin -- the candidates -- and counts
+//               those above it
+//     place     every workgroup resolves the candidates (in registers, bins as in the short form) down to the k-th key,
+//               counts what the workgroups before it have selected, and writes its own indices
+//   long: radix select in three digit passes (11/11/10 bits from the top):
+//     init, hist0 (top digit; a layer step's scoring kernels do both), hist1, hist2 (which also publishes the suffix
+//     sums of each workgroup's last-digit histogram), write.
 #include "common.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace skv {
@@ -31,7 +34,7 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kThreads = 256;
 constexpr int kBins = kTopkBins;          // digits 0 and 1: 11 bits
 constexpr int kLowBins = 1024;            // digit 2: 10 bits
-constexpr int kTargetPerBlock = 2048;     // most scores a workgroup holds in registers (eight per thread)
+constexpr int kTargetPerBlock = 2048;     // long form: most scores a workgroup holds in registers (eight per thread)
 constexpr int kSmallTarget = 1024;        // share of a workgroup when the whole call is short: more, lighter
 constexpr int64_t kSmallTotal = 262144;   // workgroups shorten each kernel's serial part
 constexpr int kMaxBlocksPerSeq = 1024;    // beyond that a workgroup's share grows instead
@@ -74,18 +77,39 @@ __global__ __launch_bounds__(kThreads) void topk_init_kernel(TAB seq, int keep_t
     idx_out[seq.out_off[b] + seq.k[b] + i] = (int32_t)(m + i);
 }
 
+// Inclusive scan over the 64 lanes: shifts inside the rows of 16, then the row totals handed on (DPP moves: six vector
+// instructions; the same scan by shuffles is six dependent trips through the LDS crossbar).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += dpp_or_zero<0x111, 0xF>(v);   // row_shr 1, 2, 4, 8
+  v += dpp_or_zero<0x112, 0xF>(v);
+  v += dpp_or_zero<0x114, 0xF>(v);
+  v += dpp_or_zero<0x118, 0xF>(v);
+  v += dpp_or_zero<0x142, 0xA>(v);   // lane 15 of a row to the next row; then lane 31 to the upper half
+  v += dpp_or_zero<0x143, 0xC>(v);
+  return v;
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(v), 63); }
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {   // same moves; lanes without a source see 0
+  v = max(v, dpp_or_zero<0x111, 0xF>(v));
+  v = max(v, dpp_or_zero<0x112, 0xF>(v));
+  v = max(v, dpp_or_zero<0x114, 0xF>(v));
+  v = max(v, dpp_or_zero<0x118, 0xF>(v));
+  v = max(v, dpp_or_zero<0x142, 0xA>(v));
+  v = max(v, dpp_or_zero<0x143, 0xC>(v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // exclusive scan of one value per thread over the workgroup (THREADS / 64 waves); returns the total.
-// Shuffle scan inside each wave, then the wave totals through LDS.
-template <int THREADS = kThreads>
+// One barrier; `sh` must not be written again before another one (TRAIL: here).
+template <int THREADS = kThreads, bool TRAIL = true>
 __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* sh /*[>= THREADS / 64]*/, uint32_t* excl) {
   constexpr int NWV = THREADS / 64;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off);
-    if (lane >= off) x += y;
-  }
+  const uint32_t x = wave_scan(v);
   if (lane == 63) sh[wv] = x;
   __syncthreads();
   uint32_t base = 0u, total = 0u;
@@ -96,34 +120,42 @@ __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* sh /*[>= THREAD
     total += wsum;
   }
   *excl = base + x - v;
-  __syncthreads();
+  if (TRAIL) __syncthreads();
   return total;
 }
 
-// Scan `nb` bins of a merged histogram from the top until `krem` keys are covered.
-// Returns the bin (all threads), and how many keys lie above it.
-template <int THREADS = kThreads>
-__device__ inline void select_bin(const uint32_t* __restrict__ gh, int nb, uint32_t krem, uint32_t* scan /*[>= THREADS / 64]*/,
-                                  uint32_t* res, uint32_t* bin_out, uint32_t* above_out) {
+// Scan the NB bins of a histogram from the top until `krem` (1 .. their sum) keys are covered.
+// Returns the bin (all threads), how many keys lie above it and how many in it.
+// Two barriers; `scan` and `res` must not be written again before another one.
+template <int THREADS, int NB>
+__device__ inline void select_bin(const uint32_t* __restrict__ gh, uint32_t krem, uint32_t* scan /*[>= THREADS / 64]*/,
+                                  uint32_t* res /*[3]*/, uint32_t* bin_out, uint32_t* above_out, uint32_t* in_bin_out = nullptr) {
+  constexpr int PER = NB / THREADS;
+  static_assert(NB % THREADS == 0, "bins split evenly over the threads");
   const int t = threadIdx.x;
-  const int per = nb / THREADS;   // 8 or 4 with 256 threads, 2 or 1 with 1024
-  uint32_t mine[8];
+  uint32_t mine[PER];   // bins NB-1-PER*t downwards
   uint32_t sum = 0;
+  if constexpr (PER % 4 == 0) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    mine[i] = i < per ? gh[nb - 1 - (t * per + i)] : 0u;
-    sum += mine[i];
+    for (int q = 0; q < PER / 4; ++q) {
+      const uint4 v = *reinterpret_cast<const uint4*>(gh + NB - PER * t - 4 * (q + 1));
+      mine[4 * q] = v.w; mine[4 * q + 1] = v.z; mine[4 * q + 2] = v.y; mine[4 * q + 3] = v.x;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) mine[i] = gh[NB - 1 - (PER * t + i)];
   }
-  if (t == 0) { res[0] = 0u; res[1] = 0u; }
-  uint32_t excl;
-  block_excl_scan<THREADS>(sum, scan, &excl);
-  if (excl < krem && excl + sum >= krem) {
-    uint32_t run = excl;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i < per && run < krem && run + mine[i] >= krem) {
-        res[0] = (uint32_t)(nb - 1 - (t * per + i));
+  for (int i = 0; i < PER; ++i) sum += mine[i];
+  uint32_t run;
+  block_excl_scan<THREADS, false>(sum, scan, &run);
+  if (run < krem && run + sum >= krem) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (run < krem && run + mine[i] >= krem) {
+        res[0] = (uint32_t)(NB - 1 - (PER * t + i));
         res[1] = run;
+        res[2] = mine[i];
       }
       run += mine[i];
     }
@@ -131,7 +163,7 @@ __device__ inline void select_bin(const uint32_t* __restrict__ gh, int nb, uint3
   __syncthreads();
   *bin_out = res[0];
   *above_out = res[1];
-  __syncthreads();
+  if (in_bin_out) *in_bin_out = res[2];
 }
 
 // add a workgroup's LDS histogram into the merged one
@@ -190,7 +222,7 @@ __global__ __launch_bounds__(kThreads) void topk_hist1_kernel(const float* __res
   short_kernel_priority();
   __shared__ uint32_t h[kBins];
   __shared__ uint32_t scan[4];
-  __shared__ uint32_t res[2];
+  __shared__ uint32_t res[3];
   const Share s = my_share(scores, seq, keep_tail);
   const int t = threadIdx.x;
   uint32_t* gh = ws.hist + (size_t)s.b * 3 * kBins;
@@ -198,10 +230,10 @@ __global__ __launch_bounds__(kThreads) void topk_hist1_kernel(const float* __res
   const bool fast = preload_strided(s, v);
   for (int i = t; i < kBins; i += kThreads) h[i] = 0u;
   uint32_t bin0, above0;
-  select_bin(gh, kBins, (uint32_t)seq.k[s.b], scan, res, &bin0, &above0);   // its barriers cover h[] = 0
+  select_bin<kThreads, kBins>(gh, (uint32_t)seq.k[s.b], scan, res, &bin0, &above0);   // its barriers cover h[] = 0
   if (s.blk == 0 && t == 0) {
-    ws.state[s.b * 4 + 0] = bin0;
-    ws.state[s.b * 4 + 1] = (uint32_t)seq.k[s.b] - above0;
+    ws.state[s.b * 8 + 0] = bin0;
+    ws.state[s.b * 8 + 1] = (uint32_t)seq.k[s.b] - above0;
   }
   for_each_strided(s, v, fast, [&](uint32_t key) {
     if ((key >> 21) == bin0) atomicAdd(&h[(key >> 10) & (kBins - 1)], 1u);
@@ -216,7 +248,7 @@ __global__ __launch_bounds__(kThreads) void topk_hist2_kernel(const float* __res
   short_kernel_priority();
   __shared__ uint32_t h[kLowBins];
   __shared__ uint32_t scan[4];
-  __shared__ uint32_t res[2];
+  __shared__ uint32_t res[3];
   __shared__ uint32_t above_cnt;
   const Share s = my_share(scores, seq, keep_tail);
   const int t = threadIdx.x;
@@ -225,13 +257,13 @@ __global__ __launch_bounds__(kThreads) void topk_hist2_kernel(const float* __res
   const bool fast = preload_strided(s, v);
   for (int i = t; i < kLowBins; i += kThreads) h[i] = 0u;
   if (t == 0) above_cnt = 0u;
-  const uint32_t bin0 = ws.state[s.b * 4 + 0], krem0 = ws.state[s.b * 4 + 1];
+  const uint32_t bin0 = ws.state[s.b * 8 + 0], krem0 = ws.state[s.b * 8 + 1];
   uint32_t bin1, above1;
-  select_bin(gh + kBins, kBins, krem0, scan, res, &bin1, &above1);   // its barriers cover h[], above_cnt = 0
+  select_bin<kThreads, kBins>(gh + kBins, krem0, scan, res, &bin1, &above1);   // its barriers cover h[], above_cnt = 0
   const uint32_t prefix = (bin0 << 11) | bin1;     // the top 22 bits of the k-th largest key
   if (s.blk == 0 && t == 0) {
-    ws.state[s.b * 4 + 2] = prefix;
-    ws.state[s.b * 4 + 3] = krem0 - above1;
+    ws.state[s.b * 8 + 2] = prefix;
+    ws.state[s.b * 8 + 3] = krem0 - above1;
   }
   uint32_t above = 0;
   for_each_strided(s, v, fast, [&](uint32_t key) {
@@ -266,7 +298,7 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* __res
                                                               int32_t* __restrict__ idx_out) {
   short_kernel_priority();
   __shared__ uint32_t scan[4];
-  __shared__ uint32_t res[2];
+  __shared__ uint32_t res[3];
   __shared__ uint32_t cnt[2];
   const Share s = my_share(scores, seq, keep_tail);
   const int t = threadIdx.x;
@@ -284,9 +316,9 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* __res
   // counts of the first workgroup this thread will add up, also requested before the scan
   const bool has0 = (uint32_t)t < s.blk;
   const uint2 m0 = has0 ? *reinterpret_cast<const uint2*>(ws.meta + 2 * ((size_t)s.first + t)) : make_uint2(0u, 0u);
-  const uint32_t prefix = ws.state[s.b * 4 + 2], krem1 = ws.state[s.b * 4 + 3];
+  const uint32_t prefix = ws.state[s.b * 8 + 2], krem1 = ws.state[s.b * 8 + 3];
   uint32_t t10, above2;
-  select_bin(gh + 2 * kBins, kLowBins, krem1, scan, res, &t10, &above2);   // its barriers cover cnt[] = 0
+  select_bin<kThreads, kLowBins>(gh + 2 * kBins, krem1, scan, res, &t10, &above2);   // its barriers cover cnt[] = 0
   const uint32_t T = (prefix << 10) | t10;   // the k-th largest key
   const uint32_t need = krem1 - above2;      // how many keys equal to T are taken (lowest indices first)
 
@@ -349,6 +381,333 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* __res
   }
 }
 
+
+// ---- short and mid forms ----------------------------------------------------------------------------------------
+
+constexpr int kWide = 1024;        // threads of a short-form workgroup
+constexpr int kMidShare = 1024;    // scores of a mid-form workgroup: four per thread
+constexpr int kMidPer = kMidShare / kThreads;
+constexpr int kListed = 64;        // keys that one wave ranks directly
+
+// LDS of resolve_key
+struct ResolveLds {
+  uint32_t hist[kBins];
+  uint32_t list[kListed];
+  uint32_t scan[16], res[3], n;
+};
+
+// The krem-th largest of the keys that `each` visits, all of them in [lo, lo + 2^width): the range in 2048 bins,
+// histogrammed in LDS; the k-th largest's bin again in 2048 bins, and so on, until the bin holds at most 64 keys (mostly
+// after one round), which every wave ranks for itself, a key per lane.  T: that key; need: how many keys equal to it are
+// among the krem.  l.hist must be zero and l.n zero, a barrier in between.
+template <int THREADS, class Each>
+__device__ inline void resolve_key(Each each, uint32_t lo, int width, uint32_t krem, ResolveLds& l, uint32_t* T, uint32_t* need) {
+  uint32_t prefix = 0u;
+  int rem = width;
+  while (rem > 0) {
+    const int bits = min(11, rem), sh = rem - bits;
+    each([&](uint32_t key) {
+      const uint32_t off = key - lo;
+      if (rem == width || (off >> rem) == prefix) atomicAdd(&l.hist[(off >> sh) & ((1u << bits) - 1u)], 1u);
+    });
+    __syncthreads();
+    uint32_t bin, above, in_bin;
+    select_bin<THREADS, kBins>(l.hist, krem, l.scan, l.res, &bin, &above, &in_bin);
+    prefix = (prefix << bits) | bin;
+    krem -= above;
+    rem = sh;
+    if (rem == 0) break;
+    if (in_bin <= (uint32_t)kListed) {
+      each([&](uint32_t key) {
+        if (((key - lo) >> rem) == prefix) l.list[atomicAdd(&l.n, 1u)] = key;
+      });
+      __syncthreads();
+      const uint32_t lane = threadIdx.x & 63;
+      const uint32_t mine = lane < in_bin ? l.list[lane] : 0u;
+      uint32_t gt = 0u, ge = 0u;
+      for (uint32_t i = 0; i < in_bin; ++i) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)i);
+        gt += o > mine;
+        ge += o >= mine;
+      }
+      const unsigned long long hit = __ballot(lane < in_bin && gt < krem && ge >= krem);
+      const int at = __ffsll((long long)hit) - 1;
+      *T = (uint32_t)__builtin_amdgcn_readlane((int)mine, at);
+      *need = krem - (uint32_t)__builtin_amdgcn_readlane((int)gt, at);
+      return;
+    }
+    for (int i = threadIdx.x; i < kBins; i += THREADS) l.hist[i] = 0u;
+    __syncthreads();
+  }
+  *T = lo + prefix;
+  *need = krem;
+}
+
+// Write the selected ones of a workgroup's PER x THREADS keys (key i of thread t stands at j0 + i*THREADS + t) in
+// ascending order: those above T and, of those equal to T, the first `need` of the sequence; g0 / e0: keys above / equal
+// to T before the workgroup.
+template <int THREADS, int PER>
+__device__ inline void place_ordered(const uint32_t (&key)[PER], int j0, int m, uint32_t T, uint32_t need, uint32_t g0,
+                                     uint32_t e0, uint32_t* tot /*[PER * THREADS / 64]*/, int32_t* __restrict__ out) {
+  constexpr int NWV = THREADS / 64, N = PER * NWV;
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  unsigned long long mg[PER], me[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const bool in = j0 + i * THREADS + t < m;
+    mg[i] = __ballot(in && key[i] > T);
+    me[i] = __ballot(in && key[i] == T);
+    if (lane == 0) tot[i * NWV + wv] = (uint32_t)__popcll(mg[i]) | ((uint32_t)__popcll(me[i]) << 16);
+  }
+  __syncthreads();
+  // every wave scans the N counts for itself (both halves of a word stay below 2^16)
+  constexpr int Q = (N + 63) / 64;
+  uint32_t own[Q], sum = 0u;
+#pragma unroll
+  for (int i = 0; i < Q; ++i) { own[i] = lane * Q + i < N ? tot[lane * Q + i] : 0u; sum += own[i]; }
+  uint32_t x = wave_scan(sum) - sum;   // before the lane's first count
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int e = i * NWV + wv;
+    uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)x, e / Q);
+#pragma unroll
+    for (int u = 0; u + 1 < Q; ++u)
+      if (u < e % Q) p += (uint32_t)__builtin_amdgcn_readlane((int)own[u], e / Q);
+    const uint32_t gb = g0 + (p & 0xFFFFu) + (uint32_t)__popcll(mg[i] & below);
+    const uint32_t eb = e0 + (p >> 16) + (uint32_t)__popcll(me[i] & below);
+    if ((mg[i] >> lane) & 1ull) out[gb + min(eb, need)] = j0 + i * THREADS + t;
+    else if (((me[i] >> lane) & 1ull) && eb < need) out[gb + eb] = j0 + i * THREADS + t;
+  }
+}
+
+// short form: one workgroup per sequence of at most PER x 1024 scores; also writes the kept window
+template <int PER, class TAB>
+__global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
+                                                           int32_t* __restrict__ idx_out) {
+  short_kernel_priority();
+  constexpr int NWV = kWide / 64;
+  __shared__ ResolveLds l;
+  __shared__ uint32_t ends[2][NWV], tot[PER * NWV];
+  const int b = blockIdx.x, t = threadIdx.x;
+  const int m = (int)(seq.cu[b + 1] - seq.cu[b]) - keep_tail;
+  const uint32_t k = (uint32_t)seq.k[b];
+  const float* sc = scores + seq.cu[b];
+  int32_t* out = idx_out + seq.out_off[b];
+  float v[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) v[i] = k > 0u && i * kWide + t < m ? sc[i * kWide + t] : 0.f;
+  for (int i = t; i < keep_tail; i += kWide) out[k + i] = m + i;
+  if (k == 0u) return;
+  for (int i = t; i < kBins; i += kWide) l.hist[i] = 0u;
+  if (t == 0) l.n = 0u;
+  uint32_t key[PER], inv = 0u, mx = 0u;   // largest ~key and largest key
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    key[i] = score_key(v[i]);
+    if (i * kWide + t < m) { inv = max(inv, ~key[i]); mx = max(mx, key[i]); }
+  }
+  inv = wave_max(inv);
+  mx = wave_max(mx);
+  if ((t & 63) == 0) { ends[0][t >> 6] = inv; ends[1][t >> 6] = mx; }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NWV; ++i) { inv = max(inv, ends[0][i]); mx = max(mx, ends[1][i]); }
+  const uint32_t mn = ~inv;
+  uint32_t T, need;
+  resolve_key<kWide>([&](auto f) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (i * kWide + t < m) f(key[i]);
+  }, mn, 32 - __clz((int)(mx - mn)), k, l, &T, &need);
+  place_ordered<kWide, PER>(key, 0, m, T, need, 0u, 0u, tot, out);
+}
+
+// mid form, alone: zero the histogram and the candidate counter, write the kept window, and centre the fine bins on the
+// k-th largest of a sample (1024 scores; it only places the bins, the result does not depend on it)
+template <class TAB>
+__global__ __launch_bounds__(kWide) void topk_mid_init_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
+                                                              TopkWs ws, int32_t* __restrict__ idx_out) {
+  short_kernel_priority();
+  __shared__ uint32_t h[kBins];
+  __shared__ uint32_t scan[kWide / 64], res[3];
+  const int b = blockIdx.x, t = threadIdx.x;
+  const int64_t m = seq.cu[b + 1] - seq.cu[b] - keep_tail;
+  const uint32_t k = (uint32_t)seq.k[b];
+  const float v = m > 0 ? scores[seq.cu[b] + (m * t) / kWide] : 0.f;
+  for (int i = t; i < kFineBins + 1; i += kWide) ws.hist[(size_t)b * 3 * kBins + i] = 0u;
+  for (int i = t; i < keep_tail; i += kWide) idx_out[seq.out_off[b] + k + i] = (int32_t)(m + i);
+  if (k == 0u) return;
+  for (int i = t; i < kBins; i += kWide) h[i] = 0u;
+  __syncthreads();
+  atomicAdd(&h[score_key(v) >> 21], 1u);
+  __syncthreads();
+  uint32_t digit, above;
+  select_bin<kWide, kBins>(h, (uint32_t)max((int64_t)1, ((int64_t)k * kWide) / m), scan, res, &digit, &above);
+  if (t == 0) {   // half of the bins' span below the digit, half above; never past the largest key
+    const uint32_t at = digit << 21, half = (uint32_t)(kFineBins / 2) << kFineShift;
+    ws.state[b * 8 + 5] = min(at > half ? at - half : 0u, 0xFFFFFFFFu - ((uint32_t)kFineBins << kFineShift));
+  }
+}
+
+// the calling workgroup's sequence b, its number inside it and its first score
+template <class TAB>
+__device__ inline void mid_share(const TAB& seq, int* b_out, uint32_t* blk, int* j0) {
+  int b = 0;
+  while (b + 1 < seq.batch && (int)blockIdx.x >= seq.chunk_start[b + 1]) ++b;
+  *b_out = b;
+  *blk = blockIdx.x - (uint32_t)seq.chunk_start[b];
+  *j0 = (int)*blk * kMidShare;
+}
+
+template <class TAB>
+__global__ __launch_bounds__(kThreads) void topk_mid_hist_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
+                                                                 TopkWs ws) {
+  short_kernel_priority();
+  __shared__ uint32_t h[kFineBins];
+  int b;
+  uint32_t blk;
+  int j0;
+  mid_share(seq, &b, &blk, &j0);
+  const int t = threadIdx.x;
+  const int m = (int)(seq.cu[b + 1] - seq.cu[b]) - keep_tail;
+  const float* sc = scores + seq.cu[b];
+  float v[kMidPer];
+#pragma unroll
+  for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * kThreads + t < m ? sc[j0 + i * kThreads + t] : 0.f;
+  const uint32_t base = ws.state[b * 8 + 5];
+  for (int i = t; i < kFineBins; i += kThreads) h[i] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kMidPer; ++i)
+    if (j0 + i * kThreads + t < m) atomicAdd(&h[fine_bin(score_key(v[i]), base)], 1u);
+  __syncthreads();
+  merge_hist(h, kFineBins, ws.hist + (size_t)b * 3 * kBins);
+}
+
+template <class TAB>
+__global__ __launch_bounds__(kThreads) void topk_compact_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
+                                                                TopkWs ws) {
+  short_kernel_priority();
+  constexpr int NWV = kThreads / 64, N = kMidPer * NWV;
+  __shared__ uint32_t scan[NWV], res[3], wtot[N], gbase;
+  int b;
+  uint32_t blk;
+  int j0;
+  mid_share(seq, &b, &blk, &j0);
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int n = (int)(seq.cu[b + 1] - seq.cu[b]), m = n - keep_tail;
+  const float* sc = scores + seq.cu[b];
+  float v[kMidPer];
+#pragma unroll
+  for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * kThreads + t < m ? sc[j0 + i * kThreads + t] : 0.f;
+  uint32_t* gh = ws.hist + (size_t)b * 3 * kBins;
+  const uint32_t base = ws.mass > 0.f ? fine_base(ws.mass, n) : ws.state[b * 8 + 5];
+  const uint32_t k = (uint32_t)seq.k[b];
+  uint32_t bin, above, in_bin;
+  select_bin<kThreads, kFineBins>(gh, k, scan, res, &bin, &above, &in_bin);
+  const bool listed = in_bin <= (uint32_t)ws.cand_cap;   // else the place kernel reads the scores again
+  if (blk == 0 && t == 0) {
+    uint32_t* st = ws.state + (size_t)b * 8;
+    st[0] = bin == 0 ? 0u : base + (bin << kFineShift);
+    st[1] = bin < (uint32_t)kFineBins - 1 ? base + (bin << kFineShift) + ((1u << kFineShift) - 1u) : 0xFFFFFFFFu;
+    st[2] = bin > 0 && bin < (uint32_t)kFineBins - 1 ? (uint32_t)kFineShift : 32u;
+    st[3] = k - above;
+    st[4] = in_bin;
+  }
+  unsigned long long mc[kMidPer];
+#pragma unroll
+  for (int i = 0; i < kMidPer; ++i) {
+    const bool in = j0 + i * kThreads + t < m;
+    const uint32_t fb = fine_bin(score_key(v[i]), base);
+    mc[i] = __ballot(in && fb == bin);
+    const unsigned long long ma = __ballot(in && fb > bin);
+    if (lane == 0) wtot[i * NWV + wv] = (uint32_t)__popcll(mc[i]) | ((uint32_t)__popcll(ma) << 16);
+  }
+  __syncthreads();
+  const uint32_t own = lane < N ? wtot[lane] : 0u;   // every wave scans the counts for itself
+  const uint32_t x = wave_scan(own);
+  if (t == N - 1) {
+    ws.meta[blockIdx.x] = x >> 16;
+    const uint32_t c = x & 0xFFFFu;
+    gbase = c && listed ? atomicAdd(&gh[kFineBins], c) : 0u;
+  }
+  __syncthreads();
+  if (!listed) return;
+  uint2* cand = ws.cand + min(seq.cu[b], (int64_t)b * ws.cand_cap) + gbase;
+#pragma unroll
+  for (int i = 0; i < kMidPer; ++i) {
+    const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(x - own), i * NWV + wv) & 0xFFFFu;
+    if ((mc[i] >> lane) & 1ull) cand[before + (uint32_t)__popcll(mc[i] & ((1ull << lane) - 1ull))] = make_uint2(score_key(v[i]), blk);
+  }
+}
+
+template <class TAB>
+__global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __restrict__ scores, TAB seq, int keep_tail, TopkWs ws,
+                                                              int32_t* __restrict__ idx_out) {
+  short_kernel_priority();
+  constexpr int CPT = 4;   // candidates a thread keeps in registers; the first of them are requested before their number is known
+  __shared__ ResolveLds l;
+  __shared__ uint32_t tot[kMidPer * (kThreads / 64)], cnt[2];
+  int b;
+  uint32_t blk;
+  int j0;
+  mid_share(seq, &b, &blk, &j0);
+  const int t = threadIdx.x;
+  const int m = (int)(seq.cu[b + 1] - seq.cu[b]) - keep_tail;
+  const float* sc = scores + seq.cu[b];
+  const uint32_t* st = ws.state + (size_t)b * 8;
+  const uint32_t lo = st[0], hi = st[1], krem = st[3], c = st[4];
+  const int width = (int)st[2];
+  const uint2* cand = ws.cand + min(seq.cu[b], (int64_t)b * ws.cand_cap);
+  const uint32_t cap = (uint32_t)min((int64_t)ws.cand_cap, seq.cu[b + 1] - seq.cu[b]);   // entries that exist
+  uint2 x[CPT];
+#pragma unroll
+  for (int r = 0; r < CPT; ++r) x[r] = (uint32_t)(r * kThreads + t) < cap ? cand[r * kThreads + t] : make_uint2(0u, 0u);
+  float v[kMidPer];
+#pragma unroll
+  for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * kThreads + t < m ? sc[j0 + i * kThreads + t] : 0.f;
+  uint32_t g0 = (uint32_t)t < blk ? ws.meta[seq.chunk_start[b] + t] : 0u;   // (at most 256 workgroups per sequence)
+  for (int i = t; i < kBins; i += kThreads) l.hist[i] = 0u;
+  if (t == 0) { cnt[0] = 0u; cnt[1] = 0u; l.n = 0u; }
+  __syncthreads();
+  uint32_t T, need, e0 = 0u;
+  if (c <= (uint32_t)ws.cand_cap) {
+    auto each = [&](auto f) {
+#pragma unroll
+      for (int r = 0; r < CPT; ++r)
+        if ((uint32_t)(r * kThreads + t) < c) f(x[r]);
+      for (uint32_t i = CPT * kThreads + t; i < c; i += kThreads) f(cand[i]);
+    };
+    resolve_key<kThreads>([&](auto f) { each([&](uint2 e) { f(e.x); }); }, lo, width, krem, l, &T, &need);
+    each([&](uint2 e) {
+      g0 += e.y < blk && e.x > T;
+      e0 += e.y < blk && e.x == T;
+    });
+  } else {
+    // more candidates than are listed (nearly equal scores, or a k-th largest outside the fine bins): the scores again
+    auto each = [&](auto f) {
+      for (int j = t; j < m; j += kThreads) {
+        const uint32_t key = score_key(sc[j]);
+        if (key >= lo && key <= hi) f(key, j);
+      }
+    };
+    resolve_key<kThreads>([&](auto f) { each([&](uint32_t key, int) { f(key); }); }, lo, width, krem, l, &T, &need);
+    each([&](uint32_t key, int j) {
+      g0 += j < j0 && key > T;
+      e0 += j < j0 && key == T;
+    });
+  }
+  g0 = wave_sum(g0);
+  e0 = wave_sum(e0);
+  if ((t & 63) == 0) { atomicAdd(&cnt[0], g0); atomicAdd(&cnt[1], e0); }
+  uint32_t key[kMidPer];
+#pragma unroll
+  for (int i = 0; i < kMidPer; ++i) key[i] = score_key(v[i]);
+  __syncthreads();
+  place_ordered<kThreads, kMidPer>(key, j0, m, T, need, cnt[0], cnt[1], tot, idx_out + seq.out_off[b]);
+}
+
 // Sum of the k largest scores of each of H equally long rows instead of their indices (the top-k mass of the pivot
 // detector's sparsity, Eq. 5), after the first digit's histogram of every row has been built by whoever formed the
 // rows.  Two kernels:
@@ -373,7 +732,7 @@ __global__ __launch_bounds__(kThreads) void mass_compact_kernel(const float* __r
                                                                 float* __restrict__ part_above) {
   short_kernel_priority();
   __shared__ uint32_t scan[4];
-  __shared__ uint32_t res[2];
+  __shared__ uint32_t res[3];
   __shared__ float red[kThreads];
   __shared__ float stage[kTargetPerBlock];
   __shared__ uint32_t cnt, gbase;
@@ -389,7 +748,7 @@ __global__ __launch_bounds__(kThreads) void mass_compact_kernel(const float* __r
   if (t == 0) cnt = 0u;
   uint32_t* gh = ws.hist + (size_t)h * 3 * kBins;
   uint32_t t0, above0;
-  select_bin(gh, kBins, kk, scan, res, &t0, &above0);   // its barriers cover cnt = 0
+  select_bin<kThreads, kBins>(gh, kk, scan, res, &t0, &above0);   // its barriers cover cnt = 0
   float sum = 0.f;
 #pragma unroll
   for (int i = 0; i < kPerThread; ++i) {
@@ -432,7 +791,7 @@ __global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* _
   constexpr int NT = kSelThreads;
   __shared__ uint32_t hh[kBins];
   __shared__ uint32_t scan[NT / 64];
-  __shared__ uint32_t res[2];
+  __shared__ uint32_t res[3];
   __shared__ unsigned long long red64[NT];
   __shared__ float redf[NT];
   const int h = blockIdx.x, t = threadIdx.x;
@@ -457,7 +816,7 @@ __global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* _
   each([&](uint32_t key) { atomicAdd(&hh[(key >> 10) & (kBins - 1)], 1u); });
   __syncthreads();
   uint32_t t1, above1;
-  select_bin<NT>(hh, kBins, krem0, scan, res, &t1, &above1);
+  select_bin<NT, kBins>(hh, krem0, scan, res, &t1, &above1);
   const uint32_t krem1 = krem0 - above1;
   for (int i = t; i < kLowBins; i += NT) hh[i] = 0u;
   __syncthreads();
@@ -466,7 +825,7 @@ __global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* _
   });
   __syncthreads();
   uint32_t t2, above2;
-  select_bin<NT>(hh, kLowBins, krem1, scan, res, &t2, &above2);
+  select_bin<NT, kLowBins>(hh, krem1, scan, res, &t2, &above2);
   const uint32_t T = (t0 << 21) | (t1 << 10) | t2;
   // every candidate carries the first digit t0 -- sign, exponent and two mantissa bits -- so the candidates share
   // one exponent and their 24-bit significands add up exactly as integers, in any order
@@ -494,11 +853,12 @@ __global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* _
   }
 }
 
-// upper bound of the workgroups one call launches
+// scores per workgroup of the long form: lighter, more workgroups shorten each kernel's serial part while there are few
 inline int share_target(int64_t total_tokens) {
   return total_tokens <= kSmallTotal ? kSmallTarget : kTargetPerBlock;
 }
 
+// upper bound of the workgroups one call of the long form launches (the mid form: at most twice as many)
 size_t max_blocks(int batch, int64_t total_tokens) {
   const size_t B = (size_t)(batch > 0 ? batch : 1);
   // monotone in total_tokens, so a workspace sized for a long call also serves every shorter one
@@ -509,13 +869,21 @@ size_t max_blocks(int batch, int64_t total_tokens) {
   return nb;
 }
 
+// the suffix sums of the long form and the candidates of the mid form take turns
+size_t lists_bytes(size_t B, int64_t total_tokens, size_t nb) {
+  const size_t suf = sizeof(uint32_t) * kLowBins * nb;
+  size_t cand = B * kCandCap < kCandTotal ? B * kCandCap : kCandTotal;
+  if ((int64_t)cand > total_tokens) cand = (size_t)total_tokens;
+  return align_up(suf > sizeof(uint2) * cand ? suf : sizeof(uint2) * cand, 256);
+}
+
 }  // namespace
 
 size_t topk_workspace_bytes(int batch, int64_t total_tokens) {
   const size_t B = (size_t)(batch > 0 ? batch : 1);
   const size_t nb = max_blocks(batch, total_tokens);
-  return align_up(sizeof(uint32_t) * 3 * B * kBins, 256) + align_up(sizeof(uint32_t) * 4 * B, 256) +
-         align_up(sizeof(uint32_t) * kLowBins * nb, 256) + align_up(sizeof(uint32_t) * 2 * nb, 256);
+  return align_up(sizeof(uint32_t) * 3 * B * kBins, 256) + align_up(sizeof(uint32_t) * 8 * B, 256) +
+         lists_bytes(B, total_tokens, nb) + align_up(sizeof(uint32_t) * 2 * nb, 256);
 }
 
 // Device address and size of the static scratch on the CURRENT device (looked up once per device).
@@ -540,37 +908,63 @@ hipError_t topk_static_scratch(void** ptr, size_t* bytes) {
   return hipSuccess;
 }
 
-// workgroups per sequence (about `target` scores each, at most kMaxBlocksPerSeq; none where nothing is
-// selected) and the workspace carve
+// the form a call takes, workgroups per sequence (none where nothing is selected) and the workspace carve
 void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan, TopkWs* ws, unsigned* blocks) {
   *plan = seq_in;
   const int B = plan->batch;
-  const int target = share_target(plan->cu[B]);
+  int64_t longest = 0;
+  for (int b = 0; b < B; ++b) {
+    const int64_t m = plan->cu[b + 1] - plan->cu[b] - keep_tail;
+    if (plan->k[b] > 0 && m > longest) longest = m;
+  }
+  ws->mode = longest <= kShortSeq ? kSelShort : longest <= kMidSeq ? kSelMid : kSelLong;
+  ws->mass = 0.f;
+  ws->cand_cap = kCandTotal / (B > 0 ? B : 1) < kCandCap ? kCandTotal / (B > 0 ? B : 1) : kCandCap;
+  const int target = ws->mode == kSelMid ? kMidShare : share_target(plan->cu[B]);
   plan->chunk_start[0] = 0;
   for (int b = 0; b < B; ++b) {
     const int64_t m = plan->cu[b + 1] - plan->cu[b] - keep_tail;
     int64_t nblk = plan->k[b] > 0 ? ceil_div(m, target) : 0;
-    if (nblk > kMaxBlocksPerSeq) nblk = kMaxBlocksPerSeq;
+    if (nblk > kMaxBlocksPerSeq) nblk = kMaxBlocksPerSeq;   // (long form: shares grow; the mid form has 256 at most)
     plan->chunk_start[b + 1] = plan->chunk_start[b] + (int)nblk;
   }
   *blocks = (unsigned)plan->chunk_start[B];
-  const size_t nb = max_blocks(B, plan->cu[B]);   // blocks <= nb: sum of ceil(m_b / target) <= total / target + B
+  const size_t nb = max_blocks(B, plan->cu[B]);   // sum of ceil(m_b / target) <= total / target + B: blocks <= nb (long), 2 nb (mid)
   const size_t Bz = (size_t)(B > 0 ? B : 1);
   uint8_t* p = (uint8_t*)wsp;
   ws->hist = (uint32_t*)p;    p += align_up(sizeof(uint32_t) * 3 * Bz * kBins, 256);
-  ws->state = (uint32_t*)p;   p += align_up(sizeof(uint32_t) * 4 * Bz, 256);
-  ws->suf = (uint32_t*)p;     p += align_up(sizeof(uint32_t) * kLowBins * nb, 256);
+  ws->state = (uint32_t*)p;   p += align_up(sizeof(uint32_t) * 8 * Bz, 256);
+  ws->suf = (uint32_t*)p;
+  ws->cand = (uint2*)p;       p += lists_bytes(Bz, plan->cu[B], nb);
   ws->meta = (uint32_t*)p;
 }
 
+// What a fused layer step leaves of the selection: everything in the short form (window indices included), the last two
+// launches in the mid form, the last three in the long one.
 hipError_t launch_topk_rest(const float* scores, const SeqTable& plan, int keep_tail, const TopkWs& ws,
                             unsigned blocks, int32_t* idx_out, hipStream_t st) {
-  if (blocks == 0) return hipSuccess;
   with_table(plan, [&](const auto& tab) {
     using T = std::decay_t<decltype(tab)>;
-    hipLaunchKernelGGL((topk_hist1_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
-    hipLaunchKernelGGL((topk_hist2_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
-    hipLaunchKernelGGL((topk_write_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws, idx_out);
+    if (ws.mode == kSelShort) {
+      int64_t longest = 0;
+      for (int b = 0; b < plan.batch; ++b)
+        if (plan.k[b] > 0) longest = std::max(longest, plan.cu[b + 1] - plan.cu[b] - keep_tail);
+#define SKV_SHORT(PER) \
+  hipLaunchKernelGGL((topk_short_kernel<PER, T>), dim3((unsigned)plan.batch), dim3(kWide), 0, st, scores, tab, keep_tail, idx_out)
+      if (longest <= 2 * kWide) SKV_SHORT(2);
+      else if (longest <= 4 * kWide) SKV_SHORT(4);
+      else SKV_SHORT(8);
+#undef SKV_SHORT
+    } else if (blocks == 0) {
+      return;
+    } else if (ws.mode == kSelMid) {
+      hipLaunchKernelGGL((topk_compact_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+      hipLaunchKernelGGL((topk_place_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws, idx_out);
+    } else {
+      hipLaunchKernelGGL((topk_hist1_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+      hipLaunchKernelGGL((topk_hist2_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+      hipLaunchKernelGGL((topk_write_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws, idx_out);
+    }
   });
   return hipGetLastError();
 }
@@ -598,8 +992,13 @@ hipError_t launch_topk(const float* scores, const SeqTable& seq_in, int keep_tai
   topk_plan(seq_in, keep_tail, wsp, &seq, &ws, &blocks);
   with_table(seq, [&](const auto& tab) {
     using T = std::decay_t<decltype(tab)>;
-    hipLaunchKernelGGL((topk_init_kernel<T>), dim3(4, seq.batch), dim3(kThreads), 0, st, tab, keep_tail, ws, idx_out);
-    if (blocks > 0) hipLaunchKernelGGL((topk_hist0_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+    if (ws.mode == kSelMid) {
+      hipLaunchKernelGGL((topk_mid_init_kernel<T>), dim3((unsigned)seq.batch), dim3(kWide), 0, st, scores, tab, keep_tail, ws, idx_out);
+      if (blocks > 0) hipLaunchKernelGGL((topk_mid_hist_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+    } else if (ws.mode == kSelLong) {
+      hipLaunchKernelGGL((topk_init_kernel<T>), dim3(4, seq.batch), dim3(kThreads), 0, st, tab, keep_tail, ws, idx_out);
+      if (blocks > 0) hipLaunchKernelGGL((topk_hist0_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+    }
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -66,3 +66,47 @@ def test_fp32_matrix_scoring_kernels(sweep_mod, oracle, Hq, G, d, w, lens, pad, 
                                       (2, 1, 128, 100)])
 def test_causal_windows_on_the_bf16_kernels(sweep_mod, oracle, Hq, G, d, w):
     _check_scores(sweep_mod, oracle, Hq, G, d, w, torch.bfloat16, True, [w, w + 1, 257, 64 + w, 1111])
+
+
+def _select(B, scores, lens, ks, tail):
+    total, cu = sum(lens), np.concatenate([[0], np.cumsum(lens)]).tolist()
+    ws = torch.full((max(B.structkv_workspace_bytes(None, len(lens), total), 256),), 0xA5, dtype=torch.uint8, device="cuda")
+    out = torch.full((sum(ks) + tail * len(ks) + 1,), -7, dtype=torch.int32, device="cuda")
+    B.structkv_select_topk(scores, cu, ks, tail, out, ws)
+    got = out.cpu().numpy()
+    assert got[-1] == -7
+    return got[:-1]
+
+
+# the edges of the three forms (8192 and 262144 searched scores), of their 1024-score workgroups and of the candidate
+# lists (16384 per sequence); scores: spread, nearly equal (more candidates than are listed), all equal, alternating
+# between two values a power apart (a sample that misses the threshold's range), negative
+@pytest.mark.parametrize("lens,tail", [([1], 0), ([63, 64, 65], 3), ([1025], 1), ([8192 + 8], 8), ([8193 + 8], 8), ([9216, 5, 0], 0),
+                                       ([17000, 20000], 32), ([262144 + 7], 7), ([262145 + 7, 300], 7), ([33000] * 17, 64)])
+@pytest.mark.parametrize("kind", ["spread", "close", "equal", "two", "negative"])
+def test_selection_forms(B, oracle, lens, tail, kind):
+    total = sum(lens)
+    x = _randn(total, dtype=torch.float32, seed=3)
+    scores = {"spread": torch.exp(4.0 * x), "close": 1.0 + 1e-5 * x, "equal": torch.full_like(x, 0.25),
+              "two": torch.where(x > 2.5, 1e20, 1e-20) * (1.0 + 0.1 * x.abs()), "negative": -torch.exp(x)}[kind].contiguous()
+    for frac in (0.0, 0.003, 0.2, 1.0):
+        ks = [int(frac * max(n - tail, 0)) if n >= tail else 0 for n in lens]
+        t = min([tail] + lens)
+        ref = oracle.select_topk(scores.cpu().numpy(), lens, ks, t)
+        assert np.array_equal(_select(B, scores, lens, ks, t), np.concatenate(ref)), (kind, frac)
+
+
+# a layer step's selection on the in-degrees it has just formed: all in-degrees equal (every score a candidate), budgets
+# of one and of everything, sequences on both sides of the short form's limit
+@pytest.mark.parametrize("lens,ks", [([20000], [700]), ([20000], [1]), ([9000, 40, 100], [8968, 8, 0]), ([8192 + 32, 50], [8192, 1]),
+                                     ([300000], [1000])])
+@pytest.mark.parametrize("zero", [False, True])
+def test_layer_step_selection_forms(sweep_mod, oracle, lens, ks, zero):
+    w = 32
+    sw = sweep_mod.LayerSweep(4, 2, 64, w, torch.bfloat16, lens, ks)
+    q = _randn(len(lens), 4, w, 64, dtype=torch.bfloat16, seed=4) * (0.0 if zero else 3.0)
+    k, v = (_randn(2, sum(lens), 64, dtype=torch.bfloat16, seed=s) for s in (5, 6))
+    sw.layer(q, k, v)
+    idx = sw.idx_kv.cpu().numpy()[:sw.rows]
+    ref = np.concatenate(oracle.select_topk(sw.indeg.cpu().numpy(), lens, ks, w))
+    assert np.array_equal(idx, ref)
