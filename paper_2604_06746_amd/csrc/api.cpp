@@ -69,6 +69,7 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
   p->kshare = 1;
   p->path = mfma_ok ? 0 : 1;
   p->planes = 0;
+  p->split = 1;
   // a K of at least the memory-side cache's 256 MiB streams through the caches (see the kernel's NT parameter)
   p->stream_k = p->path == 0 && total * s.n_kv_heads * s.head_dim * 2 >= ((int64_t)256 << 20);
   if (p->path == 0) {
@@ -89,12 +90,13 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     // keys per workgroup: whole rounds of resident workgroups over the chip (256 CUs x 3 four-wave or 8 one-wave
     // workgroups), at most kMaxKC keys each, and at least 256 so that loading the query operands
     // (RPC*d*2 bytes per wave) stays small against the K stream
-    // per-head planes: a wave's RPC rows must be one head's window (w = RPC) or two (w = 32, RPC = 64)
-    if (planes && (s.window == p->RPC || (s.window == 32 && p->RPC == 64 && gs % 2 == 0)))
-      p->planes = p->RPC / s.window;
-    // the kernels' LDS column-sum capacity
-    const int64_t kMaxKC = p->planes ? (p->NW == 4 ? (p->planes == 1 ? 1376 : 736) : 1024 / p->planes)
-                                     : (p->NW == 4 ? 2048 : 896);
+    // per-head planes: a wave's RPC rows must be one head's window (w = RPC) or whole heads (w = 32, 16 or 8)
+    if (planes && s.window == p->RPC) p->planes = 1;
+    else if (planes && s.window == 32) p->planes = 2;
+    else if (planes && (s.window == 16 || s.window == 8)) { p->planes = p->RB; p->split = 32 / s.window; }
+    // the kernels' LDS column-sum capacity (per-head planes: kPlanesKeyCap there)
+    const int np = p->planes * p->split;
+    const int64_t kMaxKC = np ? (p->NW == 4 ? 1280 / np + 96 : np <= 4 ? 1024 / np : 256) : (p->NW == 4 ? 2048 : 896);
     const int64_t slots = 256 * (p->NW == 4 ? 3 : 8);
     const int64_t wg_per_chunk = s.n_kv_heads * ceil_div(p->RC, p->NW);
     const int64_t chunks_per_round = slots / wg_per_chunk > 0 ? slots / wg_per_chunk : 1;
@@ -107,7 +109,7 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     if (kc < kc_min) kc = kc_min;
     if (kc > kMaxKC) kc = kMaxKC;
     p->KC = (int)kc;
-    p->CP = p->planes ? p->RC * p->planes : (int)ceil_div(p->RC, p->NW);
+    p->CP = p->planes ? gs : (int)ceil_div(p->RC, p->NW);
   } else {
     // fp32 matrix kernels: waves of 32 rows, four to a workgroup: NW row-chunks that take the same keys, 4/NW waves
     // per row-chunk that take turns at its 32-key tiles
@@ -178,7 +180,7 @@ structkv_status run_score(const structkv_shape* shape, const void* q_win, const 
   const int64_t total = seq.cu[B];
   ScorePlan p;
   make_plan(s, &seq, B, total, !o.force_simt && mfma_eligible(s, q_win, k, ksh, kst), &p, o.planes);
-  if (o.planes && !p.planes) return fail(STRUCTKV_ERR_UNSUPPORTED, "per-head planes need the MFMA kernels and a window of 32 or 64");
+  if (o.planes && !p.planes) return fail(STRUCTKV_ERR_UNSUPPORTED, "per-head planes need the MFMA kernels and a window of 8, 16, 32 or 64");
   p.kshare = o.kshare;   // s.n_kv_heads % kshare == 0 (the caller's business)
   if (o.flip_stream_k && p.path == 0) p.stream_k = !p.stream_k;
   if (p.total_bytes > ws_bytes)

@@ -145,8 +145,9 @@ struct ScorePlan {
   int NW;            // waves (row-chunks) per workgroup sharing the key tiles (bf16: 1 or 4; fp32: 1, 2 or 4)
   int CP;            // pass-2 column-sum planes per KV head (the waves of a workgroup add theirs up first)
   int planes;        // MFMA path, pass 2: 0, or column-sum planes per WAVE (1: a wave's rows are one query head's
-                     // window; 2: each of its two 32-row blocks is) instead of one per workgroup: CP = RC * planes =
-                     // query heads per KV head, and the planes are the per-head in-degrees
+                     // window; 2: each of its two 32-row blocks is) instead of one per workgroup: CP = query heads per
+                     // KV head, and the planes are the per-head in-degrees
+  int split;         // ... times the heads of every 32-row block (windows of 16 and 8: 2 and 4; planes = RB then), else 1
   int kshare;        // consecutive groups that read the same K head (1 in ordinary scoring; the per-head
                      // scoring of the pivot metrics runs every query head as its own group: H_q/G)
   int64_t n_chunks;  // sum over sequences of ceil(n_b / KC): the stride of the per-chunk statistics

@@ -70,23 +70,25 @@ __device__ __forceinline__ void wait_vmcnt() {
 template <int NW> constexpr int kKeyCap = NW == 4 ? 2048 : 896;
 
 // Pass 2 with one column-sum plane per QUERY HEAD instead of one per workgroup (the per-head in-degrees of the
-// pivot detector's metrics, Eq. 5-6): PPW planes per wave -- 1 when a wave's rows are one head's window, 2 when
-// each of its two 32-row blocks is.  Most keys a workgroup may then be given: its LDS holds NW*PPW sums per key for
-// all tiles but the chunk's last THREE, whose sums go from the registers straight to global memory (no tile load is
-// requested after them any more, so these stores sit behind every load that a wait still counts) -- 20 KB of sums
-// beside three 4-wave workgroups' rings, which is what lets a 128K-token layer be ONE round of 768 workgroups with
-// 1376 keys each (21 KB already cost the third workgroup per CU).
+// pivot detector's metrics, Eq. 5-6): PPW * SPLIT planes per wave -- PPW = 1 when a wave's rows are one head's window,
+// 2 when each of its two 32-row blocks is; windows of 16 and 8 put SPLIT = 2 and 4 heads into every 32-row block (a
+// 32K-token layer with its metrics, window 8: 57.6 us; 94 us when the layer was re-scored head by head instead).  Most
+// keys a workgroup may then be given: its LDS holds NW * planes sums per key for all tiles but the chunk's last THREE,
+// whose sums go from the registers straight to global memory (no tile load is requested after them any more, so these
+// stores sit behind every load that a wait still counts) -- 20 KB of sums beside three 4-wave workgroups' rings, which
+// is what lets a 128K-token layer be ONE round of 768 workgroups with 1376 keys each (21 KB already cost the third
+// workgroup per CU); 4 KB beside a one-wave workgroup's ring, at least 256 keys.
 constexpr int kPlanesDirectTiles = 3;
-template <int NW, int PPW> constexpr int kPlanesKeyCap = NW == 4 ? (PPW == 1 ? 1376 : 736) : 1024 / PPW;
-// ... of which LDS holds
-template <int NW, int PPW> constexpr int kPlanesLdsKeys = kPlanesKeyCap<NW, PPW> - 32 * kPlanesDirectTiles;
+// keys whose sums LDS holds, for NP planes per wave; and the key cap
+template <int NW, int NP> constexpr int kPlanesLdsKeys = NW == 4 ? 1280 / NP : (NP <= 4 ? 1024 / NP : 256) - 32 * kPlanesDirectTiles;
+template <int NW, int NP> constexpr int kPlanesKeyCap = kPlanesLdsKeys<NW, NP> + 32 * kPlanesDirectTiles;
 
 // NW = waves per workgroup (row-chunks sharing the key tiles), NBUF = tiles in the LDS ring; PPW > 0 (pass 2):
-// planes per wave as above, written to consecutive planes of `colsum`: plane g*RC*PPW + row-chunk*PPW + block.
+// planes per head as above: head h of KV head g is plane g*(R/w) + h of `colsum`.
 // NT: the key tiles are fetched with the non-temporal cache policy -- for a K larger than the 256 MB memory-side
 // cache, whose lines no later pass would find there anyway (measured: 4-8 % off both passes on a 1.1 GB K,
 // ~1 % on 256 MiB, and 3-6 % SLOWER on 64 MiB, where pass 2 and the gather do find pass 1's lines)
-template <class TAB, int D, int NRB, int NW, int NBUF, int PASS, bool DUMP, int PPW = 0, bool NT = false>
+template <class TAB, int D, int NRB, int NW, int NBUF, int PASS, bool DUMP, int PPW = 0, bool NT = false, int SPLIT = 1>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int64_t ksh, int64_t kst, int kshare,
     TAB seq, int Hq, int G, int w, uint32_t w_recip, int causal, float c2, int R, int RC, int KC, int64_t n_chunks,
@@ -113,9 +115,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
   // whose reads the compiler then never orders behind the tile loads in flight (with the buffers as static
   // arrays, or with their addresses taken, it loses track and waits for ALL tile loads before LDS accesses).
   constexpr bool PLANES = PPW > 0;
+  constexpr int NP = PLANES ? PPW * SPLIT : 1;   // planes per wave
   // (with planes: keys per plane in LDS)
-  constexpr int KCAP = PASS == 2 ? (PLANES ? kPlanesLdsKeys<NW, (PLANES ? PPW : 1)> : kKeyCap<NW>) : 1;
+  constexpr int KCAP = PASS == 2 ? (PLANES ? kPlanesLdsKeys<NW, NP> : kKeyCap<NW>) : 1;
   static_assert(!PLANES || (PASS == 2 && !DUMP && PPW <= NRB), "per-head planes are a pass-2 output");
+  static_assert(SPLIT == 1 || PPW == NRB, "several heads per row block: every block has its own planes");
   // vector-ALU instructions the scheduler is asked to place after each MFMA of the next row block
   constexpr int VPM = PASS == 1 ? 8 : 4;
 
@@ -138,6 +142,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
   const int64_t chunk = t / rcg;
   const int grc = g * RC + rc;
   const int plane = g * rcg + (int)(t % rcg);   // pass 2: the workgroup's column-sum plane
+  const int gheads = PLANES ? R / w : 1;        // ... or the planes, one per query head of the group
   int b = 0;
   while (b + 1 < seq.batch && chunk >= seq.chunk_start[b + 1]) ++b;
   const int64_t tok0 = seq.cu[b];
@@ -250,7 +255,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
     win[rb] = PASS == 1 ? (rc * RPC + rb * 32 + l32) % w : 0;
   }
   float cs0 = 0.f, cs1 = 0.f;     // pass 2: column sum of this lane's key
-  float csp[PPW == 2 ? 2 : 1] = {};   // PPW == 2: the same per 32-row block (cs0 + cs1 of each block)
+  float csp[NP] = {};             // several planes per wave: the same per plane
 
   auto mfma_block = [&](floatx16& acc, const bf16x8 (&kf)[KS], auto rb_tag) __attribute__((always_inline)) {
     constexpr int rb = decltype(rb_tag)::value;
@@ -344,8 +349,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
           if (rbw < R) probs[((int64_t)g * R + rbw) * n + j] = pb;
         }
         cs0 += pa; cs1 += pb;
+        if constexpr (SPLIT > 1) {   // (rows 8q .. 8q+7 of the block, four of them in each lane half, are rows i = 4q .. 4q+3)
+          if (i % (16 / SPLIT) == 16 / SPLIT - 2) { csp[rb * SPLIT + i / (16 / SPLIT)] = cs0 + cs1; cs0 = 0.f; cs1 = 0.f; }
+        }
       }
-      if constexpr (PPW == 2) { csp[rb] = cs0 + cs1; cs0 = 0.f; cs1 = 0.f; }
+      if constexpr (PPW == 2 && SPLIT == 1) { csp[rb] = cs0 + cs1; cs0 = 0.f; cs1 = 0.f; }
     }
   };
 
@@ -409,21 +417,22 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
   // then waits for every outstanding tile load (which also write LDS) before it.
   auto park_colsum = [&](int jbase, auto ring_slot) __attribute__((always_inline)) {
     if (PASS == 2 && PLANES) {
-      // every wave keeps its own sums, one list per head: lane halves added here, no exchange between waves
-      constexpr int NP = PLANES ? PPW : 1;
-      const uint32_t a0 = csout_lds + (uint32_t)((wave * NP * KCAP + (jbase - key0 + l32)) * 4);
+      // every wave keeps its own sums, one list per head: lane halves added here, no exchange between waves.  With
+      // several planes the lower lane half stores one plane and the upper half the next.
+      constexpr int PAIR = NP > 1 ? 2 : 1;
+      const int half = PAIR == 2 ? lh : 0;
+      const uint32_t a0 = csout_lds + (uint32_t)(((wave * NP + half) * KCAP + (jbase - key0 + l32)) * 4);
       const bool last = jbase + 32 * kPlanesDirectTiles >= key_end;   // the chunk's last tiles: straight to their planes
 #pragma unroll
-      for (int sp = 0; sp < NP; ++sp) {
-        float cs = PPW == 2 ? csp[sp] : cs0 + cs1;
-        cs = add_lane_halves(cs);
-        const uint32_t a = a0 + (uint32_t)(sp * KCAP * 4);
-        const float val = live ? cs : 0.f;
+      for (int sp = 0; sp < NP; sp += PAIR) {
+        float val = add_lane_halves(NP > 1 ? csp[sp] : cs0 + cs1);
+        if constexpr (PAIR == 2) { const float up = add_lane_halves(csp[sp + 1]); val = lh ? up : val; }
         if (last) {
-          if (lh == 0 && live && jbase + l32 < key_end)
-            colsum[((int64_t)g * RC * NP + (int64_t)rc * NP + sp) * total + tok0 + jbase + l32] = val;
-        } else if (lh == 0) {
-          asm volatile("ds_write_b32 %0, %1" : : "v"(a), "v"(val) : "memory");
+          const int head = rc * NP + sp + half;
+          if ((PAIR == 2 || lh == 0) && live && head < gheads && jbase + l32 < key_end)
+            colsum[((int64_t)g * gheads + head) * total + tok0 + jbase + l32] = val;
+        } else if (PAIR == 2 || lh == 0) {
+          asm volatile("ds_write_b32 %0, %1" : : "v"(a0 + (uint32_t)(sp * KCAP * 4)), "v"(val) : "memory");
         }
       }
       cs0 = 0.f; cs1 = 0.f;
@@ -551,12 +560,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
   if constexpr (PASS == 2 && PLANES) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();
-    // plane of (wave, block): g*RC*PPW + (row-chunk)*PPW + block; row-chunks beyond RC do not exist
-    constexpr int NP = PLANES ? PPW : 1;
-    const int rc0 = (int)(t % rcg) * NW;
-    for (int pl = 0; pl < NW * NP; ++pl) {
-      if (rc0 + pl / NP >= RC) break;
-      float* out = colsum + ((int64_t)g * RC * NP + (int64_t)rc0 * NP + pl) * total + tok0 + key0;
+    const int head0 = (int)(t % rcg) * NW * NP;   // the workgroup's first head (heads beyond the group's do not exist)
+    for (int pl = 0; pl < NW * NP && head0 + pl < gheads; ++pl) {
+      float* out = colsum + ((int64_t)g * gheads + head0 + pl) * total + tok0 + key0;
       for (int i = threadIdx.x; i < 32 * (nsub - kPlanesDirectTiles); i += 64 * NW) {   // (the last tiles' sums are there already)
         float v;
         const uint32_t a = csout_lds + (uint32_t)(pl * KCAP + i) * 4u;
@@ -612,8 +618,10 @@ hipError_t launch_ring_cfg(const structkv_shape& s, const ScorePlan& p, const Se
   dim3 g((unsigned)grid), blk(64 * NW);
   // pass 2: dynamic LDS for the column sums of the key chunk and the waves' parked sums
   const int ppw = pass == 2 && probs == nullptr ? p.planes : 0;
-  const unsigned cs_bytes = ppw ? (unsigned)(NW * (NW == 4 ? 1280 : 928) * 4)   // NW * PPW * kPlanesLdsKeys<NW, PPW> * 4 at most
-                                : (unsigned)(kKeyCap<NW> * 4 + (NW > 1 ? 4 * NW * 64 * 4 : 0));
+  const int np = ppw * p.split;
+  auto planes_bytes = [&](auto n) { return (unsigned)(NW * decltype(n)::value * kPlanesLdsKeys<NW, decltype(n)::value> * 4); };
+  const unsigned cs_bytes = np == 1 ? planes_bytes(IntC<1>{}) : np == 2 ? planes_bytes(IntC<2>{}) : np == 4 ? planes_bytes(IntC<4>{})
+                          : np == 8 ? planes_bytes(IntC<8>{}) : (unsigned)(kKeyCap<NW> * 4 + (NW > 1 ? 4 * NW * 64 * 4 : 0));
   const unsigned dyn = pass == 1 ? 16u : cs_bytes;   // pass 1: the word of the rerun vote
   // causal masks: floor(2^32 / w) + 1 (the row modulo the window); a window of one row sees every key
   const int causal = s.causal && s.window > 1;
@@ -621,11 +629,13 @@ hipError_t launch_ring_cfg(const structkv_shape& s, const ScorePlan& p, const Se
 #define SKV_ARGS                                                                                        \
   g, blk, dyn, st, (const uint16_t*)q, (const uint16_t*)k, ksh, kst, p.kshare, tab, s.n_q_heads, s.n_kv_heads, \
       s.window, w_recip, causal, c2, p.R, p.RC, p.KC, p.n_chunks, stats, lse2, colsum, total, probs
-  if (ppw == 2 && NRB != 2) return hipErrorInvalidValue;
+  if ((ppw == 2 && NRB != 2) || (p.split > 1 && ppw != NRB && ppw != 0)) return hipErrorInvalidValue;
   with_table(seq, [&](const auto& tab) {
     using T = std::decay_t<decltype(tab)>;
     if (pass == 1 && p.stream_k) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 1, false, 0, true>), SKV_ARGS);
     else if (pass == 1) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 1, false>), SKV_ARGS);
+    else if (ppw && p.split == 2) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, false, NRB, false, 2>), SKV_ARGS);
+    else if (ppw && p.split == 4) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, false, NRB, false, 4>), SKV_ARGS);
     else if (ppw == 1) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, false, 1>), SKV_ARGS);
     else if (ppw == 2) { if constexpr (NRB == 2) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, false, 2>), SKV_ARGS); }
     else if (probs == nullptr && p.stream_k) hipLaunchKernelGGL((score_mfma_ring_kernel<T, D, NRB, NW, NBUF, 2, false, 0, true>), SKV_ARGS);
