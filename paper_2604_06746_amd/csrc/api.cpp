@@ -64,7 +64,7 @@ structkv_status check_cu(int32_t batch, const int64_t* cu, SeqTable* seq) {
 void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t total, bool mfma_ok,
                ScorePlan* p, bool planes = false) {
   const int gs = s.n_q_heads / s.n_kv_heads;
-  int64_t chunk_bound = total / 256;   // bf16 kernels: KC is at least 256
+  int64_t chunk_bound = 0;   // of the key chunks of any `total` tokens, beside one per sequence; grows with total
   p->R = gs * s.window;
   p->kshare = 1;
   p->path = mfma_ok ? 0 : 1;
@@ -104,9 +104,19 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     int64_t kc = ceil_div(ceil_div(total, chunks_per_round * rounds), 32) * 32;
     // Short inputs: at least 512 keys per workgroup while that still fills half of the resident slots (a
     // workgroup's fixed costs -- query operands, the first tiles' latency, the partial results -- weigh as much
-    // as 6-8 tiles; with layers running as chains the other half of the chip is another layer's), else 256.
-    const int64_t kc_min = ceil_div(total, 512) * wg_per_chunk * 2 >= slots ? 512 : 256;
+    // as 6-8 tiles; with layers running as chains the other half of the chip is another layer's), else 256; and where
+    // 256 leave SIMDs without a wave, as few as give every SIMD one (256 four-wave or 1024 one-wave workgroups), but
+    // two tiles: 32 heads on 8, window 8: 512 / 2048 / 4096 tokens 19 -> 13.1 / 13.4 / 14.2 us per scoring call.
+    // (More workgroups than that lose: they share CUs unevenly and leave more partial results: 8 heads on 2, window 64,
+    // 32768 tokens 30.5 us with 256 keys, 33.2 with 192.)
+    int64_t kc_min = ceil_div(total, 512) * wg_per_chunk * 2 >= slots ? 512 : 256;
+    const int64_t one_each = p->NW == 4 ? 256 : 1024;
+    if (ceil_div(total, 256) * wg_per_chunk < one_each) {
+      kc_min = ceil_div(ceil_div(total * wg_per_chunk, one_each), 32) * 32;
+      if (kc_min < 64) kc_min = 64;
+    }
     if (kc < kc_min) kc = kc_min;
+    chunk_bound = std::max(total / 256, std::min(ceil_div(total, 64), ceil_div(one_each, wg_per_chunk)));
     if (kc > kMaxKC) kc = kMaxKC;
     p->KC = (int)kc;
     p->CP = p->planes ? gs : (int)ceil_div(p->RC, p->NW);

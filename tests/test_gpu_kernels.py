@@ -132,3 +132,10 @@ def test_pivot_metrics_of_short_windows(sweep_mod, oracle, Hq, G, d, w, lens, ca
     assert np.all(np.abs(rho.cpu().numpy()[:len(lens)] - rho_ref) <= 1e-3 * rho_ref)
     # a variance is a sum of squared differences from 1/n: relative to their squares as in the other parity tests
     assert np.all(np.abs(var.cpu().numpy()[:len(lens)] - var_ref) <= 2e-3 * var_ref + 1e-4 / np.array(lens, dtype=np.float64) ** 2)
+
+
+# short inputs: key chunks of 64 .. 256 keys (two to eight tiles), one- and four-wave workgroups
+@pytest.mark.parametrize("Hq,G,w", [(8, 2, 8), (4, 2, 32), (8, 2, 32), (8, 2, 64)])
+@pytest.mark.parametrize("lens", [[64], [65, 1, 0, 200], [5000], [17000, 31]])
+def test_short_key_chunks(sweep_mod, oracle, Hq, G, w, lens):
+    _check_scores(sweep_mod, oracle, Hq, G, 128, w, torch.bfloat16, False, lens)
