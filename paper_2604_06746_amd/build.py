@@ -22,10 +22,22 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-x", "hip",
 # handling the compiler drops the canonicalising v_max it otherwise puts in front of every fmaxf operand.
 EXTRA = {"score_mfma_ring.hip": ["-fno-honor-nans"]}
 
+# Sources compiled as several objects: (macro that selects the part, number of parts)
+PARTS = {"score_mfma_ring.hip": ("SKV_RING_PART", 5)}
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = ["hipcc"] + FLAGS + EXTRA.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
+
+def _units() -> list:
+    """(source, part) of every object, the sources in parts -- the longest -- first; part is None for a whole source."""
+    units = [(s, i) for s in SOURCES if s in PARTS for i in range(PARTS[s][1])]
+    return units + [(s, None) for s in SOURCES if s not in PARTS]
+
+
+def _compile(unit) -> str:
+    src, part = unit
+    stem = os.path.splitext(src)[0]
+    obj = os.path.join(OBJ, stem + (".o" if part is None else "_%d.o" % part))
+    define = [] if part is None else ["-D%s=%d" % (PARTS[src][0], part)]
+    cmd = ["hipcc"] + FLAGS + EXTRA.get(src, []) + define + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:
@@ -37,8 +49,8 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+    with concurrent.futures.ThreadPoolExecutor(max_workers=8) as ex:
+        objs = list(ex.map(_compile, _units()))
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
     if verbose:

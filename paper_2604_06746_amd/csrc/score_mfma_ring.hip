@@ -73,7 +73,7 @@ template <int NW> constexpr int kKeyCap = NW == 4 ? 2048 : 896;
 // pivot detector's metrics, Eq. 5-6): PPW * SPLIT planes per wave -- PPW = 1 when a wave's rows are one head's window,
 // 2 when each of its two 32-row blocks is; windows of 16 and 8 put SPLIT = 2 and 4 heads into every 32-row block (a
 // 32K-token layer with its metrics, window 8: 57.6 us; 94 us when the layer was re-scored head by head instead).  Most
-// keys a workgroup may then be given: its LDS holds NW * planes sums per key for all tiles but the chunk's last THREE,
+// keys a workgroup may then be given: its LDS holds NW * planes sums per key for all tiles but the loop's last THREE,
 // whose sums go from the registers straight to global memory (no tile load is requested after them any more, so these
 // stores sit behind every load that a wait still counts) -- 20 KB of sums beside three 4-wave workgroups' rings, which
 // is what lets a 128K-token layer be ONE round of 768 workgroups with 1376 keys each (21 KB already cost the third
@@ -163,6 +163,61 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
     for (int ks = 0; ks < KS; ++ks)
       qf[rb][ks] = *reinterpret_cast<const bf16x8*>(qg + (int64_t)grow * D + ks * 16 + 8 * lh);
   }
+  // pass 2: the rows' lse2, requested with the queries
+  float row_lse[PASS == 2 ? NRB : 1] = {};
+  if (PASS == 2) {
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+      row_lse[rb] = lse2[(int64_t)b * G * R + (int64_t)g * R + min(rc * RPC + rb * 32 + l32, R - 1)];
+  }
+
+  const uint16_t* kg = k + (int64_t)(g / kshare) * ksh + tok0 * kst;
+  // Pass 1 goes through the chunk's tiles forwards, pass 2 backwards: all chunks are resident at once where K is small
+  // enough to matter, so what pass 1 left in the XCD's L2 (4 MB) is the end of every chunk (a 32K-token layer with a
+  // window of 8, 64 MB of K: 53.0 -> 50.6 us).
+  auto tile_key = [&](int s) __attribute__((always_inline)) { return key0 + 32 * (PASS == 2 ? nsub - 1 - s : s); };
+  // Tile layout in LDS: 16-byte piece (key, seg) sits at unit key*SEGS + (seg ^ swz(key)); any 16
+  // consecutive keys at a fixed seg then hit 16 different groups of 4 banks (conflict-free operand reads).
+  // Loader: instruction I, lane L writes unit I*64 + L, so it must fetch that unit's (key, seg).
+  auto swz = [&](int key) __attribute__((always_inline)) { return SEGS == 16 ? (key & 15) : ((key >> 1) & 7); };
+  // per-lane byte offsets of the units this lane fetches, relative to the tile's first key row
+  uint32_t voff[IPW];
+#pragma unroll
+  for (int ii = 0; ii < IPW; ++ii) {
+    const int unit = (ii * NW + wave) * 64 + lane;
+    const int key = unit / SEGS;
+    voff[ii] = (uint32_t)(key * kst + ((unit % SEGS) ^ swz(key)) * 8) * 2u;
+  }
+  // (where the key loop is unrolled over the NBUF slots the ring slot is a compile-time number, and slot offsets
+  // fold into the instructions' immediate offsets instead of costing an address addition per LDS read)
+  auto issue_tile = [&](int s_idx, auto slot_tag) __attribute__((always_inline)) {
+    const int jbase = tile_key(s_idx);
+    uint8_t* slot = ring + slot_of(slot_tag) * TILE_BYTES + wave * 1024;
+    const uint8_t* gbase = reinterpret_cast<const uint8_t*>(kg + (int64_t)jbase * kst);   // wave-uniform
+    if (jbase + 32 <= ni) {
+#pragma unroll
+      for (int ii = 0; ii < IPW; ++ii)
+        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(gbase + voff[ii]), (lds_ptr_t)(slot + ii * NW * 1024), 16, 0, NT ? 2 : 0);
+    } else {   // ragged tail: rows past the end re-read the last valid row (their logits are masked)
+#pragma unroll
+      for (int ii = 0; ii < IPW; ++ii) {
+        const int unit = (ii * NW + wave) * 64 + lane;
+        const int key0u = unit / SEGS;
+        const int seg = (unit % SEGS) ^ swz(key0u);
+        const int key = min(key0u, ni - 1 - jbase);
+        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(gbase + (uint32_t)(key * kst + seg * 8) * 2u),
+                                         (lds_ptr_t)(slot + ii * NW * 1024), 16, 0, NT ? 2 : 0);
+      }
+    }
+  };
+  // the first tiles are requested under the query operands' latency
+  auto issue_first = [&]() __attribute__((always_inline)) {
+    if (0 < PD && 0 < nsub) issue_tile(0, IntC<0>{});
+    if (1 < PD && 1 < nsub) issue_tile(1, IntC<1 % NBUF>{});
+    if (2 < PD && 2 < nsub) issue_tile(2, IntC<2 % NBUF>{});
+  };
+  issue_first();
+
   // opaque to the compiler from here on, so that it keeps the operands in registers instead of re-loading
   // them inside the key loop (pinned only after ALL loads are in flight: one latency, not one per load)
 #pragma unroll
@@ -184,7 +239,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
       s16x4 v = {0, 0, 0, 0};
       if (lh == 0) {
         if (row < R) {
-          const float lam = -lse2[(int64_t)b * G * R + (int64_t)g * R + row] / c2;
+          const float lam = -row_lse[rb] / c2;
           const uint16_t hi = bf16_bits(lam);
           const float r1 = lam - bf16_value(hi);
           const uint16_t mid = bf16_bits(r1);
@@ -199,41 +254,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
     }
   }
 
-  const uint16_t* kg = k + (int64_t)(g / kshare) * ksh + tok0 * kst;
-  // Tile layout in LDS: 16-byte piece (key, seg) sits at unit key*SEGS + (seg ^ swz(key)); any 16
-  // consecutive keys at a fixed seg then hit 16 different groups of 4 banks (conflict-free operand reads).
-  // Loader: instruction I, lane L writes unit I*64 + L, so it must fetch that unit's (key, seg).
-  auto swz = [&](int key) __attribute__((always_inline)) { return SEGS == 16 ? (key & 15) : ((key >> 1) & 7); };
-  // per-lane byte offsets of the units this lane fetches, relative to the tile's first key row
-  uint32_t voff[IPW];
-#pragma unroll
-  for (int ii = 0; ii < IPW; ++ii) {
-    const int unit = (ii * NW + wave) * 64 + lane;
-    const int key = unit / SEGS;
-    voff[ii] = (uint32_t)(key * kst + ((unit % SEGS) ^ swz(key)) * 8) * 2u;
-  }
-  // (where the key loop is unrolled over the NBUF slots the ring slot is a compile-time number, and slot offsets
-  // fold into the instructions' immediate offsets instead of costing an address addition per LDS read)
-  auto issue_tile = [&](int s_idx, auto slot_tag) __attribute__((always_inline)) {
-    const int jbase = key0 + 32 * s_idx;
-    uint8_t* slot = ring + slot_of(slot_tag) * TILE_BYTES + wave * 1024;
-    const uint8_t* gbase = reinterpret_cast<const uint8_t*>(kg + (int64_t)jbase * kst);   // wave-uniform
-    if (jbase + 32 <= ni) {
-#pragma unroll
-      for (int ii = 0; ii < IPW; ++ii)
-        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(gbase + voff[ii]), (lds_ptr_t)(slot + ii * NW * 1024), 16, 0, NT ? 2 : 0);
-    } else {   // ragged tail: rows past the end re-read the last valid row (their logits are masked)
-#pragma unroll
-      for (int ii = 0; ii < IPW; ++ii) {
-        const int unit = (ii * NW + wave) * 64 + lane;
-        const int key0u = unit / SEGS;
-        const int seg = (unit % SEGS) ^ swz(key0u);
-        const int key = min(key0u, ni - 1 - jbase);
-        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(gbase + (uint32_t)(key * kst + seg * 8) * 2u),
-                                         (lds_ptr_t)(slot + ii * NW * 1024), 16, 0, NT ? 2 : 0);
-      }
-    }
-  };
   // Operands of the tile being consumed.  Plain loads: an asm ds_read whose result is waited for by a later
   // asm statement is NOT safe -- the compiler may copy the "loaded" register in between, before the data has
   // arrived (it did, in a software-pipelined variant of the key loop).
@@ -406,7 +426,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
       float cs = lo[0] + hi[0];
 #pragma unroll
       for (int wv = 1; wv < NW; ++wv) cs += lo[wv] + hi[wv];
-      const uint32_t o = (uint32_t)__builtin_amdgcn_readfirstlane((int)(csout_lds + (uint32_t)(128 * s_idx))) + lane_x4_lo;
+      const uint32_t o = (uint32_t)__builtin_amdgcn_readfirstlane((int)(csout_lds + (uint32_t)(128 * (nsub - 1 - s_idx)))) + lane_x4_lo;
       asm volatile("ds_write_b32 %0, %1" : : "v"(o), "v"(cs) : "memory");
     }
   };
@@ -421,8 +441,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
       // several planes the lower lane half stores one plane and the upper half the next.
       constexpr int PAIR = NP > 1 ? 2 : 1;
       const int half = PAIR == 2 ? lh : 0;
-      const uint32_t a0 = csout_lds + (uint32_t)(((wave * NP + half) * KCAP + (jbase - key0 + l32)) * 4);
-      const bool last = jbase + 32 * kPlanesDirectTiles >= key_end;   // the chunk's last tiles: straight to their planes
+      const uint32_t a0 = csout_lds + (uint32_t)(((wave * NP + half) * KCAP + (jbase - key0 - 32 * kPlanesDirectTiles + l32)) * 4);
+      const bool last = jbase < key0 + 32 * kPlanesDirectTiles;   // the last tiles of the loop: straight to their planes
 #pragma unroll
       for (int sp = 0; sp < NP; sp += PAIR) {
         float val = add_lane_halves(NP > 1 ? csp[sp] : cs0 + cs1);
@@ -498,7 +518,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
       if constexpr (std::is_same<decltype(slot_tag), int>::value) flush_colsum(s - 2, (s - 2) % 4);
       else flush_colsum(s - 2, IntC<(decltype(slot_tag)::value + 2) % 4>{});
     }
-    const int jbase = key0 + 32 * s;
+    const int jbase = tile_key(s);
     // pass 1 masks the ragged tail and the causal triangle; pass 2 only the causal triangle
     const bool masked = PASS == 1 ? (jbase + 32 > n_full) : (causal && jbase + 32 > n_full);
     if (!masked) rest_of_tile(BoolC<false>{}, jbase, fixed_mode);
@@ -506,13 +526,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
     if constexpr (std::is_same<decltype(slot_tag), int>::value) park_colsum(jbase, s % 4);
     else park_colsum(jbase, slot_tag);
   };
-  // the whole key chunk: prologue (request the first PD tiles), then the loop, unrolled over the ring slots
+  // the whole key chunk, its first PD tiles already requested: the loop, unrolled over the ring slots
   // (-2 %: a tile's ring slot, and with four slots its column-sum slot (tile mod 4), are compile-time numbers
   // inside a step)
   auto run_chunk = [&](auto fixed_mode) __attribute__((always_inline)) {
-    if (0 < PD && 0 < nsub) issue_tile(0, IntC<0>{});
-    if (1 < PD && 1 < nsub) issue_tile(1, IntC<1 % NBUF>{});
-    if (2 < PD && 2 < nsub) issue_tile(2, IntC<2 % NBUF>{});
     // the first tile on its own (it sets the reference when that is fixed), then groups of NBUF tiles
     if (nsub > 0) tile_step(0, IntC<0>{}, BoolC<false>{});
     for (int s0 = 0; s0 + 1 < nsub; s0 += NBUF) {
@@ -548,6 +565,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
       if (__builtin_amdgcn_readfirstlane(flag) != 0) {
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb) { M[rb] = kNegBig; Z[rb] = 0.f; E[rb] = 0.f; }
+        issue_first();
         run_chunk(BoolC<false>{});
       }
     }
@@ -562,8 +580,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
     __syncthreads();
     const int head0 = (int)(t % rcg) * NW * NP;   // the workgroup's first head (heads beyond the group's do not exist)
     for (int pl = 0; pl < NW * NP && head0 + pl < gheads; ++pl) {
-      float* out = colsum + ((int64_t)g * gheads + head0 + pl) * total + tok0 + key0;
-      for (int i = threadIdx.x; i < 32 * (nsub - kPlanesDirectTiles); i += 64 * NW) {   // (the last tiles' sums are there already)
+      float* out = colsum + ((int64_t)g * gheads + head0 + pl) * total + tok0 + key0 + 32 * kPlanesDirectTiles;
+      for (int i = threadIdx.x; i < key_end - key0 - 32 * kPlanesDirectTiles; i += 64 * NW) {   // (the other tiles' sums are there already)
         float v;
         const uint32_t a = csout_lds + (uint32_t)(pl * KCAP + i) * 4u;
         asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(a));
@@ -609,6 +627,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
   }
 }
 
+}  // namespace
+
+// Compiled in five parts, one object each with SKV_RING_PART = 0 .. 4 (the instantiations take minutes in one); part 0
+// also holds the dispatch.
 template <int D, int NRB, int NW, int NBUF>
 hipError_t launch_ring_cfg(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void* q,
                            const void* k, int64_t ksh, int64_t kst, float c2, float* stats,
@@ -646,7 +668,33 @@ hipError_t launch_ring_cfg(const structkv_shape& s, const ScorePlan& p, const Se
   return hipGetLastError();
 }
 
-}  // namespace
+#define SKV_RING_INST(d, nrb, nw, nbuf)                                                                          \
+  template hipError_t launch_ring_cfg<d, nrb, nw, nbuf>(const structkv_shape&, const ScorePlan&, const SeqTable&,  \
+                                                        const void*, const void*, int64_t, int64_t, float, float*, \
+                                                        const float*, float*, int64_t, float*, int, hipStream_t)
+#if SKV_RING_PART == 0
+SKV_RING_INST(128, 2, 4, 4);
+#elif SKV_RING_PART == 1
+SKV_RING_INST(128, 1, 4, 4);
+SKV_RING_INST(128, 1, 1, 2);
+#elif SKV_RING_PART == 2
+SKV_RING_INST(128, 2, 1, 2);
+#elif SKV_RING_PART == 3
+SKV_RING_INST(64, 2, 4, 4);
+SKV_RING_INST(64, 1, 4, 4);
+#else
+SKV_RING_INST(64, 2, 1, 2);
+SKV_RING_INST(64, 1, 1, 2);
+#endif
+
+#if SKV_RING_PART == 0
+extern SKV_RING_INST(128, 1, 4, 4);
+extern SKV_RING_INST(128, 2, 1, 2);
+extern SKV_RING_INST(128, 1, 1, 2);
+extern SKV_RING_INST(64, 2, 4, 4);
+extern SKV_RING_INST(64, 1, 4, 4);
+extern SKV_RING_INST(64, 2, 1, 2);
+extern SKV_RING_INST(64, 1, 1, 2);
 
 hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq,
                                   const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
@@ -654,7 +702,9 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
                                   float* probs, int pass, hipStream_t st) {
   if (p.grid_chunks == 0) return hipSuccess;
   // four waves per workgroup (row-chunks of 64 rows for a KV group of more than 128 rows, of 32 rows for 65..128)
-  // with a 4-tile ring; up to 64 rows: single-wave workgroups with a 2-tile ring (eight of them share a CU's LDS)
+  // with a 4-tile ring; up to 64 rows: single-wave workgroups with a 2-tile ring (eight of them share a CU's LDS; with
+  // a 4-tile ring for the launches that leave four per CU a short ragged layer took 28.3 us instead of 25.1 and a 32K
+  // layer 50.5 instead of 49.6: twice the unrolled code, and no load was waited for longer)
 #define SKV_RING(d, nrb, nw, nbuf)                                                                      \
   if (s.head_dim == d && p.RB == nrb && p.NW == nw)                                                      \
     return launch_ring_cfg<d, nrb, nw, nbuf>(s, p, seq, q, k, ksh, kst, c2, stats, lse2, colsum, total, probs, pass, st)
@@ -669,5 +719,8 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
 #undef SKV_RING
   return hipErrorInvalidValue;
 }
+
+#endif
+#undef SKV_RING_INST
 
 }  // namespace skv
