@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libstructkv.so")
-SOURCES = ["api.cpp", "score_mfma_ring.hip", "score_f32.hip", "score_combine.hip", "topk.hip", "gather.hip",
+SOURCES = ["api.cpp", "score_mfma_ring.hip", "score_f32.hip", "score_short.hip", "score_combine.hip", "topk.hip", "gather.hip",
            "aggregate.hip", "pivot.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-x", "hip",
          # packed-fp32 instruction selection is switched off for all device code

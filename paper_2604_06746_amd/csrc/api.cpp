@@ -152,6 +152,42 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
   p->total_bytes = off;
 }
 
+// carve of a plan of path 2: row entropies, column-sum planes, entropies per head
+void short_carve(const structkv_shape& s, int batch, int64_t total, ScorePlan* p) {
+  size_t off = 0;
+  p->off_stats = p->off_lse = 0;
+  p->off_rowent = off;  off += align_up(sizeof(float) * (size_t)batch * s.n_q_heads * s.window, 256);
+  p->off_colsum = off;  off += align_up(sizeof(float) * (size_t)s.n_kv_heads * p->CP * (size_t)total, 256);
+  p->off_enthead = off; off += align_up(sizeof(float) * (size_t)batch * s.n_q_heads, 256);
+  p->total_bytes = off;
+}
+
+// Short sequences in one scoring launch (score_short.hip) where that is one round of workgroups, at most one per CU, whose
+// registers hold the logits of 2048 (bf16) or 1024 (fp32) keys.  A workgroup reads all keys of its sequence, so the work per
+// CU grows with the length, and beyond 1024 keys more than 32 planes make the sum over them the longer part.
+// A layer step of 32 heads on 8, us a call (in a graph, where launches are cheap), two passes -> one launch:
+//   window 8:  512 keys 30.5 -> 19.5 (18.2 -> 13.4), 1024 keys 30.1 -> 19.1 (18.3 -> 15.8), 2048 keys 30.5 -> 21.8 (19.0 -> 21.1)
+//   window 64: 1024 keys 29.3 -> 22.0 (23.5 -> 21.6); 2048 keys, on the two passes by the rule: 30.9 (24.9), here 30.5 (29.9)
+//   fp32, 8 heads, window 32, d = 64: 1024 keys 29.4 -> 19.8 (23.1 -> 18.9); d = 128, 1000 keys, window 8: 31.1 -> 27.7 (28.5 -> 27.1)
+constexpr int kShortKeysBf16 = 2048, kShortKeysF32 = 1024;
+bool short_plan(const structkv_shape& s, int batch, int64_t longest, int64_t total, ScorePlan* p) {
+  const bool bf16 = s.dtype == STRUCTKV_DTYPE_BF16;
+  if (s.head_dim != 64 && s.head_dim != 128) return false;
+  if (total < 1 || longest > (bf16 ? kShortKeysBf16 : kShortKeysF32)) return false;
+  memset(p, 0, sizeof(*p));
+  p->path = 2;
+  p->R = s.n_q_heads / s.n_kv_heads * s.window;
+  // rows per workgroup: 16, or (bf16) 32 where 16 would make too many planes or workgroups
+  p->RPC = 16;
+  if (bf16 && s.n_kv_heads * ceil_div(p->R, 16) * std::max(batch, 4) > 256) p->RPC = 32;
+  p->RC = p->CP = (int)ceil_div(p->R, p->RPC);
+  p->RB = p->NW = p->WK = p->split = p->kshare = 1;
+  const int planes = longest <= 1024 ? kReduceShortPlanes : kReduceShortPlanes / 2;
+  if ((int64_t)s.n_kv_heads * p->RC > planes || (int64_t)batch * s.n_kv_heads * p->RC > 256) return false;
+  short_carve(s, batch, total, p);
+  return true;
+}
+
 bool mfma_eligible(const structkv_shape& s, const void* q, const void* k, int64_t ksh, int64_t kst) {
   if (s.dtype != STRUCTKV_DTYPE_BF16) return false;
   if (s.head_dim != 64 && s.head_dim != 128) return false;
@@ -179,6 +215,7 @@ struct ScoreOpts {
   bool planes = false;         // pass 2 keeps one column-sum plane per query head (the pivot metrics' input)
   uint32_t* zero_ptr = nullptr;   // words the combine kernel clears on the way (someone's histograms)
   int64_t zero_words = 0;
+  ReduceWork* defer = nullptr;    // where the selection's launch may do the reduce kernel's work: filled in, colsum != NULL
 };
 
 structkv_status run_score(const structkv_shape* shape, const void* q_win, const void* k, int64_t ksh,
@@ -191,6 +228,15 @@ structkv_status run_score(const structkv_shape* shape, const void* q_win, const 
   ScorePlan p;
   make_plan(s, &seq, B, total, !o.force_simt && mfma_eligible(s, q_win, k, ksh, kst), &p, o.planes);
   if (o.planes && !p.planes) return fail(STRUCTKV_ERR_UNSUPPORTED, "per-head planes need the MFMA kernels and a window of 8, 16, 32 or 64");
+  // short sequences: both passes in one launch (with a workspace of less than what structkv_workspace_bytes asks for, the
+  // general plan, which may need less)
+  int64_t longest = 0;
+  for (int b = 0; b < B; ++b) longest = std::max(longest, seq.cu[b + 1] - seq.cu[b]);
+  if (o.step_mask == 15 && !o.force_simt && !o.cache_groups && !o.probs && !o.planes && o.kshare == 1 && !o.fuse && !o.zero_ptr &&
+      (s.dtype == STRUCTKV_DTYPE_BF16 ? p.path == 0 : ksh % 4 == 0 && kst % 4 == 0 && (((uintptr_t)q_win | (uintptr_t)k) & 15) == 0)) {
+    ScorePlan sp;
+    if (short_plan(s, B, longest, total, &sp) && sp.total_bytes <= ws_bytes) p = sp;
+  }
   p.kshare = o.kshare;   // s.n_kv_heads % kshare == 0 (the caller's business)
   if (o.flip_stream_k && p.path == 0) p.stream_k = !p.stream_k;
   if (p.total_bytes > ws_bytes)
@@ -198,7 +244,7 @@ structkv_status run_score(const structkv_shape* shape, const void* q_win, const 
   if ((int64_t)s.n_kv_heads * p.RC * p.n_chunks >= ((int64_t)1 << 31))
     return fail(STRUCTKV_ERR_UNSUPPORTED, "too many workgroups for one launch");
   seq.chunk_start[0] = 0;
-  for (int b = 0; b < B; ++b) {
+  for (int b = 0; b < B && p.path != 2; ++b) {
     const int64_t c = seq.chunk_start[b] + ceil_div(seq.cu[b + 1] - seq.cu[b], p.KC);
     if (c >= ((int64_t)1 << 31)) return fail(STRUCTKV_ERR_UNSUPPORTED, "too many key chunks");
     seq.chunk_start[b + 1] = (int32_t)c;
@@ -273,7 +319,9 @@ structkv_status run_score(const structkv_shape* shape, const void* q_win, const 
       SKV_HIP_CHECK(pass(s, gp, sub, q_g, k, ksh, kst, c2, stats_g, lse2_g, colsum, total, o.probs, 2, st));
     return STRUCTKV_OK;
   };
-  if ((o.step_mask & 7) == 7) {
+  if (p.path == 2) {
+    SKV_HIP_CHECK(launch_score_simt(s, p, seq, q_win, k, ksh, kst, c2, row_ent, nullptr, colsum, total, nullptr, 3, st));
+  } else if ((o.step_mask & 7) == 7) {
     for (int gi = 0; gi < n_groups; ++gi) {
       const structkv_status gs = run_group(gi, 7);
       if (gs != STRUCTKV_OK) return gs;
@@ -286,7 +334,10 @@ structkv_status run_score(const structkv_shape* shape, const void* q_win, const 
           if (gs != STRUCTKV_OK) return gs;
         }
   }
-  if (o.step_mask & 8)
+  if (o.defer && o.step_mask == 15 && !o.fuse && longest <= kReduceShortSeq && s.n_kv_heads * p.CP <= kReduceShortPlanes)
+    *o.defer = {colsum, s.n_kv_heads * p.CP, total, indeg, row_ent, ent_head, entropy, s.n_q_heads, s.window, o.centrality,
+                o.lambda, o.inv_w};
+  else if (o.step_mask & 8)
     SKV_HIP_CHECK(launch_score_reduce(s, p, seq, colsum, total, indeg, row_ent, ent_head, entropy, o.centrality,
                                       o.lambda, o.inv_w, o.fuse, st));
   if (o.groups) SKV_HIP_CHECK(launch_group_sums(s, p, colsum, total, o.groups, st));
@@ -314,6 +365,9 @@ size_t structkv_workspace_bytes(const structkv_shape* shape, int32_t batch, int6
       make_plan(*shape, nullptr, batch, total_tokens, mfma == 1, &p);
       if (p.total_bytes > need) need = p.total_bytes;
     }
+    ScorePlan p;   // (grows with total_tokens: from the longest short call on it stays)
+    const int64_t most = (int64_t)batch * (shape->dtype == STRUCTKV_DTYPE_BF16 ? kShortKeysBf16 : kShortKeysF32);
+    if (short_plan(*shape, batch, 0, std::min(total_tokens, most), &p) && p.total_bytes > need) need = p.total_bytes;
   }
   return align_up(need, 256);
 }
@@ -663,13 +717,16 @@ structkv_status layer_finish_impl(const structkv_shape* shape, const LayerStepPl
 }
 }  // namespace
 
-structkv_status structkv_layer_begin(const structkv_shape* shape, const void* q_win, const void* k, const void* v,
+// The first half of a layer step.  defer: the second half follows in the same call, and its selection may do the reduce
+// kernel's work (then filled in).
+static structkv_status layer_begin_impl(const structkv_shape* shape, const void* q_win, const void* k, const void* v,
                                      int64_t kv_stride_head, int64_t kv_stride_tok, int32_t batch,
                                      const int64_t* cu_seqlens, const int64_t* k_per_seq, int32_t keep_tail,
                                      float* indeg_out, float* centrality, float lambda, float inv_w,
                                      float* entropy_out, float* entropy_per_head_out, int32_t* idx_out, void* k_dst,
                                      void* v_dst, int64_t dst_stride_head, int64_t dst_stride_tok, void* workspace,
-                                     size_t workspace_bytes, void* stream) {
+                                     size_t workspace_bytes, void* stream, LayerStepPlan* plan, bool* done,
+                                     ReduceWork* defer) {
   clear_error();
   if (centrality) {
     if (!(lambda > 0.f && lambda <= 1.f)) return fail(STRUCTKV_ERR_INVALID_ARG, "lambda must be in (0,1]");
@@ -677,17 +734,31 @@ structkv_status structkv_layer_begin(const structkv_shape* shape, const void* q_
     if ((uintptr_t)centrality & 3) return fail(STRUCTKV_ERR_INVALID_ARG, "centrality is not 4-byte aligned");
     if (centrality == indeg_out) return fail(STRUCTKV_ERR_INVALID_ARG, "centrality must not alias indeg_out");
   }
-  LayerStepPlan p;
-  bool done = false;
+  LayerStepPlan& p = *plan;
   structkv_status st = plan_layer_step(shape, k, v, kv_stride_head, kv_stride_tok, batch, cu_seqlens, k_per_seq,
                                        keep_tail, indeg_out, idx_out, k_dst, v_dst, dst_stride_head, dst_stride_tok,
-                                       workspace, workspace_bytes, &p, &done);
-  if (st != STRUCTKV_OK || done) return st;
+                                       workspace, workspace_bytes, &p, done);
+  if (st != STRUCTKV_OK || *done) return st;
   ScoreOpts o;
   o.centrality = centrality; o.lambda = lambda; o.inv_w = inv_w;
   o.fuse = p.rows > 0 && p.tws.mode != kSelShort ? &p.fuse : nullptr;   // (the short form needs nothing from the scoring)
+  if (p.rows > 0 && p.tws.mode == kSelShort) o.defer = defer;
   return score_layer_impl(shape, q_win, k, kv_stride_head, kv_stride_tok, batch, cu_seqlens, indeg_out, entropy_out,
                           entropy_per_head_out, workspace, p.score_bytes, stream, o, &p.sel);
+}
+
+structkv_status structkv_layer_begin(const structkv_shape* shape, const void* q_win, const void* k, const void* v,
+                                     int64_t kv_stride_head, int64_t kv_stride_tok, int32_t batch,
+                                     const int64_t* cu_seqlens, const int64_t* k_per_seq, int32_t keep_tail,
+                                     float* indeg_out, float* centrality, float lambda, float inv_w,
+                                     float* entropy_out, float* entropy_per_head_out, int32_t* idx_out, void* k_dst,
+                                     void* v_dst, int64_t dst_stride_head, int64_t dst_stride_tok, void* workspace,
+                                     size_t workspace_bytes, void* stream) {
+  LayerStepPlan p;
+  bool done = false;
+  return layer_begin_impl(shape, q_win, k, v, kv_stride_head, kv_stride_tok, batch, cu_seqlens, k_per_seq, keep_tail,
+                          indeg_out, centrality, lambda, inv_w, entropy_out, entropy_per_head_out, idx_out, k_dst, v_dst,
+                          dst_stride_head, dst_stride_tok, workspace, workspace_bytes, stream, &p, &done, nullptr);
 }
 
 structkv_status structkv_layer_finish(const structkv_shape* shape, const void* k, const void* v,
@@ -714,14 +785,17 @@ structkv_status structkv_layer_step(const structkv_shape* shape, const void* q_w
                                     float* entropy_out, float* entropy_per_head_out, int32_t* idx_out, void* k_dst,
                                     void* v_dst, int64_t dst_stride_head, int64_t dst_stride_tok, void* workspace,
                                     size_t workspace_bytes, void* stream) {
-  structkv_status st = structkv_layer_begin(shape, q_win, k, v, kv_stride_head, kv_stride_tok, batch, cu_seqlens,
-                                            k_per_seq, keep_tail, indeg_out, centrality, lambda, inv_w, entropy_out,
-                                            entropy_per_head_out, idx_out, k_dst, v_dst, dst_stride_head,
-                                            dst_stride_tok, workspace, workspace_bytes, stream);
-  if (st != STRUCTKV_OK) return st;
-  return structkv_layer_finish(shape, k, v, kv_stride_head, kv_stride_tok, batch, cu_seqlens, k_per_seq, keep_tail,
-                               indeg_out, idx_out, k_dst, v_dst, dst_stride_head, dst_stride_tok, workspace,
-                               workspace_bytes, stream);
+  LayerStepPlan p;
+  ReduceWork red{};
+  bool done = false;
+  const structkv_status st =
+      layer_begin_impl(shape, q_win, k, v, kv_stride_head, kv_stride_tok, batch, cu_seqlens, k_per_seq, keep_tail, indeg_out,
+                       centrality, lambda, inv_w, entropy_out, entropy_per_head_out, idx_out, k_dst, v_dst, dst_stride_head,
+                       dst_stride_tok, workspace, workspace_bytes, stream, &p, &done, &red);
+  if (st != STRUCTKV_OK || done) return st;
+  if (red.colsum) p.tws.red = &red;
+  return layer_finish_impl(shape, p, k, v, kv_stride_head, kv_stride_tok, keep_tail, indeg_out, idx_out, k_dst, v_dst,
+                           dst_stride_head, dst_stride_tok, (hipStream_t)stream);
 }
 
 structkv_status structkv_truncate_hidden(const void* h_src, int64_t src_stride_tok, void* h_dst,

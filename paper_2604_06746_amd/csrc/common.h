@@ -66,6 +66,39 @@ __device__ inline void merge_stats(float& M, float& Z, float& E, float M2, float
 }
 #endif
 
+#ifdef __HIPCC__
+// Eq. 4's means over window rows and heads for sequence b, by the first 256 threads of the calling workgroup (all of its
+// threads call): eight lanes share a head, each sums every eighth window row, then a fixed shuffle tree
+__device__ inline void finish_entropy(const float* __restrict__ row_ent, float* __restrict__ ent_head, float* __restrict__ entropy,
+                                      int b, int Hq, int w, float (&hsum)[256]) {
+  float part = 0.f;
+  for (int h0i = 0; h0i < Hq && threadIdx.x < 256; h0i += 32) {   // (whole waves)
+    const int h = h0i + (threadIdx.x >> 3);
+    float s = 0.f;
+    if (h < Hq) {
+      const float* re = row_ent + ((int64_t)b * Hq + h) * w;
+      for (int i = threadIdx.x & 7; i < w; i += 8) s += re[i];
+    }
+    s += __shfl_xor(s, 1);
+    s += __shfl_xor(s, 2);
+    s += __shfl_xor(s, 4);
+    if (h < Hq && (threadIdx.x & 7) == 0) {
+      s /= (float)w;
+      ent_head[(int64_t)b * Hq + h] = s;
+      part += s;
+    }
+  }
+  if (threadIdx.x < 256) hsum[threadIdx.x] = part;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float s = 0.f;
+    for (int t = 0; t < 256; t += 8) s += hsum[t];
+    entropy[b] = s / (float)Hq;
+  }
+  __syncthreads();
+}
+#endif
+
 // ---- selection (radix select on order-preserving keys) ---------------------------------------
 constexpr int kTopkBins = 2048;      // digits 0 and 1: 11 bits each; digit 2: the last 10 bits
 
@@ -118,7 +151,24 @@ struct TopkWs {
   int cand_cap;      // mid: most candidates listed per sequence
   int mode;          // kSelShort / kSelMid / kSelLong
   float mass;        // > 0: the scores are in-degrees with this sum per sequence (fused layer step)
+  const struct ReduceWork* red;   // (host) short: the kernel forms the scores itself (a layer step of short sequences)
 };
+
+// What the reduce kernel does after pass 2; in a layer step of short sequences the selection's only launch does it.
+struct ReduceWork {
+  const float* colsum;   // [planes][total]
+  int planes;
+  int64_t total;
+  float* indeg;
+  const float* row_ent;  // [B][Hq][w]
+  float* ent_head;
+  float* entropy;
+  int Hq, w;
+  float* cen;            // or NULL; C <- lambda C + inv_w D
+  float lambda, inv_w;
+};
+// ... up to this many tokens a sequence and planes: a workgroup sums its sequence's planes alone, eight or sixteen in flight
+constexpr int kReduceShortSeq = 2048, kReduceShortPlanes = 64;
 
 // What the scoring call's small kernels do for the selection that follows it in a fused layer step: the
 // combine kernel zeroes the digit histograms, the reduce kernel histograms the first digit of the scores
@@ -135,7 +185,7 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 
 // ---- scoring plan: how one structkv_score_layer call is cut into workgroups ----------------
 struct ScorePlan {
-  int path;          // 0 = bf16 kernels, 1 = fp32 kernels (inputs widened)
+  int path;          // 0 = bf16 kernels, 1 = fp32 kernels (inputs widened), 2 = both passes at once (score_short.hip)
   int R;             // query rows per KV head: (H_q/G) * w
   int RPC;           // rows per row-chunk (a workgroup's share of R)
   int RC;            // row-chunks per KV head
@@ -162,10 +212,13 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
                                   const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
                                   float* stats, const float* lse2, float* colsum, int64_t total,
                                   float* probs, int pass, hipStream_t st);
+// pass 3 (a plan of path 2): both passes in one launch (launch_score_short); `stats` takes the row entropies
 hipError_t launch_score_simt(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq,
                              const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
                              float* stats, const float* lse2, float* colsum, int64_t total,
                              float* probs, int pass, hipStream_t st);
+hipError_t launch_score_short(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void* q, const void* k,
+                              int64_t ksh, int64_t kst, float c2, float* row_ent, float* colsum, int64_t total, hipStream_t st);
 // zero_words > 0: the kernel also clears that many 32-bit words at zero_ptr (the selection's histograms)
 hipError_t launch_score_combine(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq,
                                 const float* stats, float* lse2, float* row_ent, uint32_t* zero_ptr,

@@ -177,34 +177,8 @@ __global__ __launch_bounds__(FUSE ? 1024 : 256) void score_reduce_kernel(
       fs.idx_out[seq.out_off[b] + seq.k[b] + i] = (int32_t)(seq.cu[b + 1] - seq.cu[b] - tail + i);
     }
   }
-  for (int b = blockIdx.x; b < B; b += gridDim.x) {   // uniform per workgroup
-    // eight lanes share a head: each sums every eighth window row, then a fixed shuffle tree
-    float part = 0.f;
-    for (int h0i = 0; h0i < Hq && threadIdx.x < 256; h0i += 32) {   // (whole waves)
-      const int h = h0i + (threadIdx.x >> 3);
-      float s = 0.f;
-      if (h < Hq) {
-        const float* re = row_ent + ((int64_t)b * Hq + h) * w;
-        for (int i = threadIdx.x & 7; i < w; i += 8) s += re[i];
-      }
-      s += __shfl_xor(s, 1);
-      s += __shfl_xor(s, 2);
-      s += __shfl_xor(s, 4);
-      if (h < Hq && (threadIdx.x & 7) == 0) {
-        s /= (float)w;
-        ent_head[(int64_t)b * Hq + h] = s;
-        part += s;
-      }
-    }
-    if (threadIdx.x < 256) hsum[threadIdx.x] = part;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float s = 0.f;
-      for (int t = 0; t < 256; t += 8) s += hsum[t];
-      entropy[b] = s / (float)Hq;
-    }
-    __syncthreads();
-  }
+  for (int b = blockIdx.x; b < B; b += gridDim.x)   // uniform per workgroup
+    finish_entropy(row_ent, ent_head, entropy, b, Hq, w, hsum);
 }
 
 // per-KV-head in-degree: the column-sum planes of head g added up in plane order

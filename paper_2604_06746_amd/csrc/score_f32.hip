@@ -222,6 +222,7 @@ hipError_t launch_cfg(const structkv_shape& s, const ScorePlan& p, const SeqTabl
 hipError_t launch_score_simt(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void* q,
                              const void* k, int64_t ksh, int64_t kst, float c2, float* stats, const float* lse2,
                              float* colsum, int64_t total, float* probs, int pass, hipStream_t st) {
+  if (pass == 3) return launch_score_short(s, p, seq, q, k, ksh, kst, c2, stats, colsum, total, st);
   if (p.grid_chunks == 0) return hipSuccess;
   const size_t e = s.dtype == STRUCTKV_DTYPE_F32 ? 4 : 2;
   // four components per load: whole groups of eight, rows and pointers aligned to the load

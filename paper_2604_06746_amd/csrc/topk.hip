@@ -385,6 +385,7 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* __res
 // ---- short and mid forms ----------------------------------------------------------------------------------------
 
 constexpr int kWide = 1024;        // threads of a short-form workgroup
+static_assert(kReduceShortSeq <= 2 * kWide, "a workgroup that forms the scores holds two per thread");
 constexpr int kMidShare = 1024;    // scores of a mid-form workgroup: four per thread
 constexpr int kMidPer = kMidShare / kThreads;
 constexpr int kListed = 64;        // keys that one wave ranks directly
@@ -481,10 +482,13 @@ __device__ inline void place_ordered(const uint32_t (&key)[PER], int j0, int m, 
   }
 }
 
-// short form: one workgroup per sequence of at most PER x 1024 scores; also writes the kept window
-template <int PER, class TAB>
+// short form: one workgroup per sequence of at most PER x 1024 scores; also writes the kept window.
+// SUM (a layer step): it first does what the reduce kernel does -- the column-sum planes of its sequence's tokens (at most
+// PER x 1024 with the window) added up in ascending order, the centrality update, the entropies' means -- and selects on the
+// scores it holds: one launch fewer (a layer step of 1K tokens is a handful of 3 us kernels: see short_plan in api.cpp).
+template <int PER, class TAB, bool SUM>
 __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
-                                                           int32_t* __restrict__ idx_out) {
+                                                           int32_t* __restrict__ idx_out, ReduceWork red) {
   short_kernel_priority();
   constexpr int NWV = kWide / 64;
   __shared__ ResolveLds l;
@@ -495,8 +499,40 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
   const float* sc = scores + seq.cu[b];
   int32_t* out = idx_out + seq.out_off[b];
   float v[PER];
+  if constexpr (SUM) {
+    __shared__ float hsum[256];
+    constexpr int U = 16 / PER;   // planes in flight
+    const int n = m + keep_tail;
+    int64_t at[PER];
+    float c[PER];
 #pragma unroll
-  for (int i = 0; i < PER; ++i) v[i] = k > 0u && i * kWide + t < m ? sc[i * kWide + t] : 0.f;
+    for (int i = 0; i < PER; ++i) {
+      at[i] = seq.cu[b] + max(0, min(i * kWide + t, n - 1));   // (an empty sequence reads nothing below)
+      v[i] = 0.f;
+      c[i] = red.cen && n > 0 ? red.cen[at[i]] : 0.f;
+    }
+    for (int p = 0; n > 0 && p < red.planes; p += U) {
+      float x[U][PER];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) x[u][i] = p + u < red.planes ? red.colsum[(int64_t)(p + u) * red.total + at[i]] : 0.f;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) v[i] += x[u][i];
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (i * kWide + t < n) {
+        red.indeg[at[i]] = v[i];
+        if (red.cen) red.cen[at[i]] = fmaf(red.lambda, c[i], red.inv_w * v[i]);
+      }
+    finish_entropy(red.row_ent, red.ent_head, red.entropy, b, red.Hq, red.w, hsum);
+  } else {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) v[i] = k > 0u && i * kWide + t < m ? sc[i * kWide + t] : 0.f;
+  }
   for (int i = t; i < keep_tail; i += kWide) out[k + i] = m + i;
   if (k == 0u) return;
   for (int i = t; i < kBins; i += kWide) l.hist[i] = 0u;
@@ -919,6 +955,7 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
   }
   ws->mode = longest <= kShortSeq ? kSelShort : longest <= kMidSeq ? kSelMid : kSelLong;
   ws->mass = 0.f;
+  ws->red = nullptr;
   ws->cand_cap = kCandTotal / (B > 0 ? B : 1) < kCandCap ? kCandTotal / (B > 0 ? B : 1) : kCandCap;
   const int target = ws->mode == kSelMid ? kMidShare : share_target(plan->cu[B]);
   plan->chunk_start[0] = 0;
@@ -948,12 +985,15 @@ hipError_t launch_topk_rest(const float* scores, const SeqTable& plan, int keep_
     if (ws.mode == kSelShort) {
       int64_t longest = 0;
       for (int b = 0; b < plan.batch; ++b)
-        if (plan.k[b] > 0) longest = std::max(longest, plan.cu[b + 1] - plan.cu[b] - keep_tail);
-#define SKV_SHORT(PER) \
-  hipLaunchKernelGGL((topk_short_kernel<PER, T>), dim3((unsigned)plan.batch), dim3(kWide), 0, st, scores, tab, keep_tail, idx_out)
-      if (longest <= 2 * kWide) SKV_SHORT(2);
-      else if (longest <= 4 * kWide) SKV_SHORT(4);
-      else SKV_SHORT(8);
+        if (ws.red || plan.k[b] > 0) longest = std::max(longest, plan.cu[b + 1] - plan.cu[b] - (ws.red ? 0 : keep_tail));
+      const ReduceWork red = ws.red ? *ws.red : ReduceWork{};
+#define SKV_SHORT(PER, SUM)                                                                                             \
+  hipLaunchKernelGGL((topk_short_kernel<PER, T, SUM>), dim3((unsigned)plan.batch), dim3(kWide), 0, st, scores, tab, keep_tail, \
+                     idx_out, red)
+      if (ws.red) { if (longest <= kWide) SKV_SHORT(1, true); else SKV_SHORT(2, true); }
+      else if (longest <= 2 * kWide) SKV_SHORT(2, false);
+      else if (longest <= 4 * kWide) SKV_SHORT(4, false);
+      else SKV_SHORT(8, false);
 #undef SKV_SHORT
     } else if (blocks == 0) {
       return;

@@ -139,3 +139,52 @@ def test_pivot_metrics_of_short_windows(sweep_mod, oracle, Hq, G, d, w, lens, ca
 @pytest.mark.parametrize("lens", [[64], [65, 1, 0, 200], [5000], [17000, 31]])
 def test_short_key_chunks(sweep_mod, oracle, Hq, G, w, lens):
     _check_scores(sweep_mod, oracle, Hq, G, 128, w, torch.bfloat16, False, lens)
+
+
+# short sequences in one scoring launch: edges of the 16-key tiles, of the two, four and eight tiles per wave (512, 1024,
+# 2048 keys) and of the path itself (1024 fp32 / 2048 bf16 keys, 64 column-sum planes), rows around the 16- and 32-row
+# blocks, one and two row blocks per workgroup, empty sequences; then the layer step, whose selection forms the in-degrees itself, against the separate calls
+@pytest.mark.parametrize("Hq,G,d,w", [(1, 1, 64, 1), (3, 1, 128, 5), (8, 8, 64, 32), (32, 8, 128, 8), (4, 2, 64, 17), (16, 2, 128, 64),
+                                      (32, 8, 64, 64)])
+@pytest.mark.parametrize("lens", [[1], [15, 0, 17], [255, 256, 257], [512, 513], [1024], [1025, 33], [2048], [2049, 5]])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("causal", [False, True])
+def test_short_sequences_in_one_scoring_launch(sweep_mod, oracle, Hq, G, d, w, lens, dtype, causal):
+    if causal:
+        lens = [max(n, w) if n else 0 for n in lens]
+    _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens)
+    lens = [max(n, w) for n in lens]
+    ks = [(n - w) // 3 for n in lens]
+    q = _randn(len(lens), Hq, w, d, dtype=dtype, seed=9)
+    k, v = (_randn(G, sum(lens), d, dtype=dtype, seed=s) for s in (10, 11))
+    sweeps = [sweep_mod.LayerSweep(Hq, G, d, w, dtype, lens, ks, causal=causal) for _ in range(2)]
+    for _ in range(2):   # (the second layer updates a centrality that is not zero)
+        sweeps[0].layer(q, k, v)
+        sweeps[1].layer_separate_calls(q, k, v)
+    for name in ("indeg", "centrality", "entropy", "entropy_per_head", "idx_kv", "k_cache", "v_cache"):
+        assert torch.equal(getattr(sweeps[0], name), getattr(sweeps[1], name)), name
+
+
+# ... and the same plan with a workspace that only the two-pass plan fits
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_short_sequences_with_a_smaller_workspace(B, oracle, dtype):
+    Hq, G, d, w, n = 16, 2, 64, 64, 900
+    code = B.STRUCTKV_DTYPE_F32 if dtype == torch.float32 else B.STRUCTKV_DTYPE_BF16
+    shape = B.make_shape(Hq, G, d, w, code)
+    need = B.structkv_workspace_bytes(shape, 1, n)
+    q, k = _randn(1, Hq, w, d, dtype=dtype, seed=12), _randn(G, n, d, dtype=dtype, seed=13)
+    D, ent, ent_h, _ = oracle.score_layer(to_oracle_array(q), to_oracle_array(k), Hq, G, d, w, [n])
+    tol = 1e-5 if dtype == torch.float32 else 1e-3
+    refused = 0
+    for nbytes in range(need, 0, -max(need // 16 // 256 * 256, 256)):
+        out, e, eh = torch.zeros(n, device="cuda"), torch.zeros(1, device="cuda"), torch.zeros(1, Hq, device="cuda")
+        ws = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+        try:
+            B.structkv_score_layer(shape, q, k, [0, n], out, e, eh, ws)
+        except B.StructKVError as err:
+            assert err.status == B.STRUCTKV_ERR_WORKSPACE and nbytes < need
+            refused += 1
+            continue
+        assert not refused   # (a larger one was accepted)
+        assert_close_floor(out.cpu().numpy(), D, tol, "indeg")
+        assert_entropy(e.cpu().numpy(), ent, tol)
