@@ -54,6 +54,15 @@ void with_table(const SeqTable& s, F f) {
 #ifdef __HIPCC__
 __device__ __forceinline__ void short_kernel_priority() { __builtin_amdgcn_s_setprio(2); }
 
+// the exponent of a masked logit (-infinity) made one whose terms vanish: 2^-200 = 0, and 0 * -200 = 0.  The maximum is the
+// one that passes NaN on: fmaxf would take a logit that is not a number for a masked one (and the builtin becomes fmaxf
+// where a file is compiled without regard to NaN).
+__device__ __forceinline__ float clamp_exponent(float x) {
+  float r;
+  asm("v_maximum3_f32 %0, %1, %2, %2" : "=v"(r) : "v"(x), "s"(-200.f));
+  return r;
+}
+
 // merge partial softmax statistics (M, Z, E) of two disjoint key sets, log2 domain:
 //   Z = sum 2^(x-M),  E = sum 2^(x-M) (x-M)
 __device__ inline void merge_stats(float& M, float& Z, float& E, float M2, float Z2, float E2) {

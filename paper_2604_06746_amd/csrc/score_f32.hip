@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256, DP == 256 ? 1 : 2) void score_f32_kernel(
       float z = Z * f, e = (E + dl * Z) * f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const float x = fmaxf(fmaf(acc[i], c2, -Mn), -200.f);   // 2^-200 = 0, and 0 * -200 = 0
+        const float x = clamp_exponent(fmaf(acc[i], c2, -Mn));
         const float p = __builtin_amdgcn_exp2f(x);
         z += p;
         e = fmaf(p, x, e);

@@ -313,7 +313,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
         for (int i = 0; i < 16; i += 2) {
           float ta = fmaf(acc[i], c2, nm);
           float tb = fmaf(acc[i + 1], c2, nm);
-          if (MASKED) { ta = fmaxf(ta, -200.f); tb = fmaxf(tb, -200.f); }
+          if (MASKED) { ta = clamp_exponent(ta); tb = clamp_exponent(tb); }
           const float pa = __builtin_amdgcn_exp2f(ta);
           const float pb = __builtin_amdgcn_exp2f(tb);
           z0 += pa; z1 += pb;
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
       for (int i = 0; i < 16; i += 2) {
         float ta = fmaf(acc[i], c2, nm);
         float tb = fmaf(acc[i + 1], c2, nm);
-        if (MASKED) { ta = fmaxf(ta, -200.f); tb = fmaxf(tb, -200.f); }   // 2^-200 = 0, and 0 * -200 = 0
+        if (MASKED) { ta = clamp_exponent(ta); tb = clamp_exponent(tb); }
         const float pa = __builtin_amdgcn_exp2f(ta);
         const float pb = __builtin_amdgcn_exp2f(tb);
         z0 += pa; z1 += pb;

@@ -136,12 +136,14 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
 
   // tiles that some row does not see whole (uniform in the wave): the masks and their clamp cost a fifth of the vector work
   auto masked = [&](int i) __attribute__((always_inline)) { return tile0(i) + 16 > (causal ? n - w : n); };
+  // keys a row sees: all, or up to its own place in the window (the row modulo the window; rows stay below 65536)
+  auto seen = [&](int row) __attribute__((always_inline)) {
+    return causal ? n - w + row - w * (int)__umulhi((uint32_t)row, w_recip) + 1 : n;
+  };
   float M[NRB], Z[NRB], E[NRB];
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) {
-    const int row = (rc * NRB + rb) * 16 + l16;
-    // keys this row sees: all, or up to its own place in the window (the row modulo the window; rows stay below 65536)
-    const int lim = causal ? n - w + row - w * (int)__umulhi((uint32_t)row, w_recip) + 1 : n;
+    const int lim = seen((rc * NRB + rb) * 16 + l16);
     float m = -INFINITY;
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
       for (int j = 0; j < 4; ++j) xs[j] = fmaf(acc[rb][i][j], c2, -M[rb]);
       if (masked(i)) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) xs[j] = fmaxf(xs[j], -200.f);   // 2^-200 = 0, and 0 * -200 = 0
+        for (int j = 0; j < 4; ++j) xs[j] = clamp_exponent(xs[j]);
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -204,11 +206,23 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
     const int key = tile0(i) + 4 * lg + l16;   // (of the lanes that write: l16 < 4)
     if (tile0(i) >= n) continue;
     float mine = 0.f;
+    if (masked(i)) {   // (a row that is not a number stays off the keys that it does not see)
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (tile0(i) + 4 * lg + j >= seen((rc * NRB + rb) * 16 + l16)) acc[rb][i][j] = -INFINITY;
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float s = acc[0][i][j] * inv[0];
+      float s = 0.f;
+      if (masked(i)) {
 #pragma unroll
-      for (int rb = 1; rb < NRB; ++rb) s = fmaf(acc[rb][i][j], inv[rb], s);
+        for (int rb = 0; rb < NRB; ++rb) s = acc[rb][i][j] == -INFINITY ? s : fmaf(acc[rb][i][j], inv[rb], s);
+      } else {
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) s = fmaf(acc[rb][i][j], inv[rb], s);
+      }
       s = row_sum(s);
       if (l16 == j) mine = s;
     }

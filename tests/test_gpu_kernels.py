@@ -188,3 +188,34 @@ def test_short_sequences_with_a_smaller_workspace(B, oracle, dtype):
         assert not refused   # (a larger one was accepted)
         assert_close_floor(out.cpu().numpy(), D, tol, "indeg")
         assert_entropy(e.cpu().numpy(), ent, tol)
+
+
+# inputs that are not finite: a NaN key makes its whole sequence NaN (in the masked tiles too), a NaN query row reaches
+# the keys that it sees and no others; the sequences beside it are untouched
+@pytest.mark.parametrize("dtype,w,lens", [(torch.float32, 32, [1500, 40]), (torch.float32, 8, [900, 300]), (torch.bfloat16, 8, [3000, 90]),
+                                          (torch.bfloat16, 64, [5000, 64]), (torch.bfloat16, 8, [700, 33]), (torch.bfloat16, 64, [1000, 65])])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_inputs_that_are_not_finite(sweep_mod, oracle, dtype, w, lens, causal, value):
+    Hq, G, d = 8, 2, 128
+    q, k = _randn(2, Hq, w, d, dtype=dtype, seed=14), _randn(G, sum(lens), d, dtype=dtype, seed=15)
+    tol = 1e-5 if dtype == torch.float32 else 1e-3
+    D, ent, _, _ = oracle.score_layer(to_oracle_array(q), to_oracle_array(k), Hq, G, d, w, lens, causal=causal)
+    n = lens[0]
+    sw = sweep_mod.LayerSweep(Hq, G, d, w, dtype, lens, [0, 0], causal=causal)
+    for key in (0, n // 2, n - w, n - w + 3, n - 1):
+        bad = k.clone()
+        bad[1, key] = value   # (an infinite key: logits of both signs, or NaN)
+        sw.score(q, bad)
+        got, e = sw.indeg.cpu().numpy(), sw.entropy.cpu().numpy()
+        assert np.isnan(got[:n]).all() and np.isnan(e[0]), key   # (the window's last row sees every key)
+        assert_close_floor(got[n:], D[n:], tol, "the other sequence")
+        assert_entropy(e[1:2], ent[1:2], tol)
+    for row in (0, 3, w - 1):
+        bad = q.clone()
+        bad[0, 5, row] = float("nan")
+        sw.score(bad, k)
+        got = sw.indeg.cpu().numpy()
+        seen = n - w + row + 1 if causal else n
+        assert np.isnan(got[:seen]).all() and not np.isnan(got[seen:]).any(), row
+        assert_close_floor(got[n:], D[n:], tol, "the other sequence")
