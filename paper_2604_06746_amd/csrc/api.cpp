@@ -570,11 +570,11 @@ structkv_status structkv_select_topk_static(const float* scores, int32_t batch, 
   size_t scratch_bytes = 0;
   SKV_HIP_CHECK(topk_static_scratch(&scratch_ptr, &scratch_bytes));
   const size_t need = topk_workspace_bytes(batch, seq.cu[batch]);
-  if (need > scratch_bytes)
+  if (!topk_static_fits(batch, seq.cu[batch]) || need > scratch_bytes)
     return fail(STRUCTKV_ERR_UNSUPPORTED,
-                "this selection needs %zu bytes of scratch, the library's static scratch holds %zu "
+                "this selection needs %zu bytes of scratch, more than the library's static scratch is meant for "
                 "(enough for %d sequences with %d tokens in all); use structkv_select_topk with a workspace",
-                need, scratch_bytes, kMaxBatch, STRUCTKV_STATIC_TOPK_MAX_TOKENS);
+                need, kMaxBatch, STRUCTKV_STATIC_TOPK_MAX_TOKENS);
   SKV_HIP_CHECK(launch_topk(scores, seq, keep_tail, idx_out, scratch_ptr, (hipStream_t)stream));
   return STRUCTKV_OK;
 }

@@ -250,7 +250,9 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
 hipError_t launch_topk_rest(const float* scores, const SeqTable& plan, int keep_tail, const TopkWs& ws,
                             unsigned blocks, int32_t* idx_out, hipStream_t st);
 size_t topk_workspace_bytes(int batch, int64_t total_tokens);
-// the library's own top-k scratch on the current device (structkv_select_topk_static); no allocation
+// the library's own top-k scratch on the current device (structkv_select_topk_static); no allocation.  It takes the calls
+// that topk_static_fits names (whatever forms the selection takes, and whatever words those need)
+bool topk_static_fits(int batch, int64_t total_tokens);
 hipError_t topk_static_scratch(void** ptr, size_t* bytes);
 // pivot metrics: partial sums part [H][kPivotMaxSlices][2] of every head, then the means over the heads
 constexpr int kPivotMaxSlices = 64;

@@ -28,7 +28,9 @@ namespace {
 // search state and per-workgroup suffix sums that structkv_select_topk takes from the caller's workspace live
 // here instead.  Every GPU the library runs on holds its own copy until the process ends.  In host code the
 // array's name is only a handle for hipGetSymbolAddress; kernels get the address that call returns.
-constexpr size_t kStaticScratchBytes = (size_t)4 << 20;
+// It takes the calls whose histograms and suffix sums fill 4 MiB at most; the mid form's words come on top.
+constexpr size_t kStaticScratchLists = (size_t)4 << 20;
+constexpr size_t kStaticScratchBytes = kStaticScratchLists + kMaxBatch * 256;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 constexpr int kThreads = 256;
@@ -920,6 +922,14 @@ size_t topk_workspace_bytes(int batch, int64_t total_tokens) {
   const size_t nb = max_blocks(batch, total_tokens);
   return align_up(sizeof(uint32_t) * 3 * B * kBins, 256) + align_up(sizeof(uint32_t) * 8 * B, 256) +
          lists_bytes(B, total_tokens, nb) + align_up(sizeof(uint32_t) * 2 * nb, 256);
+}
+
+// digit histograms, search state of the long form, suffix sums and counts: what the static scratch's limit is stated in
+bool topk_static_fits(int batch, int64_t total_tokens) {
+  const size_t B = (size_t)(batch > 0 ? batch : 1);
+  const size_t nb = max_blocks(batch, total_tokens);
+  return align_up(sizeof(uint32_t) * 3 * B * kBins, 256) + align_up(sizeof(uint32_t) * 4 * B, 256) +
+         align_up(sizeof(uint32_t) * kLowBins * nb, 256) + align_up(sizeof(uint32_t) * 2 * nb, 256) <= kStaticScratchLists;
 }
 
 // Device address and size of the static scratch on the CURRENT device (looked up once per device).

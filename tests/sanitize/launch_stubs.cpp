@@ -63,6 +63,7 @@ hipError_t launch_topk(const float*, const SeqTable&, int, int32_t*, void*, hipS
 size_t topk_workspace_bytes(int batch, int64_t total_tokens) {
   return 256 * (size_t)(batch > 0 ? batch : 1) + 4 * (size_t)(total_tokens > 0 ? total_tokens : 0) + 256;
 }
+bool topk_static_fits(int, int64_t total_tokens) { return total_tokens <= 2 * (int64_t)STRUCTKV_STATIC_TOPK_MAX_TOKENS; }
 hipError_t topk_static_scratch(void** ptr, size_t* bytes) {
   alignas(256) static unsigned char host_stand_in[(size_t)4 << 20];   // never touched: the launchers are stubs
   *ptr = host_stand_in;

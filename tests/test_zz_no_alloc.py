@@ -59,3 +59,24 @@ def test_static_scratch_topk_limit_and_errors():
     torch.cuda.synchronize()
     top = torch.topk(big.view(64, -1), 8, dim=1).indices.sort(dim=1).values.to(torch.int32).reshape(-1)
     assert torch.equal(out, top)
+
+
+# the last call of a batch size that the 4 MiB of histograms and suffix sums cover, and the first that they do not
+# (24 KB and 16 bytes a sequence, 4 KB and 8 bytes for every 2048 tokens begun and every sequence)
+@pytest.mark.parametrize("batch,blocks", [(1, 1015), (9, 968), (10, 962), (64, 638)])
+def test_static_scratch_topk_limit_by_batch(batch, blocks):
+    from paper_2604_06746_amd import binding as B
+    most = (blocks - batch) * 2048 + 2047
+    for total in (most, most + 1):
+        lens = [total - (batch - 1) * 1000] + [1000] * (batch - 1)
+        cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
+        scores = torch.randperm(total, device="cuda").float()   # (distinct)
+        idx = torch.empty(5 * batch, dtype=torch.int32, device="cuda")
+        if total > most:
+            with pytest.raises(B.StructKVError) as e:
+                B.structkv_select_topk_static(scores, cu, [5] * batch, 0, idx)
+            assert e.value.status == B.STRUCTKV_ERR_UNSUPPORTED
+            continue
+        B.structkv_select_topk_static(scores, cu, [5] * batch, 0, idx)
+        top = [torch.topk(x, 5).indices.sort().values.to(torch.int32) for x in scores.split(lens)]
+        assert torch.equal(idx, torch.cat(top))
