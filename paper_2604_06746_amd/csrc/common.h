@@ -125,39 +125,98 @@ __device__ inline uint32_t score_key(float f) {
 //          against 15.3 us for the mid form's four launches (in a layer step, where two of those fall away, about
 //          even); at 16384 one workgroup needs 13.2 us.
 //   mid    up to kMidSeq: a histogram whose fine bins lie around the scores that matter, so that the k-th largest's bin
-//          holds few scores (the candidates); one launch lists them, one resolves them and places the indices.
-//          131072 scores: 18.0 us, long form 22.6; in a layer step 12.5 us after the reduce kernel, long form 20.6.
+//          holds few scores (the candidates) or, where the scores crowd together, few different ones; one launch lists
+//          or counts them, one resolves them and places the indices.  131072 scores: 17.7 us spread over octaves, 19.4
+//          within 0.3 % of each other, 20.0 all equal (the long form 22.6, 24.7 and 24.7); in a layer step two launches
+//          after the reduce kernel, 12.5 us against 20.6 for the long form's three.
 //   long   beyond: three radix digits (11/11/10 bits), one launch each, then the placement.  Every workgroup of the mid
 //          form reads all candidates of its sequence and all counts before it, a thread each: 256 workgroups at most.
-//          At the limit 21.8 us (mid) and 24.4 us (long).
+//          At the limit 20.7 us (mid; all equal 23.3) and 25.9 us (long; 29.2).
 enum { kSelShort = 0, kSelMid = 1, kSelLong = 2 };
 constexpr int kShortSeq = 8192;
 constexpr int kMidSeq = 262144;
-constexpr int kFineBins = 4096, kFineShift = 16;   // fine bins: 1/128 of an octave wide, 32 octaves of them
-constexpr int kCandCap = 16384;                    // most candidates of a sequence that are listed (beyond: the scores are
-constexpr int kCandTotal = 262144;                 // read again), and of a call
+
+// Bins of the mid form, ascending with the keys, in four tiers of 1024: half octaves over all keys; around a centre 16 octaves
+// in bins of 1/64 instead, four octaves in bins of 1/256, and an eighth of an octave in bins of 1/8192.  Even bins of 1/128
+// octave held more scores than can be listed once the scores differ by a few per cent, as the in-degrees of diffuse attention
+// do (N(0,1) queries and keys, a window of 64: 3 %), and for ties no width is small enough: a crowded bin is counted in
+// kSubBins instead (compact), which for the innermost bins are single keys.  Why not three tiers: with end bins that took all
+// keys beyond 32 octaves a crowd in one of them took 196 us at 131072 scores; with quarter octaves over all keys in their
+// place a 32K-token layer whose threshold lies among heavy hitters, four octaves above the mean, took 0.9 us longer.  Why no
+// finer third tier: every bin that is hit is an addition into the merged histogram (scores spread over two octaves, bins of
+// 1/512: 0.6 us).
+constexpr int kTiers = 4, kTierBins = 1024;
+constexpr int kTierShift[kTiers + 1] = {22, 17, 15, 10, 10};   // (the last entry stands for what is not there)
+static_assert((uint64_t)kTierBins << kTierShift[0] == (uint64_t)1 << 32, "the outermost tier covers all keys");
+// bins of a tier that the next one takes the place of, and how many bins more its place then has, its own splits included
+constexpr uint32_t kTierSplit[kTiers] = {kTierBins >> 5, kTierBins >> 2, kTierBins >> 5, 0};
+constexpr uint32_t kTierExtra[kTiers] = {3 * kTierBins - 32 - 256 - 32, 2 * kTierBins - 256 - 32, kTierBins - 32, 0};
+static_assert(kTierSplit[0] == 32 && kTierSplit[1] == 256 && kTierSplit[2] == 32, "the differences of the shifts");
+constexpr int kUsedBins = kTierBins + (int)kTierExtra[0];
+constexpr int kFineBins = 4096;                    // words of the histogram (the rest stays zero)
+static_assert(kUsedBins <= kFineBins, "the bins fit the histogram");
+constexpr int kSubBits = 10, kSubBins = 1 << kSubBits;   // bins of a crowded bin
+static_assert(kTierShift[kTiers - 1] == kSubBits, "an innermost bin's sub-bins are single keys");
+constexpr int kKeyEnds = kFineBins + kSubBins + 512;      // smallest and largest key of a crowded bin, by workgroup
+static_assert(kKeyEnds + 2 * (kMidSeq / 1024) <= 3 * kTopkBins, "histograms, candidate counter and key ends share one sequence's words");
+constexpr int kCandCap = 2048;                            // most candidates of a sequence that are listed (list_cap)
+
+// where the tiers lie: a tier's first bin, in keys >> its shift, and that bin's number
+struct BinTiers {
+  uint32_t start[kTiers + 1], first[kTiers + 1];
+};
+__host__ __device__ inline BinTiers bins_around(uint32_t centre) {
+  BinTiers t{};
+#pragma unroll
+  for (int i = 1; i < kTiers; ++i) {   // (in bins of the tier outside, which it must not leave)
+    const uint32_t half = kTierSplit[i - 1] / 2, least = t.start[i - 1], most = least + kTierBins - 2 * half;
+    const uint32_t c = centre >> kTierShift[i - 1];
+    uint32_t at = c < least + half ? least : c - half;
+    at = at < most ? at : most;
+    t.start[i] = at << (kTierShift[i - 1] - kTierShift[i]);
+    t.first[i] = t.first[i - 1] + (at - least);
+  }
+  return t;
+}
+// bin of a key
+__host__ __device__ inline uint32_t fine_bin(uint32_t key, const BinTiers& t) {
+  uint32_t bin = 0;
+#pragma unroll
+  for (int i = 0; i < kTiers; ++i) {   // (the innermost tier that has the key)
+    const uint32_t k = (key >> kTierShift[i]) - t.start[i];
+    const uint32_t extra = key >= (t.start[i + 1] << kTierShift[i + 1]) ? kTierExtra[i] : 0u;
+    if (k < (uint32_t)kTierBins) bin = t.first[i] + k + extra;
+  }
+  return bin;
+}
+// first key of a bin, and the bits that tell its keys apart
+__host__ __device__ inline void fine_range(uint32_t bin, const BinTiers& t, uint32_t* lo, uint32_t* width) {
+#pragma unroll
+  for (int i = 0; i < kTiers; ++i) {   // (the innermost tier in whose place the bin is)
+    const uint32_t u = bin - t.first[i];
+    const uint32_t extra = bin >= t.first[i + 1] ? kTierExtra[i] : 0u;
+    if (u < kTierBins + kTierExtra[i]) {
+      *lo = (t.start[i] + u - extra) << kTierShift[i];
+      *width = (uint32_t)kTierShift[i];
+    }
+  }
+}
 
 #ifdef __HIPCC__
-// first key of the fine bins for the in-degrees of a sequence: they add up to `mass` over n keys, so no more than n/64 of
-// them lie above 64 times their mean; 26 octaves below it and 6 above
-__device__ inline uint32_t fine_base(float mass, int64_t n) {
-  return score_key(mass / (float)(n > 0 ? n : 1)) - (26u << 23);
-}
-// bin of a key; the first and the last bin also take what lies beyond them
-__device__ inline uint32_t fine_bin(uint32_t key, uint32_t base) {
-  return key < base ? 0u : min((key - base) >> kFineShift, (uint32_t)(kFineBins - 1));
-}
+// the bins for the in-degrees of a sequence, which add up to `mass` over n keys
+__device__ inline BinTiers bins_around_mean(float mass, int64_t n) { return bins_around(score_key(mass / (float)(n > 0 ? n : 1))); }
 #endif
 
 struct TopkWs {
-  uint32_t* hist;    // [B][3][kTopkBins]; mid: the fine histogram in the first kFineBins words, then the candidate counter
+  uint32_t* hist;    // [B][3][kTopkBins]; mid: the histogram in the first kFineBins words, that of a crowded bin in the next
+                     //         kSubBins, then the candidate counter; from kKeyEnds on the key ends
   uint32_t* state;   // [B][8]; long: digit 0, k left after it, 22-bit prefix, k left after it
-                     //         mid: first and last key of the k-th largest's bin, its width in bits, k left inside it,
-                     //              keys in it, first key of the fine bins
+                     //         mid: first key of the k-th largest's bin, its width in bits, k left inside it, keys in it,
+                     //              the centre of the bins
   uint32_t* suf;     // long: [blocks][1024] suffix sums of the workgroup's last-digit histogram
-  uint2* cand;       // mid: candidates (key, workgroup) of sequence b from min(cu[b], b*cand_cap) on
+                     // mid: [blocks] x kSubBins 16-bit words: suffix sums of the workgroup's counts in a crowded bin, or, in
+                     //      the words of a sequence's workgroups, its candidates (key, workgroup)
   uint32_t* meta;    // long: [blocks][2] keys above the 22-bit prefix, keys equal to it; mid: [blocks] keys above the bin
-  int cand_cap;      // mid: most candidates listed per sequence
   int mode;          // kSelShort / kSelMid / kSelLong
   float mass;        // > 0: the scores are in-degrees with this sum per sequence (fused layer step)
   const struct ReduceWork* red;   // (host) short: the kernel forms the scores itself (a layer step of short sequences)

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kCombRows* kCombSlots) void score_combine_kernel(
 // Workgroups b < B also finish Eq. 4 for sequence b.  With `cen` != NULL the kernel also applies
 // C <- lambda C + inv_w D with the arithmetic of accumulate_kernel (one fma on the rounded product).
 // FUSE > 0 (a fused layer step, Eq. 13 follows Eq. 2 directly): the kernel also starts the selection on the scores it has
-// just formed -- their histogram (kSelMid: fine bins around their mean, kSelLong: the top 11 bits of their keys) and the
+// just formed -- their histogram (kSelMid: bins that are finest around their mean, kSelLong: the top 11 bits of their keys) and the
 // kept window's indices; workgroups of 1024 threads then, so that there are fewer histograms to merge.
 template <class TAB, int V, int FUSE>
 __global__ __launch_bounds__(FUSE ? 1024 : 256) void score_reduce_kernel(
@@ -96,15 +96,14 @@ __global__ __launch_bounds__(FUSE ? 1024 : 256) void score_reduce_kernel(
   constexpr int BINS = FUSE == kSelMid ? kFineBins : kTopkBins;
   __shared__ uint32_t h0[FUSED ? BINS : 1];
   const float mass = (float)w * (float)Hq;
-  auto bin_of = [&](uint32_t key, int b) {
-    return FUSE == kSelMid ? fine_bin(key, fine_base(mass, seq.cu[b + 1] - seq.cu[b])) : key >> 21;
-  };
   const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
   int b_wg = 0;   // FUSED: the sequence of the workgroup's first token; its digits are counted in LDS
+  BinTiers tiers{};   // kSelMid: that sequence's bins
   if constexpr (FUSED) {
     for (int i = threadIdx.x; i < BINS; i += NT) h0[i] = 0u;
     const int64_t first = min((int64_t)blockIdx.x * blockDim.x * V, total > 0 ? total - 1 : 0);
     while (b_wg + 1 < B && first >= seq.cu[b_wg + 1]) ++b_wg;
+    if constexpr (FUSE == kSelMid) tiers = bins_around_mean(mass, seq.cu[b_wg + 1] - seq.cu[b_wg]);
     __syncthreads();
   }
   if (i0 < total) {   // V == 4 only when total % 4 == 0
@@ -156,7 +155,10 @@ __global__ __launch_bounds__(FUSE ? 1024 : 256) void score_reduce_kernel(
         while (b + 1 < B && i >= seq.cu[b + 1]) ++b;
         // only the prefix [0, n_b - keep_tail) of a sequence with a budget is searched
         if (seq.k[b] > 0 && i - seq.cu[b] < seq.cu[b + 1] - seq.cu[b] - fs.keep_tail) {
-          const uint32_t digit = bin_of(score_key(a[j]), b);
+          const uint32_t key = score_key(a[j]);
+          uint32_t digit = key >> 21;
+          if constexpr (FUSE == kSelMid)
+            digit = fine_bin(key, b == b_wg ? tiers : bins_around_mean(mass, seq.cu[b + 1] - seq.cu[b]));
           if (b == b_wg) atomicAdd(&h0[digit], 1u);
           else atomicAdd(&fs.hist[(size_t)b * 3 * kTopkBins + digit], 1u);
         }

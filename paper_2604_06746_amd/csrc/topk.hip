@@ -8,11 +8,11 @@
 //     the largest key is cut into 2048 bins, then the k-th largest's bin again, until it is one key.
 //   mid (fused into the scoring kernels: two launches; alone: four):
 //     [init]    zero the histogram, write the kept window, find from a sample where the k-th largest lies (alone only)
-//     [hist]    histogram over 4096 fine bins around it (in a layer step the reduce kernel does this)
-//     compact   find the k-th largest's bin; every workgroup lists its scores in that bin -- the candidates -- and counts
-//               those above it
-//     place     every workgroup resolves the candidates (in registers, bins as in the short form) down to the k-th key,
-//               counts what the workgroups before it have selected, and writes its own indices
+//     [hist]    histogram over bins that are finest around it (in a layer step the reduce kernel does this)
+//     compact   find the k-th largest's bin; every workgroup counts its scores above the bin and lists those in it -- the
+//               candidates -- or, where these are many, counts them in 1024 sub-bins, for all workgroups and for its own
+//     place     every workgroup resolves the candidates (in registers, bins as in the short form) or the sub-bins down to
+//               the k-th key, counts what the workgroups before it have selected, and writes its own indices
 //   long: radix select in three digit passes (11/11/10 bits from the top):
 //     init, hist0 (top digit; a layer step's scoring kernels do both), hist1, hist2 (which also publishes the suffix
 //     sums of each workgroup's last-digit histogram), write.
@@ -399,11 +399,26 @@ struct ResolveLds {
   uint32_t scan[16], res[3], n;
 };
 
+// One more in h[bin] for every calling lane; lanes that share one of two values add up first (an LDS atomic of 64 lanes on one
+// word takes 64 turns: 131072 equal scores, 100 us a sweep).
+__device__ __forceinline__ void count_ties(uint32_t* h, uint32_t bin) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const bool mine = bin == (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
+    const unsigned long long same = __ballot(mine);
+    if (mine) {
+      if ((int)(threadIdx.x & 63) == __ffsll((long long)same) - 1) atomicAdd(&h[bin], (uint32_t)__popcll(same));
+      return;
+    }
+  }
+  atomicAdd(&h[bin], 1u);
+}
+
 // The krem-th largest of the keys that `each` visits, all of them in [lo, lo + 2^width): the range in 2048 bins,
 // histogrammed in LDS; the k-th largest's bin again in 2048 bins, and so on, until the bin holds at most 64 keys (mostly
 // after one round), which every wave ranks for itself, a key per lane.  T: that key; need: how many keys equal to it are
-// among the krem.  l.hist must be zero and l.n zero, a barrier in between.
-template <int THREADS, class Each>
+// among the krem.  l.hist must be zero and l.n zero, a barrier in between.  TIES: many of the keys are expected to be equal.
+template <int THREADS, bool TIES = false, class Each>
 __device__ inline void resolve_key(Each each, uint32_t lo, int width, uint32_t krem, ResolveLds& l, uint32_t* T, uint32_t* need) {
   uint32_t prefix = 0u;
   int rem = width;
@@ -411,7 +426,10 @@ __device__ inline void resolve_key(Each each, uint32_t lo, int width, uint32_t k
     const int bits = min(11, rem), sh = rem - bits;
     each([&](uint32_t key) {
       const uint32_t off = key - lo;
-      if (rem == width || (off >> rem) == prefix) atomicAdd(&l.hist[(off >> sh) & ((1u << bits) - 1u)], 1u);
+      if (rem == width || (off >> rem) == prefix) {
+        const uint32_t at = (off >> sh) & ((1u << bits) - 1u);
+        if constexpr (TIES) count_ties(l.hist, at); else atomicAdd(&l.hist[at], 1u);
+      }
     });
     __syncthreads();
     uint32_t bin, above, in_bin;
@@ -561,31 +579,44 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
   place_ordered<kWide, PER>(key, 0, m, T, need, 0u, 0u, tot, out);
 }
 
-// mid form, alone: zero the histogram and the candidate counter, write the kept window, and centre the fine bins on the
-// k-th largest of a sample (1024 scores; it only places the bins, the result does not depend on it)
+// mid form, alone: zero the histograms and the candidate counter, write the kept window, and centre the bins on the k-th
+// largest of a sample (1024 scores; it only places the bins, the result does not depend on it)
 template <class TAB>
 __global__ __launch_bounds__(kWide) void topk_mid_init_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
                                                               TopkWs ws, int32_t* __restrict__ idx_out) {
   short_kernel_priority();
+  constexpr int NWV = kWide / 64;
   __shared__ uint32_t h[kBins];
-  __shared__ uint32_t scan[kWide / 64], res[3];
+  __shared__ uint32_t scan[NWV], res[3], ends[2][NWV];
   const int b = blockIdx.x, t = threadIdx.x;
   const int64_t m = seq.cu[b + 1] - seq.cu[b] - keep_tail;
   const uint32_t k = (uint32_t)seq.k[b];
   const float v = m > 0 ? scores[seq.cu[b] + (m * t) / kWide] : 0.f;
-  for (int i = t; i < kFineBins + 1; i += kWide) ws.hist[(size_t)b * 3 * kBins + i] = 0u;
+  for (int i = t; i < kFineBins + kSubBins + 1; i += kWide) ws.hist[(size_t)b * 3 * kBins + i] = 0u;
   for (int i = t; i < keep_tail; i += kWide) idx_out[seq.out_off[b] + k + i] = (int32_t)(m + i);
   if (k == 0u) return;
   for (int i = t; i < kBins; i += kWide) h[i] = 0u;
   __syncthreads();
-  atomicAdd(&h[score_key(v) >> 21], 1u);
+  const uint32_t key = score_key(v);
+  atomicAdd(&h[key >> 21], 1u);
   __syncthreads();
-  uint32_t digit, above;
-  select_bin<kWide, kBins>(h, (uint32_t)max((int64_t)1, ((int64_t)k * kWide) / m), scan, res, &digit, &above);
-  if (t == 0) {   // half of the bins' span below the digit, half above; never past the largest key
-    const uint32_t at = digit << 21, half = (uint32_t)(kFineBins / 2) << kFineShift;
-    ws.state[b * 8 + 5] = min(at > half ? at - half : 0u, 0xFFFFFFFFu - ((uint32_t)kFineBins << kFineShift));
+  uint32_t digit, above, in_digit;
+  const uint32_t rank = (uint32_t)max((int64_t)1, ((int64_t)k * kWide) / m);
+  select_bin<kWide, kBins>(h, rank, scan, res, &digit, &above, &in_digit);
+  // where the rank lies among the sample's keys with that digit, as if they filled it evenly; where they crowd together,
+  // between the smallest and the largest of them
+  uint32_t least = digit << 21, span = (1u << 21) - 1u;
+  if (in_digit > (uint32_t)kWide / 6) {   // (scores spread over two octaves: 140; a quarter microsecond saved)
+    const bool in = (key >> 21) == digit;
+    const uint32_t wmx = wave_max(in ? key : 0u), winv = wave_max(in ? ~key : 0u);
+    if ((t & 63) == 0) { ends[0][t >> 6] = wmx; ends[1][t >> 6] = winv; }
+    __syncthreads();
+    uint32_t mx = 0u, inv = 0u;
+    for (int i = 0; i < NWV; ++i) { mx = max(mx, ends[0][i]); inv = max(inv, ends[1][i]); }
+    least = ~inv;
+    span = mx - least;
   }
+  if (t == 0) ws.state[b * 8 + 4] = least + span - span / in_digit * (rank - above);   // (rank - above: 1 .. in_digit)
 }
 
 // the calling workgroup's sequence b, its number inside it and its first score
@@ -613,14 +644,27 @@ __global__ __launch_bounds__(kThreads) void topk_mid_hist_kernel(const float* __
   float v[kMidPer];
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * kThreads + t < m ? sc[j0 + i * kThreads + t] : 0.f;
-  const uint32_t base = ws.state[b * 8 + 5];
+  const BinTiers tiers = bins_around(ws.state[b * 8 + 4]);
   for (int i = t; i < kFineBins; i += kThreads) h[i] = 0u;
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i)
-    if (j0 + i * kThreads + t < m) atomicAdd(&h[fine_bin(score_key(v[i]), base)], 1u);
+    if (j0 + i * kThreads + t < m) atomicAdd(&h[fine_bin(score_key(v[i]), tiers)], 1u);
   __syncthreads();
   merge_hist(h, kFineBins, ws.hist + (size_t)b * 3 * kBins);
+}
+
+// Most candidates of a sequence of `nblk` workgroups that are listed; the list lies in the words of their suffix sums.  In an
+// innermost bin the sub-bins are the better of the two as soon as a list takes more than one entry a thread (131072 scores within
+// 0.3 / 0.1 / 0.05 %, 870 / 2400 / 4400 candidates: 19.6 / 22.0 / 27.0 us as lists, 18.7 / 18.9 / 18.6 as sub-bins); in a wider
+// one the sub-bin's keys have to be picked out of the scores (a layer step of 131072 tokens, window 8, 700 candidates in a
+// bin of 1/256 octave: 43.0 us with the list, 48.3 with sub-bins), which is worth it where the list's words or its time run out.
+__device__ __forceinline__ uint32_t list_cap(uint32_t nblk, uint32_t width) {
+  return width <= (uint32_t)kSubBits ? (uint32_t)kThreads
+                                     : min((uint32_t)kCandCap, nblk * (uint32_t)(kSubBins * sizeof(uint16_t) / sizeof(uint2)));
+}
+__device__ __forceinline__ uint16_t* sub_sums(const TopkWs& ws, uint32_t workgroup) {
+  return reinterpret_cast<uint16_t*>(ws.suf) + (size_t)workgroup * kSubBins;
 }
 
 template <class TAB>
@@ -628,55 +672,92 @@ __global__ __launch_bounds__(kThreads) void topk_compact_kernel(const float* __r
                                                                 TopkWs ws) {
   short_kernel_priority();
   constexpr int NWV = kThreads / 64, N = kMidPer * NWV;
-  __shared__ uint32_t scan[NWV], res[3], wtot[N], gbase;
+  __shared__ uint32_t scan[NWV], res[3], wtot[N], gbase, ends[2][NWV];
+  __shared__ uint32_t h[kSubBins];
   int b;
   uint32_t blk;
   int j0;
   mid_share(seq, &b, &blk, &j0);
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int n = (int)(seq.cu[b + 1] - seq.cu[b]), m = n - keep_tail;
+  const uint32_t first = (uint32_t)seq.chunk_start[b], nblk = (uint32_t)seq.chunk_start[b + 1] - first;
   const float* sc = scores + seq.cu[b];
   float v[kMidPer];
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * kThreads + t < m ? sc[j0 + i * kThreads + t] : 0.f;
   uint32_t* gh = ws.hist + (size_t)b * 3 * kBins;
-  const uint32_t base = ws.mass > 0.f ? fine_base(ws.mass, n) : ws.state[b * 8 + 5];
+  const BinTiers tiers = ws.mass > 0.f ? bins_around_mean(ws.mass, n) : bins_around(ws.state[b * 8 + 4]);
   const uint32_t k = (uint32_t)seq.k[b];
-  uint32_t bin, above, in_bin;
+  uint32_t bin, above, in_bin, lo, width;
   select_bin<kThreads, kFineBins>(gh, k, scan, res, &bin, &above, &in_bin);
-  const bool listed = in_bin <= (uint32_t)ws.cand_cap;   // else the place kernel reads the scores again
+  fine_range(bin, tiers, &lo, &width);
+  const uint32_t hi = lo + ((1u << width) - 1u);
+  const bool listed = in_bin <= list_cap(nblk, width);
   if (blk == 0 && t == 0) {
     uint32_t* st = ws.state + (size_t)b * 8;
-    st[0] = bin == 0 ? 0u : base + (bin << kFineShift);
-    st[1] = bin < (uint32_t)kFineBins - 1 ? base + (bin << kFineShift) + ((1u << kFineShift) - 1u) : 0xFFFFFFFFu;
-    st[2] = bin > 0 && bin < (uint32_t)kFineBins - 1 ? (uint32_t)kFineShift : 32u;
-    st[3] = k - above;
-    st[4] = in_bin;
+    st[0] = lo;
+    st[1] = width;
+    st[2] = k - above;
+    st[3] = in_bin;
   }
+  uint32_t key[kMidPer];
   unsigned long long mc[kMidPer];
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i) {
     const bool in = j0 + i * kThreads + t < m;
-    const uint32_t fb = fine_bin(score_key(v[i]), base);
-    mc[i] = __ballot(in && fb == bin);
-    const unsigned long long ma = __ballot(in && fb > bin);
+    key[i] = score_key(v[i]);
+    mc[i] = __ballot(in && key[i] >= lo && key[i] <= hi);
+    const unsigned long long ma = __ballot(in && key[i] > hi);
     if (lane == 0) wtot[i * NWV + wv] = (uint32_t)__popcll(mc[i]) | ((uint32_t)__popcll(ma) << 16);
   }
+  if (!listed)
+    for (int i = t; i < kSubBins; i += kThreads) h[i] = 0u;
   __syncthreads();
   const uint32_t own = lane < N ? wtot[lane] : 0u;   // every wave scans the counts for itself
   const uint32_t x = wave_scan(own);
   if (t == N - 1) {
     ws.meta[blockIdx.x] = x >> 16;
     const uint32_t c = x & 0xFFFFu;
-    gbase = c && listed ? atomicAdd(&gh[kFineBins], c) : 0u;
+    gbase = c && listed ? atomicAdd(&gh[kFineBins + kSubBins], c) : 0u;
+  }
+  if (!listed) {
+    // a crowded bin: counts of its sub-bins, and for the placement the workgroup's own from the top down
+    const uint32_t sh = width - kSubBits;
+    uint32_t inv = 0u, mx = 0u;   // largest ~key and largest key
+#pragma unroll
+    for (int i = 0; i < kMidPer; ++i)
+      if ((mc[i] >> lane) & 1ull) {
+        atomicAdd(&h[(key[i] - lo) >> sh], 1u);
+        inv = max(inv, ~key[i]);
+        mx = max(mx, key[i]);
+      }
+    inv = wave_max(inv);
+    mx = wave_max(mx);
+    if (lane == 0) { ends[0][wv] = inv; ends[1][wv] = mx; }
+    __syncthreads();
+    if (t == 0) {
+      for (int i = 0; i < NWV; ++i) { inv = max(inv, ends[0][i]); mx = max(mx, ends[1][i]); }
+      *reinterpret_cast<uint2*>(gh + kKeyEnds + 2 * blk) = make_uint2(~inv, mx);
+    }
+    merge_hist(h, kSubBins, gh + kFineBins);
+    static_assert(kSubBins == 4 * kThreads, "four sub-bins a thread");
+    uint32_t c4[4], sum = 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { c4[i] = h[kSubBins - 1 - (4 * t + i)]; sum += c4[i]; }
+    uint32_t run;
+    block_excl_scan<kThreads, false>(sum, scan, &run);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { run += c4[i]; c4[i] = run; }   // (at most the workgroup's 1024 scores)
+    *reinterpret_cast<uint2*>(sub_sums(ws, blockIdx.x) + kSubBins - 4 - 4 * t) =
+        make_uint2(c4[3] | (c4[2] << 16), c4[1] | (c4[0] << 16));
+    return;
   }
   __syncthreads();
-  if (!listed) return;
-  uint2* cand = ws.cand + min(seq.cu[b], (int64_t)b * ws.cand_cap) + gbase;
+  uint2* cand = reinterpret_cast<uint2*>(sub_sums(ws, first)) + gbase;
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i) {
     const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(x - own), i * NWV + wv) & 0xFFFFu;
-    if ((mc[i] >> lane) & 1ull) cand[before + (uint32_t)__popcll(mc[i] & ((1ull << lane) - 1ull))] = make_uint2(score_key(v[i]), blk);
+    if ((mc[i] >> lane) & 1ull) cand[before + (uint32_t)__popcll(mc[i] & ((1ull << lane) - 1ull))] = make_uint2(key[i], blk);
   }
 }
 
@@ -684,61 +765,138 @@ template <class TAB>
 __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __restrict__ scores, TAB seq, int keep_tail, TopkWs ws,
                                                               int32_t* __restrict__ idx_out) {
   short_kernel_priority();
-  constexpr int CPT = 4;   // candidates a thread keeps in registers; the first of them are requested before their number is known
+  constexpr int CPT = 4;        // candidates a thread keeps in registers; the first is requested before their number is known
+  constexpr int kPicked = CPT * kThreads;   // most keys of a sub-bin that are copied together
   __shared__ ResolveLds l;
-  __shared__ uint32_t tot[kMidPer * (kThreads / 64)], cnt[2];
+  __shared__ uint32_t tot[kMidPer * (kThreads / 64)], cnt[2], npick, nhold, ends[2][kThreads / 64];
+  __shared__ uint8_t holders[kThreads];
+  __shared__ uint2 picked[kPicked];
   int b;
   uint32_t blk;
   int j0;
   mid_share(seq, &b, &blk, &j0);
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int m = (int)(seq.cu[b + 1] - seq.cu[b]) - keep_tail;
+  const uint32_t first = (uint32_t)seq.chunk_start[b], nblk = (uint32_t)seq.chunk_start[b + 1] - first;   // (at most 256)
   const float* sc = scores + seq.cu[b];
   const uint32_t* st = ws.state + (size_t)b * 8;
-  const uint32_t lo = st[0], hi = st[1], krem = st[3], c = st[4];
-  const int width = (int)st[2];
-  const uint2* cand = ws.cand + min(seq.cu[b], (int64_t)b * ws.cand_cap);
-  const uint32_t cap = (uint32_t)min((int64_t)ws.cand_cap, seq.cu[b + 1] - seq.cu[b]);   // entries that exist
+  const uint32_t lo = st[0], krem = st[2], c = st[3];
+  const int width = (int)st[1];
+  const uint2* cand = reinterpret_cast<const uint2*>(sub_sums(ws, first));
   uint2 x[CPT];
-#pragma unroll
-  for (int r = 0; r < CPT; ++r) x[r] = (uint32_t)(r * kThreads + t) < cap ? cand[r * kThreads + t] : make_uint2(0u, 0u);
+  x[0] = cand[t];   // (every sequence here has at least one workgroup, whose words hold 256)
   float v[kMidPer];
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * kThreads + t < m ? sc[j0 + i * kThreads + t] : 0.f;
-  uint32_t g0 = (uint32_t)t < blk ? ws.meta[seq.chunk_start[b] + t] : 0u;   // (at most 256 workgroups per sequence)
+  uint32_t g0 = (uint32_t)t < blk ? ws.meta[first + t] : 0u;
   for (int i = t; i < kBins; i += kThreads) l.hist[i] = 0u;
-  if (t == 0) { cnt[0] = 0u; cnt[1] = 0u; l.n = 0u; }
+  if (t == 0) { cnt[0] = 0u; cnt[1] = 0u; l.n = 0u; npick = 0u; nhold = 0u; }
   __syncthreads();
   uint32_t T, need, e0 = 0u;
-  if (c <= (uint32_t)ws.cand_cap) {
+  // the krem_-th largest of the `count` entries (key, workgroup) that `more` reads beyond those in x; all in [from, from + 2^bits)
+  auto resolve_entries = [&](const uint2* more, uint32_t count, uint32_t from, int bits, uint32_t krem_) {
     auto each = [&](auto f) {
 #pragma unroll
       for (int r = 0; r < CPT; ++r)
-        if ((uint32_t)(r * kThreads + t) < c) f(x[r]);
-      for (uint32_t i = CPT * kThreads + t; i < c; i += kThreads) f(cand[i]);
+        if ((uint32_t)(r * kThreads + t) < count) f(x[r]);
+      for (uint32_t i = CPT * kThreads + t; i < count; i += kThreads) f(more[i]);
     };
-    resolve_key<kThreads>([&](auto f) { each([&](uint2 e) { f(e.x); }); }, lo, width, krem, l, &T, &need);
+    resolve_key<kThreads>([&](auto f) { each([&](uint2 e) { f(e.x); }); }, from, bits, krem_, l, &T, &need);
     each([&](uint2 e) {
       g0 += e.y < blk && e.x > T;
       e0 += e.y < blk && e.x == T;
     });
+  };
+  if (c <= list_cap(nblk, (uint32_t)width)) {
+#pragma unroll
+    for (int r = 1; r < CPT; ++r) x[r] = (uint32_t)(r * kThreads + t) < c ? cand[r * kThreads + t] : make_uint2(0u, 0u);
+    resolve_entries(cand, c, lo, width, krem);
   } else {
-    // more candidates than are listed (nearly equal scores, or a k-th largest outside the fine bins): the scores again
-    auto each = [&](auto f) {
-      for (int j = t; j < m; j += kThreads) {
-        const uint32_t key = score_key(sc[j]);
-        if (key >= lo && key <= hi) f(key, j);
+    const uint32_t* sub = ws.hist + (size_t)b * 3 * kBins + kFineBins;
+    const int sh = width - kSubBits;
+    uint32_t s, above, in_sub;
+    select_bin<kThreads, kSubBins>(sub, krem, l.scan, l.res, &s, &above, &in_sub);
+    const uint32_t ksub = krem - above, from = lo + (s << sh);
+    uint32_t mine = 0u;   // keys of the sub-bin in workgroup t's scores
+    if ((uint32_t)t < nblk) {
+      const uint16_t* sums = sub_sums(ws, first + t);
+      const uint32_t ge = sums[s], gt = s + 1 < (uint32_t)kSubBins ? sums[s + 1] : 0u;
+      mine = ge - gt;
+      if ((uint32_t)t < blk) g0 += gt;
+    }
+    if (sh == 0) {   // an innermost bin: the sub-bin is one key
+      T = from;
+      need = ksub;
+      if ((uint32_t)t < blk) e0 = mine;
+    } else {
+      // the keys of the sub-bin are in the scores themselves, in the workgroups that have counted some
+      if (mine) holders[atomicAdd(&nhold, 1u)] = (uint8_t)t;   // (in any order: nothing below depends on it)
+      uint32_t inv = 0u, mx = 0u;
+      if (mine) {
+        const uint2 ends_of = *reinterpret_cast<const uint2*>(sub + (kKeyEnds - kFineBins) + 2 * t);
+        inv = ~ends_of.x;
+        mx = ends_of.y;
       }
-    };
-    resolve_key<kThreads>([&](auto f) { each([&](uint32_t key, int) { f(key); }); }, lo, width, krem, l, &T, &need);
-    each([&](uint32_t key, int j) {
-      g0 += j < j0 && key > T;
-      e0 += j < j0 && key == T;
-    });
+      inv = wave_max(inv);
+      mx = wave_max(mx);
+      if (lane == 0) { ends[0][wv] = inv; ends[1][wv] = mx; }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kThreads / 64; ++i) { inv = max(inv, ends[0][i]); mx = max(mx, ends[1][i]); }
+      const uint32_t nh = nhold;
+      // f(key, workgroup), a wave to the scores of kAtOnce workgroups
+      auto visit = [&](auto f) {
+        constexpr uint32_t kAtOnce = 4;
+        constexpr int PER = kMidShare / 64;
+        for (uint32_t i0 = wv * kAtOnce; i0 < nh; i0 += kAtOnce * (kThreads / 64)) {
+          float y[kAtOnce][PER];
+          int u[kAtOnce];
+#pragma unroll
+          for (uint32_t a = 0; a < kAtOnce; ++a) {
+            u[a] = __builtin_amdgcn_readfirstlane((int)holders[min(i0 + a, nh - 1)]);
+            const float* p = sc + u[a] * kMidShare;
+            const int left = m - u[a] * kMidShare;
+            if (left >= kMidShare) {
+#pragma unroll
+              for (int i = 0; i < PER; ++i) y[a][i] = p[lane + 64 * i];
+            } else {
+#pragma unroll
+              for (int i = 0; i < PER; ++i) y[a][i] = p[min(lane + 64 * i, left - 1)];
+            }
+          }
+#pragma unroll
+          for (uint32_t a = 0; a < kAtOnce; ++a) {
+            const int left = i0 + a < nh ? m - u[a] * kMidShare : 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+              const uint32_t q = score_key(y[a][i]);
+              if (q - from < (1u << sh) && lane + 64 * i < left) f(q, (uint32_t)u[a]);
+            }
+          }
+        }
+      };
+      if (~inv == mx) {   // ties
+        T = mx;
+        need = ksub;
+        if ((uint32_t)t < blk) e0 = mine;
+      } else if (in_sub <= (uint32_t)kPicked) {
+        visit([&](uint32_t q, uint32_t u) { picked[atomicAdd(&npick, 1u)] = make_uint2(q, u); });
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < CPT; ++r) x[r] = picked[r * kThreads + t];
+        resolve_entries(picked, in_sub, from, sh, ksub);
+      } else {
+        resolve_key<kThreads, true>([&](auto f) { visit([&](uint32_t q, uint32_t) { f(q); }); }, from, sh, ksub, l, &T, &need);
+        visit([&](uint32_t q, uint32_t u) {
+          g0 += u < blk && q > T;
+          e0 += u < blk && q == T;
+        });
+      }
+    }
   }
   g0 = wave_sum(g0);
   e0 = wave_sum(e0);
-  if ((t & 63) == 0) { atomicAdd(&cnt[0], g0); atomicAdd(&cnt[1], e0); }
+  if (lane == 0) { atomicAdd(&cnt[0], g0); atomicAdd(&cnt[1], e0); }
   uint32_t key[kMidPer];
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i) key[i] = score_key(v[i]);
@@ -907,13 +1065,9 @@ size_t max_blocks(int batch, int64_t total_tokens) {
   return nb;
 }
 
-// the suffix sums of the long form and the candidates of the mid form take turns
-size_t lists_bytes(size_t B, int64_t total_tokens, size_t nb) {
-  const size_t suf = sizeof(uint32_t) * kLowBins * nb;
-  size_t cand = B * kCandCap < kCandTotal ? B * kCandCap : kCandTotal;
-  if ((int64_t)cand > total_tokens) cand = (size_t)total_tokens;
-  return align_up(suf > sizeof(uint2) * cand ? suf : sizeof(uint2) * cand, 256);
-}
+// the suffix sums of the long form, or of the mid form (16-bit words, at most twice as many workgroups)
+size_t lists_bytes(size_t nb) { return align_up(sizeof(uint32_t) * kLowBins * nb, 256); }
+static_assert(2 * sizeof(uint16_t) * kSubBins == sizeof(uint32_t) * kLowBins, "the mid form's words fit the long form's");
 
 }  // namespace
 
@@ -921,7 +1075,7 @@ size_t topk_workspace_bytes(int batch, int64_t total_tokens) {
   const size_t B = (size_t)(batch > 0 ? batch : 1);
   const size_t nb = max_blocks(batch, total_tokens);
   return align_up(sizeof(uint32_t) * 3 * B * kBins, 256) + align_up(sizeof(uint32_t) * 8 * B, 256) +
-         lists_bytes(B, total_tokens, nb) + align_up(sizeof(uint32_t) * 2 * nb, 256);
+         lists_bytes(nb) + align_up(sizeof(uint32_t) * 2 * nb, 256);
 }
 
 // digit histograms, search state of the long form, suffix sums and counts: what the static scratch's limit is stated in
@@ -966,7 +1120,6 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
   ws->mode = longest <= kShortSeq ? kSelShort : longest <= kMidSeq ? kSelMid : kSelLong;
   ws->mass = 0.f;
   ws->red = nullptr;
-  ws->cand_cap = kCandTotal / (B > 0 ? B : 1) < kCandCap ? kCandTotal / (B > 0 ? B : 1) : kCandCap;
   const int target = ws->mode == kSelMid ? kMidShare : share_target(plan->cu[B]);
   plan->chunk_start[0] = 0;
   for (int b = 0; b < B; ++b) {
@@ -981,8 +1134,7 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
   uint8_t* p = (uint8_t*)wsp;
   ws->hist = (uint32_t*)p;    p += align_up(sizeof(uint32_t) * 3 * Bz * kBins, 256);
   ws->state = (uint32_t*)p;   p += align_up(sizeof(uint32_t) * 8 * Bz, 256);
-  ws->suf = (uint32_t*)p;
-  ws->cand = (uint2*)p;       p += lists_bytes(Bz, plan->cu[B], nb);
+  ws->suf = (uint32_t*)p;     p += lists_bytes(nb);
   ws->meta = (uint32_t*)p;
 }
 

@@ -14,6 +14,24 @@ extern "C" int structkv_stub_launch_count(void) { return g_launches; }
 // RB, NW, KC, planes, stream_k, RC, grid_chunks, path of the latest MFMA scoring launch
 extern "C" void structkv_stub_last_plan(int32_t* out) { for (int i = 0; i < 8; ++i) out[i] = g_last_plan[i]; }
 
+// The bins of the mid-sized selection for one centre: how many keys the two directions of the mapping disagree on, how many
+// bins do not follow on the one before, and whether they end with the last key.
+extern "C" int structkv_stub_bin_faults(uint32_t centre) {
+  int bad = 0;
+  uint32_t next = 0;
+  const BinTiers tiers = bins_around(centre);
+  for (uint32_t bin = 0; bin < (uint32_t)kUsedBins; ++bin) {
+    uint32_t lo, width;
+    fine_range(bin, tiers, &lo, &width);
+    const uint32_t hi = lo + ((1u << width) - 1u);
+    bad += lo != next || hi < lo || width < (uint32_t)kSubBits;
+    const uint32_t keys[4] = {lo, lo + (hi - lo) / 3, lo + (hi - lo) / 2, hi};
+    for (uint32_t key : keys) bad += fine_bin(key, tiers) != bin;
+    next = hi + 1;
+  }
+  return bad + (next != 0);
+}
+
 hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void*,
                                   const void*, int64_t, int64_t, float, float*, const float*, float*, int64_t total,
                                   float* probs, int pass, hipStream_t) {

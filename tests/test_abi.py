@@ -346,3 +346,13 @@ def test_tilings_chosen_for_the_named_configurations(B):
     assert p["grid_chunks"] == sum(-(-n // p["KC"]) for n in lens) and p["stream_k"] == 1     # 364 MiB of K
     p = plan(32, 8, 128, 32, [n // 2 for n in lens])
     assert p["grid_chunks"] == sum(-(-(n // 2) // p["KC"]) for n in lens) and p["stream_k"] == 0
+
+
+@pytest.mark.parametrize("centre", [0, 1, 1 << 24, (9 << 21) + 12345, 0x7FFFFFFF, 0x80000000, 0xA4000001, 0xBF800000, 0xC77FFFFF,
+                                    0xFE200000, 0xFF800000, 0xFFFFFFFF])
+def test_bins_of_the_mid_sized_selection(B, centre):
+    """Every key has one bin, bins ascend with the keys, and a bin's range holds exactly its keys.  Stub build only (the
+    mapping is inline code of the kernels' header)."""
+    if not hasattr(B._lib, "structkv_stub_bin_faults"):
+        pytest.skip("the real library launches kernels; this runs against the stub build only")
+    assert B._lib.structkv_stub_bin_faults(ctypes.c_uint32(centre)) == 0

@@ -79,21 +79,56 @@ def _select(B, scores, lens, ks, tail):
 
 
 # the edges of the three forms (8192 and 262144 searched scores), of their 1024-score workgroups and of the candidate
-# lists (16384 per sequence); scores: spread, nearly equal (more candidates than are listed), all equal, alternating
-# between two values a power apart (a sample that misses the threshold's range), negative
+# lists (2048 per sequence, 256 in a near bin); scores: spread, crowded to a few and to a few tenths of a per cent, nearly equal (a crowd around
+# a power of two), all equal, alternating between two values a power apart (a sample that misses the threshold's range),
+# zeros with as many others as are kept, a crowd of a few different keys, a crowd far below what a sample shows (its sub-bin's
+# keys are neither few nor equal), negative
 @pytest.mark.parametrize("lens,tail", [([1], 0), ([63, 64, 65], 3), ([1025], 1), ([8192 + 8], 8), ([8193 + 8], 8), ([9216, 5, 0], 0),
                                        ([17000, 20000], 32), ([262144 + 7], 7), ([262145 + 7, 300], 7), ([33000] * 17, 64)])
-@pytest.mark.parametrize("kind", ["spread", "close", "equal", "two", "negative"])
+@pytest.mark.parametrize("kind", ["spread", "crowd", "dense", "close", "equal", "two", "cliff", "steps", "ledge", "negative"])
 def test_selection_forms(B, oracle, lens, tail, kind):
     total = sum(lens)
     x = _randn(total, dtype=torch.float32, seed=3)
-    scores = {"spread": torch.exp(4.0 * x), "close": 1.0 + 1e-5 * x, "equal": torch.full_like(x, 0.25),
-              "two": torch.where(x > 2.5, 1e20, 1e-20) * (1.0 + 0.1 * x.abs()), "negative": -torch.exp(x)}[kind].contiguous()
+    u = _randn(total, dtype=torch.float32, seed=4)
+    scores = {"spread": torch.exp(4.0 * x), "crowd": 1.3 + 0.03 * x, "dense": 1.3 + 0.002 * x, "close": 1.0 + 1e-5 * x,
+              "equal": torch.full_like(x, 0.25), "two": torch.where(x > 2.5, 1e20, 1e-20) * (1.0 + 0.1 * x.abs()),
+              "cliff": torch.where(u > 0.8416, 1.0 + 0.02 * x, torch.zeros_like(x)),
+              "ledge": torch.where(u > 0.8779, 1.0 + 0.02 * x, 1e-20 * (1.0 + 0.1 * x.abs())),
+              "steps": torch.where(u > 2.0, 1.0 + x.abs(), 1e-4 * (1.0 + 2e-7 * torch.floor(x))), "negative": -torch.exp(x)}[kind].contiguous()
     for frac in (0.0, 0.003, 0.2, 1.0):
         ks = [int(frac * max(n - tail, 0)) if n >= tail else 0 for n in lens]
         t = min([tail] + lens)
         ref = oracle.select_topk(scores.cpu().numpy(), lens, ks, t)
         assert np.array_equal(_select(B, scores, lens, ks, t), np.concatenate(ref)), (kind, frac)
+
+
+# the time of a selection must not depend on how close its scores lie: digit passes over the scores took at most 1.3 times
+# as long for any of these as for spread scores, a placement that reads all scores again in every workgroup 15 to 28 times
+@pytest.mark.parametrize("n", [131072, 262144])
+def test_time_of_crowded_selections(B, n):
+    x, u = _randn(n, dtype=torch.float32, seed=1), _randn(n, dtype=torch.float32, seed=2)
+    kinds = {"spread": torch.exp(0.5 * x), "few per cent": 1.3 + 0.03 * x, "per cent": 1.3 + 0.01 * x, "per mille": 1.3 + 0.003 * x,
+             "nearly equal": 1.0 + 1e-5 * x, "equal": torch.full_like(x, 0.25),
+             "cliff": torch.where(u > 0.8416, 1.0 + 0.02 * x, torch.zeros_like(x)),
+             "zeros": torch.where(u > 3.0, 1.0 + 0.02 * x, torch.zeros_like(x)), "two values": torch.where(u > 0.9, 4.0, 1.0)}
+    ws = torch.empty(B.structkv_workspace_bytes(None, 1, n), dtype=torch.uint8, device="cuda")
+    times = {}
+    for kind, scores in kinds.items():
+        for frac in (0.1, 0.2):
+            k = int(frac * n)
+            out = torch.empty(k, dtype=torch.int32, device="cuda")
+            best = float("inf")
+            for rep in range(6):
+                start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                start.record()
+                for _ in range(10):
+                    B.structkv_select_topk(scores, [0, n], [k], 0, out, ws)
+                stop.record()
+                stop.synchronize()
+                best = min(best, start.elapsed_time(stop))
+            times[kind, frac] = best
+    for kind, frac in times:
+        assert times[kind, frac] <= 3.0 * times["spread", frac], (kind, frac, times)
 
 
 # a layer step's selection on the in-degrees it has just formed: all in-degrees equal (every score a candidate), budgets
