@@ -165,15 +165,26 @@ void short_carve(const structkv_shape& s, int batch, int64_t total, ScorePlan* p
 // Short sequences in one scoring launch (score_short.hip) where that is one round of workgroups, at most one per CU, whose
 // registers hold the logits of 2048 (bf16) or 1024 (fp32) keys.  A workgroup reads all keys of its sequence, so the work per
 // CU grows with the length, and beyond 1024 keys more than 32 planes make the sum over them the longer part.
-// A layer step of 32 heads on 8, us a call (in a graph, where launches are cheap), two passes -> one launch:
-//   window 8:  512 keys 30.5 -> 19.5 (18.2 -> 13.4), 1024 keys 30.1 -> 19.1 (18.3 -> 15.8), 2048 keys 30.5 -> 21.8 (19.0 -> 21.1)
-//   window 64: 1024 keys 29.3 -> 22.0 (23.5 -> 21.6); 2048 keys, on the two passes by the rule: 30.9 (24.9), here 30.5 (29.9)
-//   fp32, 8 heads, window 32, d = 64: 1024 keys 29.4 -> 19.8 (23.1 -> 18.9); d = 128, 1000 keys, window 8: 31.1 -> 27.7 (28.5 -> 27.1)
-constexpr int kShortKeysBf16 = 2048, kShortKeysF32 = 1024;
+// A layer step of 32 heads on 8, head_dim 128, us a call (in a graph, where launches are cheap), two passes -> one launch:
+//   window 8:  512 keys 23.9 -> 18.6 (17.1 -> 13.9), 1024 keys 23.1 -> 18.7 (17.6 -> 16.5), 1280 keys 25.0 -> 19.6 (18.2 -> 18.5),
+//              1536 keys 23.3 -> 20.5 (18.7 -> 19.8), 1792 keys 25.1 -> 21.6 (18.8 -> 20.7), 2048 keys 24.0 -> 23.0 (19.3 -> 21.9);
+//              four sequences of 1536 keys 24.7 -> 22.4 (21.2 -> 21.2), of 2048 keys 24.7 -> 24.6 (22.4 -> 23.6)
+//   window 32: 512 keys 24.1 -> 18.0 (19.1 -> 15.8), 1024 keys 24.9 -> 19.9 (19.6 -> 18.7)
+//   window 64: 1024 keys 24.9 -> 22.6 (23.1 -> 21.8); four sequences of 1024 keys 30.5 -> 25.0 (27.9 -> 23.9)
+// So beyond 1280 keys of 256 bytes fewer launches win for a caller that launches each time and lose in a captured graph; the
+// line is where what they lose outweighs what they win, after 1792 keys.  Keys of 128 bytes, 8 heads on 2:
+//   window 8:  1024 keys 24.4 -> 18.4 (16.7 -> 14.2), 1536 keys 24.6 -> 18.5 (17.1 -> 15.8), 2048 keys 24.4 -> 18.7 (17.8 -> 17.3)
+//   window 64: 1024 keys 25.0 -> 18.4 (20.1 -> 15.7), 1536 keys 24.5 -> 19.4 (20.7 -> 18.5), 2048 keys 24.5 -> 21.2 (21.1 -> 20.2)
+//   fp32, 8 heads on 8, window 32: 512 keys 24.9 -> 18.8 (21.8 -> 15.4), 1024 keys 24.7 -> 20.2 (22.2 -> 19.4)
+// fp32 keys of 512 bytes, 8 heads on 2: window 8, 1024 keys 29.1 -> 27.3 (27.0 -> 26.3); window 64 30.6 -> 30.1 (28.2 -> 29.1)
+int64_t short_keys(const structkv_shape& s) {
+  if (s.dtype != STRUCTKV_DTYPE_BF16) return 1024;
+  return s.head_dim == 128 ? 1792 : 2048;
+}
 bool short_plan(const structkv_shape& s, int batch, int64_t longest, int64_t total, ScorePlan* p) {
   const bool bf16 = s.dtype == STRUCTKV_DTYPE_BF16;
   if (s.head_dim != 64 && s.head_dim != 128) return false;
-  if (total < 1 || longest > (bf16 ? kShortKeysBf16 : kShortKeysF32)) return false;
+  if (total < 1 || longest > short_keys(s)) return false;
   memset(p, 0, sizeof(*p));
   p->path = 2;
   p->R = s.n_q_heads / s.n_kv_heads * s.window;
@@ -366,7 +377,7 @@ size_t structkv_workspace_bytes(const structkv_shape* shape, int32_t batch, int6
       if (p.total_bytes > need) need = p.total_bytes;
     }
     ScorePlan p;   // (grows with total_tokens: from the longest short call on it stays)
-    const int64_t most = (int64_t)batch * (shape->dtype == STRUCTKV_DTYPE_BF16 ? kShortKeysBf16 : kShortKeysF32);
+    const int64_t most = (int64_t)batch * short_keys(*shape);
     if (short_plan(*shape, batch, 0, std::min(total_tokens, most), &p) && p.total_bytes > need) need = p.total_bytes;
   }
   return align_up(need, 256);

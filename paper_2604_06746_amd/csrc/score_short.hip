@@ -109,13 +109,18 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
 #pragma unroll
     for (int c = 0; c < F::PIECES; ++c) qf[rb].v[c] = *reinterpret_cast<const floatx4*>(row + (4 * c + lg) * (16 / (int)sizeof(T)));
   }
-  issue(0);
-  if (SLOTS > 1 && TW > 1) issue(1);
+  // Eight tiles: those past the sequence's end are left out (uniform in the wave), so that a length of just over 1024 keys
+  // costs five of them (a layer step of 1280 keys, 32 heads on 8, window 8, in a graph: 20.4 -> 18.5 us).  With two or four
+  // the tests cost more than they save (1024 fp32 keys 19.9 -> 20.3 us).
+  auto has = [&](int i) __attribute__((always_inline)) { return TW < 8 || tile0(i) < n; };
+  if (has(0)) issue(0);
+  if (SLOTS > 1 && TW > 1 && has(1)) issue(1);
   // (never fewer than two: an array of exactly 32 floats becomes ONE 32-register value, and 400 registers spill)
   floatx4 acc[NRB < 2 ? 2 : NRB][TW];
 #pragma unroll
   for (int i = 0; i < TW; ++i) {
-    if (i + 1 < TW && SLOTS > 1) wait_vmcnt<INST>(); else wait_vmcnt<0>();
+    if (!has(i)) break;
+    if (i + 1 < TW && SLOTS > 1 && has(i + 1)) wait_vmcnt<INST>(); else wait_vmcnt<0>();
     asm volatile("" ::: "memory");
     F kf;
     const uint8_t* slot = slots + (i % SLOTS) * TILEB;
@@ -124,7 +129,7 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
       kf.v[c] = *reinterpret_cast<const floatx4*>(slot + (l16 * SEGS + ((4 * c + lg) ^ swz(l16))) * 16);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the operands are in registers: the slot may be overwritten
     __builtin_amdgcn_sched_barrier(0);
-    if (i + SLOTS < TW) issue(i + SLOTS);
+    if (i + SLOTS < TW && has(i + SLOTS)) issue(i + SLOTS);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) acc[rb][i] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -147,6 +152,7 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
     float m = -INFINITY;
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
+      if (!has(i)) break;
       if (masked(i)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -169,6 +175,7 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
     float z = 0.f, e = 0.f;
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
+      if (!has(i)) break;
       floatx4 xs;
 #pragma unroll
       for (int j = 0; j < 4; ++j) xs[j] = fmaf(acc[rb][i][j], c2, -M[rb]);

@@ -11,8 +11,14 @@ namespace skv {
 static int g_launches = 0;
 static int32_t g_last_plan[8];
 extern "C" int structkv_stub_launch_count(void) { return g_launches; }
-// RB, NW, KC, planes, stream_k, RC, grid_chunks, path of the latest MFMA scoring launch
+// RB, NW, KC, planes, stream_k, RC, grid_chunks, path of the latest scoring launch
 extern "C" void structkv_stub_last_plan(int32_t* out) { for (int i = 0; i < 8; ++i) out[i] = g_last_plan[i]; }
+
+static void keep_plan(const ScorePlan& p) {
+  ++g_launches;
+  const int32_t plan[8] = {p.RB, p.NW, p.KC, p.planes, p.stream_k, p.RC, (int32_t)p.grid_chunks, p.path};
+  for (int i = 0; i < 8; ++i) g_last_plan[i] = plan[i];
+}
 
 // The bins of the mid-sized selection for one centre: how many keys the two directions of the mapping disagree on, how many
 // bins do not follow on the one before, and whether they end with the last key.
@@ -35,9 +41,7 @@ extern "C" int structkv_stub_bin_faults(uint32_t centre) {
 hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void*,
                                   const void*, int64_t, int64_t, float, float*, const float*, float*, int64_t total,
                                   float* probs, int pass, hipStream_t) {
-  ++g_launches;
-  const int32_t plan[8] = {p.RB, p.NW, p.KC, p.planes, p.stream_k, p.RC, (int32_t)p.grid_chunks, p.path};
-  for (int i = 0; i < 8; ++i) g_last_plan[i] = plan[i];
+  keep_plan(p);
   if (p.grid_chunks == 0) return hipSuccess;
   bool ok = p.path == 0 && (s.head_dim == 64 || s.head_dim == 128) && (pass == 1 || pass == 2);
   ok = ok && ((p.RB == 2 && p.NW == 4) || (p.RB == 1 && p.NW == 4) || (p.RB == 2 && p.NW == 1) || (p.RB == 1 && p.NW == 1));
@@ -55,9 +59,9 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
   }
   return ok ? hipSuccess : hipErrorInvalidValue;
 }
-hipError_t launch_score_simt(const structkv_shape&, const ScorePlan&, const SeqTable&, const void*, const void*,
+hipError_t launch_score_simt(const structkv_shape&, const ScorePlan& p, const SeqTable&, const void*, const void*,
                              int64_t, int64_t, float, float*, const float*, float*, int64_t, float*, int,
-                             hipStream_t) { ++g_launches; return hipSuccess; }
+                             hipStream_t) { keep_plan(p); return hipSuccess; }
 hipError_t launch_score_combine(const structkv_shape&, const ScorePlan&, const SeqTable&, const float*, float*,
                                 float*, uint32_t*, int64_t, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_score_reduce(const structkv_shape&, const ScorePlan&, const SeqTable&, const float*, int64_t,

@@ -348,6 +348,24 @@ def test_tilings_chosen_for_the_named_configurations(B):
     assert p["grid_chunks"] == sum(-(-(n // 2) // p["KC"]) for n in lens) and p["stream_k"] == 0
 
 
+def test_longest_sequences_of_the_one_launch_scoring(B):
+    """Keys of 256 bytes go through one scoring launch up to 1792 of them, where it still wins more for a caller that launches
+    eagerly than it costs a captured replay; shorter keys up to 2048, fp32 up to 1024.  Stub build only."""
+    lib = B._lib
+    if not hasattr(lib, "structkv_stub_last_plan"):
+        pytest.skip("the real library launches kernels; this runs against the stub build only")
+    fake, fake2 = ctypes.c_void_p(1 << 20), ctypes.c_void_p(1 << 21)
+    for Hq, G, d, dtype, most, beyond in [(32, 8, 128, 1, 1792, 0), (8, 2, 64, 1, 2048, 0), (8, 8, 64, 0, 1024, 1), (8, 2, 128, 0, 1024, 1)]:
+        for n in (most, most + 1):
+            shape = B.make_shape(Hq, G, d, 8, dtype, False)
+            need = B.structkv_workspace_bytes(shape, 1, n)
+            assert lib.structkv_score_layer(ctypes.byref(shape), fake, fake, n * d, d, 1, (ctypes.c_int64 * 2)(0, n), fake, fake, None,
+                                            fake2, need, None) == B.STRUCTKV_OK, B.structkv_last_error()
+            out = (ctypes.c_int32 * 8)()
+            lib.structkv_stub_last_plan(out)
+            assert out[7] == (2 if n == most else beyond), (Hq, d, dtype, n)
+
+
 @pytest.mark.parametrize("centre", [0, 1, 1 << 24, (9 << 21) + 12345, 0x7FFFFFFF, 0x80000000, 0xA4000001, 0xBF800000, 0xC77FFFFF,
                                     0xFE200000, 0xFF800000, 0xFFFFFFFF])
 def test_bins_of_the_mid_sized_selection(B, centre):
