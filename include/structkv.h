@@ -64,6 +64,8 @@ int32_t structkv_version(void);
  * for a batch of `batch` sequences holding `total_tokens` tokens in all.  With shape == NULL
  * only the top-k requirement is returned.  Returns 0 on invalid arguments.  The workspace must
  * be 256-byte aligned; its contents need not be preserved between calls and need no initialisation.
+ * A scoring call also takes a smaller workspace where one of its plans fits it; it may then be another plan, whose
+ * sums are formed in another order, than with the size returned here (short sequences: the two-pass plan).
  */
 size_t structkv_workspace_bytes(const structkv_shape* shape, int32_t batch, int64_t total_tokens);
 
@@ -79,7 +81,8 @@ size_t structkv_workspace_bytes(const structkv_shape* shape, int32_t batch, int6
  * cu_seqlens : HOST pointer, [B+1], cu[0]=0, non-decreasing, cu[B] = total tokens; n_b = 0 is allowed
  *              (no output, entropy 0), otherwise n_b >= 1 (and n_b >= w if causal).
  * indeg_out [total], entropy_out [B], entropy_per_head_out [B][H_q]: fp32.
- * Deterministic: the same inputs give bit-identical outputs (no floating-point atomics).
+ * Deterministic: the same inputs give bit-identical outputs (no floating-point atomics), whatever the workspace's size
+ * from structkv_workspace_bytes(shape, batch, total) on.
  */
 structkv_status structkv_score_layer(const structkv_shape* shape, const void* q_win, const void* k,
                                      int64_t k_stride_head, int64_t k_stride_tok, int32_t batch,
@@ -256,7 +259,7 @@ structkv_status structkv_block_scores(const float* scores, int32_t batch, const 
  * vector over the n_b keys of sequence b.  Per sequence:
  *   sparsity_out[b] = (1/H_q) sum_h ( sum of the k largest a_h[j] ),   k = ceil(top_frac * n_b) in double arithmetic (paper: 0.1)
  *   variance_out[b] = (1/H_q) sum_h (1/n_b) sum_j (a_h[j] - 1/n_b)^2
- * (0 for an empty sequence).  With bf16 inputs, head_dim 64 or 128 and a window of 8, 16, 32 or 64 the per-head in-degrees
+ * (0 for an empty sequence).  With bf16 inputs, head_dim 64 or 128 and a window of 8, 16, 32 or 64 (64: not with two query heads per KV head) the per-head in-degrees
  * come out of the scoring pass itself (its second pass keeps one column-sum plane per query head) and the call
  * costs one scoring of the layer plus four short kernels over those planes (a radix select for the top-k mass);
  * other shapes are re-scored head by head, which costs about as much as scoring the layer twice.

@@ -225,6 +225,24 @@ def test_short_sequences_with_a_smaller_workspace(B, oracle, dtype):
         assert_entropy(e.cpu().numpy(), ent, tol)
 
 
+# the size of the workspace, from the reported one on, does not show in the results
+@pytest.mark.parametrize("dtype,lens", [(torch.float32, [900]), (torch.bfloat16, [900]), (torch.bfloat16, [700, 33, 1500, 64]),
+                                        (torch.bfloat16, [3000, 5])])
+def test_results_do_not_depend_on_a_larger_workspace(B, dtype, lens):
+    Hq, G, d, w = 16, 2, 64, 32
+    shape = B.make_shape(Hq, G, d, w, B.STRUCTKV_DTYPE_F32 if dtype == torch.float32 else B.STRUCTKV_DTYPE_BF16)
+    need = B.structkv_workspace_bytes(shape, len(lens), sum(lens))
+    q, k = _randn(len(lens), Hq, w, d, dtype=dtype, seed=12), _randn(G, sum(lens), d, dtype=dtype, seed=13)
+    cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
+    outs = []
+    for nbytes in (need, need + 256, 4 * need):
+        out, e, eh = torch.zeros(sum(lens), device="cuda"), torch.zeros(len(lens), device="cuda"), torch.zeros(len(lens), Hq, device="cuda")
+        B.structkv_score_layer(shape, q, k, cu, out, e, eh, torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda"))
+        outs.append((out, e, eh))
+    for other in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(outs[0], other))
+
+
 # inputs that are not finite: a NaN key makes its whole sequence NaN (in the masked tiles too), a NaN query row reaches
 # the keys that it sees and no others; the sequences beside it are untouched
 @pytest.mark.parametrize("dtype,w,lens", [(torch.float32, 32, [1500, 40]), (torch.float32, 8, [900, 300]), (torch.bfloat16, 8, [3000, 90]),
