@@ -128,7 +128,8 @@ __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* sh /*[>= THREAD
 
 // Scan the NB bins of a histogram from the top until `krem` (1 .. their sum) keys are covered.
 // Returns the bin (all threads), how many keys lie above it and how many in it.
-// Two barriers; `scan` and `res` must not be written again before another one.
+// Two barriers; `scan` and `res` must not be written again before another one.  gh: 16-byte aligned where a thread has four
+// bins or more.
 template <int THREADS, int NB>
 __device__ inline void select_bin(const uint32_t* __restrict__ gh, uint32_t krem, uint32_t* scan /*[>= THREADS / 64]*/,
                                   uint32_t* res /*[3]*/, uint32_t* bin_out, uint32_t* above_out, uint32_t* in_bin_out = nullptr) {
@@ -392,12 +393,13 @@ constexpr int kMidShare = 1024;    // scores of a mid-form workgroup: four per t
 constexpr int kMidPer = kMidShare / kThreads;
 constexpr int kListed = 64;        // keys that one wave ranks directly
 
-// LDS of resolve_key
+// LDS of resolve_key (select_bin reads the histogram sixteen bytes at a time)
 struct ResolveLds {
-  uint32_t hist[kBins];
+  alignas(16) uint32_t hist[kBins];
   uint32_t list[kListed];
   uint32_t scan[16], res[3], n;
 };
+static_assert(alignof(ResolveLds) >= 16 && offsetof(ResolveLds, hist) == 0, "select_bin's 16-byte reads");
 
 // One more in h[bin] for every calling lane; lanes that share one of two values add up first (an LDS atomic of 64 lanes on one
 // word takes 64 turns: 131072 equal scores, 100 us a sweep).
