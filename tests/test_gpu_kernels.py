@@ -32,16 +32,29 @@ def _randn(*shape, dtype, seed):
     return torch.randn(*shape, generator=g, device="cuda").to(dtype)
 
 
-def _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens, pad=0):
-    """Score one layer and compare in-degree and entropies; pad: extra elements between key rows (odd strides)."""
+def _score(B, sw, q, k, two_pass):
+    """The scoring call; two_pass: its four kernels one by one, which never go through the one launch of short sequences."""
+    if not two_pass:
+        sw.score(q, k)
+        return
+    for step in (1, 2, 4, 8):
+        B.structkv_debug_score_steps(sw.shape, q, k, sw.cu, sw.indeg, sw.entropy, sw.entropy_per_head, sw.workspace, step)
+
+
+def _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens, pad=0, scale=0.0, two_pass=False, late=0.0):
+    """Score one layer and compare in-degree and entropies; pad: extra elements between key rows (odd strides); late: from this
+    share of every sequence on its keys are 24 times larger."""
     total = sum(lens)
-    sw = sweep_mod.LayerSweep(Hq, G, d, w, dtype, lens, [0] * len(lens), causal=causal)
+    sw = sweep_mod.LayerSweep(Hq, G, d, w, dtype, lens, [0] * len(lens), causal=causal, scale=scale)
     q = _randn(len(lens), Hq, w, d, dtype=dtype, seed=1)
     k = _randn(G, total, d + pad, dtype=dtype, seed=2)[:, :, :d]
+    if late:
+        for b in range(len(lens)):
+            k[:, sw.cu[b] + int(late * lens[b]):sw.cu[b + 1], :] *= 24.0
     sw.indeg.fill_(-7.0)
-    sw.score(q, k)
+    _score(sweep_mod.B, sw, q, k, two_pass)
     torch.cuda.synchronize()
-    D, ent, ent_h, _ = oracle.score_layer(to_oracle_array(q), to_oracle_array(k), Hq, G, d, w, lens, causal=causal)
+    D, ent, ent_h, _ = oracle.score_layer(to_oracle_array(q), to_oracle_array(k), Hq, G, d, w, lens, causal=causal, scale=scale)
     tol = 1e-5 if dtype == torch.float32 else 1e-3
     assert_close_floor(sw.indeg.cpu().numpy(), D, tol, "indeg")
     assert_entropy(sw.entropy.cpu().numpy()[:len(lens)], ent, tol)
@@ -55,17 +68,42 @@ def _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens, pad=0):
                                                (2, 1, 256, 40, [300], 0), (3, 3, 200, 8, [64, 1, 700], 3)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("causal", [False, True])
-def test_fp32_matrix_scoring_kernels(sweep_mod, oracle, Hq, G, d, w, lens, pad, dtype, causal):
+@pytest.mark.parametrize("two_pass", [False, True])
+def test_fp32_matrix_scoring_kernels(sweep_mod, oracle, Hq, G, d, w, lens, pad, dtype, causal, two_pass):
     if causal:
         lens = [max(n, w) for n in lens]
-    _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens, pad)
+    _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens, pad, two_pass=two_pass)
 
 
-# causal windows that are no multiple of the 32-row blocks: heads straddle row blocks and waves
+# causal windows that are no multiple of the 32-row blocks: heads straddle row blocks and waves; one- and four-wave workgroups
 @pytest.mark.parametrize("Hq,G,d,w", [(8, 2, 128, 1), (8, 2, 128, 7), (32, 8, 128, 8), (4, 4, 64, 33), (10, 2, 64, 24), (8, 2, 128, 40),
-                                      (2, 1, 128, 100)])
-def test_causal_windows_on_the_bf16_kernels(sweep_mod, oracle, Hq, G, d, w):
-    _check_scores(sweep_mod, oracle, Hq, G, d, w, torch.bfloat16, True, [w, w + 1, 257, 64 + w, 1111])
+                                      (2, 1, 128, 100), (3, 1, 64, 40)])
+@pytest.mark.parametrize("two_pass", [False, True])
+def test_causal_windows_on_the_bf16_kernels(sweep_mod, oracle, Hq, G, d, w, two_pass):
+    _check_scores(sweep_mod, oracle, Hq, G, d, w, torch.bfloat16, True, [w, w + 1, 257, 64 + w, 1111], two_pass=two_pass)
+
+
+# the two-pass bf16 kernels on sequences that ordinary calls score in one launch: one and two row blocks, one and four waves,
+# both head sizes; keys late in a chunk that outgrow its first tile's reference by far (pass 1 runs it again)
+@pytest.mark.parametrize("Hq,G,d,w,lens", [(8, 2, 128, 8, [1234, 77]), (4, 2, 128, 32, [1700]), (4, 4, 64, 32, [1111]), (2, 2, 64, 64, [900, 45]),
+                                           (6, 2, 128, 32, [1700, 45]), (10, 2, 64, 24, [1203]), (8, 2, 128, 40, [999]),
+                                           (8, 2, 64, 64, [1500])])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("late", [0.0, 0.4])
+def test_two_pass_kernels_on_short_sequences(sweep_mod, oracle, Hq, G, d, w, lens, causal, late):
+    if causal:
+        lens = [max(n, w) for n in lens]
+    _check_scores(sweep_mod, oracle, Hq, G, d, w, torch.bfloat16, causal, lens, two_pass=True, late=late)
+
+
+# one scoring launch: keys with gaps between the rows, another scale than 1/sqrt(head_dim), the table of 64 sequences
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Hq,G,d,w,lens,pad,scale", [(8, 2, 128, 8, [700, 33], 8, 0.0), (4, 2, 64, 32, [300], 24, 0.07), (8, 8, 64, 16, [1000], 0, 0.3),
+                                                     (32, 8, 128, 8, [513], 128, 0.0), (2, 1, 64, 8, [8 + 3 * i for i in range(64)], 0, 0.0),
+                                                     (2, 1, 128, 8, [0, 9] + [40] * 60 + [600, 0], 8, 0.05)])
+def test_one_scoring_launch_strides_scale_and_batch(sweep_mod, oracle, Hq, G, d, w, lens, pad, scale, dtype, causal):
+    _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens, pad, scale)
 
 
 def _select(B, scores, lens, ks, tail):
@@ -173,15 +211,16 @@ def test_pivot_metrics_of_short_windows(sweep_mod, oracle, Hq, G, d, w, lens, ca
 @pytest.mark.parametrize("Hq,G,w", [(8, 2, 8), (4, 2, 32), (8, 2, 32), (8, 2, 64)])
 @pytest.mark.parametrize("lens", [[64], [65, 1, 0, 200], [5000], [17000, 31]])
 def test_short_key_chunks(sweep_mod, oracle, Hq, G, w, lens):
-    _check_scores(sweep_mod, oracle, Hq, G, 128, w, torch.bfloat16, False, lens)
+    _check_scores(sweep_mod, oracle, Hq, G, 128, w, torch.bfloat16, False, lens, two_pass=True)
 
 
 # short sequences in one scoring launch: edges of the 16-key tiles, of the two, four and eight tiles per wave (512, 1024,
-# 2048 keys) and of the path itself (1024 fp32 / 2048 bf16 keys, 64 column-sum planes), rows around the 16- and 32-row
+# 2048 keys) and of the path itself (1024 fp32 / 1792 or 2048 bf16 keys, 64 column-sum planes), rows around the 16- and 32-row
 # blocks, one and two row blocks per workgroup, empty sequences; then the layer step, whose selection forms the in-degrees itself, against the separate calls
 @pytest.mark.parametrize("Hq,G,d,w", [(1, 1, 64, 1), (3, 1, 128, 5), (8, 8, 64, 32), (32, 8, 128, 8), (4, 2, 64, 17), (16, 2, 128, 64),
                                       (32, 8, 64, 64)])
-@pytest.mark.parametrize("lens", [[1], [15, 0, 17], [255, 256, 257], [512, 513], [1024], [1025, 33], [2048], [2049, 5]])
+@pytest.mark.parametrize("lens", [[1], [15, 0, 17], [255, 256, 257], [512, 513], [1024], [1025, 33], [1281, 1536], [1792], [1793],
+                                  [2048], [2049, 5]])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("causal", [False, True])
 def test_short_sequences_in_one_scoring_launch(sweep_mod, oracle, Hq, G, d, w, lens, dtype, causal):
