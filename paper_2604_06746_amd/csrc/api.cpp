@@ -94,9 +94,8 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     if (planes && s.window == p->RPC) p->planes = 1;
     else if (planes && s.window == 32) p->planes = 2;
     else if (planes && (s.window == 16 || s.window == 8)) { p->planes = p->RB; p->split = 32 / s.window; }
-    // the kernels' LDS column-sum capacity (per-head planes: kPlanesKeyCap there)
     const int np = p->planes * p->split;
-    const int64_t kMaxKC = np ? (p->NW == 4 ? 1280 / np + 96 : np <= 4 ? 1024 / np : 256) : (p->NW == 4 ? 2048 : 896);
+    const int64_t kMaxKC = np ? planes_key_cap(p->NW, np) : ring_key_cap(p->NW);
     const int64_t slots = 256 * (p->NW == 4 ? 3 : 8);
     const int64_t wg_per_chunk = s.n_kv_heads * ceil_div(p->RC, p->NW);
     const int64_t chunks_per_round = slots / wg_per_chunk > 0 ? slots / wg_per_chunk : 1;
@@ -106,7 +105,8 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     // workgroup's fixed costs -- query operands, the first tiles' latency, the partial results -- weigh as much
     // as 6-8 tiles; with layers running as chains the other half of the chip is another layer's), else 256; and where
     // 256 leave SIMDs without a wave, as few as give every SIMD one (256 four-wave or 1024 one-wave workgroups), but
-    // two tiles: 32 heads on 8, window 8: 512 / 2048 / 4096 tokens 19 -> 13.1 / 13.4 / 14.2 us per scoring call.
+    // two tiles: 32 heads on 8, window 8: 512 / 2048 / 4096 tokens 19 -> 13.1 / 13.4 / 14.2 us per scoring call (512 now go
+    // through one launch, see short_plan).
     // (More workgroups than that lose: they share CUs unevenly and leave more partial results: 8 heads on 2, window 64,
     // 32768 tokens 30.5 us with 256 keys, 33.2 with 192.)
     int64_t kc_min = ceil_div(total, 512) * wg_per_chunk * 2 >= slots ? 512 : 256;
@@ -127,13 +127,13 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     p->RC = (int)ceil_div(p->R, p->RPC);
     p->NW = p->RC > 2 ? 4 : p->RC;
     p->CP = (int)ceil_div(p->RC, p->NW);
-    // keys per workgroup: one round of workgroups (256 CUs x 2), but at least one tile per wave, at most the 1024
+    // keys per workgroup: one round of workgroups (256 CUs x 2), but at least one tile per wave, at most those
     // whose column sums the kernels hold in LDS
     const int64_t chunks_per_round = ceil_div(512, (int64_t)s.n_kv_heads * p->CP);
     const int64_t step = 32 * (4 / p->NW);
     int64_t kc = ceil_div(ceil_div(total > 0 ? total : 1, chunks_per_round), step) * step;
-    p->KC = (int)(kc > 1024 ? 1024 : kc);
-    chunk_bound = std::max(std::min(chunks_per_round, ceil_div(total, step)), total / 1024);   // (grows with total)
+    p->KC = (int)(kc > kF32KeyCap ? kF32KeyCap : kc);
+    chunk_bound = std::max(std::min(chunks_per_round, ceil_div(total, step)), total / kF32KeyCap);   // (grows with total)
   }
   if (seq) {
     p->n_chunks = 0;
@@ -268,7 +268,7 @@ structkv_status run_score(const structkv_shape* shape, const void* q_win, const 
   float* ent_head = ent_head_out ? ent_head_out : (float*)(w8 + p.off_enthead);
   const float scale = s.scale > 0.f ? s.scale : 1.0f / std::sqrt((float)s.head_dim);
   const float c2 = (float)((double)scale * 1.4426950408889634);
-  auto pass = p.path == 0 ? launch_score_mfma_ring : launch_score_simt;
+  auto pass = p.path == 0 ? launch_score_mfma_ring : launch_score_f32;
 
   // Cache-resident second pass (a measurement hook, not the default).  A batch whose keys exceed the 256 MB
   // memory-side cache can be scored in groups of consecutive sequences whose keys fit it: pass 1, combine and
@@ -331,7 +331,7 @@ structkv_status run_score(const structkv_shape* shape, const void* q_win, const 
     return STRUCTKV_OK;
   };
   if (p.path == 2) {
-    SKV_HIP_CHECK(launch_score_simt(s, p, seq, q_win, k, ksh, kst, c2, row_ent, nullptr, colsum, total, nullptr, 3, st));
+    SKV_HIP_CHECK(launch_score_short(s, p, seq, q_win, k, ksh, kst, c2, row_ent, colsum, total, st));
   } else if ((o.step_mask & 7) == 7) {
     for (int gi = 0; gi < n_groups; ++gi) {
       const structkv_status gs = run_group(gi, 7);

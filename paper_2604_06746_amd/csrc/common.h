@@ -248,6 +248,17 @@ struct SelectFusion {
   int mode;              // kSelMid: fine bins; kSelLong: the top 11 bits
 };
 
+// Most keys of a workgroup: what the scoring kernels have LDS for to collect column sums in.  bf16 kernels by waves per
+// workgroup; with NP column-sum planes per wave all tiles but the loop's last three are collected there (score_mfma_ring.hip).
+constexpr int ring_key_cap(int nw) { return nw == 4 ? 2048 : 896; }
+constexpr int kPlanesDirectTiles = 3;
+constexpr int planes_lds_keys(int nw, int np) { return nw == 4 ? 1280 / np : (np <= 4 ? 1024 / np : 256) - 32 * kPlanesDirectTiles; }
+constexpr int planes_key_cap(int nw, int np) { return planes_lds_keys(nw, np) + 32 * kPlanesDirectTiles; }
+constexpr int kF32KeyCap = 1024;   // fp32 kernels: of up to four row-chunks
+
+// the form of a selection whose longest searched prefix has `longest` scores
+static inline int selection_mode(int64_t longest) { return longest <= kShortSeq ? kSelShort : longest <= kMidSeq ? kSelMid : kSelLong; }
+
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -280,11 +291,11 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
                                   const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
                                   float* stats, const float* lse2, float* colsum, int64_t total,
                                   float* probs, int pass, hipStream_t st);
-// pass 3 (a plan of path 2): both passes in one launch (launch_score_short); `stats` takes the row entropies
-hipError_t launch_score_simt(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq,
-                             const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
-                             float* stats, const float* lse2, float* colsum, int64_t total,
-                             float* probs, int pass, hipStream_t st);
+hipError_t launch_score_f32(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq,
+                            const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
+                            float* stats, const float* lse2, float* colsum, int64_t total,
+                            float* probs, int pass, hipStream_t st);
+// a plan of path 2: both passes in one launch
 hipError_t launch_score_short(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void* q, const void* k,
                               int64_t ksh, int64_t kst, float c2, float* row_ent, float* colsum, int64_t total, hipStream_t st);
 // zero_words > 0: the kernel also clears that many 32-bit words at zero_ptr (the selection's histograms)

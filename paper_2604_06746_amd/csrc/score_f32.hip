@@ -17,7 +17,8 @@
 // Measured, one layer's two passes, fp32, 8 heads x 32 rows, 1024 keys, d = 64: 107 us as dot products in vector
 // instructions with both operands in LDS (16 x 16 threads, two LDS reads per fma, one key lane's dot products one
 // after the other) -> 13.5 us here, most of it launch, load latency and the 32 matrix instructions of the one tile
-// that each wave has; the whole layer 132 -> 39.6 us.
+// that each wave has; the whole layer 132 -> 39.6 us with the kernels of that time around them.  (Ordinary calls of that
+// length now go through score_short.hip; these take longer ones and other head sizes, strides and alignments.)
 #include "common.h"
 
 #include <type_traits>
@@ -28,7 +29,6 @@ namespace {
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 
 constexpr float kNegBig = -1.0e30f;
-constexpr int kKeyCap = 1024;   // most keys of a workgroup (column sums of up to four row-chunks in LDS)
 
 __device__ __forceinline__ float widen(float v) { return v; }
 __device__ __forceinline__ float widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256, DP == 256 ? 1 : 2) void score_f32_kernel(
     float* __restrict__ stats, const float* __restrict__ lse2, float* __restrict__ colsum, int64_t total,
     float* __restrict__ probs) {
   constexpr int NC = DP / 8;   // groups of eight components; each lane holds four of every group
-  __shared__ float sh[PASS == 1 ? 4 * 3 * 32 : 4 * kKeyCap];
+  __shared__ float sh[PASS == 1 ? 4 * 3 * 32 : 4 * kF32KeyCap];
 
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256, DP == 256 ? 1 : 2) void score_f32_kernel(
       for (int i = 0; i < 16; i += 2) { cs0 += pr[i]; cs1 += pr[i + 1]; }
       float cs = cs0 + cs1;
       cs += __shfl_xor(cs, 32);
-      if (lh == 0) sh[wr * kKeyCap + 32 * s + l32] = live ? cs : 0.f;
+      if (lh == 0) sh[wr * kF32KeyCap + 32 * s + l32] = live ? cs : 0.f;
     }
   }
 
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256, DP == 256 ? 1 : 2) void score_f32_kernel(
     float* out = colsum + ((int64_t)g * rcg + t % rcg) * total + tok0 + key0;
     for (int i = threadIdx.x; i < key_end - key0; i += 256) {
       float s = sh[i];
-      for (int o = 1; o < NW; ++o) s += sh[o * kKeyCap + i];
+      for (int o = 1; o < NW; ++o) s += sh[o * kF32KeyCap + i];
       out[i] = s;
     }
   }
@@ -219,10 +219,9 @@ hipError_t launch_cfg(const structkv_shape& s, const ScorePlan& p, const SeqTabl
 
 }  // namespace
 
-hipError_t launch_score_simt(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void* q,
-                             const void* k, int64_t ksh, int64_t kst, float c2, float* stats, const float* lse2,
-                             float* colsum, int64_t total, float* probs, int pass, hipStream_t st) {
-  if (pass == 3) return launch_score_short(s, p, seq, q, k, ksh, kst, c2, stats, colsum, total, st);
+hipError_t launch_score_f32(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void* q,
+                            const void* k, int64_t ksh, int64_t kst, float c2, float* stats, const float* lse2,
+                            float* colsum, int64_t total, float* probs, int pass, hipStream_t st) {
   if (p.grid_chunks == 0) return hipSuccess;
   const size_t e = s.dtype == STRUCTKV_DTYPE_F32 ? 4 : 2;
   // four components per load: whole groups of eight, rows and pointers aligned to the load

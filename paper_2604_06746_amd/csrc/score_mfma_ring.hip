@@ -65,23 +65,18 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// most keys a workgroup may be given (pass 2 keeps one fp32 column sum per key in LDS)
-// (one-wave workgroups: 896, so that eight of them -- 16 KB ring + 3.5 KB each -- still share a CU's 160 KB)
-template <int NW> constexpr int kKeyCap = NW == 4 ? 2048 : 896;
+// Most keys a workgroup may be given (ring_key_cap): pass 2 keeps one fp32 column sum per key in LDS.  One-wave workgroups:
+// 896, so that eight of them -- 16 KB ring + 3.5 KB each -- still share a CU's 160 KB.
 
 // Pass 2 with one column-sum plane per QUERY HEAD instead of one per workgroup (the per-head in-degrees of the
 // pivot detector's metrics, Eq. 5-6): PPW * SPLIT planes per wave -- PPW = 1 when a wave's rows are one head's window,
 // 2 when each of its two 32-row blocks is; windows of 16 and 8 put SPLIT = 2 and 4 heads into every 32-row block (a
 // 32K-token layer with its metrics, window 8: 57.6 us; 94 us when the layer was re-scored head by head instead).  Most
-// keys a workgroup may then be given: its LDS holds NW * planes sums per key for all tiles but the loop's last THREE,
+// keys a workgroup may then be given (planes_key_cap): its LDS holds NW * planes sums per key for all tiles but the loop's last THREE,
 // whose sums go from the registers straight to global memory (no tile load is requested after them any more, so these
 // stores sit behind every load that a wait still counts) -- 20 KB of sums beside three 4-wave workgroups' rings, which
 // is what lets a 128K-token layer be ONE round of 768 workgroups with 1376 keys each (21 KB already cost the third
 // workgroup per CU); 4 KB beside a one-wave workgroup's ring, at least 256 keys.
-constexpr int kPlanesDirectTiles = 3;
-// keys whose sums LDS holds, for NP planes per wave; and the key cap
-template <int NW, int NP> constexpr int kPlanesLdsKeys = NW == 4 ? 1280 / NP : (NP <= 4 ? 1024 / NP : 256) - 32 * kPlanesDirectTiles;
-template <int NW, int NP> constexpr int kPlanesKeyCap = kPlanesLdsKeys<NW, NP> + 32 * kPlanesDirectTiles;
 
 // NW = waves per workgroup (row-chunks sharing the key tiles), NBUF = tiles in the LDS ring; PPW > 0 (pass 2):
 // planes per head as above: head h of KV head g is plane g*(R/w) + h of `colsum`.
@@ -117,7 +112,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
   constexpr bool PLANES = PPW > 0;
   constexpr int NP = PLANES ? PPW * SPLIT : 1;   // planes per wave
   // (with planes: keys per plane in LDS)
-  constexpr int KCAP = PASS == 2 ? (PLANES ? kPlanesLdsKeys<NW, NP> : kKeyCap<NW>) : 1;
+  constexpr int KCAP = PASS == 2 ? (PLANES ? planes_lds_keys(NW, NP) : ring_key_cap(NW)) : 1;
   static_assert(!PLANES || (PASS == 2 && !DUMP && PPW <= NRB), "per-head planes are a pass-2 output");
   static_assert(SPLIT == 1 || PPW == NRB, "several heads per row block: every block has its own planes");
   // vector-ALU instructions the scheduler is asked to place after each MFMA of the next row block
@@ -359,7 +354,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
           // row modulo the window (any window: heads may straddle row blocks), by multiplication with its
           // reciprocal -- exact for rows below 65536; only the tiles of the last w keys come here
           // (windows that are no multiple of 32 rows went to the fp32 kernels: a causal layer of four prompts of 64 to
-          // 1500 tokens with a window of 8 took 240 us and takes 41 us)
+          // 1500 tokens with a window of 8 took 240 us there and 41 us here, before score_short.hip took that length)
           const int r0 = mrow + 8 * (i / 4) + (i % 4), r1 = r0 + 1;
           if (jw > r0 - w * (int)__umulhi((uint32_t)r0, w_recip)) pa = 0.f;
           if (jw > r1 - w * (int)__umulhi((uint32_t)r1, w_recip)) pb = 0.f;
@@ -641,9 +636,9 @@ hipError_t launch_ring_cfg(const structkv_shape& s, const ScorePlan& p, const Se
   // pass 2: dynamic LDS for the column sums of the key chunk and the waves' parked sums
   const int ppw = pass == 2 && probs == nullptr ? p.planes : 0;
   const int np = ppw * p.split;
-  auto planes_bytes = [&](auto n) { return (unsigned)(NW * decltype(n)::value * kPlanesLdsKeys<NW, decltype(n)::value> * 4); };
+  auto planes_bytes = [&](auto n) { return (unsigned)(NW * decltype(n)::value * planes_lds_keys(NW, decltype(n)::value) * 4); };
   const unsigned cs_bytes = np == 1 ? planes_bytes(IntC<1>{}) : np == 2 ? planes_bytes(IntC<2>{}) : np == 4 ? planes_bytes(IntC<4>{})
-                          : np == 8 ? planes_bytes(IntC<8>{}) : (unsigned)(kKeyCap<NW> * 4 + (NW > 1 ? 4 * NW * 64 * 4 : 0));
+                          : np == 8 ? planes_bytes(IntC<8>{}) : (unsigned)(ring_key_cap(NW) * 4 + (NW > 1 ? 4 * NW * 64 * 4 : 0));
   const unsigned dyn = pass == 1 ? 16u : cs_bytes;   // pass 1: the word of the rerun vote
   // causal masks: floor(2^32 / w) + 1 (the row modulo the window); a window of one row sees every key
   const int causal = s.causal && s.window > 1;

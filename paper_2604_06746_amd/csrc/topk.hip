@@ -1119,7 +1119,7 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
     const int64_t m = plan->cu[b + 1] - plan->cu[b] - keep_tail;
     if (plan->k[b] > 0 && m > longest) longest = m;
   }
-  ws->mode = longest <= kShortSeq ? kSelShort : longest <= kMidSeq ? kSelMid : kSelLong;
+  ws->mode = selection_mode(longest);
   ws->mass = 0.f;
   ws->red = nullptr;
   const int target = ws->mode == kSelMid ? kMidShare : share_target(plan->cu[B]);

@@ -59,9 +59,11 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
   }
   return ok ? hipSuccess : hipErrorInvalidValue;
 }
-hipError_t launch_score_simt(const structkv_shape&, const ScorePlan& p, const SeqTable&, const void*, const void*,
-                             int64_t, int64_t, float, float*, const float*, float*, int64_t, float*, int,
-                             hipStream_t) { keep_plan(p); return hipSuccess; }
+hipError_t launch_score_f32(const structkv_shape&, const ScorePlan& p, const SeqTable&, const void*, const void*,
+                            int64_t, int64_t, float, float*, const float*, float*, int64_t, float*, int,
+                            hipStream_t) { keep_plan(p); return hipSuccess; }
+hipError_t launch_score_short(const structkv_shape&, const ScorePlan& p, const SeqTable&, const void*, const void*,
+                              int64_t, int64_t, float, float*, float*, int64_t, hipStream_t) { keep_plan(p); return hipSuccess; }
 hipError_t launch_score_combine(const structkv_shape&, const ScorePlan&, const SeqTable&, const float*, float*,
                                 float*, uint32_t*, int64_t, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_score_reduce(const structkv_shape&, const ScorePlan&, const SeqTable&, const float*, int64_t,
