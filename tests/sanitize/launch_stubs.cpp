@@ -1,19 +1,32 @@
 // Stand-ins for the kernel launchers of libstructkv, for the host-only sanitizer build of its C ABI:
 // api.cpp is compiled with -fsanitize=address,undefined and linked against these instead of the HIP
 // kernels, so that argument validation, work planning and workspace carving run under the sanitizers
-// on a machine without a GPU.  The stubs launch nothing and count the calls; the one that stands in for the MFMA
-// scoring kernels also checks the plan it is handed against what those kernels assume about it (tilings that are
-// instantiated, key chunks within the LDS capacity, chunk bookkeeping) and keeps it for the tests to look at.
+// on a machine without a GPU.  The stubs launch nothing and count the calls; those that stand in for the scoring
+// kernels also check the plan they are handed against what those kernels assume about it (tilings that are
+// instantiated, key chunks within the LDS capacity, chunk bookkeeping) and keep it for the tests to look at, and those of
+// the selection follow its forms by length.
 #include "../../paper_2604_06746_amd/csrc/common.h"
 
 namespace skv {
 
 static int g_launches = 0;
 static int32_t g_last_plan[8];
+static int32_t g_last_selection[3];
 extern "C" int structkv_stub_launch_count(void) { return g_launches; }
 // RB, NW, KC, planes, stream_k, RC, grid_chunks, path of the latest scoring launch
 extern "C" void structkv_stub_last_plan(int32_t* out) { for (int i = 0; i < 8; ++i) out[i] = g_last_plan[i]; }
 
+// of the latest fused layer step: the form its scoring prepared (-1: none), the form of its selection, whether that also
+// sums the scoring's planes
+extern "C" void structkv_stub_last_selection(int32_t* out) { for (int i = 0; i < 3; ++i) out[i] = g_last_selection[i]; }
+static bool chunks_fit(const ScorePlan& p, const SeqTable& seq, int64_t total) {
+  bool ok = seq.batch >= 1 && seq.batch <= kMaxBatch && seq.chunk_start[0] == 0 && seq.chunk_start[seq.batch] == p.grid_chunks;
+  for (int b = 0; ok && b < seq.batch; ++b) {
+    const int64_t n = seq.cu[b + 1] - seq.cu[b];
+    ok = n >= 0 && seq.chunk_start[b + 1] - seq.chunk_start[b] == (n + p.KC - 1) / p.KC && seq.cu[b + 1] <= total;
+  }
+  return ok;
+}
 static void keep_plan(const ScorePlan& p) {
   ++g_launches;
   const int32_t plan[8] = {p.RB, p.NW, p.KC, p.planes, p.stream_k, p.RC, (int32_t)p.grid_chunks, p.path};
@@ -48,36 +61,65 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
   ok = ok && p.RPC == 32 * p.RB && p.R == (s.n_q_heads / s.n_kv_heads) * s.window && p.RC == (p.R + p.RPC - 1) / p.RPC;
   ok = ok && (p.NW == 4 || p.RC == 1);                          // one-wave workgroups hold a KV group's only row-chunk
   const int planes = pass == 2 && probs == nullptr ? p.planes : 0;
-  ok = ok && (planes == 0 || planes == 1 || (planes == 2 && p.RB == 2));
-  const int cap = planes ? (p.NW == 4 ? (planes == 1 ? 1376 : 736) : 1024 / planes) : (p.NW == 4 ? 2048 : 896);   // keys whose sums fit the LDS
+  ok = ok && (planes == 0 || planes == 1 || (planes == 2 && p.RB == 2)) && (p.split == 1 || ((p.split == 2 || p.split == 4) && p.planes == p.RB));
+  ok = ok && (planes == 0 || p.CP == s.n_q_heads / s.n_kv_heads);
+  const int cap = planes ? planes_key_cap(p.NW, planes * p.split) : ring_key_cap(p.NW);   // keys whose sums fit the LDS
   ok = ok && p.KC >= 32 && p.KC % 32 == 0 && (pass == 1 || p.KC <= cap);
   ok = ok && (int64_t)s.n_kv_heads * ((p.RC + p.NW - 1) / p.NW) * p.grid_chunks < ((int64_t)1 << 31);
-  ok = ok && seq.batch >= 1 && seq.batch <= kMaxBatch && seq.chunk_start[0] == 0 && seq.chunk_start[seq.batch] == p.grid_chunks;
-  for (int b = 0; ok && b < seq.batch; ++b) {
-    const int64_t n = seq.cu[b + 1] - seq.cu[b];
-    ok = n >= 0 && seq.chunk_start[b + 1] - seq.chunk_start[b] == (n + p.KC - 1) / p.KC && seq.cu[b + 1] <= total;
-  }
+  return ok && chunks_fit(p, seq, total) ? hipSuccess : hipErrorInvalidValue;
+}
+hipError_t launch_score_f32(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void*, const void*,
+                            int64_t, int64_t, float, float*, const float*, float*, int64_t total, float*, int pass,
+                            hipStream_t) {
+  keep_plan(p);
+  if (p.grid_chunks == 0) return hipSuccess;
+  bool ok = p.path == 1 && s.head_dim <= 256 && (pass == 1 || pass == 2) && p.planes == 0;
+  ok = ok && p.RPC == 32 && p.R == (s.n_q_heads / s.n_kv_heads) * s.window && p.RC == (p.R + 31) / 32;
+  ok = ok && (p.NW == 1 || p.NW == 2 || p.NW == 4) && p.CP == (p.RC + p.NW - 1) / p.NW;
+  ok = ok && p.KC >= 32 && p.KC % 32 == 0 && p.KC <= kF32KeyCap;
+  ok = ok && (int64_t)s.n_kv_heads * p.CP * p.grid_chunks < ((int64_t)1 << 31);
+  return ok && chunks_fit(p, seq, total) ? hipSuccess : hipErrorInvalidValue;
+}
+hipError_t launch_score_short(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void*, const void*,
+                              int64_t, int64_t, float, float*, float*, int64_t total, hipStream_t) {
+  keep_plan(p);
+  const bool bf16 = s.dtype == STRUCTKV_DTYPE_BF16;
+  bool ok = p.path == 2 && (s.head_dim == 64 || s.head_dim == 128) && (p.RPC == 16 || (bf16 && p.RPC == 32));
+  ok = ok && p.R == (s.n_q_heads / s.n_kv_heads) * s.window && p.RC == (p.R + p.RPC - 1) / p.RPC && p.CP == p.RC;
+  ok = ok && s.n_kv_heads * p.RC <= kReduceShortPlanes && seq.batch >= 1 && seq.batch * s.n_kv_heads * p.RC <= 256;
+  for (int b = 0; ok && b < seq.batch; ++b)
+    ok = seq.cu[b + 1] >= seq.cu[b] && seq.cu[b + 1] - seq.cu[b] <= (bf16 ? 2048 : 1024) && seq.cu[b + 1] <= total;
   return ok ? hipSuccess : hipErrorInvalidValue;
 }
-hipError_t launch_score_f32(const structkv_shape&, const ScorePlan& p, const SeqTable&, const void*, const void*,
-                            int64_t, int64_t, float, float*, const float*, float*, int64_t, float*, int,
-                            hipStream_t) { keep_plan(p); return hipSuccess; }
-hipError_t launch_score_short(const structkv_shape&, const ScorePlan& p, const SeqTable&, const void*, const void*,
-                              int64_t, int64_t, float, float*, float*, int64_t, hipStream_t) { keep_plan(p); return hipSuccess; }
 hipError_t launch_score_combine(const structkv_shape&, const ScorePlan&, const SeqTable&, const float*, float*,
                                 float*, uint32_t*, int64_t, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_score_reduce(const structkv_shape&, const ScorePlan&, const SeqTable&, const float*, int64_t,
-                               float*, const float*, float*, float*, float*, float, float, const SelectFusion*,
+                               float*, const float*, float*, float*, float*, float, float, const SelectFusion* fuse,
                                hipStream_t) {
-  ++g_launches; return hipSuccess;
+  ++g_launches;
+  g_last_selection[0] = fuse ? fuse->mode : -1;
+  return !fuse || (fuse->hist && fuse->idx_out && (fuse->mode == kSelMid || fuse->mode == kSelLong)) ? hipSuccess : hipErrorInvalidValue;
 }
-void topk_plan(const SeqTable& seq_in, int, void* wsp, SeqTable* plan, TopkWs* ws, unsigned* blocks) {
+void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan, TopkWs* ws, unsigned* blocks) {
   *plan = seq_in;
   *blocks = 1;
+  int64_t longest = 0;
+  for (int b = 0; b < seq_in.batch; ++b)
+    if (seq_in.k[b] > 0 && seq_in.cu[b + 1] - seq_in.cu[b] - keep_tail > longest) longest = seq_in.cu[b + 1] - seq_in.cu[b] - keep_tail;
+  ws->mode = selection_mode(longest);
+  ws->mass = 0.f;
+  ws->red = nullptr;
   ws->hist = ws->state = ws->suf = ws->meta = (uint32_t*)wsp;
+  g_last_selection[0] = -1;
 }
-hipError_t launch_topk_rest(const float*, const SeqTable&, int, const TopkWs&, unsigned, int32_t*, hipStream_t) {
-  ++g_launches; return hipSuccess;
+hipError_t launch_topk_rest(const float*, const SeqTable& plan, int keep_tail, const TopkWs& ws, unsigned, int32_t*, hipStream_t) {
+  ++g_launches;
+  g_last_selection[1] = ws.mode;
+  g_last_selection[2] = ws.red != nullptr;
+  bool ok = ws.hist && ws.mass > 0.f;
+  for (int b = 0; ws.red && b < plan.batch; ++b)   // the selection sums the planes: at most two tokens a thread
+    ok = ok && ws.mode == kSelShort && ws.red->planes <= kReduceShortPlanes && plan.cu[b + 1] - plan.cu[b] <= kReduceShortSeq && keep_tail >= 0;
+  return ok ? hipSuccess : hipErrorInvalidValue;
 }
 hipError_t launch_group_sums(const structkv_shape&, const ScorePlan&, const float*, int64_t, float*, hipStream_t) {
   ++g_launches; return hipSuccess;

@@ -269,7 +269,8 @@ def test_host_planning_with_stub_launchers(B):
     before = lib.structkv_stub_launch_count()
     for (Hq, G, d, w, dtype, causal) in [(32, 8, 128, 64, 1, 0), (32, 8, 128, 32, 1, 1), (8, 8, 64, 32, 0, 0),
                                          (4, 1, 64, 8, 1, 0), (6, 2, 96, 5, 1, 0), (32, 32, 128, 64, 1, 0),
-                                         (16, 2, 128, 64, 1, 0)]:
+                                         (16, 2, 128, 64, 1, 0), (32, 8, 128, 8, 1, 0), (32, 8, 128, 16, 1, 1), (18, 1, 64, 8, 1, 0),
+                                         (6, 1, 128, 16, 1, 0), (8, 2, 256, 64, 0, 1), (8, 1, 40, 17, 0, 0)]:
         shape = B.make_shape(Hq, G, d, w, dtype, bool(causal))
         for batch in (1, 3, B.STRUCTKV_MAX_BATCH):
             lens = [int(x) for x in rng.integers(w, 5000, size=batch)]
@@ -346,6 +347,32 @@ def test_tilings_chosen_for_the_named_configurations(B):
     assert p["grid_chunks"] == sum(-(-n // p["KC"]) for n in lens) and p["stream_k"] == 1     # 364 MiB of K
     p = plan(32, 8, 128, 32, [n // 2 for n in lens])
     assert p["grid_chunks"] == sum(-(-(n // 2) // p["KC"]) for n in lens) and p["stream_k"] == 0
+
+
+def test_selection_forms_of_a_layer_step(B):
+    """Which form a layer step's selection takes by its longest searched prefix, whether the scoring prepares it, and when the
+    selection forms the in-degrees itself.  Stub build only."""
+    lib = B._lib
+    if not hasattr(lib, "structkv_stub_last_selection"):
+        pytest.skip("the real library launches kernels; this runs against the stub build only")
+    i64 = ctypes.c_int64
+    fake, fake2, fake3 = (ctypes.c_void_p(1 << s) for s in (20, 21, 22))
+    w, short, mid, long_ = 8, 0, 1, 2
+    for lens, want in [([1792], (-1, short, 1)), ([2048], (-1, short, 1)), ([2049], (-1, short, 0)), ([8192 + w], (-1, short, 0)),
+                       ([8193 + w], (mid, mid, 0)), ([262144 + w], (mid, mid, 0)), ([262145 + w], (long_, long_, 0)),
+                       ([500, 9000, 0], (mid, mid, 0)), ([1000, 0, 64], (-1, short, 1))]:
+        tail = w if 0 not in lens else 0
+        cu = (i64 * (len(lens) + 1))(*np.concatenate([[0], np.cumsum(lens)]).tolist())
+        ks = (i64 * len(lens))(*[max(x - w, 0) // 4 for x in lens])
+        shape = B.make_shape(32, 8, 128, w, 1, False)
+        need = B.structkv_layer_step_workspace_bytes(shape, len(lens), sum(lens))
+        rows = sum(ks) + tail * len(lens)
+        assert lib.structkv_layer_step(ctypes.byref(shape), fake, fake, fake, sum(lens) * 128, 128, len(lens), cu, ks, tail, fake3, None,
+                                       0.9, 0.1, fake, None, fake, fake2, fake2, rows * 128, 128, fake2, need, None) == B.STRUCTKV_OK, \
+            B.structkv_last_error()
+        out = (ctypes.c_int32 * 3)()
+        lib.structkv_stub_last_selection(out)
+        assert tuple(out) == want, lens
 
 
 def test_longest_sequences_of_the_one_launch_scoring(B):
