@@ -203,6 +203,15 @@ __host__ __device__ inline void fine_range(uint32_t bin, const BinTiers& t, uint
 }
 
 #ifdef __HIPCC__
+// Add a workgroup's LDS histogram of `nb` bins (even) into the merged one, two bins an addition: their counts stay below 2^32,
+// so none carries into its neighbour.  What this costs is the number of additions (1024 bins of a near tier hit by each of 128
+// workgroups: a 128K layer's reduce kernel 7.55 us one by one, 6.96 in pairs).
+__device__ inline void merge_bins(const uint32_t* h /*LDS, 8-byte aligned*/, int nb, uint32_t* __restrict__ gh, int threads) {
+  for (int i = threadIdx.x; i < nb / 2; i += threads) {
+    const unsigned long long two = reinterpret_cast<const unsigned long long*>(h)[i];
+    if (two) atomicAdd(reinterpret_cast<unsigned long long*>(gh) + i, two);
+  }
+}
 // the bins for the in-degrees of a sequence, which add up to `mass` over n keys
 __device__ inline BinTiers bins_around_mean(float mass, int64_t n) { return bins_around(score_key(mass / (float)(n > 0 ? n : 1))); }
 #endif

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(FUSE ? 1024 : 256) void score_reduce_kernel(
   constexpr bool FUSED = FUSE != 0;
   constexpr int NT = FUSED ? 1024 : 256;
   constexpr int BINS = FUSE == kSelMid ? kFineBins : kTopkBins;
-  __shared__ uint32_t h0[FUSED ? BINS : 1];
+  __shared__ alignas(8) uint32_t h0[FUSED ? BINS : 2];
   const float mass = (float)w * (float)Hq;
   const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
   int b_wg = 0;   // FUSED: the sequence of the workgroup's first token; its digits are counted in LDS
@@ -168,8 +168,7 @@ __global__ __launch_bounds__(FUSE ? 1024 : 256) void score_reduce_kernel(
   if constexpr (FUSED) {
     __syncthreads();
     uint32_t* gh = fs.hist + (size_t)b_wg * 3 * kTopkBins;
-    for (int i = threadIdx.x; i < BINS; i += NT)
-      if (h0[i]) atomicAdd(&gh[i], h0[i]);
+    merge_bins(h0, BINS, gh, NT);
     // the kept window: indices n_b - keep_tail .. n_b - 1 behind the k_b selected ones
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gsz = (int64_t)gridDim.x * blockDim.x;
     const int64_t tail = fs.keep_tail;

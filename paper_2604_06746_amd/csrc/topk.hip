@@ -635,7 +635,7 @@ template <class TAB>
 __global__ __launch_bounds__(kThreads) void topk_mid_hist_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
                                                                  TopkWs ws) {
   short_kernel_priority();
-  __shared__ uint32_t h[kFineBins];
+  __shared__ alignas(8) uint32_t h[kFineBins];
   int b;
   uint32_t blk;
   int j0;
@@ -653,7 +653,7 @@ __global__ __launch_bounds__(kThreads) void topk_mid_hist_kernel(const float* __
   for (int i = 0; i < kMidPer; ++i)
     if (j0 + i * kThreads + t < m) atomicAdd(&h[fine_bin(score_key(v[i]), tiers)], 1u);
   __syncthreads();
-  merge_hist(h, kFineBins, ws.hist + (size_t)b * 3 * kBins);
+  merge_bins(h, kFineBins, ws.hist + (size_t)b * 3 * kBins, kThreads);
 }
 
 // Most candidates of a sequence of `nblk` workgroups that are listed; the list lies in the words of their suffix sums.  In an
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(kThreads) void topk_compact_kernel(const float* __r
   short_kernel_priority();
   constexpr int NWV = kThreads / 64, N = kMidPer * NWV;
   __shared__ uint32_t scan[NWV], res[3], wtot[N], gbase, ends[2][NWV];
-  __shared__ uint32_t h[kSubBins];
+  __shared__ alignas(8) uint32_t h[kSubBins];
   int b;
   uint32_t blk;
   int j0;
@@ -741,7 +741,7 @@ __global__ __launch_bounds__(kThreads) void topk_compact_kernel(const float* __r
       for (int i = 0; i < NWV; ++i) { inv = max(inv, ends[0][i]); mx = max(mx, ends[1][i]); }
       *reinterpret_cast<uint2*>(gh + kKeyEnds + 2 * blk) = make_uint2(~inv, mx);
     }
-    merge_hist(h, kSubBins, gh + kFineBins);
+    merge_bins(h, kSubBins, gh + kFineBins, kThreads);
     static_assert(kSubBins == 4 * kThreads, "four sub-bins a thread");
     uint32_t c4[4], sum = 0u;
 #pragma unroll
