@@ -259,8 +259,8 @@ structkv_status structkv_block_scores(const float* scores, int32_t batch, const 
  * vector over the n_b keys of sequence b.  Per sequence:
  *   sparsity_out[b] = (1/H_q) sum_h ( sum of the k largest a_h[j] ),   k = ceil(top_frac * n_b) in double arithmetic (paper: 0.1)
  *   variance_out[b] = (1/H_q) sum_h (1/n_b) sum_j (a_h[j] - 1/n_b)^2
- * (0 for an empty sequence).  With bf16 inputs, head_dim 64 or 128 and a window of 8, 16, 32 or 64 (64: not with two query heads per KV head) the per-head in-degrees
- * come out of the scoring pass itself (its second pass keeps one column-sum plane per query head) and the call
+ * (0 for an empty sequence).  With bf16 inputs, head_dim 64 or 128 and a window of 8, 16, 32 or 64 (64: not with
+ * two query heads per KV head) the per-head in-degrees come out of the scoring pass itself (its second pass keeps one column-sum plane per query head) and the call
  * costs one scoring of the layer plus four short kernels over those planes (a radix select for the top-k mass);
  * other shapes are re-scored head by head, which costs about as much as scoring the layer twice.
  * q_win, k, strides, cu_seqlens, shape: as structkv_score_layer.  sparsity_out, variance_out: DEVICE fp32 [B].
