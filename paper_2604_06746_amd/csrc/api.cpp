@@ -116,6 +116,23 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
       if (kc_min < 64) kc_min = 64;
     }
     if (kc < kc_min) kc = kc_min;
+    if (p->NW == 4 && p->RB == 2 && s.head_dim == 128 && kc_min >= 256) {
+      // score_mfma_wide.hip: a CU's time is that of its workgroups' keys, almost however many of them are resident (three waves
+      // on a SIMD are about 8 % ahead of two and 28 % of one), plus about 128 keys a workgroup for what it costs to start one.
+      // So the keys per workgroup are those with which whole rounds of workgroups over the CUs take the least.  32 heads
+      // on 8, window 64, us a scoring call: 40000 tokens 512 keys (632 workgroups on 256 CUs) 72.8, 640 keys (504) 67.2;
+      // 50001 tokens 512 keys 89.6, 640 keys 83.7; 1M tokens 1408 keys 1176, 1664 keys 1165, 2048 keys 1151.  A sequence leaves
+      // half a chunk empty on average.
+      int64_t best = 0;
+      for (int64_t m = ceil_div(std::max<int64_t>(total, 1) * wg_per_chunk, 256 * kMaxKC), last = m + 5; m <= last; ++m) {
+        const int64_t chunks = 256 * m / wg_per_chunk - (batch - 1) / 2;
+        if (chunks < 1) continue;
+        const int64_t k = std::max(ceil_div(ceil_div(total, chunks), 32) * 32, kc_min);
+        if (k > kMaxKC) continue;
+        const int64_t cost = m * (k + 128) * (m == 1 ? 128 : m == 2 ? 109 : 100);
+        if (best == 0 || cost < best) { best = cost; kc = k; }
+      }
+    }
     chunk_bound = std::max(total / 256, std::min(ceil_div(total, 64), ceil_div(one_each, wg_per_chunk)));
     if (kc > kMaxKC) kc = kMaxKC;
     p->KC = (int)kc;

@@ -300,6 +300,11 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
                                   const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
                                   float* stats, const float* lse2, float* colsum, int64_t total,
                                   float* probs, int pass, hipStream_t st);
+// its kernels for more than 128 rows of 128 components (RB 2, NW 4)
+hipError_t launch_score_mfma_wide(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq,
+                                  const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
+                                  float* stats, const float* lse2, float* colsum, int64_t total,
+                                  float* probs, int pass, hipStream_t st);
 hipError_t launch_score_f32(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq,
                             const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
                             float* stats, const float* lse2, float* colsum, int64_t total,

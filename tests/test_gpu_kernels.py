@@ -106,6 +106,20 @@ def test_one_scoring_launch_strides_scale_and_batch(sweep_mod, oracle, Hq, G, d,
     _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens, pad, scale)
 
 
+# more than 128 rows of 128 components: sequences around the 32-key tiles, the tiles requested ahead (three), the two of a run and
+# the sums parked (eight); chunks of 64 to 576 keys that end with the sequence, inside a tile and inside a run; rows that fill
+# the four waves, that leave one of them idle, that leave part of a block; strides; the rerun with the running maximum
+@pytest.mark.parametrize("Hq,G,w,lens,pad", [(4, 1, 64, [31, 33, 1, 64, 95, 97, 129, 2049], 0), (8, 8, 130, [33000], 0),
+                                             (6, 2, 64, [40000, 70, 1217], 8), (12, 2, 32, [20001, 9000], 0), (40, 1, 8, [33333], 0),
+                                             (8, 1, 64, [30000], 0)])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("late", [0.0, 0.4])
+def test_wide_scoring_kernels(sweep_mod, oracle, Hq, G, w, lens, pad, causal, late):
+    if causal:
+        lens = [n for n in lens if n >= w]
+    _check_scores(sweep_mod, oracle, Hq, G, 128, w, torch.bfloat16, causal, lens, pad=pad, two_pass=True, late=late)
+
+
 def _select(B, scores, lens, ks, tail):
     total, cu = sum(lens), np.concatenate([[0], np.cumsum(lens)]).tolist()
     ws = torch.full((max(B.structkv_workspace_bytes(None, len(lens), total), 256),), 0xA5, dtype=torch.uint8, device="cuda")
