@@ -243,7 +243,8 @@ struct ScoreOpts {
   bool planes = false;         // pass 2 keeps one column-sum plane per query head (the pivot metrics' input)
   uint32_t* zero_ptr = nullptr;   // words the combine kernel clears on the way (someone's histograms)
   int64_t zero_words = 0;
-  ReduceWork* defer = nullptr;    // where the selection's launch may do the reduce kernel's work: filled in, colsum != NULL
+  ReduceWork* defer = nullptr;    // where a launch behind the scoring may do the reduce kernel's work (a selection's of short
+                                  // sequences, the pivot metrics'): filled in, colsum != NULL
 };
 
 structkv_status run_score(const structkv_shape* shape, const void* q_win, const void* k, int64_t ksh,
@@ -362,7 +363,8 @@ structkv_status run_score(const structkv_shape* shape, const void* q_win, const 
           if (gs != STRUCTKV_OK) return gs;
         }
   }
-  if (o.defer && o.step_mask == 15 && !o.fuse && longest <= kReduceShortSeq && s.n_kv_heads * p.CP <= kReduceShortPlanes)
+  if (o.defer && o.step_mask == 15 && !o.fuse &&
+      (o.planes || (longest <= kReduceShortSeq && s.n_kv_heads * p.CP <= kReduceShortPlanes)))
     *o.defer = {colsum, s.n_kv_heads * p.CP, total, indeg, row_ent, ent_head, entropy, s.n_q_heads, s.window, o.centrality,
                 o.lambda, o.inv_w};
   else if (o.step_mask & 8)
@@ -1004,32 +1006,25 @@ static structkv_status pivot_impl(const structkv_shape* shape, const void* q_win
       TopkWs tws;
       unsigned blocks = 0;
       topk_plan(hseq, 0, w8 + c.off_topk_ws, &hplan, &tws, &blocks);
-      const int Pv = pivot_plane_shares(n);
+      const int P = pivot_shares(n);
       float* var_part = (float*)idx;                       // the index scratch of the other path is free here
-      float* part_above = var_part + (size_t)Hq * Pv;      // ... Hq x n words of it: 2 Pv + 4 per head are used
-      float* mass_part = part_above + (size_t)Hq * Pv;
-      float* tail = mass_part + (size_t)Hq * 2;
+      float* part_above = var_part + (size_t)Hq * P;       // ... Hq x n words of it: 2 P + 2 per head are used
+      float* sums = part_above + (size_t)Hq * P;
+      ReduceWork red{};
       ScoreOpts o;
       o.planes = true;
+      o.defer = &red;
       o.zero_ptr = tws.hist;
-      o.zero_words = (int64_t)3 * kTopkBins * Hq;
+      o.zero_words = (int64_t)kRowWords * Hq;
       st = score_layer_impl(shape, qs, ks, k_stride_head, k_stride_tok, 1, cu1,
                             indeg_out ? indeg_out + seq.cu[b] : indeg, entropy_out ? entropy_out + b : ent,
                             entropy_head_out ? entropy_head_out + (size_t)b * Hq : ent_h, w8 + c.off_score_ws,
                             c.score_ws_bytes, stream, o);
       if (st != STRUCTKV_OK) return st;
-      // where that call left its planes: the same plan, made again
-      ScorePlan pp;
-      SeqTable one;
-      memset(&one, 0, sizeof(one));
-      one.batch = 1; one.cu[1] = n;
-      make_plan(*shape, &one, 1, n, true, &pp, true);
-      const float* planes = (const float*)(w8 + c.off_score_ws + pp.off_colsum);   // [Hq][n]: plane g*gs + hl is head h
-      SKV_HIP_CHECK(launch_pivot_planes(planes, Hq, n, 1.0f / (float)w, tws.hist, var_part, hs));
-      // (the per-head in-degrees of the other path's scratch hold the candidate lists here)
-      SKV_HIP_CHECK(launch_topk_mass(planes, Hq, n, (uint32_t)kk, tws, heads, part_above, mass_part, tail, hs));
-      SKV_HIP_CHECK(launch_pivot_finish_planes(var_part, Pv, mass_part, 1, tail, Hq, n, 1.0f / (float)w, sparsity_out + b,
-                                               variance_out + b, hs));
+      // (red.colsum: [Hq][n], plane g*gs + hl is head h; the other path's per-head in-degrees hold the candidate lists here)
+      SKV_HIP_CHECK(launch_pivot_planes(red, tws.hist, var_part, hs));
+      SKV_HIP_CHECK(launch_pivot_mass(red, (uint32_t)kk, tws.hist, tws.state, heads, part_above, var_part, sums,
+                                      sparsity_out + b, variance_out + b, hs));
       continue;
     }
     if (n > 0) {

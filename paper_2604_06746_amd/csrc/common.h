@@ -216,6 +216,34 @@ __device__ inline void merge_bins(const uint32_t* h /*LDS, 8-byte aligned*/, int
 __device__ inline BinTiers bins_around_mean(float mass, int64_t n) { return bins_around(score_key(mass / (float)(n > 0 ? n : 1))); }
 #endif
 
+// Bins of the pivot detector's rows (the in-degrees of one query head: non-negative, mean w/n), ascending with the keys: quarter
+// octaves, and in the place of the 64 around the mean 16 octaves in bins of 1/64.  The k-th largest's bin holds about 1 % of a
+// row then, where one of a quarter octave holds 10 to 25 %; finer ones mean more additions into the merged histograms (bins of
+// 1/256 are hit by a thousand of a workgroup's 4096 scores).  No bin leaves its octave.
+constexpr uint32_t kRowOuterShift = 21, kRowInnerShift = 17, kRowSplit = 64, kRowExtra = 1024 - kRowSplit;
+static_assert((kRowSplit << (kRowOuterShift - kRowInnerShift)) - kRowSplit == kRowExtra && 1024 + kRowExtra <= (uint32_t)kTopkBins,
+              "the inner bins take the place of kRowSplit outer ones and all fit the histogram");
+// the first of the outer bins that are split, in keys >> kRowOuterShift (keys of non-negative scores: 1024 and up)
+__host__ __device__ inline uint32_t row_bins_at(uint32_t centre) {
+  const uint32_t c = centre >> kRowOuterShift, least = 1024u, most = 2048u - kRowSplit;
+  const uint32_t at = c < least + kRowSplit / 2 ? least : c - kRowSplit / 2;
+  return at < most ? at : most;
+}
+__host__ __device__ inline uint32_t row_bin(uint32_t key, uint32_t at) {
+  const uint32_t o = key >> kRowOuterShift, shift = kRowOuterShift - kRowInnerShift;
+  if (o < at) return o - 1024u;
+  return o - at < kRowSplit ? (key >> kRowInnerShift) - (at << shift) + (at - 1024u) : o - 1024u + kRowExtra;
+}
+// first key of a bin, and the bits that tell its keys apart
+__host__ __device__ inline void row_bin_range(uint32_t bin, uint32_t at, uint32_t* lo, uint32_t* width) {
+  const uint32_t in = bin - (at - 1024u);
+  const bool inner = in < kRowSplit + kRowExtra;
+  *width = inner ? kRowInnerShift : kRowOuterShift;
+  *lo = inner ? ((at << (kRowOuterShift - kRowInnerShift)) + in) << kRowInnerShift
+              : (bin + 1024u - (bin >= at - 1024u ? kRowExtra : 0u)) << kRowOuterShift;
+}
+constexpr int kRowWords = kTopkBins + 64;   // of a row: its histogram, the candidate counter and (first row) the finished rows
+
 struct TopkWs {
   uint32_t* hist;    // [B][3][kTopkBins]; mid: the histogram in the first kFineBins words, that of a crowded bin in the next
                      //         kSubBins, then the candidate counter; from kKeyEnds on the key ends
@@ -345,15 +373,15 @@ hipError_t launch_pivot_heads(const float* heads, int H, int64_t n, const int32_
 hipError_t launch_zero_floats(float* p, int n, hipStream_t st);   // a fill kernel (safe inside a captured graph)
 hipError_t launch_pivot_finish(const float* part, int H, int64_t n, float inv_w, int valid, float* sparsity,
                                float* variance, hipStream_t st);
-// pivot metrics from the hot path's own scoring, whose pass 2 leaves the per-head in-degrees [H][n] in its
-// column-sum planes: first radix digit + variance partials, the top-k mass by radix select, the means over the heads
-int pivot_plane_shares(int64_t n);
-hipError_t launch_pivot_planes(const float* heads, int H, int64_t n, float inv_w, uint32_t* hist, float* part,
-                               hipStream_t st);
-hipError_t launch_topk_mass(const float* rows, int H, int64_t n, uint32_t kk, const TopkWs& ws, float* cand,
-                            float* part_above, float* mass, float* tail, hipStream_t st);
-hipError_t launch_pivot_finish_planes(const float* var_part, int Pv, const float* mass_part, int Pm, const float* tail,
-                                      int H, int64_t n, float inv_w, float* sparsity, float* variance, hipStream_t st);
+// pivot metrics from the hot path's own scoring, whose pass 2 leaves the per-head in-degrees [H][n] in its column-sum planes
+// (red.colsum): the reduce kernel's work for the layer, histograms hist [H][kRowWords] (cleared before) and variance partials
+// var_part [H][pivot_shares(n)]; then the mass of each row's kk largest and the means over the heads.  cand: H x n floats,
+// part_above: H x pivot_shares(n), state: [H][4], sums: [H][2]
+constexpr int kPivotShare = 4096;
+inline int pivot_shares(int64_t n) { return (int)((n + kPivotShare - 1) / kPivotShare); }
+hipError_t launch_pivot_planes(const ReduceWork& red, uint32_t* hist, float* var_part, hipStream_t st);
+hipError_t launch_pivot_mass(const ReduceWork& red, uint32_t kk, uint32_t* hist, uint32_t* state, float* cand, float* part_above,
+                             const float* var_part, float* sums, float* sparsity, float* variance, hipStream_t st);
 hipError_t launch_block_scores(const float* scores, const SeqTable& seq, int block, float* out, hipStream_t st);
 hipError_t launch_positions(const int64_t* pos_src, const SeqTable& seq, const int32_t* idx, int64_t* pos_dst,
                             hipStream_t st);

@@ -54,79 +54,77 @@ __global__ __launch_bounds__(256) void pivot_head_kernel(const float* __restrict
   }
 }
 
-// First pass over the per-head in-degrees that a scoring call leaves in its column-sum planes (pass 2 with one
-// plane per query head): the first radix digit of their selection and the variance partials.
-//   hist[h][digit of heads[h][j]] += 1;   part[h P + p] = sum over the workgroup's keys of (heads/w - 1/n)^2
-// grid (P, H): workgroup (p, h) takes keys [p*kPlaneShare, ...) of head h.
-constexpr int kPlaneShare = 2048;
+// Everything that reads all of the per-head in-degrees which a scoring call leaves in its column-sum planes (pass 2 with one
+// plane per query head), in one launch of 1-D workgroups:
+//   workgroup 0               the means of the row entropies (Eq. 4),
+//   then ceil(n / 512)        the layer's in-degrees, the planes added up in ascending order as the reduce kernel does,
+//   then H x pivot_shares(n)  hist[h][row_bin of heads[h][j]] += 1;   part[h][p] = sum over the share's keys of (heads/w - 1/n)^2
+// Short launches that wait on memory run side by side here instead of one after the other.  In bins of a quarter octave most
+// of a workgroup's LDS additions met in a few words.  With the finer ones and one launch, 32 heads: 128K tokens
+// 18.4 -> 9.6 us (the 16.8 MB of planes read twice, the second time from the caches), 32K 8.0 -> 4.3 us.
+constexpr int kPlaneThreads = 512;
 
-__global__ __launch_bounds__(256) void pivot_planes_kernel(const float* __restrict__ heads, int64_t n, float inv_w,
-                                                           uint32_t* __restrict__ hist, float* __restrict__ part) {
+__global__ __launch_bounds__(kPlaneThreads) void pivot_planes_kernel(ReduceWork rw, int reduce_wgs, int shares,
+                                                                     uint32_t* __restrict__ hist, float* __restrict__ part) {
   short_kernel_priority();
-  __shared__ uint32_t h0[kTopkBins];
+  constexpr int NT = kPlaneThreads, PER = kPivotShare / NT;
+  __shared__ alignas(8) uint32_t h0[kTopkBins];
   __shared__ float sh[256];
-  const int p = blockIdx.x, h = blockIdx.y, P = gridDim.x;
-  const float* d = heads + (int64_t)h * n;
-  const int64_t lo = (int64_t)p * kPlaneShare;
-  float x[kPlaneShare / 256];
+  const int64_t n = rw.total;
+  int wg = (int)blockIdx.x;
+  if (wg == 0) {
+    finish_entropy(rw.row_ent, rw.ent_head, rw.entropy, 0, rw.Hq, rw.w, sh);
+    return;
+  }
+  if (--wg < reduce_wgs) {
+    const int64_t i = (int64_t)wg * NT + threadIdx.x;
+    if (i >= n) return;
+    const float* cp = rw.colsum + i;
+    float a = 0.f;
+    int p = 0;
+    for (; p + 16 <= rw.planes; p += 16) {
+      float v[16];
 #pragma unroll
-  for (int i = 0; i < kPlaneShare / 256; ++i) {   // loads first, the histogram's clearing under them
-    const int64_t j = lo + threadIdx.x + i * 256;
+      for (int u = 0; u < 16; ++u) v[u] = cp[(int64_t)(p + u) * n];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) a += v[u];
+    }
+    for (; p < rw.planes; ++p) a += cp[(int64_t)p * n];
+    rw.indeg[i] = a;
+    return;
+  }
+  wg -= reduce_wgs;
+  const int h = wg / shares, p = wg % shares;
+  const float* d = rw.colsum + (int64_t)h * n;
+  const int64_t lo = (int64_t)p * kPivotShare;
+  float x[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {   // loads first, the histogram's clearing under them
+    const int64_t j = lo + threadIdx.x + i * NT;
     x[i] = j < n ? d[j] : 0.f;
   }
-  for (int i = threadIdx.x; i < kTopkBins; i += 256) h0[i] = 0u;
+  for (int i = threadIdx.x; i < kTopkBins; i += NT) h0[i] = 0u;
   __syncthreads();
-  const float mean = 1.0f / (float)n;
+  const float mean = 1.0f / (float)n, inv_w = 1.0f / (float)rw.w;
+  const uint32_t at = row_bins_at(score_key((float)rw.w / (float)n));
   float v = 0.f;
 #pragma unroll
-  for (int i = 0; i < kPlaneShare / 256; ++i) {
-    if (lo + threadIdx.x + i * 256 < n) {
-      atomicAdd(&h0[score_key(x[i]) >> 21], 1u);
+  for (int i = 0; i < PER; ++i) {
+    if (lo + threadIdx.x + i * NT < n) {
+      atomicAdd(&h0[row_bin(score_key(fabsf(x[i])), at)], 1u);   // (the absolute value: a NaN's sign)
       const float a = x[i] * inv_w - mean;
       v = fmaf(a, a, v);
     }
   }
-  const float vs = block_sum(v, sh);   // its barriers also complete the LDS histogram
-  uint32_t* gh = hist + (size_t)h * 3 * kTopkBins;
-  for (int i = threadIdx.x; i < kTopkBins; i += 256)
-    if (h0[i]) atomicAdd(&gh[i], h0[i]);
-  if (threadIdx.x == 0) part[(int64_t)h * P + p] = vs;
-}
-
-// the means from the partials of the planes path: variance partials var_part [H][Pv] (pivot_planes_kernel),
-// mass partials mass_part [H][Pm][2] (second of each pair; topk_mass_kernel) and, per head, tail[2h] selected keys
-// that tie with the k-th largest, of value tail[2h+1].  Eight lanes share a head: each adds every eighth
-// partial, then a fixed shuffle tree; the heads are added in order by one thread.
-__global__ __launch_bounds__(256) void pivot_finish_planes_kernel(const float* __restrict__ var_part, int Pv,
-                                                                  const float* __restrict__ mass_part, int Pm,
-                                                                  const float* __restrict__ tail, int H, int64_t n,
-                                                                  float inv_w, float* __restrict__ sparsity,
-                                                                  float* __restrict__ variance) {
-  __shared__ float sv[32], sr[32];
-  float rt = 0.f, vt = 0.f;
-  const int sub = threadIdx.x & 7;
-  for (int h0 = 0; h0 < H; h0 += 32) {   // heads in rounds of 32
-    const int h = h0 + (int)(threadIdx.x >> 3);
-    float vs = 0.f, rs = 0.f;
-    if (h < H) {
-      for (int p = sub; p < Pv; p += 8) vs += var_part[(int64_t)h * Pv + p];
-      for (int p = sub; p < Pm; p += 8) rs += mass_part[((int64_t)h * Pm + p) * 2 + 1];
-    }
-    vs += __shfl_xor(vs, 1); vs += __shfl_xor(vs, 2); vs += __shfl_xor(vs, 4);
-    rs += __shfl_xor(rs, 1); rs += __shfl_xor(rs, 2); rs += __shfl_xor(rs, 4);
-    if (sub == 0) {
-      if (h < H) rs = fmaf(tail[2 * h], tail[2 * h + 1], rs);
-      sv[threadIdx.x >> 3] = vs / (float)n;
-      sr[threadIdx.x >> 3] = rs * inv_w;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
-      for (int i = 0; i < 32 && h0 + i < H; ++i) { vt += sv[i]; rt += sr[i]; }
-    __syncthreads();
-  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();   // completes the LDS histogram too
+  merge_bins(h0, kTopkBins, hist + (size_t)h * kRowWords, NT);
   if (threadIdx.x == 0) {
-    *sparsity = rt / (float)H;
-    *variance = vt / (float)H;
+    float vs = 0.f;
+    for (int i = 0; i < NT / 64; ++i) vs += sh[i];
+    part[(int64_t)h * shares + p] = vs;
   }
 }
 
@@ -189,20 +187,11 @@ hipError_t launch_pivot_finish(const float* part, int H, int64_t n, float inv_w,
   return hipGetLastError();
 }
 
-int pivot_plane_shares(int64_t n) { return (int)((n + kPlaneShare - 1) / kPlaneShare); }
-
-hipError_t launch_pivot_planes(const float* heads, int H, int64_t n, float inv_w, uint32_t* hist, float* part,
-                               hipStream_t st) {
-  if (H == 0 || n == 0) return hipSuccess;
-  hipLaunchKernelGGL(pivot_planes_kernel, dim3((unsigned)pivot_plane_shares(n), (unsigned)H), dim3(256), 0, st, heads,
-                     n, inv_w, hist, part);
-  return hipGetLastError();
-}
-
-hipError_t launch_pivot_finish_planes(const float* var_part, int Pv, const float* mass_part, int Pm, const float* tail,
-                                      int H, int64_t n, float inv_w, float* sparsity, float* variance, hipStream_t st) {
-  hipLaunchKernelGGL(pivot_finish_planes_kernel, dim3(1), dim3(256), 0, st, var_part, Pv, mass_part, Pm, tail, H, n,
-                     inv_w, sparsity, variance);
+hipError_t launch_pivot_planes(const ReduceWork& red, uint32_t* hist, float* var_part, hipStream_t st) {
+  const int64_t reduce_wgs = ceil_div(red.total, kPlaneThreads);
+  const int shares = pivot_shares(red.total);
+  hipLaunchKernelGGL(pivot_planes_kernel, dim3((unsigned)(1 + reduce_wgs + (int64_t)red.Hq * shares)), dim3(kPlaneThreads), 0, st,
+                     red, (int)reduce_wgs, shares, hist, var_part);
   return hipGetLastError();
 }
 

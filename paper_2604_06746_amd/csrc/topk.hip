@@ -906,54 +906,60 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
   place_ordered<kThreads, kMidPer>(key, j0, m, T, need, cnt[0], cnt[1], tot, idx_out + seq.out_off[b]);
 }
 
-// Sum of the k largest scores of each of H equally long rows instead of their indices (the top-k mass of the pivot
-// detector's sparsity, Eq. 5), after the first digit's histogram of every row has been built by whoever formed the
-// rows.  Two kernels:
-//   compact : every workgroup finds the first digit t0 of the k-th largest key from the row's histogram, adds up
-//             its scores ABOVE that digit (a partial sum per workgroup, fixed order) and appends its scores WITH that
-//             digit -- the candidates -- to the row's candidate list (one integer atomic per workgroup reserves the
-//             place; the order of the list differs from run to run, and nothing below depends on it);
-//   select  : one workgroup of 1024 threads per row takes the candidates (the first 32768 in registers), finds the two remaining
-//             digits with histograms in LDS, and adds the candidates above the k-th key T as integers (they share
-//             their exponent: exact, whatever the order), `need` copies of T's own value for the ties, and the
-//             partial sums.
-// Scores must be non-negative (in-degrees), rows at most 2^24 long.
+// The pivot detector's metrics from rows of in-degrees (one per query head) whose histograms over the bins of row_bin have been
+// built by whoever read the rows first.  The sum of a row's kk largest scores takes no placement and no ordered list.  Two kernels:
+//   compact : every workgroup finds the k-th largest key's bin from the row's histogram, adds up its scores ABOVE it (a
+//             partial sum per workgroup, fixed order) and appends its scores IN it -- the candidates -- to the row's
+//             list (one integer atomic per workgroup reserves the place; the order of the list differs from run to
+//             run, and nothing below depends on it);
+//   select  : one workgroup of 1024 threads per row takes the candidates (the first 32768 in registers), finds the remaining
+//             bits 11 at a time with histograms in LDS, and adds the candidates above the k-th key T as integers (they share
+//             their exponent: exact, whatever the order), `krem` copies of T's own value for the ties, and the
+//             partial sums; also the row's variance.  The workgroup that ends last forms the means over the rows.
+// Scores must be non-negative (in-degrees), rows at most 2^24 long.  Both kernels are a few dependent reads and barriers long:
+// what they cost grows with the candidates, which is why the bins are fine around the mean, and the
+// means take no launch of their own (32 heads, compact + select + means: 128K tokens 28.2 -> 17.8 us, 32K 16.3 -> 11.5 us).
 __device__ inline float key_score(uint32_t key) {
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
 }
 
+constexpr int kCompThreads = 512;             // the compact kernel
 constexpr int kSelThreads = 1024;             // the select kernel: sixteen waves per row
 constexpr int kCandPerThread = 32;            // candidates one of its threads keeps in registers (32768 in all)
+constexpr int kFewPerThread = 2;              // ... where no thread has more
 
-__global__ __launch_bounds__(kThreads) void mass_compact_kernel(const float* __restrict__ rows, int64_t n, uint32_t kk,
-                                                                TopkWs ws, float* __restrict__ cand,
-                                                                float* __restrict__ part_above) {
+__global__ __launch_bounds__(kCompThreads) void mass_compact_kernel(const float* __restrict__ rows, int64_t n, uint32_t kk,
+                                                                    float mean, uint32_t* __restrict__ hist,
+                                                                    uint32_t* __restrict__ state, float* __restrict__ cand,
+                                                                    float* __restrict__ part_above) {
   short_kernel_priority();
-  __shared__ uint32_t scan[4];
+  constexpr int NT = kCompThreads, PER = kPivotShare / NT;
+  __shared__ uint32_t scan[NT / 64];
   __shared__ uint32_t res[3];
-  __shared__ float red[kThreads];
-  __shared__ float stage[kTargetPerBlock];
+  __shared__ float red[NT / 64];
+  __shared__ float stage[kPivotShare];
   __shared__ uint32_t cnt, gbase;
   const int p = blockIdx.x, h = blockIdx.y, P = gridDim.x, t = threadIdx.x, lane = t & 63;
   const float* d = rows + (int64_t)h * n;
-  const int64_t lo = (int64_t)p * kTargetPerBlock;
-  float x[kPerThread];
+  const int64_t lo = (int64_t)p * kPivotShare;
+  float x[PER];
 #pragma unroll
-  for (int i = 0; i < kPerThread; ++i) {   // loads first, the histogram scan under them
-    const int64_t j = lo + t + i * kThreads;
+  for (int i = 0; i < PER; ++i) {   // loads first, the histogram scan under them
+    const int64_t j = lo + t + i * NT;
     x[i] = j < n ? d[j] : 0.f;
   }
   if (t == 0) cnt = 0u;
-  uint32_t* gh = ws.hist + (size_t)h * 3 * kBins;
+  uint32_t* gh = hist + (size_t)h * kRowWords;
+  const uint32_t at = row_bins_at(score_key(mean));
   uint32_t t0, above0;
-  select_bin<kThreads, kBins>(gh, kk, scan, res, &t0, &above0);   // its barriers cover cnt = 0
+  select_bin<NT, kBins>(gh, kk, scan, res, &t0, &above0);   // its barriers cover cnt = 0
   float sum = 0.f;
 #pragma unroll
-  for (int i = 0; i < kPerThread; ++i) {
-    const bool in = lo + t + i * kThreads < n;
-    const uint32_t dg = score_key(x[i]) >> 21;
-    if (in && dg > t0) sum += x[i];
-    const bool c = in && dg == t0;
+  for (int i = 0; i < PER; ++i) {
+    const bool in = lo + t + i * NT < n;
+    const uint32_t bin = row_bin(score_key(fabsf(x[i])), at);
+    if (in && bin > t0) sum += x[i];
+    const bool c = in && bin == t0;
     const unsigned long long m = __ballot(c);
     if (m) {   // one LDS atomic per wave and step reserves the wave's places
       const int first = __ffsll((long long)m) - 1;
@@ -963,91 +969,127 @@ __global__ __launch_bounds__(kThreads) void mass_compact_kernel(const float* __r
       if (c) stage[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = x[i];
     }
   }
-  red[t] = sum;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane == 0) red[t >> 6] = sum;
   __syncthreads();
-  for (int off = kThreads / 2; off > 0; off >>= 1) {
-    if (t < off) red[t] += red[t + off];
-    __syncthreads();
-  }
   if (t == 0) {
-    part_above[(int64_t)h * P + p] = red[0];
-    gbase = cnt ? atomicAdd(&gh[kBins], cnt) : 0u;   // the row's candidate counter: first word of the (unused, zeroed) digit-1 histogram
+    gbase = cnt ? atomicAdd(&gh[kBins], cnt) : 0u;   // the row's candidate counter, behind its histogram
+    float s = 0.f;
+    for (int i = 0; i < NT / 64; ++i) s += red[i];
+    part_above[(int64_t)h * P + p] = s;
     if (p == 0) {
-      ws.state[h * 4 + 0] = t0;
-      ws.state[h * 4 + 1] = kk - above0;
+      state[h * 4 + 0] = t0;
+      state[h * 4 + 1] = kk - above0;
     }
   }
   __syncthreads();
   float* out = cand + (int64_t)h * n + gbase;
-  for (uint32_t i = t; i < cnt; i += kThreads) out[i] = stage[i];
+  for (uint32_t i = t; i < cnt; i += NT) out[i] = stage[i];
 }
 
-__global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* __restrict__ cand, int64_t n, TopkWs ws,
-                                                                  const float* __restrict__ part_above, int P,
-                                                                  float* __restrict__ mass, float* __restrict__ tail) {
-  short_kernel_priority();
+// The `krem`-th largest of c0 candidates, all of whose keys are T plus `bits` open ones: T and krem become that key and how
+// many copies of it count; returns the calling thread's share of the significands above it.  PER candidates a thread are kept
+// in registers, any others read again on each pass.
+template <int PER>
+__device__ inline unsigned long long resolve_row(const float* __restrict__ c, uint32_t c0, uint32_t bits, uint32_t* hh /*[kBins]*/,
+                                                 uint32_t* scan, uint32_t* res, uint32_t& T, uint32_t& krem) {
   constexpr int NT = kSelThreads;
-  __shared__ uint32_t hh[kBins];
-  __shared__ uint32_t scan[NT / 64];
-  __shared__ uint32_t res[3];
-  __shared__ unsigned long long red64[NT];
-  __shared__ float redf[NT];
-  const int h = blockIdx.x, t = threadIdx.x;
-  const uint32_t* gh = ws.hist + (size_t)h * 3 * kBins;
-  const uint32_t t0 = ws.state[h * 4 + 0], krem0 = ws.state[h * 4 + 1];
-  const uint32_t c0 = gh[kBins];   // candidates = keys whose first digit is t0
-  const float* c = cand + (int64_t)h * n;
-  float v[kCandPerThread];
+  const int t = threadIdx.x;
+  float v[PER];
 #pragma unroll
-  for (int r = 0; r < kCandPerThread; ++r) {
+  for (int r = 0; r < PER; ++r) {
     const uint32_t i = (uint32_t)(r * NT + t);
     v[r] = i < c0 ? c[i] : 0.f;
   }
   auto each = [&](auto f) {
 #pragma unroll
-    for (int r = 0; r < kCandPerThread; ++r)
-      if ((uint32_t)(r * NT + t) < c0) f(score_key(v[r]));
-    for (uint32_t i = (uint32_t)(kCandPerThread * NT + t); i < c0; i += NT) f(score_key(c[i]));
+    for (int r = 0; r < PER; ++r)
+      if ((uint32_t)(r * NT + t) < c0) f(score_key(fabsf(v[r])));
+    for (uint32_t i = (uint32_t)(PER * NT + t); i < c0; i += NT) f(score_key(fabsf(c[i])));
   };
-  for (int i = t; i < kBins; i += NT) hh[i] = 0u;
-  __syncthreads();
-  each([&](uint32_t key) { atomicAdd(&hh[(key >> 10) & (kBins - 1)], 1u); });
-  __syncthreads();
-  uint32_t t1, above1;
-  select_bin<NT, kBins>(hh, krem0, scan, res, &t1, &above1);
-  const uint32_t krem1 = krem0 - above1;
-  for (int i = t; i < kLowBins; i += NT) hh[i] = 0u;
-  __syncthreads();
-  each([&](uint32_t key) {
-    if (((key >> 10) & (kBins - 1)) == t1) atomicAdd(&hh[key & (kLowBins - 1)], 1u);
-  });
-  __syncthreads();
-  uint32_t t2, above2;
-  select_bin<NT, kLowBins>(hh, krem1, scan, res, &t2, &above2);
-  const uint32_t T = (t0 << 21) | (t1 << 10) | t2;
-  // every candidate carries the first digit t0 -- sign, exponent and two mantissa bits -- so the candidates share
-  // one exponent and their 24-bit significands add up exactly as integers, in any order
+  while (bits > 0) {   // 17 open bits: 11 and 6; 21: 11 and 10
+    const uint32_t take = min(bits, 11u), shift = bits - take;
+    for (int i = t; i < kBins; i += NT) hh[i] = 0u;
+    __syncthreads();
+    each([&](uint32_t key) {
+      if (((key ^ T) >> bits) == 0u) atomicAdd(&hh[(key >> shift) & ((1u << take) - 1u)], 1u);
+    });
+    __syncthreads();
+    uint32_t digit, above;
+    select_bin<NT, kBins>(hh, krem, scan, res, &digit, &above);
+    T |= digit << shift;
+    krem -= above;
+    bits = shift;
+  }
+  // every candidate lies in one quarter of an octave or less: they share one exponent and their 24-bit significands
+  // add up exactly as integers, in any order
   unsigned long long acc = 0ull;
-  const uint32_t expo = (t0 >> 2) & 0xFFu;            // biased exponent (scores are non-negative)
-  const uint32_t hidden = expo ? 0x00800000u : 0u;    // (subnormals have no hidden one)
+  const uint32_t hidden = ((T >> 23) & 0xFFu) ? 0x00800000u : 0u;   // (subnormals have no hidden one)
   each([&](uint32_t key) {
     if (key > T) acc += (unsigned long long)((key & 0x007FFFFFu) | hidden);
   });
-  red64[t] = acc;
-  float pa = 0.f;
-  for (int p = t; p < P; p += NT) pa += part_above[(int64_t)h * P + p];
-  redf[t] = pa;
-  __syncthreads();
-  for (int off = NT / 2; off > 0; off >>= 1) {
-    if (t < off) { red64[t] += red64[t + off]; redf[t] += redf[t + off]; }
-    __syncthreads();
+  return acc;
+}
+
+__global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* __restrict__ cand, int64_t n, int w,
+                                                                  uint32_t* __restrict__ hist,
+                                                                  const uint32_t* __restrict__ state,
+                                                                  const float* __restrict__ part_above,
+                                                                  const float* __restrict__ var_part, int P,
+                                                                  float* __restrict__ sums, float* __restrict__ sparsity,
+                                                                  float* __restrict__ variance) {
+  short_kernel_priority();
+  constexpr int NT = kSelThreads;
+  __shared__ uint32_t hh[kBins];
+  __shared__ uint32_t scan[NT / 64];
+  __shared__ uint32_t res[3];
+  __shared__ unsigned long long red64[NT / 64];
+  __shared__ float redf[NT / 64], redv[NT / 64];
+  __shared__ uint32_t done;
+  const int h = blockIdx.x, H = gridDim.x, t = threadIdx.x, lane = t & 63;
+  const uint32_t bin = state[h * 4 + 0];
+  uint32_t krem = state[h * 4 + 1];
+  const uint32_t c0 = hist[(size_t)h * kRowWords + kBins];   // candidates = keys in that bin
+  const float* c = cand + (int64_t)h * n;
+  float pa = 0.f, pv = 0.f;
+  for (int p = t; p < P; p += NT) { pa += part_above[(int64_t)h * P + p]; pv += var_part[(int64_t)h * P + p]; }
+  uint32_t T, bits;
+  row_bin_range(bin, row_bins_at(score_key((float)w / (float)n)), &T, &bits);
+  // few candidates: no long row of steps that find nothing (32K tokens, window 8: 10.2 us without, 6.9 with;
+  // 128K, window 64: 12.5 and 8.5)
+  unsigned long long acc = c0 <= (uint32_t)(kFewPerThread * NT) ? resolve_row<kFewPerThread>(c, c0, bits, hh, scan, res, T, krem)
+                                                                      : resolve_row<kCandPerThread>(c, c0, bits, hh, scan, res, T, krem);
+  const uint32_t expo = (T >> 23) & 0xFFu;            // biased exponent (scores are non-negative)
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    acc += __shfl_xor(acc, off);
+    pa += __shfl_xor(pa, off);
+    pv += __shfl_xor(pv, off);
   }
+  if (lane == 0) { red64[t >> 6] = acc; redf[t >> 6] = pa; redv[t >> 6] = pv; }
+  __syncthreads();
   if (t == 0) {
-    const double m = ldexp((double)red64[0], (int)(expo ? expo : 1u) - 150) + (double)(krem1 - above2) * (double)key_score(T) +
-                     (double)redf[0];
-    mass[2 * h + 1] = (float)m;
-    tail[2 * h] = 0.f;
-    tail[2 * h + 1] = 0.f;
+    unsigned long long a = 0ull;
+    float sa = 0.f, sv = 0.f;
+    for (int i = 0; i < NT / 64; ++i) { a += red64[i]; sa += redf[i]; sv += redv[i]; }
+    const double m = ldexp((double)a, (int)(expo ? expo : 1u) - 150) + (double)krem * (double)key_score(T) + (double)sa;
+    __hip_atomic_store(&sums[2 * h], sv / (float)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&sums[2 * h + 1], (float)m * (1.0f / (float)w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // release this row's sums, acquire those of the rows that ended before
+    done = __hip_atomic_fetch_add(&hist[kBins + 1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (done != (uint32_t)(H - 1)) return;   // (uniform) the last one adds the rows up, in row order
+  float* row = reinterpret_cast<float*>(hh);
+  static_assert(2 * kMaxBatch <= kBins, "the sums of all rows fit");
+  for (int i = t; i < 2 * H; i += NT) row[i] = __hip_atomic_load(&sums[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (t == 0) {
+    float vt = 0.f, rt = 0.f;
+    for (int i = 0; i < H; ++i) { vt += row[2 * i]; rt += row[2 * i + 1]; }
+    *sparsity = rt / (float)H;
+    *variance = vt / (float)H;
   }
 }
 
@@ -1173,16 +1215,13 @@ hipError_t launch_topk_rest(const float* scores, const SeqTable& plan, int keep_
   return hipGetLastError();
 }
 
-// The sum of the kk largest scores of each of H rows of n scores (see mass_compact_kernel).  ws.hist[h][0][.] must
-// hold the histogram of the rows' first digits and ws.hist[h][1][0] must be zero; cand: H x n floats of scratch;
-// part_above: H x ceil(n / 2048) floats; the sums land in mass[2h + 1], and tail[2h], tail[2h + 1] are cleared.
-hipError_t launch_topk_mass(const float* rows, int H, int64_t n, uint32_t kk, const TopkWs& ws, float* cand,
-                            float* part_above, float* mass, float* tail, hipStream_t st) {
-  if (H == 0 || n == 0) return hipSuccess;
-  const unsigned P = (unsigned)((n + kTargetPerBlock - 1) / kTargetPerBlock);
-  hipLaunchKernelGGL(mass_compact_kernel, dim3(P, (unsigned)H), dim3(kThreads), 0, st, rows, n, kk, ws, cand, part_above);
-  hipLaunchKernelGGL(mass_select_kernel, dim3((unsigned)H), dim3(kSelThreads), 0, st, cand, n, ws, part_above, (int)P, mass,
-                     tail);
+hipError_t launch_pivot_mass(const ReduceWork& red, uint32_t kk, uint32_t* hist, uint32_t* state, float* cand, float* part_above,
+                             const float* var_part, float* sums, float* sparsity, float* variance, hipStream_t st) {
+  const int P = pivot_shares(red.total);
+  hipLaunchKernelGGL(mass_compact_kernel, dim3((unsigned)P, (unsigned)red.Hq), dim3(kCompThreads), 0, st, red.colsum, red.total, kk,
+                     (float)red.w / (float)red.total, hist, state, cand, part_above);
+  hipLaunchKernelGGL(mass_select_kernel, dim3((unsigned)red.Hq), dim3(kSelThreads), 0, st, cand, red.total, red.w, hist, state,
+                     part_above, var_part, P, sums, sparsity, variance);
   return hipGetLastError();
 }
 

@@ -50,6 +50,22 @@ extern "C" int structkv_stub_bin_faults(uint32_t centre) {
   }
   return bad + (next != 0);
 }
+// The same for the bins of the pivot detector's rows and the keys of non-negative scores; no bin may leave its octave.
+extern "C" int structkv_stub_row_bin_faults(uint32_t centre) {
+  int bad = 0;
+  uint32_t next = 0x80000000u;
+  const uint32_t at = row_bins_at(centre);
+  for (uint32_t bin = 0; bin < 1024u + kRowExtra; ++bin) {
+    uint32_t lo, width;
+    row_bin_range(bin, at, &lo, &width);
+    const uint32_t hi = lo + ((1u << width) - 1u);
+    bad += lo != next || hi < lo || (lo >> 23) != (hi >> 23);
+    const uint32_t keys[4] = {lo, lo + (hi - lo) / 3, lo + (hi - lo) / 2, hi};
+    for (uint32_t key : keys) bad += row_bin(key, at) != bin;
+    next = hi + 1;
+  }
+  return bad + (next != 0);
+}
 
 hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void*,
                                   const void*, int64_t, int64_t, float, float*, const float*, float*, int64_t total,
@@ -136,15 +152,15 @@ hipError_t topk_static_scratch(void** ptr, size_t* bytes) {
   *bytes = sizeof(host_stand_in);
   return hipSuccess;
 }
-int pivot_plane_shares(int64_t n) { return (int)((n + 2047) / 2048); }
-hipError_t launch_pivot_planes(const float*, int, int64_t, float, uint32_t*, float*, hipStream_t) {
-  ++g_launches; return hipSuccess;
+hipError_t launch_pivot_planes(const ReduceWork& r, uint32_t* hist, float* var_part, hipStream_t) {
+  ++g_launches;
+  return r.colsum && r.planes == r.Hq && r.Hq <= kMaxBatch && hist && var_part ? hipSuccess : hipErrorInvalidValue;
 }
-hipError_t launch_topk_mass(const float*, int, int64_t, uint32_t, const TopkWs&, float*, float*, float*, float*, hipStream_t) {
-  ++g_launches; return hipSuccess;
+hipError_t launch_pivot_mass(const ReduceWork& r, uint32_t kk, uint32_t*, uint32_t*, float*, float*, const float*, float*, float*,
+                             float*, hipStream_t) {
+  ++g_launches;
+  return kk >= 1 && kk <= r.total && r.total <= ((int64_t)1 << 24) ? hipSuccess : hipErrorInvalidValue;
 }
-hipError_t launch_pivot_finish_planes(const float*, int, const float*, int, const float*, int, int64_t, float, float*,
-                                      float*, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_pivot_heads(const float*, int, int64_t, const int32_t*, int64_t, float, float*, hipStream_t) {
   ++g_launches; return hipSuccess;
 }

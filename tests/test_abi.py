@@ -401,3 +401,12 @@ def test_bins_of_the_mid_sized_selection(B, centre):
     if not hasattr(B._lib, "structkv_stub_bin_faults"):
         pytest.skip("the real library launches kernels; this runs against the stub build only")
     assert B._lib.structkv_stub_bin_faults(ctypes.c_uint32(centre)) == 0
+
+
+@pytest.mark.parametrize("centre", [0x80000000, 0x80000001, 0x88000000, 0xB4800000, 0xB8000001, 0xBF800000, 0xC2800000, 0xFC000000,
+                                    0xFFFFFFFF])
+def test_bins_of_the_pivot_rows(B, centre):
+    """The same for the bins of the pivot detector's rows, over the keys of non-negative scores.  Stub build only."""
+    if not hasattr(B._lib, "structkv_stub_row_bin_faults"):
+        pytest.skip("the real library launches kernels; this runs against the stub build only")
+    assert B._lib.structkv_stub_row_bin_faults(ctypes.c_uint32(centre)) == 0

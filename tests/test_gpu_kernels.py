@@ -221,6 +221,27 @@ def test_pivot_metrics_of_short_windows(sweep_mod, oracle, Hq, G, d, w, lens, ca
     assert np.all(np.abs(var.cpu().numpy()[:len(lens)] - var_ref) <= 2e-3 * var_ref + 1e-4 / np.array(lens, dtype=np.float64) ** 2)
 
 
+# the top-k mass of the per-head rows: shares of 4096 scores and their remainders; scores within a few per cent (the fine bins),
+# over many octaves (a threshold among the quarter octaves), and all equal (one bin holds the row: more candidates than the
+# registers take at 40000).  sharp scales the queries.
+@pytest.mark.parametrize("n", [64, 4095, 4096, 4097, 9000, 40000])
+@pytest.mark.parametrize("sharp", [0.0, 0.2, 1.0, 12.0])
+def test_pivot_rows(sweep_mod, oracle, n, sharp):
+    Hq, G, d, w = 4, 2, 64, 32
+    sw = sweep_mod.LayerSweep(Hq, G, d, w, torch.bfloat16, [n], [0])
+    q = (_randn(1, Hq, w, d, dtype=torch.float32, seed=11) * sharp).to(torch.bfloat16)
+    k = _randn(G, n, d, dtype=torch.bfloat16, seed=12)
+    D, ent, _, probs = oracle.score_layer(to_oracle_array(q), to_oracle_array(k), Hq, G, d, w, [n], want_probs=True)
+    rho_ref, var_ref = oracle.pivot_metrics(probs, 0.1)
+    for _ in range(2):   # a call leaves nothing behind that changes the next
+        sw.indeg.fill_(-1.0)
+        rho, var = sw.score_pivot(q, k)
+        assert_close_floor(sw.indeg.cpu().numpy(), D, 1e-3, "indeg")
+        assert_entropy(sw.entropy.cpu().numpy()[:1], ent, 1e-3)
+        assert np.all(np.abs(rho.cpu().numpy()[:1] - rho_ref) <= 1e-3 * rho_ref)
+        assert np.all(np.abs(var.cpu().numpy()[:1] - var_ref) <= 2e-3 * var_ref + 1e-4 / n ** 2)
+
+
 # short inputs: key chunks of 64 .. 256 keys (two to eight tiles), one- and four-wave workgroups
 @pytest.mark.parametrize("Hq,G,w", [(8, 2, 8), (4, 2, 32), (8, 2, 32), (8, 2, 64)])
 @pytest.mark.parametrize("lens", [[64], [65, 1, 0, 200], [5000], [17000, 31]])
