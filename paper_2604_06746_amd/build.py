@@ -23,7 +23,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-x", "hip",
 EXTRA = {"score_mfma_ring.hip": ["-fno-honor-nans"], "score_mfma_wide.hip": ["-fno-honor-nans"]}
 
 # Sources compiled as several objects: (macro that selects the part, number of parts)
-PARTS = {"score_mfma_ring.hip": ("SKV_RING_PART", 4)}
+PARTS = {"score_mfma_ring.hip": ("SKV_RING_PART", 5)}
 
 
 def _units() -> list:

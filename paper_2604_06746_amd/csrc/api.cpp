@@ -60,9 +60,41 @@ structkv_status check_cu(int32_t batch, const int64_t* cu, SeqTable* seq) {
   return STRUCTKV_OK;
 }
 
-// Decide path, tiling and workspace layout.  `n_chunk_bound` < 0: exact from seq; otherwise an upper bound.
+// Key chunks of k keys of all sequences (an upper bound without their lengths)
+int64_t key_chunks(const SeqTable* seq, int batch, int64_t total, int64_t k) {
+  if (!seq) return total / k + batch;
+  int64_t c = 0;
+  for (int b = 0; b < batch; ++b) c += (uint32_t)(seq->cu[b + 1] - seq->cu[b] + k - 1) / (uint32_t)k;   // (lengths below 2^31)
+  return c;
+}
+
+// What a scoring call of more than 128 rows of 128 components costs with m workgroups of k keys on the fullest CU, by the kernels
+// of score_mfma_ring.hip or (wide) of score_mfma_wide.hip, in thousandths of what a key of three ring workgroups costs.  A CU's time
+// is that of its workgroups' keys, plus what it costs to start one, the more the fewer are resident to fill each other's waits.
+// Fitted to the times of 460 layers and 160 pivot calls of 2K to 500K tokens, in batches of 1 to 40 sequences, with three to thirty
+// plans each.  The rule built on it takes 0.4 % (pivot calls 0.3 %) longer than the best of these on average; the wide kernel
+// alone, in the fewest rounds of the longest chunks, took 3.4 % (1.4 %) longer.
+// The wide kernel's tiles are cheaper, but its loop takes longer to start and leaves ragged and masked tiles out, which then
+// end the launch; with one plane per head the ring kernel's tiles cost more.  Layers of 32 heads on 8, window 64, us in a graph,
+// ring / wide:
+//   one workgroup a CU:   64 keys 23.3 / 24.4, 128 28.9 / 29.2, 256 36.9 / 36.4 (where the sequence ends inside a tile 36.8 / 38.2),
+//                         288 38.6 / 39.5, 352 44.5 / 43.4, 512 54.6 / 53.7, 864 70.1 / 65.1; causal 256 keys 38.0 / 39.6, 512 55.6 / 57.1
+//   two:                  256 keys 52.1 / 53.9, 320 54.2 / 56.0, 448 64.2 / 65.3, 640 77.2 / 77.6, 1280 122.3 / 120.5
+//   three:                288 keys 65.0 / 66.5, 608 98.2 / 97.7, 864 123.5 / 121.4, 1376 183.3 / 179.9
+//   more (pivot calls):   256 keys 101.9 / 95.1
+int64_t score_cost(const structkv_shape& s, bool wide, bool planes, int64_t m, int64_t k) {
+  // keys that starting a workgroup is worth, keys that a row of the window with masked tiles is worth (thousandths); by m: 1, 2, 3, more
+  struct Kind { int64_t start, masked, rate[4]; };
+  static const Kind ring = {82, 0, {1310, 985, 1000, 1000}}, loop = {130, 250, {1160, 1000, 915, 905}};
+  static const Kind loop_planes = {112, 400, {1180, 945, 900, 900}};
+  const Kind& c = !wide ? ring : planes ? loop_planes : loop;
+  return m * (k + c.start) * c.rate[std::min<int64_t>(m, 4) - 1] + (s.causal ? c.masked * s.window : 0);
+}
+
+// Decide path, tiling and workspace layout: exact with seq, an upper bound without.  small: where the keys per workgroup are
+// chosen by cost, the most of them instead, with the fewest partial results.
 void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t total, bool mfma_ok,
-               ScorePlan* p, bool planes = false) {
+               ScorePlan* p, bool planes = false, bool small = false) {
   const int gs = s.n_q_heads / s.n_kv_heads;
   int64_t chunk_bound = 0;   // of the key chunks of any `total` tokens, beside one per sequence; grows with total
   p->R = gs * s.window;
@@ -70,6 +102,7 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
   p->path = mfma_ok ? 0 : 1;
   p->planes = 0;
   p->split = 1;
+  p->wide = 0;
   // a K of at least the memory-side cache's 256 MiB streams through the caches (see the kernel's NT parameter)
   p->stream_k = p->path == 0 && total * s.n_kv_heads * s.head_dim * 2 >= ((int64_t)256 << 20);
   if (p->path == 0) {
@@ -117,21 +150,21 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     }
     if (kc < kc_min) kc = kc_min;
     if (p->NW == 4 && p->RB == 2 && s.head_dim == 128 && kc_min >= 256) {
-      // score_mfma_wide.hip: a CU's time is that of its workgroups' keys, almost however many of them are resident (three waves
-      // on a SIMD are about 8 % ahead of two and 28 % of one), plus about 128 keys a workgroup for what it costs to start one.
-      // So the keys per workgroup are those with which whole rounds of workgroups over the CUs take the least.  32 heads
-      // on 8, window 64, us a scoring call: 40000 tokens 512 keys (632 workgroups on 256 CUs) 72.8, 640 keys (504) 67.2;
-      // 50001 tokens 512 keys 89.6, 640 keys 83.7; 1M tokens 1408 keys 1176, 1664 keys 1165, 2048 keys 1151.  A sequence leaves
-      // half a chunk empty on average.
+      // Whole rounds of workgroups over the CUs, m on each, the fewest possible and up to five more; of these the keys per
+      // workgroup that cost least.  Every sequence's last chunk is a workgroup too: room is left for all of these, or for half of them.
+      const int64_t fewest = ceil_div(std::max<int64_t>(total, 1) * wg_per_chunk, 256 * kMaxKC);
       int64_t best = 0;
-      for (int64_t m = ceil_div(std::max<int64_t>(total, 1) * wg_per_chunk, 256 * kMaxKC), last = m + 5; m <= last; ++m) {
-        const int64_t chunks = 256 * m / wg_per_chunk - (batch - 1) / 2;
-        if (chunks < 1) continue;
-        const int64_t k = std::max(ceil_div(ceil_div(total, chunks), 32) * 32, kc_min);
-        if (k > kMaxKC) continue;
-        const int64_t cost = m * (k + 128) * (m == 1 ? 128 : m == 2 ? 109 : 100);
-        if (best == 0 || cost < best) { best = cost; kc = k; }
-      }
+      for (int64_t m = fewest; m < fewest + 6; ++m)
+        for (int64_t ends = (batch - 1) / 2;; ends = batch - 1) {
+          const int64_t chunks = 256 * m / wg_per_chunk - ends;
+          const int64_t k = chunks < 1 ? kMaxKC + 1 : std::max<int64_t>(ceil_div(ceil_div(total, chunks), 32) * 32, 256);
+          if (k <= kMaxKC) {
+            const int64_t on_cu = ceil_div(wg_per_chunk * key_chunks(seq, batch, total, k), 256);
+            const int64_t cost = small ? kMaxKC + 1 - k : std::min(score_cost(s, false, np > 0, on_cu, k), score_cost(s, true, np > 0, on_cu, k));
+            if (best == 0 || cost < best) { best = cost; kc = k; }
+          }
+          if (ends == batch - 1) break;
+        }
     }
     chunk_bound = std::max(total / 256, std::min(ceil_div(total, 64), ceil_div(one_each, wg_per_chunk)));
     if (kc > kMaxKC) kc = kMaxKC;
@@ -153,12 +186,15 @@ void make_plan(const structkv_shape& s, const SeqTable* seq, int batch, int64_t 
     chunk_bound = std::max(std::min(chunks_per_round, ceil_div(total, step)), total / kF32KeyCap);   // (grows with total)
   }
   if (seq) {
-    p->n_chunks = 0;
-    for (int b = 0; b < batch; ++b) p->n_chunks += ceil_div(seq->cu[b + 1] - seq->cu[b], p->KC);
+    p->n_chunks = key_chunks(seq, batch, total, p->KC);
   } else {
     p->n_chunks = chunk_bound + batch;
   }
   p->grid_chunks = p->n_chunks;
+  if (p->path == 0 && p->NW == 4 && p->RB == 2 && s.head_dim == 128) {
+    const int64_t m = std::max<int64_t>(ceil_div((int64_t)s.n_kv_heads * ceil_div(p->RC, p->NW) * p->n_chunks, 256), 1);
+    p->wide = score_cost(s, true, p->planes > 0, m, p->KC) < score_cost(s, false, p->planes > 0, m, p->KC);
+  }
   const size_t GRC = (size_t)s.n_kv_heads * p->RC;
   size_t off = 0;
   p->off_stats = off;   off += align_up(sizeof(float) * GRC * (size_t)p->n_chunks * p->WK * 3 * p->RPC, 256);
@@ -256,6 +292,8 @@ structkv_status run_score(const structkv_shape* shape, const void* q_win, const 
   const int64_t total = seq.cu[B];
   ScorePlan p;
   make_plan(s, &seq, B, total, !o.force_simt && mfma_eligible(s, q_win, k, ksh, kst), &p, o.planes);
+  if (p.total_bytes > ws_bytes)   // (a workspace of less than what structkv_workspace_bytes asks for)
+    make_plan(s, &seq, B, total, !o.force_simt && mfma_eligible(s, q_win, k, ksh, kst), &p, o.planes, true);
   if (o.planes && !p.planes) return fail(STRUCTKV_ERR_UNSUPPORTED, "per-head planes need the MFMA kernels and a window of 8, 16, 32 or 64");
   // short sequences: both passes in one launch (with a workspace of less than what structkv_workspace_bytes asks for, the
   // general plan, which may need less)

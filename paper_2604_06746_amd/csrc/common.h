@@ -314,6 +314,7 @@ struct ScorePlan {
                      // window; 2: each of its two 32-row blocks is) instead of one per workgroup: CP = query heads per
                      // KV head, and the planes are the per-head in-degrees
   int split;         // ... times the heads of every 32-row block (windows of 16 and 8: 2 and 4; planes = RB then), else 1
+  int wide;          // 1 = the kernels of score_mfma_wide.hip (more than 128 rows of 128 components, long key chunks)
   int kshare;        // consecutive groups that read the same K head (1 in ordinary scoring; the per-head
                      // scoring of the pivot metrics runs every query head as its own group: H_q/G)
   int64_t n_chunks;  // sum over sequences of ceil(n_b / KC): the stride of the per-chunk statistics
@@ -328,7 +329,7 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
                                   const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
                                   float* stats, const float* lse2, float* colsum, int64_t total,
                                   float* probs, int pass, hipStream_t st);
-// its kernels for more than 128 rows of 128 components (RB 2, NW 4)
+// the kernels of a plan with `wide` set (RB 2, NW 4, head_dim 128)
 hipError_t launch_score_mfma_wide(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq,
                                   const void* q, const void* k, int64_t ksh, int64_t kst, float c2,
                                   float* stats, const float* lse2, float* colsum, int64_t total,

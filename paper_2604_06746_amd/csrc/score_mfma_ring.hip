@@ -12,7 +12,7 @@
 //     operands in registers for the whole kernel, and reads each key operand from LDS once per 32-key tile;
 //   * a KV group of 256 rows (GQA 4 x window 64) is four row-chunks of 64 rows = the four waves of a workgroup
 //     (128 rows: four row-chunks of 32), which share the LDS tiles, so K crosses HBM -> L2 -> LDS once per pass
-//     (more than 128 rows of 128 components have kernels of their own: score_mfma_wide.hip);
+//     (more than 128 rows of 128 components in long key chunks have kernels of their own: score_mfma_wide.hip);
 //   * tiles are fetched with global_load_lds_dwordx4 (16 B per lane, lane L lands at base + 16 L), three
 //     tiles ahead, into an XOR-swizzled layout that makes the operand reads bank-conflict free;
 //   * inside a wave the MFMAs of row block rb+1 are issued under the softmax arithmetic of row block rb.
@@ -625,7 +625,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void score_mfma_ring_kern
 
 }  // namespace
 
-// Compiled in four parts, one object each with SKV_RING_PART = 0 .. 3 (the instantiations take minutes in one); part 0
+// Compiled in five parts, one object each with SKV_RING_PART = 0 .. 4 (the instantiations take minutes in one); part 0
 // also holds the dispatch.
 template <int D, int NRB, int NW, int NBUF>
 hipError_t launch_ring_cfg(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void* q,
@@ -669,11 +669,13 @@ hipError_t launch_ring_cfg(const structkv_shape& s, const ScorePlan& p, const Se
                                                         const void*, const void*, int64_t, int64_t, float, float*, \
                                                         const float*, float*, int64_t, float*, int, hipStream_t)
 #if SKV_RING_PART == 0
+SKV_RING_INST(128, 2, 4, 4);
+#elif SKV_RING_PART == 1
 SKV_RING_INST(128, 1, 4, 4);
 SKV_RING_INST(128, 1, 1, 2);
-#elif SKV_RING_PART == 1
-SKV_RING_INST(128, 2, 1, 2);
 #elif SKV_RING_PART == 2
+SKV_RING_INST(128, 2, 1, 2);
+#elif SKV_RING_PART == 3
 SKV_RING_INST(64, 2, 4, 4);
 SKV_RING_INST(64, 1, 4, 4);
 #else
@@ -682,7 +684,9 @@ SKV_RING_INST(64, 1, 1, 2);
 #endif
 
 #if SKV_RING_PART == 0
+extern SKV_RING_INST(128, 1, 4, 4);
 extern SKV_RING_INST(128, 2, 1, 2);
+extern SKV_RING_INST(128, 1, 1, 2);
 extern SKV_RING_INST(64, 2, 4, 4);
 extern SKV_RING_INST(64, 1, 4, 4);
 extern SKV_RING_INST(64, 2, 1, 2);
@@ -700,8 +704,9 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
 #define SKV_RING(d, nrb, nw, nbuf)                                                                      \
   if (s.head_dim == d && p.RB == nrb && p.NW == nw)                                                      \
     return launch_ring_cfg<d, nrb, nw, nbuf>(s, p, seq, q, k, ksh, kst, c2, stats, lse2, colsum, total, probs, pass, st)
-  if (s.head_dim == 128 && p.RB == 2 && p.NW == 4)   // more than 128 rows
+  if (p.wide)
     return launch_score_mfma_wide(s, p, seq, q, k, ksh, kst, c2, stats, lse2, colsum, total, probs, pass, st);
+  SKV_RING(128, 2, 4, 4);
   SKV_RING(128, 1, 4, 4);
   SKV_RING(128, 2, 1, 2);
   SKV_RING(128, 1, 1, 2);

@@ -1,7 +1,8 @@
 // bf16 MFMA scoring kernels for more than 128 query rows per KV head and head_dim 128 (GQA 4 x window 64: the headline
-// shape), paper Eq. 1, Eq. 2, Eq. 4.  The work of a workgroup -- four waves of 64 rows that share 32-key tiles in an LDS ring,
-// a key chunk, its partial statistics or column sums -- is that of score_mfma_ring.hip, whose plan, partial results and
-// column-sum planes these kernels share; what differs is the loop.
+// shape) in long key chunks (the plan says from where on; shorter ones stay with score_mfma_ring.hip), paper Eq. 1, Eq. 2,
+// Eq. 4.  The work of a workgroup -- four waves of 64 rows that share 32-key tiles in an LDS ring, a key chunk, its partial
+// statistics or column sums -- is that of score_mfma_ring.hip, whose plan, partial results and column-sum planes these kernels
+// share; what differs is the loop.
 //
 // What bounds these shapes is power, and the issue port at the clock that the chip then grants: a loop of nothing but this
 // softmax and these MFMAs on N(0,1) data runs at 1.7 GHz with v_mfma_f32_32x32x16_bf16 and at 2.05 GHz with
@@ -567,7 +568,7 @@ __global__ __launch_bounds__(64 * NW, 3) void score_mfma_wide_kernel(
 hipError_t launch_score_mfma_wide(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void* q, const void* k,
                                   int64_t ksh, int64_t kst, float c2, float* stats, const float* lse2, float* colsum,
                                   int64_t total, float* probs, int pass, hipStream_t st) {
-  if (s.head_dim != D || p.RB != NRB || p.NW != NW) return hipErrorInvalidValue;
+  if (!p.wide || s.head_dim != D || p.RB != NRB || p.NW != NW) return hipErrorInvalidValue;
   const dim3 g((unsigned)((int64_t)s.n_kv_heads * ceil_div(p.RC, NW) * p.grid_chunks)), blk(64 * NW);
   // dynamic LDS: pass 1 the word of the rerun vote; pass 2 the column sums of the key chunk and the waves' parked sums
   const int ppw = pass == 2 && probs == nullptr ? p.planes : 0, np = ppw * p.split;

@@ -133,3 +133,11 @@ def load_rational_sweep():
         k[0, :, 1] = np.log(np.array(layer["head1_weights"], np.float64))
         qs.append(q); ks.append(k)
     return doc, qs, ks
+
+
+# Scoring calls of more than 128 rows of 128 components whose key chunks are long enough for the kernels of score_mfma_wide.hip, causal
+# or not: (Hq, G, window, lengths, extra elements between key rows).  Rows that fill the four waves, that leave one idle, that leave
+# part of a block; strides.  Chunks of 352 and 416 keys (11 and 13 tiles), the last ones of a sequence ending in tile 3 to 13,
+# full and ragged.
+LONG_CHUNKS = [(40, 1, 64, [6000, 95, 96, 97, 128, 160, 161, 289], 0), (40, 1, 64, [8612, 96, 129, 289], 0), (6, 2, 64, [49998, 70, 1217], 8),
+               (12, 2, 32, [32222, 20001], 0), (17, 1, 8, [84666], 0), (40, 1, 8, [43333], 0), (8, 1, 64, [51109], 0)]

@@ -12,10 +12,13 @@ namespace skv {
 static int g_launches = 0;
 static int32_t g_last_plan[8];
 static int32_t g_last_selection[3];
+static int g_last_wide;
 extern "C" int structkv_stub_launch_count(void) { return g_launches; }
 // RB, NW, KC, planes, stream_k, RC, grid_chunks, path of the latest scoring launch
 extern "C" void structkv_stub_last_plan(int32_t* out) { for (int i = 0; i < 8; ++i) out[i] = g_last_plan[i]; }
 
+// whether that one was for the kernels of score_mfma_wide.hip
+extern "C" int structkv_stub_last_wide(void) { return g_last_wide; }
 // of the latest fused layer step: the form its scoring prepared (-1: none), the form of its selection, whether that also
 // sums the scoring's planes
 extern "C" void structkv_stub_last_selection(int32_t* out) { for (int i = 0; i < 3; ++i) out[i] = g_last_selection[i]; }
@@ -31,6 +34,7 @@ static void keep_plan(const ScorePlan& p) {
   ++g_launches;
   const int32_t plan[8] = {p.RB, p.NW, p.KC, p.planes, p.stream_k, p.RC, (int32_t)p.grid_chunks, p.path};
   for (int i = 0; i < 8; ++i) g_last_plan[i] = plan[i];
+  g_last_wide = p.wide;
 }
 
 // The bins of the mid-sized selection for one centre: how many keys the two directions of the mapping disagree on, how many
@@ -76,6 +80,7 @@ hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, c
   ok = ok && ((p.RB == 2 && p.NW == 4) || (p.RB == 1 && p.NW == 4) || (p.RB == 2 && p.NW == 1) || (p.RB == 1 && p.NW == 1));
   ok = ok && p.RPC == 32 * p.RB && p.R == (s.n_q_heads / s.n_kv_heads) * s.window && p.RC == (p.R + p.RPC - 1) / p.RPC;
   ok = ok && (p.NW == 4 || p.RC == 1);                          // one-wave workgroups hold a KV group's only row-chunk
+  ok = ok && (!p.wide || (p.RB == 2 && p.NW == 4 && s.head_dim == 128));
   const int planes = pass == 2 && probs == nullptr ? p.planes : 0;
   ok = ok && (planes == 0 || planes == 1 || (planes == 2 && p.RB == 2)) && (p.split == 1 || ((p.split == 2 || p.split == 4) && p.planes == p.RB));
   ok = ok && (planes == 0 || p.CP == s.n_q_heads / s.n_kv_heads);

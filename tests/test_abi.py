@@ -349,6 +349,40 @@ def test_tilings_chosen_for_the_named_configurations(B):
     assert p["grid_chunks"] == sum(-(-(n // 2) // p["KC"]) for n in lens) and p["stream_k"] == 0
 
 
+def test_kernel_and_keys_for_more_than_128_rows(B):
+    """Which of the two bf16 kernels a scoring call of more than 128 rows of 128 components takes, and with how many keys per
+    workgroup: the one whose loop starts quickly in short chunks, the one with the cheaper tiles in long ones.  Stub build only."""
+    from helpers import LONG_CHUNKS
+    lib = B._lib
+    if not hasattr(lib, "structkv_stub_last_wide"):
+        pytest.skip("the real library launches kernels; this runs against the stub build only")
+    fake, fake2 = ctypes.c_void_p(1 << 20), ctypes.c_void_p(1 << 21)
+
+    def plan(Hq, G, w, lens, causal, less=0):
+        shape = B.make_shape(Hq, G, 128, w, 1, causal)
+        cu = (ctypes.c_int64 * (len(lens) + 1))(*np.concatenate([[0], np.cumsum(lens)]).tolist())
+        need = B.structkv_workspace_bytes(shape, len(lens), sum(lens)) - less
+        assert lib.structkv_score_layer(ctypes.byref(shape), fake, fake, sum(lens) * 128, 128, len(lens), cu, fake, fake, None,
+                                        fake2, need, None) == B.STRUCTKV_OK, B.structkv_last_error()
+        out = (ctypes.c_int32 * 8)()
+        lib.structkv_stub_last_plan(out)
+        return lib.structkv_stub_last_wide(), out[2]
+
+    for causal in (False, True):
+        for Hq, G, w, lens, _ in LONG_CHUNKS:
+            assert plan(Hq, G, w, lens, causal)[0] == 1, (Hq, G, w, lens, causal)
+        assert plan(32, 8, 64, [131072], causal) == (1, 1376) and plan(32, 8, 64, [1048576], causal) == (1, 2048)
+        # one workgroup a CU with less than 300 keys; two a CU rather than one with 512
+        for n in (2000, 4096, 6143, 8191):
+            assert plan(32, 8, 64, [n], causal)[0] == 0, n
+        assert plan(32, 8, 64, [16383], causal) == (0, 256) and plan(8, 2, 64, [65535], causal) == (0, 256)
+        # a workspace without room for 31 of the 64 chunks' partial results, 24 KB each
+        assert plan(32, 8, 64, [16383], causal, less=31 * 3 * 4 * 32 * 64)[1] == 512
+        # (an empty sequence between others, the largest batch)
+        for lens in ([30000, 0, 20000], [1777] * B.STRUCTKV_MAX_BATCH, [70] * B.STRUCTKV_MAX_BATCH):
+            plan(32, 8, 64, lens, causal)
+
+
 def test_selection_forms_of_a_layer_step(B):
     """Which form a layer step's selection takes by its longest searched prefix, whether the scoring prepares it, and when the
     selection forms the in-degrees itself.  Stub build only."""

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import assert_close_floor, assert_entropy, to_oracle_array
+from helpers import LONG_CHUNKS, assert_close_floor, assert_entropy, to_oracle_array
 
 pytestmark = pytest.mark.gpu
 
@@ -106,9 +106,9 @@ def test_one_scoring_launch_strides_scale_and_batch(sweep_mod, oracle, Hq, G, d,
     _check_scores(sweep_mod, oracle, Hq, G, d, w, dtype, causal, lens, pad, scale)
 
 
-# more than 128 rows of 128 components: sequences around the 32-key tiles, the tiles requested ahead (three), the two of a run and
-# the sums parked (eight); chunks of 64 to 576 keys that end with the sequence, inside a tile and inside a run; rows that fill
-# the four waves, that leave one of them idle, that leave part of a block; strides; the rerun with the running maximum
+# more than 128 rows of 128 components in short key chunks (64 to 416 keys): sequences around the 32-key tiles and the two or three
+# of a whole chunk; rows that fill the four waves, that leave one of them idle, that leave part of a block; strides; the rerun
+# with the running maximum
 @pytest.mark.parametrize("Hq,G,w,lens,pad", [(4, 1, 64, [31, 33, 1, 64, 95, 97, 129, 2049], 0), (8, 8, 130, [33000], 0),
                                              (6, 2, 64, [40000, 70, 1217], 8), (12, 2, 32, [20001, 9000], 0), (40, 1, 8, [33333], 0),
                                              (8, 1, 64, [30000], 0)])
@@ -117,6 +117,15 @@ def test_one_scoring_launch_strides_scale_and_batch(sweep_mod, oracle, Hq, G, d,
 def test_wide_scoring_kernels(sweep_mod, oracle, Hq, G, w, lens, pad, causal, late):
     if causal:
         lens = [n for n in lens if n >= w]
+    _check_scores(sweep_mod, oracle, Hq, G, 128, w, torch.bfloat16, causal, lens, pad=pad, two_pass=True, late=late)
+
+
+# ... and in long ones: the pipelined loop's first and last tiles, its runs of two and the half of one, the tiles requested ahead
+# (three), the sums parked (eight), what it leaves to the plain loop (helpers.LONG_CHUNKS; the host tests hold the plan to it)
+@pytest.mark.parametrize("Hq,G,w,lens,pad", LONG_CHUNKS)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("late", [0.0, 0.4])
+def test_scoring_in_long_key_chunks(sweep_mod, oracle, Hq, G, w, lens, pad, causal, late):
     _check_scores(sweep_mod, oracle, Hq, G, 128, w, torch.bfloat16, causal, lens, pad=pad, two_pass=True, late=late)
 
 
@@ -320,7 +329,8 @@ def test_results_do_not_depend_on_a_larger_workspace(B, dtype, lens):
 # inputs that are not finite: a NaN key makes its whole sequence NaN (in the masked tiles too), a NaN query row reaches
 # the keys that it sees and no others; the sequences beside it are untouched
 @pytest.mark.parametrize("dtype,w,lens", [(torch.float32, 32, [1500, 40]), (torch.float32, 8, [900, 300]), (torch.bfloat16, 8, [3000, 90]),
-                                          (torch.bfloat16, 64, [5000, 64]), (torch.bfloat16, 8, [700, 33]), (torch.bfloat16, 64, [1000, 65])])
+                                          (torch.bfloat16, 64, [5000, 64]), (torch.bfloat16, 8, [700, 33]), (torch.bfloat16, 64, [1000, 65]),
+                                          (torch.bfloat16, 64, [50979, 65])])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 def test_inputs_that_are_not_finite(sweep_mod, oracle, dtype, w, lens, causal, value):
