@@ -141,3 +141,9 @@ def load_rational_sweep():
 # full and ragged.
 LONG_CHUNKS = [(40, 1, 64, [6000, 95, 96, 97, 128, 160, 161, 289], 0), (40, 1, 64, [8612, 96, 129, 289], 0), (6, 2, 64, [49998, 70, 1217], 8),
                (12, 2, 32, [32222, 20001], 0), (17, 1, 8, [84666], 0), (40, 1, 8, [43333], 0), (8, 1, 64, [51109], 0)]
+
+# The same for pivot calls, whose pass 2 keeps one plane per head: (Hq, G, window, length).  Windows of 64 (a wave's rows are a head's),
+# 32, 16 and 8 (two, four and eight heads a wave); last workgroups of a group with idle waves, with part of a wave's heads.  Chunks of
+# 224 to 416 keys (7 to 13 tiles, the last three of a chunk written directly, the others collected in LDS), their last ones ragged.
+LONG_CHUNKS_PIVOT = [(37, 1, 64, 9665), (3, 1, 64, 105236), (45, 1, 32, 13550), (45, 1, 32, 17435), (50, 1, 16, 16658), (34, 2, 16, 82703),
+                     (50, 1, 8, 25019), (50, 1, 8, 98911)]

@@ -352,7 +352,7 @@ def test_tilings_chosen_for_the_named_configurations(B):
 def test_kernel_and_keys_for_more_than_128_rows(B):
     """Which of the two bf16 kernels a scoring call of more than 128 rows of 128 components takes, and with how many keys per
     workgroup: the one whose loop starts quickly in short chunks, the one with the cheaper tiles in long ones.  Stub build only."""
-    from helpers import LONG_CHUNKS
+    from helpers import LONG_CHUNKS, LONG_CHUNKS_PIVOT
     lib = B._lib
     if not hasattr(lib, "structkv_stub_last_wide"):
         pytest.skip("the real library launches kernels; this runs against the stub build only")
@@ -371,6 +371,14 @@ def test_kernel_and_keys_for_more_than_128_rows(B):
     for causal in (False, True):
         for Hq, G, w, lens, _ in LONG_CHUNKS:
             assert plan(Hq, G, w, lens, causal)[0] == 1, (Hq, G, w, lens, causal)
+        for Hq, G, w, n in LONG_CHUNKS_PIVOT:
+            shape = B.make_shape(Hq, G, 128, w, 1, causal)
+            need = B.structkv_pivot_workspace_bytes(shape, n)
+            assert lib.structkv_score_layer_pivot(ctypes.byref(shape), fake, fake, n * 128, 128, 1, (ctypes.c_int64 * 2)(0, n), 0.1, fake, fake,
+                                                  None, fake, fake, fake2, need, None) == B.STRUCTKV_OK, B.structkv_last_error()
+            out = (ctypes.c_int32 * 8)()
+            lib.structkv_stub_last_plan(out)
+            assert lib.structkv_stub_last_wide() == 1 and out[3] > 0 and out[2] >= 224, (Hq, G, w, n, causal)
         assert plan(32, 8, 64, [131072], causal) == (1, 1376) and plan(32, 8, 64, [1048576], causal) == (1, 2048)
         # one workgroup a CU with less than 300 keys; two a CU rather than one with 512
         for n in (2000, 4096, 6143, 8191):

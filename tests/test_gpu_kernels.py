@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import LONG_CHUNKS, assert_close_floor, assert_entropy, to_oracle_array
+from helpers import LONG_CHUNKS, LONG_CHUNKS_PIVOT, assert_close_floor, assert_entropy, to_oracle_array
 
 pytestmark = pytest.mark.gpu
 
@@ -208,14 +208,7 @@ def test_layer_step_selection_forms(sweep_mod, oracle, lens, ks, zero):
     assert np.array_equal(idx, ref)
 
 
-# per-head planes with several heads per 32-row block (windows of 8 and 16): one- and four-wave workgroups, one and two
-# row blocks per wave, groups whose last wave or block is partly empty, chunks of less than the three direct tiles
-@pytest.mark.parametrize("Hq,G,d,w,lens", [(32, 8, 128, 8, [700, 33, 1500]), (4, 4, 64, 8, [40, 300]), (16, 2, 128, 8, [2100]),
-                                           (24, 2, 128, 8, [1000]), (34, 2, 64, 8, [1300, 65]), (32, 8, 128, 16, [999]),
-                                           (5, 1, 128, 16, [513, 97]), (3, 1, 64, 16, [64]), (18, 2, 128, 16, [1111]),
-                                           (10, 2, 128, 32, [1400])])
-@pytest.mark.parametrize("causal", [False, True])
-def test_pivot_metrics_of_short_windows(sweep_mod, oracle, Hq, G, d, w, lens, causal):
+def _check_pivot(sweep_mod, oracle, Hq, G, d, w, lens, causal):
     total = sum(lens)
     sw = sweep_mod.LayerSweep(Hq, G, d, w, torch.bfloat16, lens, [0] * len(lens), causal=causal)
     q = _randn(len(lens), Hq, w, d, dtype=torch.bfloat16, seed=7)
@@ -228,6 +221,25 @@ def test_pivot_metrics_of_short_windows(sweep_mod, oracle, Hq, G, d, w, lens, ca
     assert np.all(np.abs(rho.cpu().numpy()[:len(lens)] - rho_ref) <= 1e-3 * rho_ref)
     # a variance is a sum of squared differences from 1/n: relative to their squares as in the other parity tests
     assert np.all(np.abs(var.cpu().numpy()[:len(lens)] - var_ref) <= 2e-3 * var_ref + 1e-4 / np.array(lens, dtype=np.float64) ** 2)
+
+
+# per-head planes with several heads per 32-row block (windows of 8 and 16): one- and four-wave workgroups, one and two
+# row blocks per wave, groups whose last wave or block is partly empty, chunks of less than the three direct tiles
+@pytest.mark.parametrize("Hq,G,d,w,lens", [(32, 8, 128, 8, [700, 33, 1500]), (4, 4, 64, 8, [40, 300]), (16, 2, 128, 8, [2100]),
+                                           (24, 2, 128, 8, [1000]), (34, 2, 64, 8, [1300, 65]), (32, 8, 128, 16, [999]),
+                                           (5, 1, 128, 16, [513, 97]), (3, 1, 64, 16, [64]), (18, 2, 128, 16, [1111]),
+                                           (10, 2, 128, 32, [1400])])
+@pytest.mark.parametrize("causal", [False, True])
+def test_pivot_metrics_of_short_windows(sweep_mod, oracle, Hq, G, d, w, lens, causal):
+    _check_pivot(sweep_mod, oracle, Hq, G, d, w, lens, causal)
+
+
+# ... in long key chunks of more than 128 rows: the pipelined loop with planes, what it collects in LDS and what it writes directly
+# (helpers.LONG_CHUNKS_PIVOT; the host tests hold the plan to it)
+@pytest.mark.parametrize("Hq,G,w,n", LONG_CHUNKS_PIVOT)
+@pytest.mark.parametrize("causal", [False, True])
+def test_pivot_metrics_in_long_key_chunks(sweep_mod, oracle, Hq, G, w, n, causal):
+    _check_pivot(sweep_mod, oracle, Hq, G, 128, w, [n], causal)
 
 
 # the top-k mass of the per-head rows: shares of 4096 scores and their remainders; scores within a few per cent (the fine bins),
