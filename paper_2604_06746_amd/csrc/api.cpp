@@ -1032,7 +1032,7 @@ static structkv_status pivot_impl(const structkv_shape* shape, const void* q_win
     if (kk < 1) kk = 1;
     if (kk > n) kk = n;
     // (the planes path keeps its partial sums where the other path keeps indices: Hq x n words)
-    if (n > 0 && from_planes && 2 * ceil_div(n, 2048) + 4 <= n && n <= ((int64_t)1 << 24)) {
+    if (n > 0 && from_planes && 2 * (int64_t)pivot_shares(n) + 2 <= n && n <= ((int64_t)1 << 24)) {
       // selection scratch for the Hq heads as "sequences" of one call; its histograms are cleared by the
       // scoring call's combine kernel and their first digit is filled by the kernel that forms the variance
       SeqTable hseq;
@@ -1059,9 +1059,10 @@ static structkv_status pivot_impl(const structkv_shape* shape, const void* q_win
                             entropy_head_out ? entropy_head_out + (size_t)b * Hq : ent_h, w8 + c.off_score_ws,
                             c.score_ws_bytes, stream, o);
       if (st != STRUCTKV_OK) return st;
+      const uint32_t at = row_bins_of(w, n);
       // (red.colsum: [Hq][n], plane g*gs + hl is head h; the other path's per-head in-degrees hold the candidate lists here)
-      SKV_HIP_CHECK(launch_pivot_planes(red, tws.hist, var_part, hs));
-      SKV_HIP_CHECK(launch_pivot_mass(red, (uint32_t)kk, tws.hist, tws.state, heads, part_above, var_part, sums,
+      SKV_HIP_CHECK(launch_pivot_planes(red, at, tws.hist, var_part, hs));
+      SKV_HIP_CHECK(launch_pivot_mass(red, (uint32_t)kk, at, tws.hist, tws.state, heads, part_above, var_part, sums,
                                       sparsity_out + b, variance_out + b, hs));
       continue;
     }

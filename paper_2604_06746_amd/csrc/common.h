@@ -234,6 +234,14 @@ __host__ __device__ inline uint32_t row_bin(uint32_t key, uint32_t at) {
   if (o < at) return o - 1024u;
   return o - at < kRowSplit ? (key >> kRowInnerShift) - (at << shift) + (at - 1024u) : o - 1024u + kRowExtra;
 }
+// the same for the rows of a call: in-degrees that add up to w over n keys.  Computed once, on the host, and handed to the three
+// kernels that have to agree on the bins.
+inline uint32_t row_bins_of(int w, int64_t n) {
+  const float mean = (float)w / (float)n;
+  uint32_t bits;
+  __builtin_memcpy(&bits, &mean, sizeof(bits));
+  return row_bins_at(bits | 0x80000000u);   // (score_key of a positive number)
+}
 // first key of a bin, and the bits that tell its keys apart
 __host__ __device__ inline void row_bin_range(uint32_t bin, uint32_t at, uint32_t* lo, uint32_t* width) {
   const uint32_t in = bin - (at - 1024u);
@@ -376,13 +384,13 @@ hipError_t launch_pivot_finish(const float* part, int H, int64_t n, float inv_w,
                                float* variance, hipStream_t st);
 // pivot metrics from the hot path's own scoring, whose pass 2 leaves the per-head in-degrees [H][n] in its column-sum planes
 // (red.colsum): the reduce kernel's work for the layer, histograms hist [H][kRowWords] (cleared before) and variance partials
-// var_part [H][pivot_shares(n)]; then the mass of each row's kk largest and the means over the heads.  cand: H x n floats,
-// part_above: H x pivot_shares(n), state: [H][4], sums: [H][2]
+// var_part [H][pivot_shares(n)]; then the mass of each row's kk largest and the means over the heads.  at: row_bins_of(w, n), the same
+// for both; cand: H x n floats, part_above: H x pivot_shares(n), state: [H][4], sums: [H][2]
 constexpr int kPivotShare = 4096;
 inline int pivot_shares(int64_t n) { return (int)((n + kPivotShare - 1) / kPivotShare); }
-hipError_t launch_pivot_planes(const ReduceWork& red, uint32_t* hist, float* var_part, hipStream_t st);
-hipError_t launch_pivot_mass(const ReduceWork& red, uint32_t kk, uint32_t* hist, uint32_t* state, float* cand, float* part_above,
-                             const float* var_part, float* sums, float* sparsity, float* variance, hipStream_t st);
+hipError_t launch_pivot_planes(const ReduceWork& red, uint32_t at, uint32_t* hist, float* var_part, hipStream_t st);
+hipError_t launch_pivot_mass(const ReduceWork& red, uint32_t kk, uint32_t at, uint32_t* hist, uint32_t* state, float* cand,
+                             float* part_above, const float* var_part, float* sums, float* sparsity, float* variance, hipStream_t st);
 hipError_t launch_block_scores(const float* scores, const SeqTable& seq, int block, float* out, hipStream_t st);
 hipError_t launch_positions(const int64_t* pos_src, const SeqTable& seq, const int32_t* idx, int64_t* pos_dst,
                             hipStream_t st);

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void pivot_head_kernel(const float* __restrict
 // 18.4 -> 9.6 us (the 16.8 MB of planes read twice, the second time from the caches), 32K 8.0 -> 4.3 us.
 constexpr int kPlaneThreads = 512;
 
-__global__ __launch_bounds__(kPlaneThreads) void pivot_planes_kernel(ReduceWork rw, int reduce_wgs, int shares,
+__global__ __launch_bounds__(kPlaneThreads) void pivot_planes_kernel(ReduceWork rw, int reduce_wgs, int shares, uint32_t at,
                                                                      uint32_t* __restrict__ hist, float* __restrict__ part) {
   short_kernel_priority();
   constexpr int NT = kPlaneThreads, PER = kPivotShare / NT;
@@ -106,7 +106,6 @@ __global__ __launch_bounds__(kPlaneThreads) void pivot_planes_kernel(ReduceWork 
   for (int i = threadIdx.x; i < kTopkBins; i += NT) h0[i] = 0u;
   __syncthreads();
   const float mean = 1.0f / (float)n, inv_w = 1.0f / (float)rw.w;
-  const uint32_t at = row_bins_at(score_key((float)rw.w / (float)n));
   float v = 0.f;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
@@ -187,11 +186,11 @@ hipError_t launch_pivot_finish(const float* part, int H, int64_t n, float inv_w,
   return hipGetLastError();
 }
 
-hipError_t launch_pivot_planes(const ReduceWork& red, uint32_t* hist, float* var_part, hipStream_t st) {
+hipError_t launch_pivot_planes(const ReduceWork& red, uint32_t at, uint32_t* hist, float* var_part, hipStream_t st) {
   const int64_t reduce_wgs = ceil_div(red.total, kPlaneThreads);
   const int shares = pivot_shares(red.total);
   hipLaunchKernelGGL(pivot_planes_kernel, dim3((unsigned)(1 + reduce_wgs + (int64_t)red.Hq * shares)), dim3(kPlaneThreads), 0, st,
-                     red, (int)reduce_wgs, shares, hist, var_part);
+                     red, (int)reduce_wgs, shares, at, hist, var_part);
   return hipGetLastError();
 }
 

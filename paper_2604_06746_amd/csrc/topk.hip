@@ -935,7 +935,7 @@ constexpr int kCandPerThread = 32;            // candidates one of its threads k
 constexpr int kFewPerThread = 2;              // ... where no thread has more
 
 __global__ __launch_bounds__(kCompThreads) void mass_compact_kernel(const float* __restrict__ rows, int64_t n, uint32_t kk,
-                                                                    float mean, uint32_t* __restrict__ hist,
+                                                                    uint32_t at, uint32_t* __restrict__ hist,
                                                                     uint32_t* __restrict__ state, float* __restrict__ cand,
                                                                     float* __restrict__ part_above) {
   short_kernel_priority();
@@ -956,7 +956,6 @@ __global__ __launch_bounds__(kCompThreads) void mass_compact_kernel(const float*
   }
   if (t == 0) cnt = 0u;
   uint32_t* gh = hist + (size_t)h * kRowWords;
-  const uint32_t at = row_bins_at(score_key(mean));
   uint32_t t0, above0;
   select_bin<NT, kBins>(gh, kk, scan, res, &t0, &above0);   // its barriers cover cnt = 0
   float sum = 0.f;
@@ -1038,7 +1037,7 @@ __device__ inline unsigned long long resolve_row(const float* __restrict__ c, ui
   return acc;
 }
 
-__global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* __restrict__ cand, int64_t n, int w,
+__global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* __restrict__ cand, int64_t n, int w, uint32_t at,
                                                                   uint32_t* __restrict__ hist,
                                                                   const uint32_t* __restrict__ state,
                                                                   const float* __restrict__ part_above,
@@ -1061,7 +1060,7 @@ __global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* _
   float pa = 0.f, pv = 0.f;
   for (int p = t; p < P; p += NT) { pa += part_above[(int64_t)h * P + p]; pv += var_part[(int64_t)h * P + p]; }
   uint32_t T, bits;
-  row_bin_range(bin, row_bins_at(score_key((float)w / (float)n)), &T, &bits);
+  row_bin_range(bin, at, &T, &bits);
   // few candidates: no long row of steps that find nothing (32K tokens, window 8: 10.2 us without, 6.9 with;
   // 128K, window 64: 12.5 and 8.5)
   unsigned long long acc = c0 <= (uint32_t)(kFewPerThread * NT) ? resolve_row<kFewPerThread>(c, c0, bits, hh, scan, res, T, krem)
@@ -1221,12 +1220,12 @@ hipError_t launch_topk_rest(const float* scores, const SeqTable& plan, int keep_
   return hipGetLastError();
 }
 
-hipError_t launch_pivot_mass(const ReduceWork& red, uint32_t kk, uint32_t* hist, uint32_t* state, float* cand, float* part_above,
-                             const float* var_part, float* sums, float* sparsity, float* variance, hipStream_t st) {
+hipError_t launch_pivot_mass(const ReduceWork& red, uint32_t kk, uint32_t at, uint32_t* hist, uint32_t* state, float* cand,
+                             float* part_above, const float* var_part, float* sums, float* sparsity, float* variance, hipStream_t st) {
   const int P = pivot_shares(red.total);
   hipLaunchKernelGGL(mass_compact_kernel, dim3((unsigned)P, (unsigned)red.Hq), dim3(kCompThreads), 0, st, red.colsum, red.total, kk,
-                     (float)red.w / (float)red.total, hist, state, cand, part_above);
-  hipLaunchKernelGGL(mass_select_kernel, dim3((unsigned)red.Hq), dim3(kSelThreads), 0, st, cand, red.total, red.w, hist, state,
+                     at, hist, state, cand, part_above);
+  hipLaunchKernelGGL(mass_select_kernel, dim3((unsigned)red.Hq), dim3(kSelThreads), 0, st, cand, red.total, red.w, at, hist, state,
                      part_above, var_part, P, sums, sparsity, variance);
   return hipGetLastError();
 }

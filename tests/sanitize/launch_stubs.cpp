@@ -157,14 +157,20 @@ hipError_t topk_static_scratch(void** ptr, size_t* bytes) {
   *bytes = sizeof(host_stand_in);
   return hipSuccess;
 }
-hipError_t launch_pivot_planes(const ReduceWork& r, uint32_t* hist, float* var_part, hipStream_t) {
+static uint32_t g_row_bins_at;
+hipError_t launch_pivot_planes(const ReduceWork& r, uint32_t at, uint32_t* hist, float* var_part, hipStream_t) {
   ++g_launches;
-  return r.colsum && r.planes == r.Hq && r.Hq <= kMaxBatch && hist && var_part ? hipSuccess : hipErrorInvalidValue;
+  g_row_bins_at = at;
+  return r.colsum && r.planes == r.Hq && r.Hq <= kMaxBatch && hist && var_part && at == row_bins_of(r.w, r.total) ? hipSuccess : hipErrorInvalidValue;
 }
-hipError_t launch_pivot_mass(const ReduceWork& r, uint32_t kk, uint32_t*, uint32_t*, float*, float*, const float*, float*, float*,
-                             float*, hipStream_t) {
+// all buffers lie behind each other: the partial sums in Hq x n words (var_part, part_above, sums), the kernels on the same bins
+hipError_t launch_pivot_mass(const ReduceWork& r, uint32_t kk, uint32_t at, uint32_t*, uint32_t*, float*, float* part_above, const float* var_part,
+                             float* sums, float*, float*, hipStream_t) {
   ++g_launches;
-  return kk >= 1 && kk <= r.total && r.total <= ((int64_t)1 << 24) ? hipSuccess : hipErrorInvalidValue;
+  const int64_t parts = (int64_t)r.Hq * pivot_shares(r.total);
+  bool ok = kk >= 1 && kk <= r.total && r.total <= ((int64_t)1 << 24) && at == g_row_bins_at;
+  ok = ok && part_above - var_part == parts && sums - part_above == parts && (sums - var_part) + 2 * r.Hq <= r.Hq * r.total;
+  return ok ? hipSuccess : hipErrorInvalidValue;
 }
 hipError_t launch_pivot_heads(const float*, int, int64_t, const int32_t*, int64_t, float, float*, hipStream_t) {
   ++g_launches; return hipSuccess;

@@ -445,6 +445,22 @@ def test_bins_of_the_mid_sized_selection(B, centre):
     assert B._lib.structkv_stub_bin_faults(ctypes.c_uint32(centre)) == 0
 
 
+def test_pivot_call_hands_its_kernels_the_same_bins_and_room(B):
+    """The three kernels behind a pivot call's scoring get one and the same position of the fine bins, and their partial sums fit
+    the words that are free for them, from the shortest sequence that goes this way on (the launcher stubs check both).
+    Stub build only."""
+    lib = B._lib
+    if not hasattr(lib, "structkv_stub_launch_count"):
+        pytest.skip("the real library launches kernels; this runs against the stub build only")
+    fake, fake2 = ctypes.c_void_p(1 << 20), ctypes.c_void_p(1 << 21)
+    for Hq, G, w in [(4, 2, 32), (64, 8, 64), (32, 8, 8), (16, 1, 16)]:
+        for n in list(range(1, 10)) + [w, 4095, 4096, 4097, 8193, 131072, (1 << 24), (1 << 24) + 1]:
+            shape = B.make_shape(Hq, G, 128, w, 1, False)
+            need = B.structkv_pivot_workspace_bytes(shape, n)
+            assert lib.structkv_score_layer_pivot(ctypes.byref(shape), fake, fake, n * 128, 128, 1, (ctypes.c_int64 * 2)(0, n), 0.1, fake, fake,
+                                                  None, fake, fake, fake2, need, None) == B.STRUCTKV_OK, (Hq, w, n, B.structkv_last_error())
+
+
 @pytest.mark.parametrize("centre", [0x80000000, 0x80000001, 0x88000000, 0xB4800000, 0xB8000001, 0xBF800000, 0xC2800000, 0xFC000000,
                                     0xFFFFFFFF])
 def test_bins_of_the_pivot_rows(B, centre):

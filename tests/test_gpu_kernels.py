@@ -224,13 +224,16 @@ def _check_pivot(sweep_mod, oracle, Hq, G, d, w, lens, causal):
 
 
 # per-head planes with several heads per 32-row block (windows of 8 and 16): one- and four-wave workgroups, one and two
-# row blocks per wave, groups whose last wave or block is partly empty, chunks of less than the three direct tiles
+# row blocks per wave, groups whose last wave or block is partly empty, chunks of less than the three direct tiles, sequences of a few tokens
+# (from four on the metrics come from the planes)
 @pytest.mark.parametrize("Hq,G,d,w,lens", [(32, 8, 128, 8, [700, 33, 1500]), (4, 4, 64, 8, [40, 300]), (16, 2, 128, 8, [2100]),
                                            (24, 2, 128, 8, [1000]), (34, 2, 64, 8, [1300, 65]), (32, 8, 128, 16, [999]),
                                            (5, 1, 128, 16, [513, 97]), (3, 1, 64, 16, [64]), (18, 2, 128, 16, [1111]),
-                                           (10, 2, 128, 32, [1400])])
+                                           (10, 2, 128, 32, [1400]), (4, 2, 128, 32, [3, 4, 5, 6, 7]), (24, 2, 128, 8, [4, 5, 9])])
 @pytest.mark.parametrize("causal", [False, True])
 def test_pivot_metrics_of_short_windows(sweep_mod, oracle, Hq, G, d, w, lens, causal):
+    if causal:
+        lens = [max(n, w) for n in lens]
     _check_pivot(sweep_mod, oracle, Hq, G, d, w, lens, causal)
 
 
