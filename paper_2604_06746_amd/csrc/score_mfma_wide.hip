@@ -425,8 +425,7 @@ __global__ __launch_bounds__(64 * NW, 3) void score_mfma_wide_kernel(
   floatx4 acc[2][4];
   // one tile with everything it can need, by itself
   auto tile_any = [&](int s) __attribute__((always_inline)) {
-    if (ready <= s) { tile_ready_any(s); ready = s + 1; }
-    else barrier();   // (behind the loop: the sums that it added up last were read from the slot that this tile's go to)
+    if (ready <= s) { tile_ready_any(s); ready = s + 1; }   // (else pass 1 behind the loop, whose last step has)
     for (; unflushed + 2 <= s; ++unflushed)   // (parked before the barrier above)
       if (wave == unflushed % NW) flush_colsum(unflushed);
     read_tile(s);
