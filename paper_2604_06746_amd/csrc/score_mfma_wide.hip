@@ -2,7 +2,7 @@
 // shape) in long key chunks (the plan says from where on; shorter ones stay with score_mfma_ring.hip), paper Eq. 1, Eq. 2,
 // Eq. 4.  The work of a workgroup -- four waves of 64 rows that share 32-key tiles in an LDS ring, a key chunk, its partial
 // statistics or column sums -- is that of score_mfma_ring.hip, whose plan, partial results and column-sum planes these kernels
-// share; what differs is the loop.
+// share; what differs is the loop.  The order of requests, waits and tiles is score_schedule.h's.
 //
 // What bounds these shapes is power, and the issue port at the clock that the chip then grants: a loop of nothing but this
 // softmax and these MFMAs on N(0,1) data runs at 1.7 GHz with v_mfma_f32_32x32x16_bf16 and at 2.05 GHz with
@@ -19,9 +19,8 @@
 // 32 heads on 8, window 64, back to back, against 32 x 32 x 16 with the masks in the loop and only the MFMAs of a tile's
 // second row block under the softmax of its first: 128K tokens pass 1 83.8 -> 82.6 us, pass 2 80.2 -> 79.0 us (one round of
 // workgroups, of which start and end are a sixth); 1M tokens 625 -> 605 and 590 -> 560 us.
-#include "common.h"
+#include "score_schedule.h"
 
-#include <type_traits>
 #include <utility>
 
 namespace skv {
@@ -32,7 +31,6 @@ typedef __attribute__((ext_vector_type(4))) float floatx4;
 
 constexpr float kNegBig = -1.0e30f;
 
-template <int V> using IntC = std::integral_constant<int, V>;
 // f(IntC<0>{}), f(IntC<1>{}), ... f(IntC<N - 1>{})
 template <class F, int... I>
 __device__ __forceinline__ void static_for_seq(F f, std::integer_sequence<int, I...>) { (f(IntC<I>{}), ...); }
@@ -117,6 +115,7 @@ __global__ __launch_bounds__(64 * NW, 3) void score_mfma_wide_kernel(
   const int key_end = min(ni, key0 + KC);
   const int n_full = causal ? ni - w : ni;   // keys below n_full are visible to every row
   const int nsub = (key_end - key0 + 31) / 32;
+  const TileChunk<PASS> chunk_tiles{key0, nsub, ni, n_full, causal};
 
   // ---- the row-chunk's queries as MFMA operands (registers, whole kernel) ----
   // piece p of block rb: row 16 (p / 4) + l16 of it, components 32 (p % 4) + 8 lg on (keys the same way)
@@ -139,8 +138,7 @@ __global__ __launch_bounds__(64 * NW, 3) void score_mfma_wide_kernel(
   }
 
   const uint16_t* kg = k + (int64_t)(g / kshare) * ksh + tok0 * kst;
-  // Pass 1 goes through the chunk's tiles forwards, pass 2 backwards (what pass 1 left in L2 is the end of every chunk)
-  auto tile_key = [&](int s) __attribute__((always_inline)) { return key0 + 32 * (PASS == 2 ? nsub - 1 - s : s); };
+  auto tile_key = [&](int s) __attribute__((always_inline)) { return chunk_tiles.key(s); };
   // Tile layout in LDS: 16-byte piece (key, seg) sits at unit key*SEGS + (seg ^ (key % 16)); any 16
   // consecutive keys at a fixed seg then hit 16 different groups of 4 banks (conflict-free operand reads).
   // Loader: instruction I, lane L writes unit I*64 + L, so it must fetch that unit's (key, seg).
@@ -157,13 +155,13 @@ __global__ __launch_bounds__(64 * NW, 3) void score_mfma_wide_kernel(
     asm volatile("" : "+v"(voff));   // opaque: 32 bits beside a scalar base, not a 64-bit pair kept across the loop
     __builtin_amdgcn_global_load_lds((gbl_ptr_t)(next + voff), (lds_ptr_t)slot, 16, 0, NT ? 2 : 0);
     __builtin_amdgcn_global_load_lds((gbl_ptr_t)(next + half_tile + voff), (lds_ptr_t)(slot + NW * 1024), 16, 0, NT ? 2 : 0);
-    if (s + 1 < nsub) next += tile_stride;
+    if (chunk_tiles.more(s)) next += tile_stride;
   };
   // (the lane number is opaque where the rarer code forms something from it: nothing of that stays in registers across the loop)
   auto opaque_lane = [&]() __attribute__((always_inline)) { int l = lane; asm volatile("" : "+v"(l)); return l; };
   auto issue_tile = [&](int s) __attribute__((always_inline)) {
     const int jbase = tile_key(s);
-    if (jbase + 32 <= ni) { issue_full(s); return; }
+    if (chunk_tiles.whole(s)) { issue_full(s); return; }
     // ragged tail: rows past the end re-read the last valid row (their logits are masked)
     uint8_t* slot = ring + (s % NBUF) * TILE_BYTES + wave * 1024;
     const int l = opaque_lane();
@@ -174,7 +172,7 @@ __global__ __launch_bounds__(64 * NW, 3) void score_mfma_wide_kernel(
       __builtin_amdgcn_global_load_lds((gbl_ptr_t)(next + (uint32_t)(min(key, ni - 1 - jbase) * kst + seg * 8) * 2u),
                                        (lds_ptr_t)(slot + ii * NW * 1024), 16, 0, NT ? 2 : 0);
     }
-    if (s + 1 < nsub) next += tile_stride;
+    if (chunk_tiles.more(s)) next += tile_stride;
   };
   // the first tiles are requested under the query operands' latency
   auto issue_first = [&]() __attribute__((always_inline)) {
@@ -396,99 +394,56 @@ __global__ __launch_bounds__(64 * NW, 3) void score_mfma_wide_kernel(
     }
   };
 
-  // Tile s ready: my share of it has landed when at most the later requests (PD-1 tiles) are outstanding, and my reads of
-  // tile s-1 are done; then the barrier: a plain s_barrier, not __syncthreads(), whose fence waits for ALL outstanding loads
-  // and would drain the ring.  After it everybody's share of tile s is in LDS (each wave waited for its own loads) and
-  // everybody is done reading tile s-1's slot, which the next request overwrites.
+  int unflushed = 0;   // pass 2: the first tile whose parked sums have not been added up
+  floatx4 acc[2][4];
+  auto wait = [&](auto later) __attribute__((always_inline)) { wait_loads_lds<decltype(later)::value * IPW>(); };
+  // a plain s_barrier, not __syncthreads(), whose fence waits for ALL outstanding loads and would drain the ring
   auto barrier = [&]() __attribute__((always_inline)) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  auto tile_ready_any = [&](int s) __attribute__((always_inline)) {
-    const int later = min(PD - 1, nsub - 1 - s);
-    if (later >= 2) wait_loads_lds<2 * IPW>();
-    else if (later == 1) wait_loads_lds<IPW>();
-    else wait_loads_lds<0>();
-    barrier();
-    if (s + PD < nsub) issue_tile(s + PD);
-  };
-  // inside the loop: always one request, past the chunk's end the last tile again (nobody reads it; it keeps the count of
-  // outstanding loads, and with it the step, free of conditions)
-  auto tile_ready = [&](int s) __attribute__((always_inline)) {
-    wait_loads_lds<(PD - 1) * IPW>();
-    barrier();
-    issue_full(s + PD);
-  };
-  int ready = 0;       // tiles made ready
-  int unflushed = 0;   // pass 2: the first tile whose parked sums have not been added up
-  floatx4 acc[2][4];
-  // one tile with everything it can need, by itself
-  auto tile_any = [&](int s) __attribute__((always_inline)) {
-    if (ready <= s) { tile_ready_any(s); ready = s + 1; }   // (else pass 1 behind the loop, whose last step has)
-    for (; unflushed + 2 <= s; ++unflushed)   // (parked before the barrier above)
-      if (wave == unflushed % NW) flush_colsum(unflushed);
-    read_tile(s);
-    static_for<NRB>([&](auto rb) __attribute__((always_inline)) { unit_mfmas(acc[0], rb); softmax_any(acc[0], rb, tile_key(s)); });
-    park_colsum(s);
-  };
   // The loop's step: one tile that every row sees whole, software-pipelined over its units: the MFMAs of a unit run under the
-  // softmax of the unit before, and the first unit of the tile was computed in the step before.
-  auto tile_step = [&](int s) __attribute__((always_inline)) {
+  // softmax of the unit before, and the first unit of the tile was computed in the step before, or by this:
+  auto begin = [&](int s) __attribute__((always_inline)) {
+    read_tile(s);
+    unit_mfmas(acc[0], IntC<0>{});
+    if (PASS == 1 && s == 0) {   // the first keys set the reference
+      unit_mfmas(acc[1], IntC<1>{});
+#pragma unroll
+      for (int t = 0; t < NST; ++t) {
+        float mx = acc[t / 2][t % 2][0];
+#pragma unroll
+        for (int i = 1; i < 8; ++i) mx = fmaxf(mx, acc[t / 2][t % 2 + i / 4 * 2][i % 4]);
+        M[t] = mx * c2;
+      }
+    }
+  };
+  auto step = [&](int s) __attribute__((always_inline)) {
     const int in = (s + 1) % NBUF;
     asm volatile("" : "+v"(piece0));   // opaque: one register across the loop, not four
     auto read = [&](auto m_tag) __attribute__((always_inline)) {   // (behind the second of the two MFMAs that use a piece)
       constexpr int m = decltype(m_tag)::value;
       if constexpr (m % 2 == 1) read_piece(in, IntC<4 * (m / 2 % 2) + m / 4>{});
     };
-    tile_ready(s + 1);
     unit_step(acc[1], IntC<1>{}, acc[0], IntC<0>{}, read);
     unit_step(acc[0], IntC<0>{}, acc[1], IntC<1>{}, [](auto) __attribute__((always_inline)) {});
     if constexpr (PASS == 1) {   // (computed here and not, all of it, behind the loop, where it is next needed)
 #pragma unroll
       for (int i = 0; i < NST; ++i) asm volatile("" : "+v"(Z[i]), "+v"(E[i]));
     }
-    park_colsum(s);
   };
-  // whether the step can take the `count` tiles from s on: they exist, every row sees them whole, and what is requested meanwhile
-  // is whole, too
-  auto clean = [&](int s, int count) __attribute__((always_inline)) {
-    if (DUMP || s + count > nsub) return false;
-    if (PASS == 2) return !causal || tile_key(s) + 32 <= n_full;
-    return tile_key(s + count - 1) + 32 <= n_full && tile_key(min(s + count + PD, nsub - 1)) + 32 <= ni;
+  // one tile with everything it can need, by itself
+  auto any = [&](int s) __attribute__((always_inline)) {
+    read_tile(s);
+    static_for<NRB>([&](auto rb) __attribute__((always_inline)) { unit_mfmas(acc[0], rb); softmax_any(acc[0], rb, tile_key(s)); });
   };
-  // the whole key chunk, its first PD tiles already requested
+  auto add_one = [&](int s) __attribute__((always_inline)) { if (wave == s % NW) flush_colsum(s); };
+  auto add_each = [&](int s) __attribute__((always_inline)) { flush_colsum(s + wave); };
+  auto ops = chunk_ops(wait, barrier, issue_tile, issue_full, begin, step, any, park_colsum, add_one, add_each);
+  // the whole key chunk, its first PD tiles already requested (the attention rows themselves only come out of the plain tiles)
   auto run_chunk = [&](bool fast) __attribute__((always_inline)) {
-    constexpr int GROUP = 2;   // tiles of one run
-    ready = 0;
-    for (int s = 0; s < nsub;) {
-      if (fast && s + PD <= nsub && clean(s, GROUP)) {   // (PD requests are outstanding)
-        if (ready <= s) tile_ready(s);
-        read_tile(s);
-        unit_mfmas(acc[0], IntC<0>{});
-        if (PASS == 1 && s == 0) {   // the first keys set the reference
-          unit_mfmas(acc[1], IntC<1>{});
-#pragma unroll
-          for (int t = 0; t < NST; ++t) {
-            float mx = acc[t / 2][t % 2][0];
-#pragma unroll
-            for (int i = 1; i < 8; ++i) mx = fmaxf(mx, acc[t / 2][t % 2 + i / 4 * 2][i % 4]);
-            M[t] = mx * c2;
-          }
-        }
-        do {   // one straight run of instructions
-          static_for<GROUP>([&](auto i) __attribute__((always_inline)) { tile_step(s + decltype(i)::value); });
-          s += GROUP;
-          if (PASS == 2 && !PLANES && s >= unflushed + NW + 1) { flush_colsum(unflushed + wave); unflushed += NW; }
-        } while (clean(s, GROUP));
-        if (clean(s, 1)) { tile_step(s); ++s; }   // (half of another run)
-        ready = s + 1;
-      } else {
-        tile_any(s);
-        ++s;
-      }
-    }
-    wait_loads_lds<0>();   // (the requests past the chunk's end)
+    go_through_chunk<PD, NW, PASS == 2 && !PLANES>(chunk_tiles, fast && !DUMP, unflushed, ops);
   };
   if constexpr (PASS == 1) {
     // Fast run with the fixed reference; then a workgroup-wide vote (every wave has to take part in a rerun:

@@ -5,7 +5,9 @@
 // kernels also check the plan they are handed against what those kernels assume about it (tilings that are
 // instantiated, key chunks within the LDS capacity, chunk bookkeeping) and keep it for the tests to look at, and those of
 // the selection follow its forms by length.
-#include "../../paper_2604_06746_amd/csrc/common.h"
+#include "../../paper_2604_06746_amd/csrc/score_schedule.h"
+
+#include <deque>
 
 namespace skv {
 
@@ -69,6 +71,93 @@ extern "C" int structkv_stub_row_bin_faults(uint32_t centre) {
     next = hi + 1;
   }
   return bad + (next != 0);
+}
+
+// score_mfma_wide.hip's way through a key chunk, run against a model of one wave's requests, the LDS ring and the slots for parked
+// sums.  All waves run the same program, so what one of them has done before a barrier all have; what lies between two barriers
+// is in no order between the waves.  Counts what would be a fault: rows outside the sequence requested, a slot requested while some wave
+// may still read it, a tile read before it has landed for everybody, sums parked over others that were not added up or may still be
+// read, sums added up before every wave has parked them; tiles left out, taken twice or by a loop that cannot mask.
+template <int PASS>
+struct RingModel {
+  static constexpr int NBUF = 4, PARKED = 8;
+  struct Parked { int tile = -1; bool added = true; int at = -1; };
+  TileChunk<PASS> c;
+  bool parks;
+  int faults = 0, barriers = 0, next = 0, computed = 0, added = 0;
+  struct Request { int tile, slot; };
+  std::deque<Request> out, waited;        // not waited for, oldest first; waited for by this wave, but not yet behind a barrier
+  int content[NBUF], read_at[NBUF];       // tile that has landed for everybody (-1: unknown); barrier count of the slot's last read
+  Parked parked[PARKED];
+  RingModel(const TileChunk<PASS>& chunk, bool p) : c(chunk), parks(p) {
+    for (int i = 0; i < NBUF; ++i) { content[i] = -1; read_at[i] = -1; }
+  }
+  void check(bool ok) { faults += !ok; }
+  void request(int s, bool whole) {
+    const int tile = next;                // (the kernel's pointer to the next tile's first row)
+    check(tile >= 0 && tile < c.nsub && c.key(tile) >= c.key0 && (whole ? c.whole(tile) : c.key(tile) < c.ni));
+    check(read_at[s % NBUF] < barriers);
+    content[s % NBUF] = -1;
+    out.push_back({tile, s % NBUF});
+    if (c.more(s)) ++next;
+  }
+  void request_any(int s) { check(next == s); request(s, c.whole(s)); }
+  void wait(int tiles) { while ((int)out.size() > tiles) { waited.push_back(out.front()); out.pop_front(); } }
+  void barrier() {
+    ++barriers;
+    for (const Request& r : waited) content[r.slot] = r.tile;
+    waited.clear();
+  }
+  void read(int s) {
+    if (s < c.nsub) check(content[s % NBUF] == s);
+    read_at[s % NBUF] = barriers;
+  }
+  void compute(int s, bool masks) {
+    check(s == computed++);
+    const bool visible = c.key(s) + 32 <= c.n_full;
+    check(masks || visible || (PASS == 2 && !c.causal));   // (pass 2 writes no key past the sequence's end)
+  }
+  void park(int s) {
+    if (!parks) return;
+    Parked& p = parked[s % PARKED];
+    check(p.added && p.at < barriers);
+    p = {s, false, barriers};
+  }
+  void add(int s) {
+    Parked& p = parked[s % PARKED];
+    check(p.tile == s && !p.added && p.at < barriers);
+    p.added = true;
+    p.at = barriers;
+    ++added;
+  }
+  int run(bool fast) {
+    constexpr int PD = NBUF - 1, NW = 4;
+    int unflushed = 0;
+    for (int s = 0; s < PD && s < c.nsub; ++s) request_any(s);
+    auto ops = chunk_ops([&](auto n) { wait(decltype(n)::value); }, [&]() { barrier(); }, [&](int s) { request_any(s); },
+                         [&](int s) { request(s, true); }, [&](int s) { read(s); }, [&](int s) { compute(s, false); read(s + 1); },
+                         [&](int s) { read(s); compute(s, true); }, [&](int s) { park(s); }, [&](int s) { add(s); },
+                         [&](int s) { for (int i = 0; i < NW; ++i) add(s + i); });
+    if (parks) go_through_chunk<PD, NW, PASS == 2>(c, fast, unflushed, ops);
+    else go_through_chunk<PD, NW, false>(c, fast, unflushed, ops);
+    check(computed == c.nsub && out.empty());
+    if (parks) {
+      barrier();
+      for (int s = unflushed; s < c.nsub; ++s) add(s);
+      check(added == c.nsub);
+    }
+    return faults;
+  }
+};
+// faults of both passes over one key chunk: keys of the sequence, the chunk's first key, most keys of a chunk, causal window or 0
+extern "C" int structkv_stub_chunk_faults(int ni, int key0, int kc, int window) {
+  const int key_end = ni < key0 + kc ? ni : key0 + kc, nsub = (key_end - key0 + 31) / 32, n_full = ni - window, causal = window > 0;
+  int faults = 0;
+  for (int fast = 0; fast < 2; ++fast) {
+    faults += RingModel<1>({key0, nsub, ni, n_full, causal}, false).run(fast);
+    for (int parks = 0; parks < 2; ++parks) faults += RingModel<2>({key0, nsub, ni, n_full, causal}, parks).run(fast);
+  }
+  return faults;
 }
 
 hipError_t launch_score_mfma_ring(const structkv_shape& s, const ScorePlan& p, const SeqTable& seq, const void*,

@@ -391,6 +391,27 @@ def test_kernel_and_keys_for_more_than_128_rows(B):
             plan(32, 8, 64, lens, causal)
 
 
+def test_way_through_a_key_chunk(B):
+    """The long-chunk scoring kernel's requests, waits, slots and parked sums, against a model of its LDS ring: chunks of 0 to 30
+    and up to 64 tiles that end with the sequence or before it, inside a tile and at one's end, the causal triangle in one tile or over
+    several, at the chunk's end, across two chunks or all over it.  Stub build only (the kernel runs the same code)."""
+    lib = B._lib
+    if not hasattr(lib, "structkv_stub_chunk_faults"):
+        pytest.skip("the real library launches kernels; this runs against the stub build only")
+    ran = 0
+    for tiles in list(range(1, 31)) + [43, 44, 63, 64]:
+        for kc in {32 * tiles, 32 * (tiles + 3), 2048}:
+            for key0 in (0, kc, 3 * kc):
+                for less in (0, 1, 31, 32, 33, 63):
+                    for more in (0, 1, 40, 100, 200):
+                        ni = key0 + 32 * tiles - less + more
+                        for window in (0, 8, 33, 64, 130, 200):
+                            if ni > key0 and ni >= window:
+                                assert lib.structkv_stub_chunk_faults(ni, key0, kc, window) == 0, (ni, key0, kc, window)
+                                ran += 1
+    assert ran > 40000
+
+
 def test_selection_forms_of_a_layer_step(B):
     """Which form a layer step's selection takes by its longest searched prefix, whether the scoring prepares it, and when the
     selection forms the in-degrees itself.  Stub build only."""
