@@ -49,8 +49,8 @@ void with_table(const SeqTable& s, F f) {
 
 // The short, latency-bound kernels of a layer (combine, reduce, accumulate, top-k, gather) call this first.  When
 // layers run as chains on several streams such a kernel shares a SIMD with waves of another layer's scoring
-// kernel, which run at priority 1 while they have MFMAs to issue: at the default priority the short kernel would
-// queue behind them, and it is the short kernels that sit on a chain's critical path.
+// kernel -- those of score_mfma_ring.hip run at priority 1 while they have MFMAs to issue (those of score_mfma_wide.hip stay at
+// the default) -- and would queue behind them, and it is the short kernels that sit on a chain's critical path.
 #ifdef __HIPCC__
 __device__ __forceinline__ void short_kernel_priority() { __builtin_amdgcn_s_setprio(2); }
 

@@ -4,12 +4,13 @@
 // statistics or column sums -- is that of score_mfma_ring.hip, whose plan, partial results and column-sum planes these kernels
 // share; what differs is the loop.  The order of requests, waits and tiles is score_schedule.h's.
 //
-// What bounds these shapes is power, and the issue port at the clock that the chip then grants: a loop of nothing but this
+// What bounds these shapes is the issue port at the clock that the power limit leaves.  A loop of nothing but this
 // softmax and these MFMAs on N(0,1) data runs at 1.7 GHz with v_mfma_f32_32x32x16_bf16 and at 2.05 GHz with
 // v_mfma_f32_16x16x32_bf16 (2.4 GHz on zeros), because the accumulators of the smaller product are moved half as often per
-// multiplication.  Per 32-key tile and 64-row wave (cycles a SIMD): 32 logits a lane x 20 (fma, add, fma of 4 cycles and an
-// exponential of 8) and 32 MFMAs x 8.5, against 16 x 7.75 of the larger ones.  With both interleaved by hand one wave alone keeps
-// the port 95 % busy, so what is left to lose is what a wave waits for: LDS, the tile barrier, branches.  Hence:
+// multiplication; with HBM traffic and all else whole launches run at 1.9 GHz (128K tokens) and 1.65 (1M).  Per 32-key tile and 64-row
+// wave (cycles a SIMD): 32 logits a lane x 20 (fma, add, fma of 4 cycles and an exponential of 8) and 32 MFMAs x 8.5, against 16 x 7.75
+// of the larger ones.  By the counters that is 99 % of pass 1's and 92 % of pass 2's cycles at 1M tokens, 81 % and 75 % at
+// 128K; what is left to lose is what a wave waits for: LDS, the tile barrier, branches.  Hence:
 //   * 16 x 16 x 32 products, two by two of them a unit of 32 keys x 32 rows;
 //   * the MFMAs of a unit are issued between the softmax instructions of the unit before, across tiles; a tile's operands are
 //     requested from LDS piece by piece as soon as the registers of the tile before are free;
