@@ -2,7 +2,8 @@
 // shape) in long key chunks (the plan says from where on; shorter ones stay with score_mfma_ring.hip), paper Eq. 1, Eq. 2,
 // Eq. 4.  The work of a workgroup -- four waves of 64 rows that share 32-key tiles in an LDS ring, a key chunk, its partial
 // statistics or column sums -- is that of score_mfma_ring.hip, whose plan, partial results and column-sum planes these kernels
-// share; what differs is the loop.  The order of requests, waits and tiles is score_schedule.h's.
+// share; what differs is the loop.  (Loader, swizzle, rerun vote, planes and final write are that file's with other lane numbers: a
+// fault found in one is to be looked for in the other.)  The order of requests, waits and tiles is score_schedule.h's.
 //
 // What bounds these shapes is the issue port at the clock that the power limit leaves.  A loop of nothing but this
 // softmax and these MFMAs on N(0,1) data runs at 1.7 GHz with v_mfma_f32_32x32x16_bf16 and at 2.05 GHz with
