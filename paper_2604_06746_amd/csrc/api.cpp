@@ -770,14 +770,34 @@ structkv_status plan_layer_step(const structkv_shape* shape, const void* k, cons
   return STRUCTKV_OK;
 }
 
+// Workgroups per sequence where the selection's last launch also copies the kept rows; 0: the gather kernel does.
+// Short form: a unit a thread where 256 workgroups suffice for that, and up to eight; beyond them the gather kernel's many light
+// workgroups are as fast (layer steps of 32 heads on 8, window 32, us in a graph, gather launch / here: 4 x 1000 tokens, 60 % kept, 4
+// units a thread, 23.6 / 21.3; 32 x 1500, 5 %, 5 units, 68.5 / 62.1; 4 x 8000, 5 %, 7 units, 49.8 / 48.8).
+int copy_parts(const SeqTable& sel, const CopyWork& c, int mode, int keep_tail) {
+  int64_t most = 0;
+  for (int b = 0; b < sel.batch; ++b) most = std::max(most, (int64_t)sel.k[b] + keep_tail);
+  if (mode != kSelShort || most == 0) return 0;
+  const int64_t units = (most * c.planes) << c.upr_shift;
+  const int64_t parts = std::min<int64_t>(ceil_div(units, 1024), std::max(1, 256 / sel.batch));
+  return ceil_div(units, parts) <= 8 * 1024 && ceil_div(most, parts) <= kCopyRows ? (int)parts : 0;
+}
+
 structkv_status layer_finish_impl(const structkv_shape* shape, const LayerStepPlan& p, const void* k, const void* v,
                                   int64_t kv_stride_head, int64_t kv_stride_tok, int32_t keep_tail, const float* indeg,
                                   int32_t* idx_out, void* k_dst, void* v_dst, int64_t dst_stride_head,
                                   int64_t dst_stride_tok, hipStream_t hs) {
   if (p.rows == 0) return STRUCTKV_OK;
-  SKV_HIP_CHECK(launch_topk_rest(indeg, p.blocks, keep_tail, p.tws, p.n_blocks, idx_out, hs));
   const int64_t e = p.elem_bytes;
-  if (!p.no_rows)
+  CopyWork copy;
+  TopkWs tws = p.tws;
+  if (!p.no_rows && make_copy_work(k_dst ? k : nullptr, v_dst ? v : nullptr, kv_stride_head * e, kv_stride_tok * e, k_dst, v_dst,
+                                   dst_stride_head * e, dst_stride_tok * e, shape->n_kv_heads, shape->head_dim * p.elem_bytes, &copy)) {
+    tws.copy_parts = copy_parts(p.sel, copy, tws.mode, keep_tail);
+    if (tws.copy_parts > 0) tws.copy = &copy;
+  }
+  SKV_HIP_CHECK(launch_topk_rest(indeg, p.blocks, keep_tail, tws, p.n_blocks, idx_out, hs));
+  if (!p.no_rows && !tws.copy)
     SKV_HIP_CHECK(launch_gather(k_dst ? k : nullptr, v_dst ? v : nullptr, kv_stride_head * e, kv_stride_tok * e, k_dst,
                                 v_dst, dst_stride_head * e, dst_stride_tok * e, shape->n_kv_heads,
                                 shape->head_dim * p.elem_bytes, p.gseq, idx_out, hs));

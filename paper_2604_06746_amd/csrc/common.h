@@ -265,6 +265,8 @@ struct TopkWs {
   int mode;          // kSelShort / kSelMid / kSelLong
   float mass;        // > 0: the scores are in-degrees with this sum per sequence (fused layer step)
   const struct ReduceWork* red;   // (host) short: the kernel forms the scores itself (a layer step of short sequences)
+  const struct CopyWork* copy;    // (host) or NULL: the last launch copies the kept rows as well (a layer step) ...
+  int copy_parts;                 //        ... with this many workgroups per sequence
 };
 
 // What the reduce kernel does after pass 2; in a layer step of short sequences the selection's only launch does it.
@@ -306,6 +308,92 @@ static inline int selection_mode(int64_t longest) { return longest <= kShortSeq 
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// ---- rows copied by the launch that selects them ----------------------------------------------
+// The cache store of a layer step whose rows the selection's last launch moves itself: 16-byte units, a power of two a row.
+struct CopyWork {
+  const uint8_t* src[2];   // K and V (one of them alone: twice the same)
+  uint8_t* dst[2];
+  int64_t ssh, sst, dsh, dst_tok;   // strides in bytes: head and token, source and destination
+  uint32_t G, planes;      // KV heads; (tensor, head) pairs: G or 2 G
+  uint32_t recip;          // floor(2^32 / planes) + 1: divides what stays below 2^32 / planes exactly (0: one plane)
+  uint32_t upr_shift;      // log2 of the 16-byte units of a row
+};
+constexpr int kCopyRows = 512;   // most rows of a workgroup
+// strides in bytes; false: other units or widths, which the gather kernel takes
+inline bool make_copy_work(const void* k_src, const void* v_src, int64_t ssh, int64_t sst, void* k_dst, void* v_dst, int64_t dsh,
+                    int64_t dst_tok, int G, int row_bytes, CopyWork* c) {
+  *c = CopyWork{};
+  c->src[0] = (const uint8_t*)k_src; c->src[1] = (const uint8_t*)v_src;
+  c->dst[0] = (uint8_t*)k_dst; c->dst[1] = (uint8_t*)v_dst;
+  if (!c->src[0]) { c->src[0] = c->src[1]; c->dst[0] = c->dst[1]; c->src[1] = nullptr; }
+  if (!c->src[0]) return false;
+  const int tensors = c->src[1] ? 2 : 1;
+  if (tensors == 1) { c->src[1] = c->src[0]; c->dst[1] = c->dst[0]; }
+  const uintptr_t bits = (uintptr_t)c->src[0] | (uintptr_t)c->src[1] | (uintptr_t)c->dst[0] | (uintptr_t)c->dst[1] |
+                         (uintptr_t)ssh | (uintptr_t)sst | (uintptr_t)dsh | (uintptr_t)dst_tok | (uintptr_t)row_bytes;
+  const uint32_t upr = (uint32_t)row_bytes / 16;
+  if ((bits & 15) != 0 || (upr & (upr - 1)) != 0 || tensors * G > 2048) return false;   // (rows x planes^2 < 2^32: recip)
+  c->ssh = ssh; c->sst = sst; c->dsh = dsh; c->dst_tok = dst_tok;
+  c->G = (uint32_t)G;
+  c->planes = (uint32_t)(tensors * G);
+  c->recip = c->planes > 1 ? (uint32_t)(((uint64_t)1 << 32) / c->planes) + 1u : 0u;
+  while ((1u << c->upr_shift) < upr) ++c->upr_shift;
+  return true;
+}
+
+#ifdef __HIPCC__
+// Every row is read once and written once and neither is touched again by this kernel: the 16-byte units move with
+// the non-temporal policy, which keeps them from displacing what the next layer's scoring will read (measured on
+// back-to-back launches: 16.0 -> 14.2 us at 34 MB, 52.6 -> 47.2 us at 221 MB; non-temporal stores alone were slower
+// at 34 MB).  The builtins take clang's own vector types, not HIP's structs.
+typedef unsigned __attribute__((ext_vector_type(4))) u32x4;
+template <typename V> __device__ inline V load_once(const uint8_t* p) {
+  if constexpr (sizeof(V) == 16) {
+    const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    V r; r.x = t[0]; r.y = t[1]; r.z = t[2]; r.w = t[3];
+    return r;
+  } else {
+    return *reinterpret_cast<const V*>(p);
+  }
+}
+template <typename V> __device__ inline void store_once(uint8_t* p, V v) {
+  if constexpr (sizeof(V) == 16) {
+    const u32x4 t = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(p));
+  } else {
+    *reinterpret_cast<V*>(p) = v;
+  }
+}
+
+// Copy rows [0, rows) of a list, `out_row` the first one's place in the destination and token0 + at(row) the source token, by all
+// THREADS threads of the workgroup.  A row's (tensor, head) pairs lie next to each other in the order of the units: few rows still
+// spread over all threads.  DEPTH units a thread are in flight.
+template <int THREADS, int DEPTH, class At>
+__device__ __forceinline__ void copy_rows(const CopyWork& c, uint32_t rows, int64_t out_row, int64_t token0, At at) {
+  const uint32_t units = (rows * c.planes) << c.upr_shift;
+  for (uint32_t u0 = threadIdx.x; u0 < units; u0 += DEPTH * THREADS) {
+    uint4 v[DEPTH];
+    uint8_t* to[DEPTH];
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) {
+      const uint32_t u = u0 + i * THREADS;
+      to[i] = nullptr;
+      if (u < units) {
+        const uint32_t part = (u & ((1u << c.upr_shift) - 1u)) << 4, q = u >> c.upr_shift;
+        const uint32_t row = c.recip ? __umulhi(q, c.recip) : q, plane = q - row * c.planes;
+        const bool second = plane >= c.G;
+        const int64_t g = second ? plane - c.G : plane;
+        v[i] = load_once<uint4>((second ? c.src[1] : c.src[0]) + g * c.ssh + (token0 + at(row)) * c.sst + part);
+        to[i] = (second ? c.dst[1] : c.dst[0]) + g * c.dsh + (out_row + row) * c.dst_tok + part;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i)
+      if (to[i]) store_once<uint4>(to[i], v[i]);
+  }
+}
+#endif
 
 // ---- scoring plan: how one structkv_score_layer call is cut into workgroups ----------------
 struct ScorePlan {

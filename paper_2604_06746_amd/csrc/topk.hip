@@ -468,10 +468,10 @@ __device__ inline void resolve_key(Each each, uint32_t lo, int width, uint32_t k
 
 // Write the selected ones of a workgroup's PER x THREADS keys (key i of thread t stands at j0 + i*THREADS + t) in
 // ascending order: those above T and, of those equal to T, the first `need` of the sequence; g0 / e0: keys above / equal
-// to T before the workgroup.
-template <int THREADS, int PER>
+// to T before the workgroup.  put(place, index): an ascending place each.
+template <int THREADS, int PER, class Put>
 __device__ inline void place_ordered(const uint32_t (&key)[PER], int j0, int m, uint32_t T, uint32_t need, uint32_t g0,
-                                     uint32_t e0, uint32_t* tot /*[PER * THREADS / 64]*/, int32_t* __restrict__ out) {
+                                     uint32_t e0, uint32_t* tot /*[PER * THREADS / 64]*/, Put put) {
   constexpr int NWV = THREADS / 64, N = PER * NWV;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const unsigned long long below = (1ull << lane) - 1ull;
@@ -499,8 +499,8 @@ __device__ inline void place_ordered(const uint32_t (&key)[PER], int j0, int m, 
       if (u < e % Q) p += (uint32_t)__builtin_amdgcn_readlane((int)own[u], e / Q);
     const uint32_t gb = g0 + (p & 0xFFFFu) + (uint32_t)__popcll(mg[i] & below);
     const uint32_t eb = e0 + (p >> 16) + (uint32_t)__popcll(me[i] & below);
-    if ((mg[i] >> lane) & 1ull) out[gb + min(eb, need)] = j0 + i * THREADS + t;
-    else if (((me[i] >> lane) & 1ull) && eb < need) out[gb + eb] = j0 + i * THREADS + t;
+    if ((mg[i] >> lane) & 1ull) put(gb + min(eb, need), j0 + i * THREADS + t);
+    else if (((me[i] >> lane) & 1ull) && eb < need) put(gb + eb, j0 + i * THREADS + t);
   }
 }
 
@@ -508,22 +508,29 @@ __device__ inline void place_ordered(const uint32_t (&key)[PER], int j0, int m, 
 // SUM (a layer step): it first does what the reduce kernel does -- the column-sum planes of its sequence's tokens (at most
 // PER x 1024 with the window) added up in ascending order, the centrality update, the entropies' means -- and selects on the
 // scores it holds: one launch fewer (a layer step of 1K tokens is a handful of 3 us kernels: see short_plan in api.cpp).
-template <int PER, class TAB, bool SUM>
+// COPY (a layer step): `parts` workgroups per sequence, which all select for themselves and then copy a share each of the kept
+// rows, instead of a gather launch that reads the indices again (one
+// launch fewer for the host as well).  A layer step, 32 heads on 8, head_dim 128, window 8, us a call eager (in a graph), a fifth kept:
+// 512 tokens 19.5 -> 17.0 (13.6 -> 13.0), 2048 25.2 -> 21.9 (18.6 -> 18.0), 8192 29.7 -> 29.1 (27.3 -> 27.6).
+template <int PER, class TAB, bool SUM, bool COPY>
 __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
-                                                           int32_t* __restrict__ idx_out, ReduceWork red) {
+                                                           int32_t* __restrict__ idx_out, ReduceWork red, CopyWork copy, int parts) {
   short_kernel_priority();
   constexpr int NWV = kWide / 64;
   __shared__ ResolveLds l;
   __shared__ uint32_t ends[2][NWV], tot[PER * NWV];
+  __shared__ int32_t mine[COPY ? kCopyRows : 1];   // the source tokens of the rows that this workgroup copies
   if constexpr (SUM) {   // the second half of the launch: the entropies' means beside the selections (ahead of them in the same
                          // workgroups: four short prompts 20.8 us a layer step, beside 20.1; 1K tokens in fp32 19.9 and 19.4)
     __shared__ float hsum[256];
-    if ((int)blockIdx.x >= seq.batch) {
-      finish_entropy(red.row_ent, red.ent_head, red.entropy, (int)blockIdx.x - seq.batch, red.Hq, red.w, hsum);
+    const int selecting = COPY ? seq.batch * parts : seq.batch;
+    if ((int)blockIdx.x >= selecting) {
+      finish_entropy(red.row_ent, red.ent_head, red.entropy, (int)blockIdx.x - selecting, red.Hq, red.w, hsum);
       return;
     }
   }
-  const int b = blockIdx.x, t = threadIdx.x;
+  const int t = threadIdx.x, b = COPY ? (int)blockIdx.x % seq.batch : (int)blockIdx.x, part = COPY ? (int)blockIdx.x / seq.batch : 0;
+  const bool writes = part == 0;   // the others' results are the same
   const int m = (int)(seq.cu[b + 1] - seq.cu[b]) - keep_tail;
   const uint32_t k = (uint32_t)seq.k[b];
   const float* sc = scores + seq.cu[b];
@@ -538,7 +545,7 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
     for (int i = 0; i < PER; ++i) {
       at[i] = seq.cu[b] + max(0, min(i * kWide + t, n - 1));   // (an empty sequence reads nothing below)
       v[i] = 0.f;
-      c[i] = red.cen && n > 0 ? red.cen[at[i]] : 0.f;
+      c[i] = writes && red.cen && n > 0 ? red.cen[at[i]] : 0.f;
     }
     for (int p = 0; n > 0 && p < red.planes; p += U) {
       float x[U][PER];
@@ -553,7 +560,7 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i)
-      if (i * kWide + t < n) {
+      if (writes && i * kWide + t < n) {
         red.indeg[at[i]] = v[i];
         if (red.cen) red.cen[at[i]] = fmaf(red.lambda, c[i], red.inv_w * v[i]);
       }
@@ -561,8 +568,23 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
 #pragma unroll
     for (int i = 0; i < PER; ++i) v[i] = k > 0u && i * kWide + t < m ? sc[i * kWide + t] : 0.f;
   }
-  for (int i = t; i < keep_tail; i += kWide) out[k + i] = m + i;
-  if (k == 0u) return;
+  for (int i = t; writes && i < keep_tail; i += kWide) out[k + i] = m + i;
+  // rows [r0, r1) of the sequence's k + keep_tail are this workgroup's to copy
+  const uint32_t rows = k + (uint32_t)keep_tail, share = COPY ? (rows + (uint32_t)parts - 1u) / (uint32_t)parts : 0u;
+  const uint32_t r0 = min(rows, (uint32_t)part * share), r1 = min(rows, r0 + share);
+  auto copy_share = [&]() __attribute__((always_inline)) {
+    copy_rows<kWide, 4>(copy, r1 - r0, seq.out_off[b] + r0, seq.cu[b], [&](uint32_t r) {
+      return r0 + r < k ? mine[r] : m + (int)(r0 + r - k);
+    });
+  };
+  if (k == 0u) {
+    if constexpr (COPY) copy_share();
+    return;
+  }
+  if (COPY && !writes && r0 >= k) {   // (nothing but the kept window)
+    copy_share();
+    return;
+  }
   for (int i = t; i < kBins; i += kWide) l.hist[i] = 0u;
   if (t == 0) l.n = 0u;
   uint32_t key[PER], inv = 0u, mx = 0u;   // largest ~key and largest key
@@ -584,7 +606,15 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
     for (int i = 0; i < PER; ++i)
       if (i * kWide + t < m) f(key[i]);
   }, mn, 32 - __clz((int)(mx - mn)), k, l, &T, &need);
-  place_ordered<kWide, PER>(key, 0, m, T, need, 0u, 0u, tot, out);
+  place_ordered<kWide, PER>(key, 0, m, T, need, 0u, 0u, tot, [&](uint32_t at, int j) {
+    if (writes) out[at] = j;
+    if constexpr (COPY)
+      if (at - r0 < r1 - r0) mine[at - r0] = j;
+  });
+  if constexpr (COPY) {
+    __syncthreads();
+    copy_share();
+  }
 }
 
 // mid form, alone: zero the histograms and the candidate counter, write the kept window, and centre the bins on the k-th
@@ -909,7 +939,8 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i) key[i] = score_key(v[i]);
   __syncthreads();
-  place_ordered<kThreads, kMidPer>(key, j0, m, T, need, cnt[0], cnt[1], tot, idx_out + seq.out_off[b]);
+  int32_t* out = idx_out + seq.out_off[b];
+  place_ordered<kThreads, kMidPer>(key, j0, m, T, need, cnt[0], cnt[1], tot, [&](uint32_t at, int j) { out[at] = j; });
 }
 
 // The pivot detector's metrics from rows of in-degrees (one per query head) whose histograms over the bins of row_bin have been
@@ -1169,6 +1200,7 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
   ws->mode = selection_mode(longest);
   ws->mass = 0.f;
   ws->red = nullptr;
+  ws->copy = nullptr;
   const int target = ws->mode == kSelMid ? kMidShare : share_target(plan->cu[B]);
   plan->chunk_start[0] = 0;
   for (int b = 0; b < B; ++b) {
@@ -1198,13 +1230,18 @@ hipError_t launch_topk_rest(const float* scores, const SeqTable& plan, int keep_
       for (int b = 0; b < plan.batch; ++b)
         if (ws.red || plan.k[b] > 0) longest = std::max(longest, plan.cu[b + 1] - plan.cu[b] - (ws.red ? 0 : keep_tail));
       const ReduceWork red = ws.red ? *ws.red : ReduceWork{};
-#define SKV_SHORT(PER, SUM)                                                                                             \
-  hipLaunchKernelGGL((topk_short_kernel<PER, T, SUM>), dim3((unsigned)(SUM ? 2 * plan.batch : plan.batch)), dim3(kWide), 0, st,     \
-                     scores, tab, keep_tail, idx_out, red)
-      if (ws.red) { if (longest <= kWide) SKV_SHORT(1, true); else SKV_SHORT(2, true); }
-      else if (longest <= 2 * kWide) SKV_SHORT(2, false);
-      else if (longest <= 4 * kWide) SKV_SHORT(4, false);
-      else SKV_SHORT(8, false);
+      const CopyWork copy = ws.copy ? *ws.copy : CopyWork{};
+      const int parts = ws.copy ? ws.copy_parts : 1;
+#define SKV_SHORT_(PER, SUM, COPY)                                                                                      \
+  hipLaunchKernelGGL((topk_short_kernel<PER, T, SUM, COPY>), dim3((unsigned)(plan.batch * (SUM ? parts + 1 : parts))), dim3(kWide), 0, st, \
+                     scores, tab, keep_tail, idx_out, red, copy, parts)
+#define SKV_SHORT(PER, SUM)                                                  \
+  if (ws.copy) SKV_SHORT_(PER, SUM, true); else SKV_SHORT_(PER, SUM, false)
+      if (ws.red) { if (longest <= kWide) { SKV_SHORT(1, true); } else { SKV_SHORT(2, true); } }
+      else if (longest <= 2 * kWide) { SKV_SHORT(2, false); }
+      else if (longest <= 4 * kWide) { SKV_SHORT(4, false); }
+      else { SKV_SHORT(8, false); }
+#undef SKV_SHORT_
 #undef SKV_SHORT
     } else if (blocks == 0) {
       return;

@@ -1,0 +1,61 @@
+"""A layer step whose selection copies the kept rows itself, against the four calls (whose gather kernel copies them): the same
+bits, for shares of one row, none and many, K or V alone, strided and misaligned destinations, small and large tables."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+SHORT = [
+    # lens, budgets, kept window
+    ((1000,), (100,), 8),
+    ((33, 1500, 64), (1, 700, 0), 8),            # fewer rows than workgroups, a window alone
+    ((2048,), (2040,), 8),                       # everything kept
+    ((8, 8, 8), (0, 0, 0), 8),                   # nothing but the window
+    ((4000, 5000), (800, 3), 32),
+    ((8192,), (6000,), 0),                       # many units a workgroup; no window
+    ((8192 + 32,) * 3, (7000, 10, 100), 32),     # too many rows for the selection: the gather kernel
+    (tuple(range(200, 200 + 12 * 37, 37)), tuple(range(3, 3 + 12 * 9, 9)), 8),   # more sequences than the small table holds
+]
+
+
+@pytest.mark.parametrize("form", ["both", "k", "v", "strided", "misaligned"])
+@pytest.mark.parametrize("lens,ks,tail", SHORT)
+def test_rows_copied_by_the_selection(lens, ks, tail, form):
+    from paper_2604_06746_amd import binding as B
+    from paper_2604_06746_amd.sweep import LayerSweep
+    Hq, G, d, w = 8, 2, 64, 8
+    sw = LayerSweep(Hq, G, d, w, torch.bfloat16, lens, ks)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(sum(lens) + tail)
+    q = torch.randn(len(lens), Hq, w, d, generator=g, device="cuda").to(torch.bfloat16)
+    k = torch.randn(G, sum(lens), d, generator=g, device="cuda").to(torch.bfloat16)
+    v = torch.randn(G, sum(lens), d, generator=g, device="cuda").to(torch.bfloat16)
+    rows = [x + tail for x in ks]
+    total = sum(rows)
+
+    def dst():
+        if form == "strided":
+            return torch.full((G, 2 * total + 3, 2 * d), -7.0, device="cuda", dtype=torch.bfloat16)[:, :total, :d]
+        if form == "misaligned":
+            return torch.full((G * total * d + 2,), -7.0, device="cuda", dtype=torch.bfloat16)[2:].view(G, total, d)
+        return torch.full((G, total, d), -7.0, device="cuda", dtype=torch.bfloat16)
+    want_k, want_v, got_k, got_v = (dst() for _ in range(4))
+    cen = torch.rand(sum(lens), generator=g, device="cuda")
+    cen2 = cen.clone()
+    idx = torch.full((total,), -1, dtype=torch.int32, device="cuda")
+    B.structkv_score_layer(sw.shape, q, k, sw.cu, sw.indeg, sw.entropy, sw.entropy_per_head, sw.workspace)
+    B.structkv_accumulate_centrality(cen, sw.indeg, 0.9, 1.0 / w)
+    B.structkv_select_topk(sw.indeg, sw.cu, ks, tail, idx, sw.topk_workspace)
+    B.structkv_gather_kv(k if form != "v" else None, v if form != "k" else None, want_k if form != "v" else None,
+                         want_v if form != "k" else None, sw.cu, rows, idx)
+    indeg, ent, enth = torch.full_like(sw.indeg, -1), torch.full_like(sw.entropy, -1), torch.full_like(sw.entropy_per_head, -1)
+    got_idx = torch.full_like(idx, -1)
+    sw.workspace.fill_(0xA5)
+    B.structkv_layer_step(sw.shape, q, k, v, sw.cu, ks, tail, indeg, cen2, 0.9, 1.0 / w, ent, enth, got_idx,
+                          got_k if form != "v" else None, got_v if form != "k" else None, sw.workspace)
+    torch.cuda.synchronize()
+    assert torch.equal(got_idx, idx)
+    for a, b in ((got_k, want_k), (got_v, want_v)):
+        base = (lambda x: x._base if x._base is not None else x)   # (the gaps of a strided destination too)
+        assert torch.equal(base(a), base(b))
+    assert torch.equal(indeg, sw.indeg) and torch.equal(cen2, cen) and torch.equal(ent, sw.entropy) and torch.equal(enth, sw.entropy_per_head)
