@@ -224,6 +224,7 @@ void short_carve(const structkv_shape& s, int batch, int64_t total, ScorePlan* p
 //              four sequences of 1536 keys 24.7 -> 22.4 (21.2 -> 21.2), of 2048 keys 24.7 -> 24.6 (22.4 -> 23.6)
 //   window 32: 512 keys 24.1 -> 18.0 (19.1 -> 15.8), 1024 keys 24.9 -> 19.9 (19.6 -> 18.7)
 //   window 64: 1024 keys 24.9 -> 22.6 (23.1 -> 21.8); four sequences of 1024 keys 30.5 -> 25.0 (27.9 -> 23.9)
+// (Before the kernel's sums and query loads became cheaper: one launch now takes 11.5 us in a graph at 512 keys and a window of 8, 13.5 at 1024.)
 // So beyond 1280 keys of 256 bytes fewer launches win for a caller that launches each time and lose in a captured graph; the
 // line is where what they lose outweighs what they win, after 1792 keys.  Keys of 128 bytes, 8 heads on 2:
 //   window 8:  1024 keys 24.4 -> 18.4 (16.7 -> 14.2), 1536 keys 24.6 -> 18.5 (17.1 -> 15.8), 2048 keys 24.4 -> 18.7 (17.8 -> 17.3)

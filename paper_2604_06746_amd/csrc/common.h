@@ -108,6 +108,32 @@ __device__ inline void finish_entropy(const float* __restrict__ row_ent, float* 
 }
 #endif
 
+#ifdef __HIPCC__
+// Rows of 16-byte pieces as matrix operands: a lane holds pieces of ONE row, so neighbouring lanes of a load straight into that
+// layout read different rows and every load instruction takes 64 line look-ups.  Loaded instead by quads of lanes that read 64
+// contiguous bytes, register r the quad's row r, and exchanged inside the quad: 16 look-ups and, for four registers, 64 vector instructions.
+typedef __attribute__((ext_vector_type(4))) float quad_piece_t;
+template <int CTRL>
+__device__ __forceinline__ void quad_exchange(quad_piece_t& a, quad_piece_t& b, bool second) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float x = a[e], y = b[e];
+    const float ox = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+    const float oy = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(y), CTRL, 0xF, 0xF, true));
+    a[e] = second ? oy : x;
+    b[e] = second ? y : ox;
+  }
+}
+// piece r of lane c of a quad <-> piece c of lane r
+__device__ __forceinline__ void quad_transpose(quad_piece_t& v0, quad_piece_t& v1, quad_piece_t& v2, quad_piece_t& v3) {
+  const bool odd = threadIdx.x & 1, upper = threadIdx.x & 2;
+  quad_exchange<0xB1>(v0, v1, odd);     // quad_perm 1,0,3,2
+  quad_exchange<0xB1>(v2, v3, odd);
+  quad_exchange<0x4E>(v0, v2, upper);   // quad_perm 2,3,0,1
+  quad_exchange<0x4E>(v1, v3, upper);
+}
+#endif
+
 // ---- selection (radix select on order-preserving keys) ---------------------------------------
 constexpr int kTopkBins = 2048;      // digits 0 and 1: 11 bits each; digit 2: the last 10 bits
 

@@ -12,6 +12,12 @@
 //         costs: more rows per key, and half the column-sum planes)
 //   fp32: v_mfma_f32_16x16x4_f32, one row block (n d / 8 cycles of matrix pipe per workgroup bind: more, lighter workgroups)
 // Where the line lies (short_plan in api.cpp) and what it measured stands there.
+// What a workgroup takes, by cycle counters: the keys' way into the CU (1500 keys of 256 bytes: 6 of 16 k cycles, 56 bytes a cycle;
+// fp32: the matrix instructions, 256 a SIMD, about 60 cycles each beside everything else), then maxima, sums and column sums, 8 k
+// cycles.  Of the latter a third was LDS reads of every wave's maxima and sums by every lane (now a quarter each, exchanged between the
+// rows of lanes) and sums over 16 lanes one at a time (now four together), and before the first tile 4 k cycles of line look-ups for the
+// query operands (now by quads of lanes): a layer step of 1K tokens in fp32 18.0 -> 17.0 us, four short prompts 18.8 -> 16.6 us.
+// Other workgroups that pull the keys into the XCD's L2 meanwhile: 0.1 us, not kept.
 #include "common.h"
 
 namespace skv {
@@ -23,18 +29,29 @@ typedef __attribute__((ext_vector_type(4))) float floatx4;
 constexpr int kWaves = 16;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// sum over the 16 lanes of a DPP row, in every lane of it: exchanges inside quads, then mirrored halves and rows
 template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+__device__ __forceinline__ float dpp(float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true)); }
+// The sums of s[0..3] over the 16 lanes of a DPP row, that of s[j] in the lanes j, j + 4, ... of it: two halvings inside the quads, then
+// the quads added up (eleven instructions where four sums of sixteen lanes each take twenty).
+__device__ __forceinline__ float row_sums(const float (&s)[4], bool odd, bool upper) {
+  const float a = (odd ? s[1] : s[0]) + dpp<0xB1>(odd ? s[0] : s[1]);   // quad_perm 1,0,3,2
+  const float b = (odd ? s[3] : s[2]) + dpp<0xB1>(odd ? s[2] : s[3]);
+  float c = (upper ? b : a) + dpp<0x4E>(upper ? a : b);                 // quad_perm 2,3,0,1
+  c += dpp<0x124>(c);                                                   // row_ror 4, 8
+  return c + dpp<0x128>(c);
 }
-__device__ __forceinline__ float row_sum(float v) {
-  return dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(v))));
+// a value of each of the four rows of lanes, combined, in all of them
+template <class F>
+__device__ __forceinline__ float over_groups(float v, F f) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 // matrix operands of one row or key: lane l holds row l%16.  bf16: of every 32 components the eight of its quarter l/16;
 // fp32: of every 16 components the four of its quarter (the four steps of a group take them in the same order on both sides):
-// either way its piece c is the 16-byte piece 4 c + l/16 of the row.
+// either way its piece c is the 16-byte piece PIECES (l/16) + c of the row (any order will do that both sides share).
 template <typename T, int D> struct Frag {
   static constexpr int PIECES = D * (int)sizeof(T) / 64;
   floatx4 v[PIECES];
@@ -105,9 +122,17 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
   F qf[NRB];
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) {
-    const T* row = qg + (int64_t)min((rc * NRB + rb) * 16 + l16, R - 1) * D;
+    constexpr int E = 16 / (int)sizeof(T);   // elements of a piece
+    if constexpr (F::PIECES % 4 == 0) {      // by quads of lanes, see quad_transpose
 #pragma unroll
-    for (int c = 0; c < F::PIECES; ++c) qf[rb].v[c] = *reinterpret_cast<const floatx4*>(row + (4 * c + lg) * (16 / (int)sizeof(T)));
+      for (int c = 0; c < F::PIECES; ++c)
+        qf[rb].v[c] = *reinterpret_cast<const floatx4*>(qg + (int64_t)min((rc * NRB + rb) * 16 + (l16 & 12) + c % 4, R - 1) * D +
+                                                        (F::PIECES * lg + c / 4 * 4 + (lane & 3)) * E);
+    } else {
+      const T* row = qg + (int64_t)min((rc * NRB + rb) * 16 + l16, R - 1) * D;
+#pragma unroll
+      for (int c = 0; c < F::PIECES; ++c) qf[rb].v[c] = *reinterpret_cast<const floatx4*>(row + (F::PIECES * lg + c) * E);
+    }
   }
   // Eight tiles: those past the sequence's end are left out (uniform in the wave), so that a length of just over 1024 keys
   // costs five of them (a layer step of 1280 keys, 32 heads on 8, window 8, in a graph: 20.4 -> 18.5 us).  With two or four
@@ -115,6 +140,16 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
   auto has = [&](int i) __attribute__((always_inline)) { return TW < 8 || tile0(i) < n; };
   if (has(0)) issue(0);
   if (SLOTS > 1 && TW > 1 && has(1)) issue(1);
+  if constexpr (F::PIECES % 4 == 0) {
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+      for (int c = 0; c < F::PIECES; c += 4) {
+        quad_transpose(qf[rb].v[c], qf[rb].v[c + 1], qf[rb].v[c + 2], qf[rb].v[c + 3]);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) asm volatile("" : "+v"(qf[rb].v[c + x]));
+      }
+  }
   // (never fewer than two: an array of exactly 32 floats becomes ONE 32-register value, and 400 registers spill)
   floatx4 acc[NRB < 2 ? 2 : NRB][TW];
 #pragma unroll
@@ -126,7 +161,7 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
     const uint8_t* slot = slots + (i % SLOTS) * TILEB;
 #pragma unroll
     for (int c = 0; c < F::PIECES; ++c)
-      kf.v[c] = *reinterpret_cast<const floatx4*>(slot + (l16 * SEGS + ((4 * c + lg) ^ swz(l16))) * 16);
+      kf.v[c] = *reinterpret_cast<const floatx4*>(slot + (l16 * SEGS + ((F::PIECES * lg + c) ^ swz(l16))) * 16);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the operands are in registers: the slot may be overwritten
     __builtin_amdgcn_sched_barrier(0);
     if (i + SLOTS < TW && has(i + SLOTS)) issue(i + SLOTS);
@@ -161,17 +196,16 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
 #pragma unroll
       for (int j = 0; j < 4; ++j) m = fmaxf(m, acc[rb][i][j]);
     }
-    m = fmaxf(m, __shfl_xor(m, 16));
-    m = fmaxf(m, __shfl_xor(m, 32));
+    m = over_groups(m, [](float x, float y) { return fmaxf(x, y); });
     if (lg == 0) sM[wave][rb * 16 + l16] = m;
   }
   __syncthreads();
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) {
-    float m = sM[0][rb * 16 + l16];
+    float m = sM[lg][rb * 16 + l16];   // (each row of lanes reads a quarter of the waves': the reads were what the phase took)
 #pragma unroll
-    for (int v = 1; v < kWaves; ++v) m = fmaxf(m, sM[v][rb * 16 + l16]);
-    M[rb] = m * c2;
+    for (int v = 4; v < kWaves; v += 4) m = fmaxf(m, sM[v + lg][rb * 16 + l16]);
+    M[rb] = over_groups(m, [](float x, float y) { return fmaxf(x, y); }) * c2;
     float z = 0.f, e = 0.f;
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
@@ -192,8 +226,9 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
         e = fmaf(p, x, e);
       }
     }
-    z += __shfl_xor(z, 16); e += __shfl_xor(e, 16);
-    z += __shfl_xor(z, 32); e += __shfl_xor(e, 32);
+    auto add = [](float x, float y) { return x + y; };
+    z = over_groups(z, add);
+    e = over_groups(e, add);
     if (lg == 0) { sZ[wave][rb * 16 + l16] = z; sE[wave][rb * 16 + l16] = e; }
   }
   __syncthreads();
@@ -201,18 +236,24 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) {
     const int row = (rc * NRB + rb) * 16 + l16;
-    Z[rb] = sZ[0][rb * 16 + l16]; E[rb] = sE[0][rb * 16 + l16];
+    Z[rb] = sZ[lg][rb * 16 + l16];
 #pragma unroll
-    for (int v = 1; v < kWaves; ++v) { Z[rb] += sZ[v][rb * 16 + l16]; E[rb] += sE[v][rb * 16 + l16]; }
+    for (int v = 4; v < kWaves; v += 4) Z[rb] += sZ[v + lg][rb * 16 + l16];
+    Z[rb] = over_groups(Z[rb], [](float x, float y) { return x + y; });
     inv[rb] = row < R ? 1.0f / Z[rb] : 0.f;                                 // a padded row adds nothing
-    if (wave == 0 && lg == 0 && row < R) ent_out[row] = kLn2 * (__log2f(Z[rb]) - E[rb] / Z[rb]);
+    if (wave == 0) {
+      E[rb] = sE[lg][rb * 16 + l16];
+#pragma unroll
+      for (int v = 4; v < kWaves; v += 4) E[rb] += sE[v + lg][rb * 16 + l16];
+      E[rb] = over_groups(E[rb], [](float x, float y) { return x + y; });
+      if (lg == 0 && row < R) ent_out[row] = kLn2 * (__log2f(Z[rb]) - E[rb] / Z[rb]);
+    }
   }
   float* out = colsum + ((int64_t)g * RC + rc) * total + tok0;
 #pragma unroll
   for (int i = 0; i < TW; ++i) {
     const int key = tile0(i) + 4 * lg + l16;   // (of the lanes that write: l16 < 4)
     if (tile0(i) >= n) continue;
-    float mine = 0.f;
     if (masked(i)) {   // (a row that is not a number stays off the keys that it does not see)
 #pragma unroll
       for (int rb = 0; rb < NRB; ++rb)
@@ -220,19 +261,19 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
         for (int j = 0; j < 4; ++j)
           if (tile0(i) + 4 * lg + j >= seen((rc * NRB + rb) * 16 + l16)) acc[rb][i][j] = -INFINITY;
     }
+    float s[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float s = 0.f;
+      s[j] = 0.f;
       if (masked(i)) {
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) s = acc[rb][i][j] == -INFINITY ? s : fmaf(acc[rb][i][j], inv[rb], s);
+        for (int rb = 0; rb < NRB; ++rb) s[j] = acc[rb][i][j] == -INFINITY ? s[j] : fmaf(acc[rb][i][j], inv[rb], s[j]);
       } else {
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) s = fmaf(acc[rb][i][j], inv[rb], s);
+        for (int rb = 0; rb < NRB; ++rb) s[j] = fmaf(acc[rb][i][j], inv[rb], s[j]);
       }
-      s = row_sum(s);
-      if (l16 == j) mine = s;
     }
+    const float mine = row_sums(s, lane & 1, lane & 2);
     if (l16 < 4 && key < n) out[key] = mine;
   }
 }
