@@ -105,6 +105,23 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {   // same moves; lane
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// Inclusive scan over the first NWV lanes: one value per wave of the workgroup, read from LDS by a lane each and not all of them by
+// every lane (16 waves x 16 reads are a thousand cycles of the LDS; an 8192-score selection does that four times).
+template <int NWV>
+__device__ __forceinline__ uint32_t waves_scan(uint32_t v) {
+  static_assert(NWV == 4 || NWV == 8 || NWV == 16, "lanes of one DPP row");
+  v += dpp_or_zero<0x111, 0xF>(v);
+  v += dpp_or_zero<0x112, 0xF>(v);
+  if (NWV > 4) v += dpp_or_zero<0x114, 0xF>(v);
+  if (NWV > 8) v += dpp_or_zero<0x118, 0xF>(v);
+  return v;
+}
+// ... of which the waves before the calling one
+__device__ __forceinline__ uint32_t waves_before(uint32_t scan) {
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  return wv ? (uint32_t)__builtin_amdgcn_readlane((int)scan, wv - 1) : 0u;
+}
+
 // exclusive scan of one value per thread over the workgroup (THREADS / 64 waves); returns the total.
 // One barrier; `sh` must not be written again before another one (TRAIL: here).
 template <int THREADS = kThreads, bool TRAIL = true>
@@ -114,16 +131,10 @@ __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* sh /*[>= THREAD
   const uint32_t x = wave_scan(v);
   if (lane == 63) sh[wv] = x;
   __syncthreads();
-  uint32_t base = 0u, total = 0u;
-#pragma unroll
-  for (int i = 0; i < NWV; ++i) {
-    const uint32_t wsum = sh[i];
-    if (i < wv) base += wsum;
-    total += wsum;
-  }
-  *excl = base + x - v;
+  const uint32_t s = waves_scan<NWV>(sh[lane & (NWV - 1)]);
+  *excl = waves_before(s) + x - v;
   if (TRAIL) __syncthreads();
-  return total;
+  return (uint32_t)__builtin_amdgcn_readlane((int)s, NWV - 1);
 }
 
 // Scan the NB bins of a histogram from the top until `krem` (1 .. their sum) keys are covered.
@@ -466,41 +477,44 @@ __device__ inline void resolve_key(Each each, uint32_t lo, int width, uint32_t k
   *need = krem;
 }
 
-// Write the selected ones of a workgroup's PER x THREADS keys (key i of thread t stands at j0 + i*THREADS + t) in
-// ascending order: those above T and, of those equal to T, the first `need` of the sequence; g0 / e0: keys above / equal
-// to T before the workgroup.  put(place, index): an ascending place each.
+// Place the selected ones of a workgroup's PER x THREADS keys in ascending order: those above T and, of those equal to T, the first
+// `need` of the sequence; g0 / e0: keys above / equal to T before the workgroup.  A wave's keys are consecutive (key i of a lane stands at
+// j0 + 64 i + lane), so that what counts between its rounds is scalar and only the waves' totals go through LDS; with rounds over the
+// whole workgroup 128 counts were scanned by every wave (8192 scores 5.5 k cycles of 18 k).  put(place, index): an ascending place each.
 template <int THREADS, int PER, class Put>
 __device__ inline void place_ordered(const uint32_t (&key)[PER], int j0, int m, uint32_t T, uint32_t need, uint32_t g0,
-                                     uint32_t e0, uint32_t* tot /*[PER * THREADS / 64]*/, Put put) {
-  constexpr int NWV = THREADS / 64, N = PER * NWV;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const unsigned long long below = (1ull << lane) - 1ull;
+                                     uint32_t e0, uint32_t* tot /*[THREADS / 64]*/, Put put) {
+  constexpr int NWV = THREADS / 64;
+  static_assert(PER * THREADS < 65536, "both counts of a word stay below 2^16");
+  const int lane = threadIdx.x & 63;
+  auto before = [](unsigned long long mask) __attribute__((always_inline)) {
+    return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+  };
   unsigned long long mg[PER], me[PER];
+  uint32_t cg = 0u, ce = 0u;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const bool in = j0 + i * THREADS + t < m;
+    const bool in = j0 + 64 * i + lane < m;
     mg[i] = __ballot(in && key[i] > T);
     me[i] = __ballot(in && key[i] == T);
-    if (lane == 0) tot[i * NWV + wv] = (uint32_t)__popcll(mg[i]) | ((uint32_t)__popcll(me[i]) << 16);
+    cg += (uint32_t)__popcll(mg[i]);
+    ce += (uint32_t)__popcll(me[i]);
   }
+  if (lane == 0) tot[threadIdx.x >> 6] = cg | (ce << 16);
   __syncthreads();
-  // every wave scans the N counts for itself (both halves of a word stay below 2^16)
-  constexpr int Q = (N + 63) / 64;
-  uint32_t own[Q], sum = 0u;
-#pragma unroll
-  for (int i = 0; i < Q; ++i) { own[i] = lane * Q + i < N ? tot[lane * Q + i] : 0u; sum += own[i]; }
-  uint32_t x = wave_scan(sum) - sum;   // before the lane's first count
+  const uint32_t p = waves_before(waves_scan<NWV>(tot[lane & (NWV - 1)]));
+  uint32_t g = g0 + (p & 0xFFFFu), e = e0 + (p >> 16);
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const int e = i * NWV + wv;
-    uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)x, e / Q);
-#pragma unroll
-    for (int u = 0; u + 1 < Q; ++u)
-      if (u < e % Q) p += (uint32_t)__builtin_amdgcn_readlane((int)own[u], e / Q);
-    const uint32_t gb = g0 + (p & 0xFFFFu) + (uint32_t)__popcll(mg[i] & below);
-    const uint32_t eb = e0 + (p >> 16) + (uint32_t)__popcll(me[i] & below);
-    if ((mg[i] >> lane) & 1ull) put(gb + min(eb, need), j0 + i * THREADS + t);
-    else if (((me[i] >> lane) & 1ull) && eb < need) put(gb + eb, j0 + i * THREADS + t);
+    if (me[i] == 0ull || e >= need) {   // (uniform) no key of the round is equal to T, or none of those is taken
+      if ((mg[i] >> lane) & 1ull) put(g + before(mg[i]) + min(e, need), j0 + 64 * i + lane);
+    } else {
+      const uint32_t gb = g + before(mg[i]), eb = e + before(me[i]);
+      if ((mg[i] >> lane) & 1ull) put(gb + min(eb, need), j0 + 64 * i + lane);
+      else if (((me[i] >> lane) & 1ull) && eb < need) put(gb + eb, j0 + 64 * i + lane);
+    }
+    g += (uint32_t)__popcll(mg[i]);
+    e += (uint32_t)__popcll(me[i]);
   }
 }
 
@@ -518,7 +532,7 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
   short_kernel_priority();
   constexpr int NWV = kWide / 64;
   __shared__ ResolveLds l;
-  __shared__ uint32_t ends[2][NWV], tot[PER * NWV];
+  __shared__ uint32_t ends[2][NWV], tot[NWV];
   __shared__ int32_t mine[COPY ? kCopyRows : 1];   // the source tokens of the rows that this workgroup copies
   if constexpr (SUM) {   // the second half of the launch: the entropies' means beside the selections (ahead of them in the same
                          // workgroups: four short prompts 20.8 us a layer step, beside 20.1; 1K tokens in fp32 19.9 and 19.4)
@@ -531,6 +545,7 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
   }
   const int t = threadIdx.x, b = COPY ? (int)blockIdx.x % seq.batch : (int)blockIdx.x, part = COPY ? (int)blockIdx.x / seq.batch : 0;
   const bool writes = part == 0;   // the others' results are the same
+  const int j0 = (t >> 6) * (64 * PER), lane = t & 63;   // key i of a lane: place_ordered
   const int m = (int)(seq.cu[b + 1] - seq.cu[b]) - keep_tail;
   const uint32_t k = (uint32_t)seq.k[b];
   const float* sc = scores + seq.cu[b];
@@ -543,7 +558,7 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
     float c[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      at[i] = seq.cu[b] + max(0, min(i * kWide + t, n - 1));   // (an empty sequence reads nothing below)
+      at[i] = seq.cu[b] + max(0, min(j0 + 64 * i + lane, n - 1));   // (an empty sequence reads nothing below)
       v[i] = 0.f;
       c[i] = writes && red.cen && n > 0 ? red.cen[at[i]] : 0.f;
     }
@@ -560,13 +575,13 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i)
-      if (writes && i * kWide + t < n) {
+      if (writes && j0 + 64 * i + lane < n) {
         red.indeg[at[i]] = v[i];
         if (red.cen) red.cen[at[i]] = fmaf(red.lambda, c[i], red.inv_w * v[i]);
       }
   } else {
 #pragma unroll
-    for (int i = 0; i < PER; ++i) v[i] = k > 0u && i * kWide + t < m ? sc[i * kWide + t] : 0.f;
+    for (int i = 0; i < PER; ++i) v[i] = k > 0u && j0 + 64 * i + lane < m ? sc[j0 + 64 * i + lane] : 0.f;
   }
   for (int i = t; writes && i < keep_tail; i += kWide) out[k + i] = m + i;
   // rows [r0, r1) of the sequence's k + keep_tail are this workgroup's to copy
@@ -591,22 +606,22 @@ __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restri
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     key[i] = score_key(v[i]);
-    if (i * kWide + t < m) { inv = max(inv, ~key[i]); mx = max(mx, key[i]); }
+    if (j0 + 64 * i + lane < m) { inv = max(inv, ~key[i]); mx = max(mx, key[i]); }
   }
   inv = wave_max(inv);
   mx = wave_max(mx);
-  if ((t & 63) == 0) { ends[0][t >> 6] = inv; ends[1][t >> 6] = mx; }
+  if (lane == 0) { ends[0][t >> 6] = inv; ends[1][t >> 6] = mx; }
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NWV; ++i) { inv = max(inv, ends[0][i]); mx = max(mx, ends[1][i]); }
+  inv = wave_max(ends[0][lane & (NWV - 1)]);
+  mx = wave_max(ends[1][lane & (NWV - 1)]);
   const uint32_t mn = ~inv;
   uint32_t T, need;
   resolve_key<kWide>([&](auto f) {
 #pragma unroll
     for (int i = 0; i < PER; ++i)
-      if (i * kWide + t < m) f(key[i]);
+      if (j0 + 64 * i + lane < m) f(key[i]);
   }, mn, 32 - __clz((int)(mx - mn)), k, l, &T, &need);
-  place_ordered<kWide, PER>(key, 0, m, T, need, 0u, 0u, tot, [&](uint32_t at, int j) {
+  place_ordered<kWide, PER>(key, j0, m, T, need, 0u, 0u, tot, [&](uint32_t at, int j) {
     if (writes) out[at] = j;
     if constexpr (COPY)
       if (at - r0 < r1 - r0) mine[at - r0] = j;
@@ -806,7 +821,7 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
   constexpr int CPT = 4;        // candidates a thread keeps in registers; the first is requested before their number is known
   constexpr int kPicked = CPT * kThreads;   // most keys of a sub-bin that are copied together
   __shared__ ResolveLds l;
-  __shared__ uint32_t tot[kMidPer * (kThreads / 64)], cnt[2], npick, nhold, ends[2][kThreads / 64];
+  __shared__ uint32_t tot[kThreads / 64], cnt[2], npick, nhold, ends[2][kThreads / 64];
   __shared__ uint8_t holders[kThreads];
   __shared__ uint2 picked[kPicked];
   int b;
@@ -814,6 +829,7 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
   int j0;
   mid_share(seq, &b, &blk, &j0);
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  j0 += wv * (64 * kMidPer);   // the wave's first score: place_ordered
   const int m = (int)(seq.cu[b + 1] - seq.cu[b]) - keep_tail;
   const uint32_t first = (uint32_t)seq.chunk_start[b], nblk = (uint32_t)seq.chunk_start[b + 1] - first;   // (at most 256)
   const float* sc = scores + seq.cu[b];
@@ -825,7 +841,7 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
   x[0] = cand[t];   // (every sequence here has at least one workgroup, whose words hold 256)
   float v[kMidPer];
 #pragma unroll
-  for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * kThreads + t < m ? sc[j0 + i * kThreads + t] : 0.f;
+  for (int i = 0; i < kMidPer; ++i) v[i] = j0 + 64 * i + lane < m ? sc[j0 + 64 * i + lane] : 0.f;
   uint32_t g0 = (uint32_t)t < blk ? ws.meta[first + t] : 0u;
   for (int i = t; i < kBins; i += kThreads) l.hist[i] = 0u;
   if (t == 0) { cnt[0] = 0u; cnt[1] = 0u; l.n = 0u; npick = 0u; nhold = 0u; }
