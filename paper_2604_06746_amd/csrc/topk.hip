@@ -6,13 +6,14 @@
 // So there are three forms, by the longest sequence (topk_plan):
 //   short (one launch): a workgroup of 1024 threads per sequence, keys in registers; the range between the smallest and
 //     the largest key is cut into 2048 bins, then the k-th largest's bin again, until it is one key.
-//   mid (fused into the scoring kernels: two launches; alone: four):
+//   mid (fused into the scoring kernels: two launches or one; alone: four or three):
 //     [init]    zero the histogram, write the kept window, find from a sample where the k-th largest lies (alone only)
 //     [hist]    histogram over bins that are finest around it (in a layer step the reduce kernel does this)
 //     compact   find the k-th largest's bin; every workgroup counts its scores above the bin and lists those in it -- the
 //               candidates -- or, where these are many, counts them in 1024 sub-bins, for all workgroups and for its own
 //     place     every workgroup resolves the candidates (in registers, bins as in the short form) or the sub-bins down to
 //               the k-th key, counts what the workgroups before it have selected, and writes its own indices
+//     or, up to 16384 scores, direct: the work of both, every workgroup on all scores of its sequence
 //   long: radix select in three digit passes (11/11/10 bits from the top):
 //     init, hist0 (top digit; a layer step's scoring kernels do both), hist1, hist2 (which also publishes the suffix
 //     sums of each workgroup's last-digit histogram), write.
@@ -959,6 +960,109 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
   place_ordered<kThreads, kMidPer>(key, j0, m, T, need, cnt[0], cnt[1], tot, [&](uint32_t at, int j) { out[at] = j; });
 }
 
+// Mid form, up to kDirectSeq scores a sequence: compact and place in one launch.  Every workgroup reads ALL scores of its sequence, a
+// thread sixteen of them in registers: lists the candidates in LDS (or, where they are too many, resolves them where they are), counts what
+// stands before its own share of 1024, and places that.  The launch that it saves is worth 4.5 us, a thread's sixteen scores cost 2.5,
+// 32 of them more than the launch (layer steps of 32 heads on 8, window 8, us in a graph, compact + place / here: 9000 tokens 29.8 / 27.9, 16392
+// 37.1 / 34.7; with 32 scores a thread 24000 tokens 43.5 / 43.4, 32768 48.8 / 49.7).
+constexpr int kDirectList = 4096;
+template <class TAB>
+__global__ __launch_bounds__(kWide) void topk_direct_kernel(const float* __restrict__ scores, TAB seq, int keep_tail, TopkWs ws,
+                                                            int32_t* __restrict__ idx_out) {
+  short_kernel_priority();
+  constexpr int NWV = kWide / 64, PER = kDirectSeq / kWide;
+  static_assert(kMidShare == kWide, "a key of the share per thread");
+  __shared__ ResolveLds l;
+  __shared__ uint32_t list[kDirectList], tot[NWV], cnt[2], listed;
+  int b;
+  uint32_t blk;
+  int j0;
+  mid_share(seq, &b, &blk, &j0);
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int n = (int)(seq.cu[b + 1] - seq.cu[b]), m = n - keep_tail;
+  const float* sc = scores + seq.cu[b];
+  const int w0 = wv * (64 * PER);   // the wave's first score: its round i is scores w0 + 64 i to w0 + 64 i + 63
+  uint32_t key[PER];
+  const bool whole = w0 + 64 * PER <= m;   // (uniform) the wave's scores all exist
+  if (whole) {
+    const float* mine = sc + w0 + lane;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) key[i] = __float_as_uint(mine[64 * i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) key[i] = __float_as_uint(sc[min(w0 + 64 * i + lane, m - 1)]);
+  }
+  const uint32_t own[1] = {score_key(sc[min(j0 + t, m - 1)])};
+  for (int i = t; i < kBins; i += kWide) l.hist[i] = 0u;
+  if (t == 0) { l.n = 0u; listed = 0u; cnt[0] = 0u; cnt[1] = 0u; }
+  const BinTiers tiers = ws.mass > 0.f ? bins_around_mean(ws.mass, n) : bins_around(ws.state[b * 8 + 4]);
+  uint32_t bin, above, in_bin, lo, width;
+  select_bin<kWide, kFineBins>(ws.hist + (size_t)b * 3 * kBins, (uint32_t)seq.k[b], l.scan, l.res, &bin, &above, &in_bin);
+  fine_range(bin, tiers, &lo, &width);
+  const uint32_t krem = (uint32_t)seq.k[b] - above, span = (1u << width) - 1u;
+  // keys (score_key; where no score of the wave has its sign bit set, one instruction instead of five)
+  uint32_t any = 0u;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) any |= key[i];
+  if (__ballot((int)any < 0) == 0ull) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) key[i] |= 0x80000000u;
+  } else {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) key[i] = score_key(__uint_as_float(key[i]));
+  }
+  if (!whole) {   // what does not exist lies below the bin, and below T
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (w0 + 64 * i + lane >= m) key[i] = lo - 1u;   // (a bin from 0 on: the largest key, which no finite score has)
+  }
+  if (in_bin <= (uint32_t)kDirectList) {
+    uint32_t found = 0u;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) found += (uint32_t)__popcll(__ballot(key[i] - lo <= span));
+    uint32_t at = 0u;
+    if (found) {   // (uniform)
+      if (lane == 0) at = atomicAdd(&listed, found);
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const bool c = key[i] - lo <= span;
+        const unsigned long long mc = __ballot(c);
+        if (mc) {
+          if (c) list[at + (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(mc >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mc, 0u))] = key[i];
+          at += (uint32_t)__popcll(mc);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  uint32_t T, need;
+  if (in_bin <= (uint32_t)kDirectList) {
+    resolve_key<kWide>([&](auto f) {
+      for (uint32_t i = t; i < in_bin; i += kWide) f(list[i]);
+    }, lo, (int)width, krem, l, &T, &need);
+  } else {
+    resolve_key<kWide, true>([&](auto f) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (key[i] - lo <= span) f(key[i]);
+    }, lo, (int)width, krem, l, &T, &need);
+  }
+  // keys above and equal to T in the shares before this one, whole rounds of 64
+  uint32_t g = 0u, e = 0u;
+#pragma unroll
+  for (int i = 0; i < PER; ++i)
+    if (w0 + 64 * i < j0) {   // (uniform; all of them lie before the prefix's end)
+      g += (uint32_t)__popcll(__ballot(key[i] > T));
+      e += (uint32_t)__popcll(__ballot(key[i] == T));
+    }
+  if (lane == 0 && g) atomicAdd(&cnt[0], g);
+  if (lane == 0 && e) atomicAdd(&cnt[1], e);
+  __syncthreads();
+  int32_t* out = idx_out + seq.out_off[b];
+  place_ordered<kWide, 1>(own, j0 + wv * 64, m, T, need, cnt[0], cnt[1], tot, [&](uint32_t at, int j) { out[at] = j; });
+}
+
 // The pivot detector's metrics from rows of in-degrees (one per query head) whose histograms over the bins of row_bin have been
 // built by whoever read the rows first.  The sum of a row's kk largest scores takes no placement and no ordered list.  Two kernels:
 //   compact : every workgroup finds the k-th largest key's bin from the row's histogram, adds up its scores ABOVE it (a
@@ -1217,6 +1321,7 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
   ws->mass = 0.f;
   ws->red = nullptr;
   ws->copy = nullptr;
+  ws->direct = longest <= kDirectSeq;
   const int target = ws->mode == kSelMid ? kMidShare : share_target(plan->cu[B]);
   plan->chunk_start[0] = 0;
   for (int b = 0; b < B; ++b) {
@@ -1261,6 +1366,8 @@ hipError_t launch_topk_rest(const float* scores, const SeqTable& plan, int keep_
 #undef SKV_SHORT
     } else if (blocks == 0) {
       return;
+    } else if (ws.mode == kSelMid && ws.direct) {
+      hipLaunchKernelGGL((topk_direct_kernel<T>), dim3(blocks), dim3(kWide), 0, st, scores, tab, keep_tail, ws, idx_out);
     } else if (ws.mode == kSelMid) {
       hipLaunchKernelGGL((topk_compact_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
       hipLaunchKernelGGL((topk_place_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws, idx_out);

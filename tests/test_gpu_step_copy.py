@@ -59,3 +59,33 @@ def test_rows_copied_by_the_selection(lens, ks, tail, form):
         base = (lambda x: x._base if x._base is not None else x)   # (the gaps of a strided destination too)
         assert torch.equal(base(a), base(b))
     assert torch.equal(indeg, sw.indeg) and torch.equal(cen2, cen) and torch.equal(ent, sw.entropy) and torch.equal(enth, sw.entropy_per_head)
+
+
+def _scores(kind, n, g):
+    x = torch.randn(n, generator=g, device="cuda")
+    return {"spread": lambda: torch.exp(0.5 * x) / n, "signed": lambda: torch.where(x.abs() < 0.5, -0.0 * x.abs(), x),
+            "close": lambda: 1.0 + 1e-4 * x, "equal": lambda: torch.full_like(x, 0.25),
+            "two": lambda: torch.where(x > 0, 3.0, 2.0), "zeros": lambda: torch.where(x > 1, x, torch.zeros_like(x))}[kind]()
+
+
+@pytest.mark.parametrize("kind", ["spread", "signed", "close", "equal", "two", "zeros"])
+@pytest.mark.parametrize("lens,tail", [((8193,), 0), ((8200, 100), 8), ((9217, 16384, 12), 0), ((16384 + 32,), 32), ((16385,), 0)])
+def test_selection_of_up_to_16384_scores(lens, tail, kind):
+    """One launch behind the histogram, and the first size that takes two: lists of candidates, too many for a list, ties."""
+    from paper_2604_06746_amd import binding as B
+    g = torch.Generator(device="cuda")
+    g.manual_seed(sum(lens))
+    scores = torch.cat([_scores(kind, n, g) for n in lens])
+    cu = [sum(lens[:i]) for i in range(len(lens) + 1)]
+    ws = torch.empty(B.structkv_workspace_bytes(None, len(lens), cu[-1]), dtype=torch.uint8, device="cuda")
+    for share in (0.0, 1e-4, 0.03, 0.5, 1.0):
+        ks = [int(share * (n - tail)) for n in lens]
+        idx = torch.full((sum(ks) + tail * len(lens) + 1,), -1, dtype=torch.int32, device="cuda")
+        ws.fill_(0x5A)
+        B.structkv_select_topk(scores, cu, ks, tail, idx, ws)
+        want = []
+        for b, n in enumerate(lens):
+            order = torch.argsort(scores[cu[b]:cu[b] + n - tail] + 0.0, descending=True, stable=True)[:ks[b]]
+            want += [order.sort().values, torch.arange(n - tail, n, device="cuda")]
+        torch.cuda.synchronize()
+        assert torch.equal(idx[:-1].long(), torch.cat(want)) and int(idx[-1]) == -1, (share, kind)
