@@ -10,10 +10,10 @@
 // the statistics are per lane and the sum over the 16 rows is four DPP moves inside a row of lanes.
 //   bf16: v_mfma_f32_16x16x32_bf16, two row blocks per workgroup (the keys' way from L2 into the CU is what a workgroup
 //         costs: more rows per key, and half the column-sum planes)
-//   fp32: v_mfma_f32_16x16x4_f32, one row block (n d / 8 cycles of matrix pipe per workgroup bind: more, lighter workgroups)
+//   fp32: one row block (the products bind: more, lighter workgroups), v_mfma_f32_16x16x4_f32 or, of 64 components, bf16 thirds (ThirdsOfRows)
 // Where the line lies (short_plan in api.cpp) and what it measured stands there.
 // What a workgroup takes, by cycle counters: the keys' way into the CU (1500 keys of 256 bytes: 6 of 16 k cycles, 56 bytes a cycle;
-// fp32: the matrix instructions, 256 a SIMD, about 60 cycles each beside everything else), then maxima, sums and column sums, 8 k
+// fp32: the products, 13 of 22 k), then maxima, sums and column sums, 8 k
 // cycles.  Of the latter a third was LDS reads of every wave's maxima and sums by every lane (now a quarter each, exchanged between the
 // rows of lanes) and sums over 16 lanes one at a time (now four together), and before the first tile 4 k cycles of line look-ups for the
 // query operands (now by quads of lanes): a layer step of 1K tokens in fp32 18.0 -> 17.0 us, four short prompts 18.8 -> 16.6 us.
@@ -64,6 +64,69 @@ template <typename T, int D> struct Frag {
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[c][e], b.v[c][e], acc, 0, 0, 0);
       }
+    }
+  }
+};
+
+// One side's eight components of a 16 x 16 x 32 product, by their upper, middle and lower eight bits: x = h + m + l exactly (cut off,
+// not rounded: a finite x stays finite, and what is left after two cuts has eight bits).
+struct Thirds {
+  bf16x8 h, m, l;
+  __device__ __forceinline__ static Thirds of(floatx4 a, floatx4 b) {
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    u32x4 h, m, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float x = i < 2 ? a[2 * i] : b[2 * i - 4], y = i < 2 ? a[2 * i + 1] : b[2 * i - 3];
+      const float x1 = x - upper(x), y1 = y - upper(y), x2 = x1 - upper(x1), y2 = y1 - upper(y1);
+      h[i] = pair(x, y);
+      m[i] = pair(x1, y1);
+      l[i] = pair(x2, y2);
+    }
+    return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+  }
+  __device__ __forceinline__ static float upper(float x) { return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); }
+  __device__ __forceinline__ static uint32_t pair(float x, float y) {
+    return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
+  }
+};
+
+// Query rows of 64 fp32 components as the products' second operand: eight of the nine products of thirds (the ninth is 2^-32 of the
+// whole), the largest and the others summed apart.  The fp32 instruction runs on the vector ALU's multipliers, keeps all waves of the
+// SIMD from them and took 60 cycles for four components; eight of these take 128 for 32, beside the 90 vector instructions that cut up
+// the keys.  Infinities have no thirds and end as NaN: a tile with logits that are not finite is taken again with the fp32
+// instruction.  A layer step of 1K tokens 16.7 -> 15.9 us; its error against 64 bits (2-norm, N(0, 1) inputs with heavy hitters)
+// 1.3e-7 -> 0.8e-7, eight times larger logits 1.6e-6 -> 0.6e-6: 32 products a rounding, not one.  (128 components: the thirds of the queries
+// and the keys' registers do not fit, 24.5 -> 28.2 us.)
+struct ThirdsOfRows {
+  typedef Frag<float, 64> F;
+  static constexpr int STEPS = F::PIECES / 2;
+  Thirds q[STEPS];
+  __device__ __forceinline__ explicit ThirdsOfRows(const F& f) {
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) q[i] = Thirds::of(f.v[2 * i], f.v[2 * i + 1]);
+  }
+  __device__ __forceinline__ void mul(floatx4& acc, const F& k, const float* row) const {   // row: where the lane's components stand
+    floatx4 large = acc, small = {0.f, 0.f, 0.f, 0.f};
+#define SKV_MUL(sum, x, y) sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.x, q[i].y, sum, 0, 0, 0)
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+      const Thirds t = Thirds::of(k.v[2 * i], k.v[2 * i + 1]);
+      SKV_MUL(small, l, m); SKV_MUL(large, h, h);
+      SKV_MUL(small, m, l); SKV_MUL(small, m, m);
+      SKV_MUL(small, l, h); SKV_MUL(small, h, l);
+      SKV_MUL(small, m, h); SKV_MUL(small, h, m);
+    }
+#undef SKV_MUL
+    large += small;
+    const float none = (large[0] - large[0]) + (large[1] - large[1]) + ((large[2] - large[2]) + (large[3] - large[3]));
+    if (__ballot(none != 0.f) != 0ull) {   // (uniform)
+      F f;
+#pragma unroll
+      for (int c = 0; c < F::PIECES; ++c) f.v[c] = *reinterpret_cast<const floatx4*>(row + 4 * c);
+      F::mul(acc, k, f);
+    } else {
+      acc = large;
     }
   }
 };
@@ -150,6 +213,9 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
         for (int x = 0; x < 4; ++x) asm volatile("" : "+v"(qf[rb].v[c + x]));
       }
   }
+  constexpr bool CUT = sizeof(T) == 4 && D == 64 && TW > 2;   // (300 keys, two tiles a wave: 12.1 us in a graph without, 12.3 with)
+  const auto thirds = [&]() __attribute__((always_inline)) { if constexpr (CUT) return ThirdsOfRows(qf[0]); else return 0; }();
+  static_assert(!CUT || NRB == 1, "one row block");
   // (never fewer than two: an array of exactly 32 floats becomes ONE 32-register value, and 400 registers spill)
   floatx4 acc[NRB < 2 ? 2 : NRB][TW];
 #pragma unroll
@@ -170,7 +236,10 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
     for (int rb = 0; rb < NRB; ++rb) acc[rb][i] = floatx4{0.f, 0.f, 0.f, 0.f};
     if (tile0(i) < n) {   // (uniform in the wave)
 #pragma unroll
-      for (int rb = 0; rb < NRB; ++rb) F::mul(acc[rb][i], kf, qf[rb]);
+      for (int rb = 0; rb < NRB; ++rb) {
+        if constexpr (CUT) thirds.mul(acc[rb][i], kf, qg + (int64_t)min(rc * 16 + l16, R - 1) * D + F::PIECES * lg * 4);
+        else F::mul(acc[rb][i], kf, qf[rb]);
+      }
     }
   }
 
