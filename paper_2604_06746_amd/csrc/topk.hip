@@ -683,29 +683,34 @@ __device__ inline void mid_share(const TAB& seq, int* b_out, uint32_t* blk, int*
   *j0 = (int)*blk * kMidShare;
 }
 
+// workgroups of 1024 threads on two shares: what this costs is clearing and merging a histogram per workgroup (131072 scores, the
+// kernel: 256 threads on one share 5.5 us, 1024 on one 4.9, on two 4.5, on four 4.6)
+constexpr int kHistShares = 2;
 template <class TAB>
-__global__ __launch_bounds__(kThreads) void topk_mid_hist_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
-                                                                 TopkWs ws) {
+__global__ __launch_bounds__(kWide) void topk_mid_hist_kernel(const float* __restrict__ scores, TAB seq, int keep_tail, TopkWs ws) {
   short_kernel_priority();
+  static_assert(kMidShare == kWide, "a score of every share per thread");
   __shared__ alignas(8) uint32_t h[kFineBins];
-  int b;
-  uint32_t blk;
-  int j0;
-  mid_share(seq, &b, &blk, &j0);
-  const int t = threadIdx.x;
+  int b = 0, at = (int)blockIdx.x;
+  for (; b + 1 < seq.batch; ++b) {
+    const int wgs = (seq.chunk_start[b + 1] - seq.chunk_start[b] + kHistShares - 1) / kHistShares;
+    if (at < wgs) break;
+    at -= wgs;
+  }
+  const int t = threadIdx.x, j0 = at * (kHistShares * kMidShare);
   const int m = (int)(seq.cu[b + 1] - seq.cu[b]) - keep_tail;
   const float* sc = scores + seq.cu[b];
-  float v[kMidPer];
+  float v[kHistShares];
 #pragma unroll
-  for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * kThreads + t < m ? sc[j0 + i * kThreads + t] : 0.f;
+  for (int i = 0; i < kHistShares; ++i) v[i] = j0 + i * kWide + t < m ? sc[j0 + i * kWide + t] : 0.f;
   const BinTiers tiers = bins_around(ws.state[b * 8 + 4]);
-  for (int i = t; i < kFineBins; i += kThreads) h[i] = 0u;
+  for (int i = t; i < kFineBins; i += kWide) h[i] = 0u;
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < kMidPer; ++i)
-    if (j0 + i * kThreads + t < m) atomicAdd(&h[fine_bin(score_key(v[i]), tiers)], 1u);
+  for (int i = 0; i < kHistShares; ++i)
+    if (j0 + i * kWide + t < m) atomicAdd(&h[fine_bin(score_key(v[i]), tiers)], 1u);
   __syncthreads();
-  merge_bins(h, kFineBins, ws.hist + (size_t)b * 3 * kBins, kThreads);
+  merge_bins(h, kFineBins, ws.hist + (size_t)b * 3 * kBins, kWide);
 }
 
 // Most candidates of a sequence of `nblk` workgroups that are listed; the list lies in the words of their suffix sums.  In an
@@ -1402,7 +1407,9 @@ hipError_t launch_topk(const float* scores, const SeqTable& seq_in, int keep_tai
     using T = std::decay_t<decltype(tab)>;
     if (ws.mode == kSelMid) {
       hipLaunchKernelGGL((topk_mid_init_kernel<T>), dim3((unsigned)seq.batch), dim3(kWide), 0, st, scores, tab, keep_tail, ws, idx_out);
-      if (blocks > 0) hipLaunchKernelGGL((topk_mid_hist_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
+      unsigned hist_wgs = 0;
+      for (int b = 0; b < seq.batch; ++b) hist_wgs += (unsigned)ceil_div(seq.chunk_start[b + 1] - seq.chunk_start[b], kHistShares);
+      if (hist_wgs > 0) hipLaunchKernelGGL((topk_mid_hist_kernel<T>), dim3(hist_wgs), dim3(kWide), 0, st, scores, tab, keep_tail, ws);
     } else if (ws.mode == kSelLong) {
       hipLaunchKernelGGL((topk_init_kernel<T>), dim3(4, seq.batch), dim3(kThreads), 0, st, tab, keep_tail, ws, idx_out);
       if (blocks > 0) hipLaunchKernelGGL((topk_hist0_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
