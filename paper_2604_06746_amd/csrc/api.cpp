@@ -863,6 +863,7 @@ structkv_status structkv_layer_finish(const structkv_shape* shape, const void* k
                                        keep_tail, indeg, idx_out, k_dst, v_dst, dst_stride_head, dst_stride_tok,
                                        workspace, workspace_bytes, &p, &done);
   if (st != STRUCTKV_OK || done) return st;
+  p.tws.beside = 1;
   return layer_finish_impl(shape, p, k, v, kv_stride_head, kv_stride_tok, keep_tail, indeg, idx_out, k_dst, v_dst,
                            dst_stride_head, dst_stride_tok, (hipStream_t)stream);
 }

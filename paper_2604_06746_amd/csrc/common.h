@@ -291,6 +291,7 @@ struct TopkWs {
   uint32_t* meta;    // long: [blocks][2] keys above the 22-bit prefix, keys equal to it; mid: [blocks] keys above the bin
   int mode;          // kSelShort / kSelMid / kSelLong
   int direct;        // mid: one launch behind the histogram (every sequence has at most kDirectSeq scores), not two
+  int beside;        // mid: other layers' scoring is expected to run at the same time (the second half of a layer step)
   float mass;        // > 0: the scores are in-degrees with this sum per sequence (fused layer step)
   const struct ReduceWork* red;   // (host) short: the kernel forms the scores itself (a layer step of short sequences)
   const struct CopyWork* copy;    // (host) or NULL: the last launch copies the kept rows as well (a layer step) ...

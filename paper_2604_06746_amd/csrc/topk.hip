@@ -402,7 +402,7 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* __res
 constexpr int kWide = 1024;        // threads of a short-form workgroup
 static_assert(kReduceShortSeq <= 2 * kWide, "a workgroup that forms the scores holds two per thread");
 constexpr int kMidShare = 1024;    // scores of a mid-form workgroup: four per thread
-constexpr int kMidPer = kMidShare / kThreads;
+
 constexpr int kListed = 64;        // keys that one wave ranks directly
 
 // LDS of resolve_key (select_bin reads the histogram sixteen bytes at a time)
@@ -719,18 +719,23 @@ __global__ __launch_bounds__(kWide) void topk_mid_hist_kernel(const float* __res
 // one the sub-bin's keys have to be picked out of the scores (a layer step of 131072 tokens, window 8, 700 candidates in a
 // bin of 1/256 octave: 43.0 us with the list, 48.3 with sub-bins), which is worth it where the list's words or its time run out.
 __device__ __forceinline__ uint32_t list_cap(uint32_t nblk, uint32_t width) {
-  return width <= (uint32_t)kSubBits ? (uint32_t)kThreads
+  return width <= (uint32_t)kSubBits ? 256u
                                      : min((uint32_t)kCandCap, nblk * (uint32_t)(kSubBins * sizeof(uint16_t) / sizeof(uint2)));
 }
 __device__ __forceinline__ uint16_t* sub_sums(const TopkWs& ws, uint32_t workgroup) {
   return reinterpret_cast<uint16_t*>(ws.suf) + (size_t)workgroup * kSubBins;
 }
 
-template <class TAB>
-__global__ __launch_bounds__(kThreads) void topk_compact_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
+// NT threads a workgroup of compact and place: a thread's share of the histogram, the candidates and the scores is a chain of its own, so
+// 512 threads end sooner than 256 (layer steps of 32K tokens 48.3 -> 47.2 us, a truncation at 128K 96.2 -> 95.0; 1024 are no better).  Not
+// where there are more than 256 workgroups (554K tokens in eight sequences 478 -> 483 us), nor in the second half of a layer step by itself,
+// which runs beside other layers' scoring and gets on the chip the sooner the smaller its workgroups are (32 layers of
+// 128K tokens on four streams 5.20 ms with 256, 5.22 with 512, 5.29 with 1024).
+template <int NT, class TAB>
+__global__ __launch_bounds__(NT) void topk_compact_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
                                                                 TopkWs ws) {
   short_kernel_priority();
-  constexpr int NWV = kThreads / 64, N = kMidPer * NWV;
+  constexpr int NWV = NT / 64, kMidPer = kMidShare / NT, N = kMidPer * NWV;
   __shared__ uint32_t scan[NWV], res[3], wtot[N], gbase, ends[2][NWV];
   __shared__ alignas(8) uint32_t h[kSubBins];
   int b;
@@ -743,12 +748,12 @@ __global__ __launch_bounds__(kThreads) void topk_compact_kernel(const float* __r
   const float* sc = scores + seq.cu[b];
   float v[kMidPer];
 #pragma unroll
-  for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * kThreads + t < m ? sc[j0 + i * kThreads + t] : 0.f;
+  for (int i = 0; i < kMidPer; ++i) v[i] = j0 + i * NT + t < m ? sc[j0 + i * NT + t] : 0.f;
   uint32_t* gh = ws.hist + (size_t)b * 3 * kBins;
   const BinTiers tiers = ws.mass > 0.f ? bins_around_mean(ws.mass, n) : bins_around(ws.state[b * 8 + 4]);
   const uint32_t k = (uint32_t)seq.k[b];
   uint32_t bin, above, in_bin, lo, width;
-  select_bin<kThreads, kFineBins>(gh, k, scan, res, &bin, &above, &in_bin);
+  select_bin<NT, kFineBins>(gh, k, scan, res, &bin, &above, &in_bin);
   fine_range(bin, tiers, &lo, &width);
   const uint32_t hi = lo + ((1u << width) - 1u);
   const bool listed = in_bin <= list_cap(nblk, width);
@@ -763,14 +768,14 @@ __global__ __launch_bounds__(kThreads) void topk_compact_kernel(const float* __r
   unsigned long long mc[kMidPer];
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i) {
-    const bool in = j0 + i * kThreads + t < m;
+    const bool in = j0 + i * NT + t < m;
     key[i] = score_key(v[i]);
     mc[i] = __ballot(in && key[i] >= lo && key[i] <= hi);
     const unsigned long long ma = __ballot(in && key[i] > hi);
     if (lane == 0) wtot[i * NWV + wv] = (uint32_t)__popcll(mc[i]) | ((uint32_t)__popcll(ma) << 16);
   }
   if (!listed)
-    for (int i = t; i < kSubBins; i += kThreads) h[i] = 0u;
+    for (int i = t; i < kSubBins; i += NT) h[i] = 0u;
   __syncthreads();
   const uint32_t own = lane < N ? wtot[lane] : 0u;   // every wave scans the counts for itself
   const uint32_t x = wave_scan(own);
@@ -798,17 +803,16 @@ __global__ __launch_bounds__(kThreads) void topk_compact_kernel(const float* __r
       for (int i = 0; i < NWV; ++i) { inv = max(inv, ends[0][i]); mx = max(mx, ends[1][i]); }
       *reinterpret_cast<uint2*>(gh + kKeyEnds + 2 * blk) = make_uint2(~inv, mx);
     }
-    merge_bins(h, kSubBins, gh + kFineBins, kThreads);
-    static_assert(kSubBins == 4 * kThreads, "four sub-bins a thread");
-    uint32_t c4[4], sum = 0u;
+    merge_bins(h, kSubBins, gh + kFineBins, NT);
+    constexpr int SB = kSubBins / NT;
+    uint32_t cs[SB], sum = 0u;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { c4[i] = h[kSubBins - 1 - (4 * t + i)]; sum += c4[i]; }
+    for (int i = 0; i < SB; ++i) { cs[i] = h[kSubBins - 1 - (SB * t + i)]; sum += cs[i]; }
     uint32_t run;
-    block_excl_scan<kThreads, false>(sum, scan, &run);
+    block_excl_scan<NT, false>(sum, scan, &run);
+    uint16_t* out = sub_sums(ws, blockIdx.x) + kSubBins - 1 - SB * t;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { run += c4[i]; c4[i] = run; }   // (at most the workgroup's 1024 scores)
-    *reinterpret_cast<uint2*>(sub_sums(ws, blockIdx.x) + kSubBins - 4 - 4 * t) =
-        make_uint2(c4[3] | (c4[2] << 16), c4[1] | (c4[0] << 16));
+    for (int i = 0; i < SB; ++i) { run += cs[i]; out[-i] = (uint16_t)run; }   // (at most the workgroup's 1024 scores)
     return;
   }
   __syncthreads();
@@ -820,15 +824,15 @@ __global__ __launch_bounds__(kThreads) void topk_compact_kernel(const float* __r
   }
 }
 
-template <class TAB>
-__global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __restrict__ scores, TAB seq, int keep_tail, TopkWs ws,
+template <int NT, class TAB>
+__global__ __launch_bounds__(NT) void topk_place_kernel(const float* __restrict__ scores, TAB seq, int keep_tail, TopkWs ws,
                                                               int32_t* __restrict__ idx_out) {
   short_kernel_priority();
-  constexpr int CPT = 4;        // candidates a thread keeps in registers; the first is requested before their number is known
-  constexpr int kPicked = CPT * kThreads;   // most keys of a sub-bin that are copied together
+  constexpr int kMidPer = kMidShare / NT, CPT = 4;   // candidates a thread keeps in registers; the first is requested before their number is known
+  constexpr int kPicked = CPT * NT;   // most keys of a sub-bin that are copied together
   __shared__ ResolveLds l;
-  __shared__ uint32_t tot[kThreads / 64], cnt[2], npick, nhold, ends[2][kThreads / 64];
-  __shared__ uint8_t holders[kThreads];
+  __shared__ uint32_t tot[NT / 64], cnt[2], npick, nhold, ends[2][NT / 64];
+  __shared__ uint8_t holders[256];
   __shared__ uint2 picked[kPicked];
   int b;
   uint32_t blk;
@@ -844,12 +848,12 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
   const int width = (int)st[1];
   const uint2* cand = reinterpret_cast<const uint2*>(sub_sums(ws, first));
   uint2 x[CPT];
-  x[0] = cand[t];   // (every sequence here has at least one workgroup, whose words hold 256)
+  x[0] = t < 256 ? cand[t] : make_uint2(0u, 0u);   // (every sequence here has at least one workgroup, whose words hold 256)
   float v[kMidPer];
 #pragma unroll
   for (int i = 0; i < kMidPer; ++i) v[i] = j0 + 64 * i + lane < m ? sc[j0 + 64 * i + lane] : 0.f;
   uint32_t g0 = (uint32_t)t < blk ? ws.meta[first + t] : 0u;
-  for (int i = t; i < kBins; i += kThreads) l.hist[i] = 0u;
+  for (int i = t; i < kBins; i += NT) l.hist[i] = 0u;
   if (t == 0) { cnt[0] = 0u; cnt[1] = 0u; l.n = 0u; npick = 0u; nhold = 0u; }
   __syncthreads();
   uint32_t T, need, e0 = 0u;
@@ -858,10 +862,10 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
     auto each = [&](auto f) {
 #pragma unroll
       for (int r = 0; r < CPT; ++r)
-        if ((uint32_t)(r * kThreads + t) < count) f(x[r]);
-      for (uint32_t i = CPT * kThreads + t; i < count; i += kThreads) f(more[i]);
+        if ((uint32_t)(r * NT + t) < count) f(x[r]);
+      for (uint32_t i = CPT * NT + t; i < count; i += NT) f(more[i]);
     };
-    resolve_key<kThreads>([&](auto f) { each([&](uint2 e) { f(e.x); }); }, from, bits, krem_, l, &T, &need);
+    resolve_key<NT>([&](auto f) { each([&](uint2 e) { f(e.x); }); }, from, bits, krem_, l, &T, &need);
     each([&](uint2 e) {
       g0 += e.y < blk && e.x > T;
       e0 += e.y < blk && e.x == T;
@@ -869,13 +873,14 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
   };
   if (c <= list_cap(nblk, (uint32_t)width)) {
 #pragma unroll
-    for (int r = 1; r < CPT; ++r) x[r] = (uint32_t)(r * kThreads + t) < c ? cand[r * kThreads + t] : make_uint2(0u, 0u);
+    for (int r = 0; r < CPT; ++r)
+      if (r > 0 || t >= 256) x[r] = (uint32_t)(r * NT + t) < c ? cand[r * NT + t] : make_uint2(0u, 0u);
     resolve_entries(cand, c, lo, width, krem);
   } else {
     const uint32_t* sub = ws.hist + (size_t)b * 3 * kBins + kFineBins;
     const int sh = width - kSubBits;
     uint32_t s, above, in_sub;
-    select_bin<kThreads, kSubBins>(sub, krem, l.scan, l.res, &s, &above, &in_sub);
+    select_bin<NT, kSubBins>(sub, krem, l.scan, l.res, &s, &above, &in_sub);
     const uint32_t ksub = krem - above, from = lo + (s << sh);
     uint32_t mine = 0u;   // keys of the sub-bin in workgroup t's scores
     if ((uint32_t)t < nblk) {
@@ -902,13 +907,13 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
       if (lane == 0) { ends[0][wv] = inv; ends[1][wv] = mx; }
       __syncthreads();
 #pragma unroll
-      for (int i = 0; i < kThreads / 64; ++i) { inv = max(inv, ends[0][i]); mx = max(mx, ends[1][i]); }
+      for (int i = 0; i < NT / 64; ++i) { inv = max(inv, ends[0][i]); mx = max(mx, ends[1][i]); }
       const uint32_t nh = nhold;
       // f(key, workgroup), a wave to the scores of kAtOnce workgroups
       auto visit = [&](auto f) {
         constexpr uint32_t kAtOnce = 4;
         constexpr int PER = kMidShare / 64;
-        for (uint32_t i0 = wv * kAtOnce; i0 < nh; i0 += kAtOnce * (kThreads / 64)) {
+        for (uint32_t i0 = wv * kAtOnce; i0 < nh; i0 += kAtOnce * (NT / 64)) {
           float y[kAtOnce][PER];
           int u[kAtOnce];
 #pragma unroll
@@ -943,10 +948,10 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
         visit([&](uint32_t q, uint32_t u) { picked[atomicAdd(&npick, 1u)] = make_uint2(q, u); });
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < CPT; ++r) x[r] = picked[r * kThreads + t];
+        for (int r = 0; r < CPT; ++r) x[r] = picked[r * NT + t];
         resolve_entries(picked, in_sub, from, sh, ksub);
       } else {
-        resolve_key<kThreads, true>([&](auto f) { visit([&](uint32_t q, uint32_t) { f(q); }); }, from, sh, ksub, l, &T, &need);
+        resolve_key<NT, true>([&](auto f) { visit([&](uint32_t q, uint32_t) { f(q); }); }, from, sh, ksub, l, &T, &need);
         visit([&](uint32_t q, uint32_t u) {
           g0 += u < blk && q > T;
           e0 += u < blk && q == T;
@@ -962,7 +967,7 @@ __global__ __launch_bounds__(kThreads) void topk_place_kernel(const float* __res
   for (int i = 0; i < kMidPer; ++i) key[i] = score_key(v[i]);
   __syncthreads();
   int32_t* out = idx_out + seq.out_off[b];
-  place_ordered<kThreads, kMidPer>(key, j0, m, T, need, cnt[0], cnt[1], tot, [&](uint32_t at, int j) { out[at] = j; });
+  place_ordered<NT, kMidPer>(key, j0, m, T, need, cnt[0], cnt[1], tot, [&](uint32_t at, int j) { out[at] = j; });
 }
 
 // Mid form, up to kDirectSeq scores a sequence: compact and place in one launch.  Every workgroup reads ALL scores of its sequence, a
@@ -1326,6 +1331,7 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
   ws->mass = 0.f;
   ws->red = nullptr;
   ws->copy = nullptr;
+  ws->beside = 0;
   ws->direct = longest <= kDirectSeq;
   const int target = ws->mode == kSelMid ? kMidShare : share_target(plan->cu[B]);
   plan->chunk_start[0] = 0;
@@ -1374,8 +1380,11 @@ hipError_t launch_topk_rest(const float* scores, const SeqTable& plan, int keep_
     } else if (ws.mode == kSelMid && ws.direct) {
       hipLaunchKernelGGL((topk_direct_kernel<T>), dim3(blocks), dim3(kWide), 0, st, scores, tab, keep_tail, ws, idx_out);
     } else if (ws.mode == kSelMid) {
-      hipLaunchKernelGGL((topk_compact_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
-      hipLaunchKernelGGL((topk_place_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws, idx_out);
+#define SKV_MID(NT)                                                                                                          \
+  hipLaunchKernelGGL((topk_compact_kernel<NT, T>), dim3(blocks), dim3(NT), 0, st, scores, tab, keep_tail, ws);                \
+  hipLaunchKernelGGL((topk_place_kernel<NT, T>), dim3(blocks), dim3(NT), 0, st, scores, tab, keep_tail, ws, idx_out)
+      if (ws.beside || blocks > 256) { SKV_MID(256); } else { SKV_MID(512); }
+#undef SKV_MID
     } else {
       hipLaunchKernelGGL((topk_hist1_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
       hipLaunchKernelGGL((topk_hist2_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);
