@@ -1079,7 +1079,7 @@ __global__ __launch_bounds__(kWide) void topk_direct_kernel(const float* __restr
 //             partial sum per workgroup, fixed order) and appends its scores IN it -- the candidates -- to the row's
 //             list (one integer atomic per workgroup reserves the place; the order of the list differs from run to
 //             run, and nothing below depends on it);
-//   select  : one workgroup of 1024 threads per row takes the candidates (the first 32768 in registers), finds the remaining
+//   select  : one workgroup of 512 or 1024 threads per row takes the candidates (the first 16384 or 32768 in registers), finds the remaining
 //             bits 11 at a time with histograms in LDS, and adds the candidates above the k-th key T as integers (they share
 //             their exponent: exact, whatever the order), `krem` copies of T's own value for the ties, and the
 //             partial sums; also the row's variance.  The workgroup that ends last forms the means over the rows.
@@ -1091,8 +1091,11 @@ __device__ inline float key_score(uint32_t key) {
 }
 
 constexpr int kCompThreads = 512;             // the compact kernel
-constexpr int kSelThreads = 1024;             // the select kernel: sixteen waves per row
-constexpr int kCandPerThread = 32;            // candidates one of its threads keeps in registers (32768 in all)
+// Threads of the select kernel, a workgroup per row: up to 32768 keys mostly a few hundred candidates, for which eight waves meet at a barrier
+// sooner than sixteen (32 heads, window 8, us a call: 2048 keys 26.0 -> 25.3, 32K 44.7 -> 44.1); beyond, diffuse rows have thousands, and
+// with half as many threads to them calls of 128K keys take 132 -> 135 us at a window of 32, 183 -> 188 at 64.
+inline int mass_select_threads(int64_t n) { return n <= 32768 ? 512 : 1024; }
+constexpr int kCandPerThread = 32;            // candidates one of its threads keeps in registers
 constexpr int kFewPerThread = 2;              // ... where no thread has more
 
 __global__ __launch_bounds__(kCompThreads) void mass_compact_kernel(const float* __restrict__ rows, int64_t n, uint32_t kk,
@@ -1157,10 +1160,9 @@ __global__ __launch_bounds__(kCompThreads) void mass_compact_kernel(const float*
 // The `krem`-th largest of c0 candidates, all of whose keys are T plus `bits` open ones: T and krem become that key and how
 // many copies of it count; returns the calling thread's share of the significands above it.  PER candidates a thread are kept
 // in registers, any others read again on each pass.
-template <int PER>
+template <int NT, int PER>
 __device__ inline unsigned long long resolve_row(const float* __restrict__ c, uint32_t c0, uint32_t bits, uint32_t* hh /*[kBins]*/,
                                                  uint32_t* scan, uint32_t* res, uint32_t& T, uint32_t& krem) {
-  constexpr int NT = kSelThreads;
   const int t = threadIdx.x;
   float v[PER];
 #pragma unroll
@@ -1198,7 +1200,8 @@ __device__ inline unsigned long long resolve_row(const float* __restrict__ c, ui
   return acc;
 }
 
-__global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* __restrict__ cand, int64_t n, int w, uint32_t at,
+template <int NT>
+__global__ __launch_bounds__(NT) void mass_select_kernel(const float* __restrict__ cand, int64_t n, int w, uint32_t at,
                                                                   uint32_t* __restrict__ hist,
                                                                   const uint32_t* __restrict__ state,
                                                                   const float* __restrict__ part_above,
@@ -1206,7 +1209,6 @@ __global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* _
                                                                   float* __restrict__ sums, float* __restrict__ sparsity,
                                                                   float* __restrict__ variance) {
   short_kernel_priority();
-  constexpr int NT = kSelThreads;
   __shared__ uint32_t hh[kBins];
   __shared__ uint32_t scan[NT / 64];
   __shared__ uint32_t res[3];
@@ -1224,8 +1226,8 @@ __global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* _
   row_bin_range(bin, at, &T, &bits);
   // few candidates: no long row of steps that find nothing (32K tokens, window 8: 10.2 us without, 6.9 with;
   // 128K, window 64: 12.5 and 8.5)
-  unsigned long long acc = c0 <= (uint32_t)(kFewPerThread * NT) ? resolve_row<kFewPerThread>(c, c0, bits, hh, scan, res, T, krem)
-                                                                      : resolve_row<kCandPerThread>(c, c0, bits, hh, scan, res, T, krem);
+  unsigned long long acc = c0 <= (uint32_t)(kFewPerThread * NT) ? resolve_row<NT, kFewPerThread>(c, c0, bits, hh, scan, res, T, krem)
+                                                                      : resolve_row<NT, kCandPerThread>(c, c0, bits, hh, scan, res, T, krem);
   const uint32_t expo = (T >> 23) & 0xFFu;            // biased exponent (scores are non-negative)
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -1399,8 +1401,11 @@ hipError_t launch_pivot_mass(const ReduceWork& red, uint32_t kk, uint32_t at, ui
   const int P = pivot_shares(red.total);
   hipLaunchKernelGGL(mass_compact_kernel, dim3((unsigned)P, (unsigned)red.Hq), dim3(kCompThreads), 0, st, red.colsum, red.total, kk,
                      at, hist, state, cand, part_above);
-  hipLaunchKernelGGL(mass_select_kernel, dim3((unsigned)red.Hq), dim3(kSelThreads), 0, st, cand, red.total, red.w, at, hist, state,
-                     part_above, var_part, P, sums, sparsity, variance);
+#define SKV_SELECT(NT)                                                                                                          \
+  hipLaunchKernelGGL((mass_select_kernel<NT>), dim3((unsigned)red.Hq), dim3(NT), 0, st, cand, red.total, red.w, at, hist, state, \
+                     part_above, var_part, P, sums, sparsity, variance)
+  if (mass_select_threads(red.total) == 512) SKV_SELECT(512); else SKV_SELECT(1024);
+#undef SKV_SELECT
   return hipGetLastError();
 }
 
