@@ -4,7 +4,7 @@
 //
 // These kernels move a few bytes per score; launches, dependent memory round trips and barriers are what they cost.
 // So there are three forms, by the longest sequence (topk_plan):
-//   short (one launch): a workgroup of 1024 threads per sequence, keys in registers; the range between the smallest and
+//   short (one launch): a workgroup of 1024 threads per sequence (several where they also copy the kept rows), keys in registers; the range between the smallest and
 //     the largest key is cut into 2048 bins, then the k-th largest's bin again, until it is one key.
 //   mid (fused into the scoring kernels: two launches or one; alone: four or three):
 //     [init]    zero the histogram, write the kept window, find from a sample where the k-th largest lies (alone only)
