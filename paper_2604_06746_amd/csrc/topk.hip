@@ -138,14 +138,27 @@ __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* sh /*[>= THREAD
   return (uint32_t)__builtin_amdgcn_readlane((int)s, NWV - 1);
 }
 
+// What select_bin reads, sixteen bytes at a time where a thread has four bins or more: a histogram in LDS, whose type carries the
+// alignment (a plain array of words is promised four bytes), or a merged one in the workspace, whose carve keeps it.
+template <int NB>
+struct alignas(16) LdsBins {
+  uint32_t n[NB];
+  __device__ __forceinline__ uint32_t& operator[](uint32_t i) { return n[i]; }
+};
+struct MergedBins {
+  const uint32_t* n;   // 16-byte aligned
+};
+static_assert(3 * kBins % 4 == 0 && kRowWords % 4 == 0, "every sequence's and every row's histogram keeps the workspace's alignment");
+
 // Scan the NB bins of a histogram from the top until `krem` (1 .. their sum) keys are covered.
 // Returns the bin (all threads), how many keys lie above it and how many in it.
-// Two barriers; `scan` and `res` must not be written again before another one.  gh: 16-byte aligned where a thread has four
-// bins or more.
-template <int THREADS, int NB>
-__device__ inline void select_bin(const uint32_t* __restrict__ gh, uint32_t krem, uint32_t* scan /*[>= THREADS / 64]*/,
+// Two barriers; `scan` and `res` must not be written again before another one.
+template <int THREADS, int NB, class Bins>
+__device__ inline void select_bin(const Bins& bins, uint32_t krem, uint32_t* scan /*[>= THREADS / 64]*/,
                                   uint32_t* res /*[3]*/, uint32_t* bin_out, uint32_t* above_out, uint32_t* in_bin_out = nullptr) {
+  static_assert(std::is_same_v<Bins, LdsBins<NB>> || std::is_same_v<Bins, MergedBins>, "bins that are 16-byte aligned");
   constexpr int PER = NB / THREADS;
+  const uint32_t* __restrict__ gh = bins.n;
   static_assert(NB % THREADS == 0, "bins split evenly over the threads");
   const int t = threadIdx.x;
   uint32_t mine[PER];   // bins NB-1-PER*t downwards
@@ -245,7 +258,7 @@ __global__ __launch_bounds__(kThreads) void topk_hist1_kernel(const float* __res
   const bool fast = preload_strided(s, v);
   for (int i = t; i < kBins; i += kThreads) h[i] = 0u;
   uint32_t bin0, above0;
-  select_bin<kThreads, kBins>(gh, (uint32_t)seq.k[s.b], scan, res, &bin0, &above0);   // its barriers cover h[] = 0
+  select_bin<kThreads, kBins>(MergedBins{gh}, (uint32_t)seq.k[s.b], scan, res, &bin0, &above0);   // its barriers cover h[] = 0
   if (s.blk == 0 && t == 0) {
     ws.state[s.b * 8 + 0] = bin0;
     ws.state[s.b * 8 + 1] = (uint32_t)seq.k[s.b] - above0;
@@ -274,7 +287,7 @@ __global__ __launch_bounds__(kThreads) void topk_hist2_kernel(const float* __res
   if (t == 0) above_cnt = 0u;
   const uint32_t bin0 = ws.state[s.b * 8 + 0], krem0 = ws.state[s.b * 8 + 1];
   uint32_t bin1, above1;
-  select_bin<kThreads, kBins>(gh + kBins, krem0, scan, res, &bin1, &above1);   // its barriers cover h[], above_cnt = 0
+  select_bin<kThreads, kBins>(MergedBins{gh + kBins}, krem0, scan, res, &bin1, &above1);   // its barriers cover h[], above_cnt = 0
   const uint32_t prefix = (bin0 << 11) | bin1;     // the top 22 bits of the k-th largest key
   if (s.blk == 0 && t == 0) {
     ws.state[s.b * 8 + 2] = prefix;
@@ -333,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* __res
   const uint2 m0 = has0 ? *reinterpret_cast<const uint2*>(ws.meta + 2 * ((size_t)s.first + t)) : make_uint2(0u, 0u);
   const uint32_t prefix = ws.state[s.b * 8 + 2], krem1 = ws.state[s.b * 8 + 3];
   uint32_t t10, above2;
-  select_bin<kThreads, kLowBins>(gh + 2 * kBins, krem1, scan, res, &t10, &above2);   // its barriers cover cnt[] = 0
+  select_bin<kThreads, kLowBins>(MergedBins{gh + 2 * kBins}, krem1, scan, res, &t10, &above2);   // its barriers cover cnt[] = 0
   const uint32_t T = (prefix << 10) | t10;   // the k-th largest key
   const uint32_t need = krem1 - above2;      // how many keys equal to T are taken (lowest indices first)
 
@@ -405,13 +418,12 @@ constexpr int kMidShare = 1024;    // scores of a mid-form workgroup: four per t
 
 constexpr int kListed = 64;        // keys that one wave ranks directly
 
-// LDS of resolve_key (select_bin reads the histogram sixteen bytes at a time)
+// LDS of resolve_key
 struct ResolveLds {
-  alignas(16) uint32_t hist[kBins];
+  LdsBins<kBins> hist;
   uint32_t list[kListed];
   uint32_t scan[16], res[3], n;
 };
-static_assert(alignof(ResolveLds) >= 16 && offsetof(ResolveLds, hist) == 0, "select_bin's 16-byte reads");
 
 // One more in h[bin] for every calling lane; lanes that share one of two values add up first (an LDS atomic of 64 lanes on one
 // word takes 64 turns: 131072 equal scores, 100 us a sweep).
@@ -442,7 +454,7 @@ __device__ inline void resolve_key(Each each, uint32_t lo, int width, uint32_t k
       const uint32_t off = key - lo;
       if (rem == width || (off >> rem) == prefix) {
         const uint32_t at = (off >> sh) & ((1u << bits) - 1u);
-        if constexpr (TIES) count_ties(l.hist, at); else atomicAdd(&l.hist[at], 1u);
+        if constexpr (TIES) count_ties(l.hist.n, at); else atomicAdd(&l.hist[at], 1u);
       }
     });
     __syncthreads();
@@ -640,7 +652,7 @@ __global__ __launch_bounds__(kWide) void topk_mid_init_kernel(const float* __res
                                                               TopkWs ws, int32_t* __restrict__ idx_out) {
   short_kernel_priority();
   constexpr int NWV = kWide / 64;
-  __shared__ uint32_t h[kBins];
+  __shared__ LdsBins<kBins> h;
   __shared__ uint32_t scan[NWV], res[3], ends[2][NWV];
   const int b = blockIdx.x, t = threadIdx.x;
   const int64_t m = seq.cu[b + 1] - seq.cu[b] - keep_tail;
@@ -753,7 +765,7 @@ __global__ __launch_bounds__(NT) void topk_compact_kernel(const float* __restric
   const BinTiers tiers = ws.mass > 0.f ? bins_around_mean(ws.mass, n) : bins_around(ws.state[b * 8 + 4]);
   const uint32_t k = (uint32_t)seq.k[b];
   uint32_t bin, above, in_bin, lo, width;
-  select_bin<NT, kFineBins>(gh, k, scan, res, &bin, &above, &in_bin);
+  select_bin<NT, kFineBins>(MergedBins{gh}, k, scan, res, &bin, &above, &in_bin);
   fine_range(bin, tiers, &lo, &width);
   const uint32_t hi = lo + ((1u << width) - 1u);
   const bool listed = in_bin <= list_cap(nblk, width);
@@ -880,7 +892,7 @@ __global__ __launch_bounds__(NT) void topk_place_kernel(const float* __restrict_
     const uint32_t* sub = ws.hist + (size_t)b * 3 * kBins + kFineBins;
     const int sh = width - kSubBits;
     uint32_t s, above, in_sub;
-    select_bin<NT, kSubBins>(sub, krem, l.scan, l.res, &s, &above, &in_sub);
+    select_bin<NT, kSubBins>(MergedBins{sub}, krem, l.scan, l.res, &s, &above, &in_sub);
     const uint32_t ksub = krem - above, from = lo + (s << sh);
     uint32_t mine = 0u;   // keys of the sub-bin in workgroup t's scores
     if ((uint32_t)t < nblk) {
@@ -1007,7 +1019,7 @@ __global__ __launch_bounds__(kWide) void topk_direct_kernel(const float* __restr
   if (t == 0) { l.n = 0u; listed = 0u; cnt[0] = 0u; cnt[1] = 0u; }
   const BinTiers tiers = ws.mass > 0.f ? bins_around_mean(ws.mass, n) : bins_around(ws.state[b * 8 + 4]);
   uint32_t bin, above, in_bin, lo, width;
-  select_bin<kWide, kFineBins>(ws.hist + (size_t)b * 3 * kBins, (uint32_t)seq.k[b], l.scan, l.res, &bin, &above, &in_bin);
+  select_bin<kWide, kFineBins>(MergedBins{ws.hist + (size_t)b * 3 * kBins}, (uint32_t)seq.k[b], l.scan, l.res, &bin, &above, &in_bin);
   fine_range(bin, tiers, &lo, &width);
   const uint32_t krem = (uint32_t)seq.k[b] - above, span = (1u << width) - 1u;
   // keys (score_key; where no score of the wave has its sign bit set, one instruction instead of five)
@@ -1121,7 +1133,7 @@ __global__ __launch_bounds__(kCompThreads) void mass_compact_kernel(const float*
   if (t == 0) cnt = 0u;
   uint32_t* gh = hist + (size_t)h * kRowWords;
   uint32_t t0, above0;
-  select_bin<NT, kBins>(gh, kk, scan, res, &t0, &above0);   // its barriers cover cnt = 0
+  select_bin<NT, kBins>(MergedBins{gh}, kk, scan, res, &t0, &above0);   // its barriers cover cnt = 0
   float sum = 0.f;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
@@ -1161,7 +1173,7 @@ __global__ __launch_bounds__(kCompThreads) void mass_compact_kernel(const float*
 // many copies of it count; returns the calling thread's share of the significands above it.  PER candidates a thread are kept
 // in registers, any others read again on each pass.
 template <int NT, int PER>
-__device__ inline unsigned long long resolve_row(const float* __restrict__ c, uint32_t c0, uint32_t bits, uint32_t* hh /*[kBins]*/,
+__device__ inline unsigned long long resolve_row(const float* __restrict__ c, uint32_t c0, uint32_t bits, LdsBins<kBins>& hh,
                                                  uint32_t* scan, uint32_t* res, uint32_t& T, uint32_t& krem) {
   const int t = threadIdx.x;
   float v[PER];
@@ -1209,7 +1221,7 @@ __global__ __launch_bounds__(NT) void mass_select_kernel(const float* __restrict
                                                                   float* __restrict__ sums, float* __restrict__ sparsity,
                                                                   float* __restrict__ variance) {
   short_kernel_priority();
-  __shared__ uint32_t hh[kBins];
+  __shared__ LdsBins<kBins> hh;
   __shared__ uint32_t scan[NT / 64];
   __shared__ uint32_t res[3];
   __shared__ unsigned long long red64[NT / 64];
@@ -1249,7 +1261,7 @@ __global__ __launch_bounds__(NT) void mass_select_kernel(const float* __restrict
   }
   __syncthreads();
   if (done != (uint32_t)(H - 1)) return;   // (uniform) the last one adds the rows up, in row order
-  float* row = reinterpret_cast<float*>(hh);
+  float* row = reinterpret_cast<float*>(hh.n);
   static_assert(2 * kMaxBatch <= kBins, "the sums of all rows fit");
   for (int i = t; i < 2 * H; i += NT) row[i] = __hip_atomic_load(&sums[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
