@@ -68,8 +68,9 @@ template <typename T, int D> struct Frag {
   }
 };
 
-// One side's eight components of a 16 x 16 x 32 product, by their upper, middle and lower eight bits: x = h + m + l exactly (cut off,
-// not rounded: a finite x stays finite, and what is left after two cuts has eight bits).
+// One side's eight components of a 16 x 16 x 32 product, by their upper, middle and lower eight bits: x = h + m + l (cut off,
+// not rounded: a finite x stays finite, and what is left after two cuts has eight bits).  Exactly so from 2^-110 on; below, the lower third
+// loses the bits under 2^-133, where bf16 numbers end.
 struct Thirds {
   bf16x8 h, m, l;
   __device__ __forceinline__ static Thirds of(floatx4 a, floatx4 b) {
@@ -86,18 +87,27 @@ struct Thirds {
     return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
   }
   __device__ __forceinline__ static float upper(float x) { return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); }
+  // the bits of x that the lower third has no place for
+  __device__ __forceinline__ static uint32_t lost(float x) {
+    const float x1 = x - upper(x);
+    return __float_as_uint(x1 - upper(x1)) & 0xFFFFu;
+  }
   __device__ __forceinline__ static uint32_t pair(float x, float y) {
     return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
   }
 };
 
-// Query rows of 64 fp32 components as the products' second operand: eight of the nine products of thirds (the ninth is 2^-32 of the
-// whole), the largest and the others summed apart.  The fp32 instruction runs on the vector ALU's multipliers, keeps all waves of the
+// Query rows of 64 fp32 components as the products' second operand: eight of the nine products of thirds (the ninth is at most 2^-30 of
+// the whole), the largest and the others summed apart.  The fp32 instruction runs on the vector ALU's multipliers, keeps all waves of the
 // SIMD from them and took 60 cycles for four components; eight of these take 128 for 32, beside the 90 vector instructions that cut up
-// the keys.  Infinities have no thirds and end as NaN: a tile with logits that are not finite is taken again with the fp32
-// instruction.  A layer step of 1K tokens 16.7 -> 15.9 us; its error against 64 bits (2-norm, N(0, 1) inputs with heavy hitters)
+// the keys.  A layer step of 1K tokens 16.7 -> 15.9 us; its error against 64 bits (2-norm, N(0, 1) inputs with heavy hitters)
 // 1.3e-7 -> 0.8e-7, eight times larger logits 1.6e-6 -> 0.6e-6: 32 products a rounding, not one.  (128 components: the thirds of the queries
 // and the keys' registers do not fit, 24.5 -> 28.2 us.)
+// The fp32 instruction takes a tile again whose logits are not finite (infinities have no thirds and end as NaN), and all tiles where what
+// the lower third loses of numbers below 2^-110 may matter.  Of a key that is less than 2^-133 a component, and with queries (times the
+// scale) below 2^90 less than 2^-37 of 64 products together: nothing to an exponent in fp32.  So the queries alone decide: larger ones,
+// or such as lose something themselves.  One wave looks at them, and the others hear of it behind the barrier of the rows' maxima (0.1 us
+// a layer step; every wave asking its queries 0.27, its keys 0.4).
 struct ThirdsOfRows {
   typedef Frag<float, 64> F;
   static constexpr int STEPS = F::PIECES / 2;
@@ -105,6 +115,25 @@ struct ThirdsOfRows {
   __device__ __forceinline__ explicit ThirdsOfRows(const F& f) {
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) q[i] = Thirds::of(f.v[2 * i], f.v[2 * i + 1]);
+  }
+  // whether products of these rows (all of the wave's) and tiny numbers need the fp32 instruction
+  __device__ __forceinline__ static bool inexact(const F& f, float c2) {
+    uint32_t lost = 0u;
+    float most = 0.f;
+#pragma unroll
+    for (int c = 0; c < F::PIECES; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lost |= Thirds::lost(f.v[c][e]);
+        most = fmaxf(most, fabsf(f.v[c][e]));
+      }
+    return __ballot(lost != 0u || most * fmaxf(c2, 1.f) >= 0x1p90f) != 0ull;
+  }
+  __device__ __forceinline__ static F operand(const float* row) {
+    F f;
+#pragma unroll
+    for (int c = 0; c < F::PIECES; ++c) f.v[c] = *reinterpret_cast<const floatx4*>(row + 4 * c);
+    return f;
   }
   __device__ __forceinline__ void mul(floatx4& acc, const F& k, const float* row) const {   // row: where the lane's components stand
     floatx4 large = acc, small = {0.f, 0.f, 0.f, 0.f};
@@ -121,10 +150,7 @@ struct ThirdsOfRows {
     large += small;
     const float none = (large[0] - large[0]) + (large[1] - large[1]) + ((large[2] - large[2]) + (large[3] - large[3]));
     if (__ballot(none != 0.f) != 0ull) {   // (uniform)
-      F f;
-#pragma unroll
-      for (int c = 0; c < F::PIECES; ++c) f.v[c] = *reinterpret_cast<const floatx4*>(row + 4 * c);
-      F::mul(acc, k, f);
+      F::mul(acc, k, operand(row));
     } else {
       acc = large;
     }
@@ -216,6 +242,13 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
   constexpr bool CUT = sizeof(T) == 4 && D == 64 && TW > 2;   // (300 keys, two tiles a wave: 12.1 us in a graph without, 12.3 with)
   const auto thirds = [&]() __attribute__((always_inline)) { if constexpr (CUT) return ThirdsOfRows(qf[0]); else return 0; }();
   static_assert(!CUT || NRB == 1, "one row block");
+  __shared__ int again;   // all tiles with the fp32 instruction
+  if constexpr (CUT)
+    if (wave == 1) {
+      const bool inexact = ThirdsOfRows::inexact(qf[0], c2);
+      if (lane == 0) again = inexact;
+    }
+  auto q_row = [&]() __attribute__((always_inline)) { return qg + (int64_t)min(rc * 16 + l16, R - 1) * D + F::PIECES * lg * (16 / (int)sizeof(T)); };
   // (never fewer than two: an array of exactly 32 floats becomes ONE 32-register value, and 400 registers spill)
   floatx4 acc[NRB < 2 ? 2 : NRB][TW];
 #pragma unroll
@@ -237,7 +270,7 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
     if (tile0(i) < n) {   // (uniform in the wave)
 #pragma unroll
       for (int rb = 0; rb < NRB; ++rb) {
-        if constexpr (CUT) thirds.mul(acc[rb][i], kf, qg + (int64_t)min(rc * 16 + l16, R - 1) * D + F::PIECES * lg * 4);
+        if constexpr (CUT) thirds.mul(acc[rb][i], kf, q_row());
         else F::mul(acc[rb][i], kf, qf[rb]);
       }
     }
@@ -250,31 +283,54 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
     return causal ? n - w + row - w * (int)__umulhi((uint32_t)row, w_recip) + 1 : n;
   };
   float M[NRB], Z[NRB], E[NRB];
+  auto wave_maxima = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int rb = 0; rb < NRB; ++rb) {
-    const int lim = seen((rc * NRB + rb) * 16 + l16);
-    float m = -INFINITY;
+    for (int rb = 0; rb < NRB; ++rb) {
+      const int lim = seen((rc * NRB + rb) * 16 + l16);
+      float m = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < TW; ++i) {
-      if (!has(i)) break;
-      if (masked(i)) {
+      for (int i = 0; i < TW; ++i) {
+        if (!has(i)) break;
+        if (masked(i)) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (tile0(i) + 4 * lg + j >= lim) acc[rb][i][j] = -INFINITY;
+          for (int j = 0; j < 4; ++j)
+            if (tile0(i) + 4 * lg + j >= lim) acc[rb][i][j] = -INFINITY;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m = fmaxf(m, acc[rb][i][j]);
       }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) m = fmaxf(m, acc[rb][i][j]);
+      m = over_groups(m, [](float x, float y) { return fmaxf(x, y); });
+      if (lg == 0) sM[wave][rb * 16 + l16] = m;
     }
-    m = over_groups(m, [](float x, float y) { return fmaxf(x, y); });
-    if (lg == 0) sM[wave][rb * 16 + l16] = m;
-  }
+  };
+  auto row_maxima = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+      float m = sM[lg][rb * 16 + l16];   // (each row of lanes reads a quarter of the waves': the reads were what the phase took)
+#pragma unroll
+      for (int v = 4; v < kWaves; v += 4) m = fmaxf(m, sM[v + lg][rb * 16 + l16]);
+      M[rb] = over_groups(m, [](float x, float y) { return fmaxf(x, y); }) * c2;
+    }
+  };
+  wave_maxima();
   __syncthreads();
+  row_maxima();
+  if constexpr (CUT)
+    if (__builtin_amdgcn_readfirstlane(again) != 0) {   // (the same for all waves)
+      const F qr = ThirdsOfRows::operand(q_row());
+#pragma unroll
+      for (int i = 0; i < TW; ++i) {
+        acc[0][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (tile0(i) < n)
+          F::mul(acc[0][i], ThirdsOfRows::operand(kg + (int64_t)min(tile0(i) + l16, n - 1) * kst + F::PIECES * lg * 4), qr);
+      }
+      __syncthreads();   // (the maxima have been read)
+      wave_maxima();
+      __syncthreads();
+      row_maxima();
+    }
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) {
-    float m = sM[lg][rb * 16 + l16];   // (each row of lanes reads a quarter of the waves': the reads were what the phase took)
-#pragma unroll
-    for (int v = 4; v < kWaves; v += 4) m = fmaxf(m, sM[v + lg][rb * 16 + l16]);
-    M[rb] = over_groups(m, [](float x, float y) { return fmaxf(x, y); }) * c2;
     float z = 0.f, e = 0.f;
 #pragma unroll
     for (int i = 0; i < TW; ++i) {

@@ -48,3 +48,44 @@ def test_products_by_thirds(H, G, w, n, causal, values):
     if values == "infinite":   # (an entropy term of 0 times infinity is not a number)
         return
     assert float((sw.entropy_per_head[0].double() - ent).norm() / ent.norm()) < 2e-6
+
+
+@pytest.mark.parametrize("side", ["keys", "queries"])
+@pytest.mark.parametrize("exponent", [60, 89, 91, 108, 112, 115, 118, 122, 124])
+def test_products_by_thirds_of_tiny_operands(side, exponent):
+    """One side so small that its lower thirds, or all of them, lie below the smallest bf16 number, the other as much larger: the same
+    logits, and the same tolerance.  The small side holds zeros and ordinary numbers too.  (The fp32 instruction takes over at 2^90.)"""
+    from paper_2604_06746_amd.sweep import LayerSweep
+    H, G, w, n = 8, 2, 8, 900
+    g = torch.Generator(device="cuda")
+    g.manual_seed(exponent)
+    q = torch.randn(H, w, 64, generator=g, device="cuda")
+    k = torch.randn(G, n, 64, generator=g, device="cuda")
+    up = torch.full((64,), float(exponent), device="cuda")
+    up[::7] = 0.0                       # (components that both sides have in full)
+    up = torch.exp2(up)
+    k[:, ::5, ::3] = 0.0
+    q, k = (q * up, k / up) if side == "keys" else (q / up, k * up)
+    sw = LayerSweep(H, G, 64, w, torch.float32, [n], [n // 8])
+    sw.score(q[None].contiguous(), k)
+    torch.cuda.synchronize()
+    D, ent = _exact(q, k, w, False)
+    assert float((sw.indeg.double() - D).norm() / D.norm()) < 2e-6
+    assert float((sw.entropy_per_head[0].double() - ent).norm() / ent.norm()) < 2e-6
+
+
+def test_products_by_thirds_of_tiny_keys_under_a_large_scale():
+    from paper_2604_06746_amd import binding as B
+    from paper_2604_06746_amd.sweep import LayerSweep
+    H, G, w, n = 8, 2, 8, 900
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    q = torch.randn(H, w, 64, generator=g, device="cuda")
+    k = torch.randn(G, n, 64, generator=g, device="cuda") * 2.0 ** -118
+    sw = LayerSweep(H, G, 64, w, torch.float32, [n], [n // 8])
+    shape = B.make_shape(H, G, 64, w, B.STRUCTKV_DTYPE_F32, scale=2.0 ** 115)   # (2^118 / 8)
+    B.structkv_score_layer(shape, q[None].contiguous(), k, sw.cu, sw.indeg, sw.entropy, sw.entropy_per_head, sw.workspace)
+    torch.cuda.synchronize()
+    D, ent = _exact(q, k * 2.0 ** 118, w, False)
+    assert float((sw.indeg.double() - D).norm() / D.norm()) < 2e-6
+    assert float((sw.entropy_per_head[0].double() - ent).norm() / ent.norm()) < 2e-6
