@@ -1091,7 +1091,7 @@ __global__ __launch_bounds__(kWide) void topk_direct_kernel(const float* __restr
 //             partial sum per workgroup, fixed order) and appends its scores IN it -- the candidates -- to the row's
 //             list (one integer atomic per workgroup reserves the place; the order of the list differs from run to
 //             run, and nothing below depends on it);
-//   select  : one workgroup of 512 or 1024 threads per row takes the candidates (the first 16384 or 32768 in registers), finds the remaining
+//   select  : one workgroup per row takes the candidates (the first 32768 in registers), finds the remaining
 //             bits 11 at a time with histograms in LDS, and adds the candidates above the k-th key T as integers (they share
 //             their exponent: exact, whatever the order), `krem` copies of T's own value for the ties, and the
 //             partial sums; also the row's variance.  The workgroup that ends last forms the means over the rows.
@@ -1103,10 +1103,8 @@ __device__ inline float key_score(uint32_t key) {
 }
 
 constexpr int kCompThreads = 512;             // the compact kernel
-// Threads of the select kernel, a workgroup per row: up to 32768 keys mostly a few hundred candidates, for which eight waves meet at a barrier
-// sooner than sixteen (32 heads, window 8, us a call: 2048 keys 26.0 -> 25.3, 32K 44.7 -> 44.1); beyond, diffuse rows have thousands, and
-// with half as many threads to them calls of 128K keys take 132 -> 135 us at a window of 32, 183 -> 188 at 64.
-inline int mass_select_threads(int64_t n) { return n <= 32768 ? 512 : 1024; }
+constexpr int kSelThreads = 1024;             // the select kernel: sixteen waves per row ...
+constexpr int kSelFew = 512;                  // ... of which eight end at once where they are enough for the candidates
 constexpr int kCandPerThread = 32;            // candidates one of its threads keeps in registers
 constexpr int kFewPerThread = 2;              // ... where no thread has more
 
@@ -1212,8 +1210,12 @@ __device__ inline unsigned long long resolve_row(const float* __restrict__ c, ui
   return acc;
 }
 
-template <int NT>
-__global__ __launch_bounds__(NT) void mass_select_kernel(const float* __restrict__ cand, int64_t n, int w, uint32_t at,
+// Few candidates: no long row of steps that find nothing (32K tokens, window 8: 10.2 us without, 6.9 with; 128K, window 64: 12.5
+// and 8.5), and up to a thousand of them eight waves, which meet at a barrier sooner than sixteen (a barrier waits for the waves
+// that have not ended).  How many there are the row decides and not its length: of a flat row all keys are candidates, of others a
+// hundredth (32 heads, window 8, us a call in a graph with sixteen waves / eight up to 32768 keys / here: 2048 keys 26.7 / 25.8 / 25.5,
+// 32K 45.4 / 44.7 / 44.2; flat rows 32.0 / 32.3 / 31.4 and 113.4 / 117.9 / 112.7).
+__global__ __launch_bounds__(kSelThreads) void mass_select_kernel(const float* __restrict__ cand, int64_t n, int w, uint32_t at,
                                                                   uint32_t* __restrict__ hist,
                                                                   const uint32_t* __restrict__ state,
                                                                   const float* __restrict__ part_above,
@@ -1221,6 +1223,7 @@ __global__ __launch_bounds__(NT) void mass_select_kernel(const float* __restrict
                                                                   float* __restrict__ sums, float* __restrict__ sparsity,
                                                                   float* __restrict__ variance) {
   short_kernel_priority();
+  constexpr int NT = kSelThreads;
   __shared__ LdsBins<kBins> hh;
   __shared__ uint32_t scan[NT / 64];
   __shared__ uint32_t res[3];
@@ -1232,14 +1235,19 @@ __global__ __launch_bounds__(NT) void mass_select_kernel(const float* __restrict
   uint32_t krem = state[h * 4 + 1];
   const uint32_t c0 = hist[(size_t)h * kRowWords + kBins];   // candidates = keys in that bin
   const float* c = cand + (int64_t)h * n;
-  float pa = 0.f, pv = 0.f;
-  for (int p = t; p < P; p += NT) { pa += part_above[(int64_t)h * P + p]; pv += var_part[(int64_t)h * P + p]; }
+  const float* pas = part_above + (int64_t)h * P;
+  const float* pvs = var_part + (int64_t)h * P;
+  float pa = t < P ? pas[t] : 0.f, pv = t < P ? pvs[t] : 0.f;
+  const bool few = c0 <= (uint32_t)(kFewPerThread * kSelFew);   // (uniform)
+  const int threads = few ? kSelFew : NT, waves = threads / 64;
+  if (t >= threads) return;
+  for (int p = t + threads; p < P; p += threads) { pa += pas[p]; pv += pvs[p]; }
   uint32_t T, bits;
   row_bin_range(bin, at, &T, &bits);
-  // few candidates: no long row of steps that find nothing (32K tokens, window 8: 10.2 us without, 6.9 with;
-  // 128K, window 64: 12.5 and 8.5)
-  unsigned long long acc = c0 <= (uint32_t)(kFewPerThread * NT) ? resolve_row<NT, kFewPerThread>(c, c0, bits, hh, scan, res, T, krem)
-                                                                      : resolve_row<NT, kCandPerThread>(c, c0, bits, hh, scan, res, T, krem);
+  unsigned long long acc;
+  if (few) acc = resolve_row<kSelFew, kFewPerThread>(c, c0, bits, hh, scan, res, T, krem);
+  else if (c0 <= (uint32_t)(kFewPerThread * NT)) acc = resolve_row<NT, kFewPerThread>(c, c0, bits, hh, scan, res, T, krem);
+  else acc = resolve_row<NT, kCandPerThread>(c, c0, bits, hh, scan, res, T, krem);
   const uint32_t expo = (T >> 23) & 0xFFu;            // biased exponent (scores are non-negative)
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -1252,7 +1260,7 @@ __global__ __launch_bounds__(NT) void mass_select_kernel(const float* __restrict
   if (t == 0) {
     unsigned long long a = 0ull;
     float sa = 0.f, sv = 0.f;
-    for (int i = 0; i < NT / 64; ++i) { a += red64[i]; sa += redf[i]; sv += redv[i]; }
+    for (int i = 0; i < waves; ++i) { a += red64[i]; sa += redf[i]; sv += redv[i]; }
     const double m = ldexp((double)a, (int)(expo ? expo : 1u) - 150) + (double)krem * (double)key_score(T) + (double)sa;
     __hip_atomic_store(&sums[2 * h], sv / (float)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&sums[2 * h + 1], (float)m * (1.0f / (float)w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1263,7 +1271,7 @@ __global__ __launch_bounds__(NT) void mass_select_kernel(const float* __restrict
   if (done != (uint32_t)(H - 1)) return;   // (uniform) the last one adds the rows up, in row order
   float* row = reinterpret_cast<float*>(hh.n);
   static_assert(2 * kMaxBatch <= kBins, "the sums of all rows fit");
-  for (int i = t; i < 2 * H; i += NT) row[i] = __hip_atomic_load(&sums[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int i = t; i < 2 * H; i += threads) row[i] = __hip_atomic_load(&sums[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (t == 0) {
     float vt = 0.f, rt = 0.f;
@@ -1413,11 +1421,8 @@ hipError_t launch_pivot_mass(const ReduceWork& red, uint32_t kk, uint32_t at, ui
   const int P = pivot_shares(red.total);
   hipLaunchKernelGGL(mass_compact_kernel, dim3((unsigned)P, (unsigned)red.Hq), dim3(kCompThreads), 0, st, red.colsum, red.total, kk,
                      at, hist, state, cand, part_above);
-#define SKV_SELECT(NT)                                                                                                          \
-  hipLaunchKernelGGL((mass_select_kernel<NT>), dim3((unsigned)red.Hq), dim3(NT), 0, st, cand, red.total, red.w, at, hist, state, \
-                     part_above, var_part, P, sums, sparsity, variance)
-  if (mass_select_threads(red.total) == 512) SKV_SELECT(512); else SKV_SELECT(1024);
-#undef SKV_SELECT
+  hipLaunchKernelGGL(mass_select_kernel, dim3((unsigned)red.Hq), dim3(kSelThreads), 0, st, cand, red.total, red.w, at, hist, state,
+                     part_above, var_part, P, sums, sparsity, variance);
   return hipGetLastError();
 }
 

@@ -246,9 +246,9 @@ def test_pivot_metrics_in_long_key_chunks(sweep_mod, oracle, Hq, G, w, n, causal
 
 
 # the top-k mass of the per-head rows: shares of 4096 scores and their remainders; scores within a few per cent (the fine bins),
-# over many octaves (a threshold among the quarter octaves), and all equal (one bin holds the row: more candidates than the
-# registers take at 40000).  sharp scales the queries.
-@pytest.mark.parametrize("n", [64, 4095, 4096, 4097, 9000, 40000])
+# over many octaves (a threshold among the quarter octaves), and all equal (one bin holds the row: as many candidates as keys, around
+# what eight and sixteen waves hold two a thread, and more than the registers take, 32768).  sharp scales the queries.
+@pytest.mark.parametrize("n", [64, 1024, 1025, 2048, 2049, 4095, 4096, 4097, 9000, 16385, 32768, 32769, 40000])
 @pytest.mark.parametrize("sharp", [0.0, 0.2, 1.0, 12.0])
 def test_pivot_rows(sweep_mod, oracle, n, sharp):
     Hq, G, d, w = 4, 2, 64, 32
