@@ -161,7 +161,8 @@ __device__ inline uint32_t score_key(float f) {
 enum { kSelShort = 0, kSelMid = 1, kSelLong = 2 };
 constexpr int kShortSeq = 8192;
 constexpr int kMidSeq = 262144;
-constexpr int kDirectSeq = 16384;   // ... of which up to here one launch behind the histogram (topk_direct_kernel)
+constexpr int kDirectSeq = 16384;   // ... of which up to here one launch behind the histogram (topk_direct_kernel), where ...
+constexpr int kDirectBlocks = 256;  // ... no more workgroups than this read a whole sequence each
 
 // Bins of the mid form, ascending with the keys, in four tiers of 1024: half octaves over all keys; around a centre 16 octaves
 // in bins of 1/64 instead, four octaves in bins of 1/256, and an eighth of an octave in bins of 1/8192.  Even bins of 1/128
@@ -290,7 +291,7 @@ struct TopkWs {
                      //      the words of a sequence's workgroups, its candidates (key, workgroup)
   uint32_t* meta;    // long: [blocks][2] keys above the 22-bit prefix, keys equal to it; mid: [blocks] keys above the bin
   int mode;          // kSelShort / kSelMid / kSelLong
-  int direct;        // mid: one launch behind the histogram (every sequence has at most kDirectSeq scores), not two
+  int direct;        // mid: one launch behind the histogram (at most kDirectSeq scores a sequence, kDirectBlocks workgroups), not two
   int beside;        // mid: other layers' scoring is expected to run at the same time (the second half of a layer step)
   float mass;        // > 0: the scores are in-degrees with this sum per sequence (fused layer step)
   const struct ReduceWork* red;   // (host) short: the kernel forms the scores itself (a layer step of short sequences)

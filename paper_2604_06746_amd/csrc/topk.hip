@@ -986,8 +986,12 @@ __global__ __launch_bounds__(NT) void topk_place_kernel(const float* __restrict_
 // thread sixteen of them in registers: lists the candidates in LDS (or, where they are too many, resolves them where they are), counts what
 // stands before its own share of 1024, and places that.  The launch that it saves is worth 4.5 us, a thread's sixteen scores cost 2.5,
 // 32 of them more than the launch (layer steps of 32 heads on 8, window 8, us in a graph, compact + place / here: 9000 tokens 29.8 / 27.9, 16392
-// 37.1 / 34.7; with 32 scores a thread 24000 tokens 43.5 / 43.4, 32768 48.8 / 49.7).
-constexpr int kDirectList = 4096;
+// 37.1 / 34.7; with 32 scores a thread 24000 tokens 43.5 / 43.4, 32768 48.8 / 49.7).  Also beside other layers: 13 layers of 9000 to 16384
+// tokens on four streams 32 / 29 us a layer.  The workgroups' own share of the work is a sixteenth, which costs nothing while each has a CU
+// to itself and more than the launch beyond kDirectBlocks of them (selections alone, us in a graph: 8 x 16000 scores 15.9 / 14.7, 17 x 9000
+// 19.0 / 17.5, 17 x 16000 -- 272 workgroups -- 19.3 / 19.2, 32 x 12000 24.3 / 25.1, 64 x 9000 36.3 / 41.4, 64 x 16000 43.5 / 52.6).
+constexpr int kDirectList = 4096;   // candidates that are listed; more are resolved where they are ...
+constexpr int kDirectFew = 512;     // ... and above this many they are expected to be equal (16000 scores, 3200 of them equal, 16.2 -> 14.2 us)
 template <class TAB>
 __global__ __launch_bounds__(kWide) void topk_direct_kernel(const float* __restrict__ scores, TAB seq, int keep_tail, TopkWs ws,
                                                             int32_t* __restrict__ idx_out) {
@@ -1059,15 +1063,19 @@ __global__ __launch_bounds__(kWide) void topk_direct_kernel(const float* __restr
   }
   __syncthreads();
   uint32_t T, need;
-  if (in_bin <= (uint32_t)kDirectList) {
+  if (in_bin <= (uint32_t)kDirectFew) {
     resolve_key<kWide>([&](auto f) {
       for (uint32_t i = t; i < in_bin; i += kWide) f(list[i]);
     }, lo, (int)width, krem, l, &T, &need);
-  } else {
+  } else {   // a crowd: mostly ties
     resolve_key<kWide, true>([&](auto f) {
+      if (in_bin <= (uint32_t)kDirectList) {
+        for (uint32_t i = t; i < in_bin; i += kWide) f(list[i]);
+      } else {
 #pragma unroll
-      for (int i = 0; i < PER; ++i)
-        if (key[i] - lo <= span) f(key[i]);
+        for (int i = 0; i < PER; ++i)
+          if (key[i] - lo <= span) f(key[i]);
+      }
     }, lo, (int)width, krem, l, &T, &need);
   }
   // keys above and equal to T in the shares before this one, whole rounds of 64
@@ -1354,7 +1362,6 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
   ws->red = nullptr;
   ws->copy = nullptr;
   ws->beside = 0;
-  ws->direct = longest <= kDirectSeq;
   const int target = ws->mode == kSelMid ? kMidShare : share_target(plan->cu[B]);
   plan->chunk_start[0] = 0;
   for (int b = 0; b < B; ++b) {
@@ -1364,6 +1371,7 @@ void topk_plan(const SeqTable& seq_in, int keep_tail, void* wsp, SeqTable* plan,
     plan->chunk_start[b + 1] = plan->chunk_start[b] + (int)nblk;
   }
   *blocks = (unsigned)plan->chunk_start[B];
+  ws->direct = longest <= kDirectSeq && *blocks <= (unsigned)kDirectBlocks;
   const size_t nb = max_blocks(B, plan->cu[B]);   // sum of ceil(m_b / target) <= total / target + B: blocks <= nb (long), 2 nb (mid)
   const size_t Bz = (size_t)(B > 0 ? B : 1);
   uint8_t* p = (uint8_t*)wsp;

@@ -64,14 +64,17 @@ def test_rows_copied_by_the_selection(lens, ks, tail, form):
 def _scores(kind, n, g):
     x = torch.randn(n, generator=g, device="cuda")
     return {"spread": lambda: torch.exp(0.5 * x) / n, "signed": lambda: torch.where(x.abs() < 0.5, -0.0 * x.abs(), x),
-            "close": lambda: 1.0 + 1e-4 * x, "equal": lambda: torch.full_like(x, 0.25),
+            "close": lambda: 1.0 + 1e-4 * x, "plateau": lambda: torch.where(x.abs() < 0.13, 0.0 * x, x),
+            "equal": lambda: torch.full_like(x, 0.25),
             "two": lambda: torch.where(x > 0, 3.0, 2.0), "zeros": lambda: torch.where(x > 1, x, torch.zeros_like(x))}[kind]()
 
 
-@pytest.mark.parametrize("kind", ["spread", "signed", "close", "equal", "two", "zeros"])
-@pytest.mark.parametrize("lens,tail", [((8193,), 0), ((8200, 100), 8), ((9217, 16384, 12), 0), ((16384 + 32,), 32), ((16385,), 0)])
+@pytest.mark.parametrize("kind", ["spread", "signed", "close", "plateau", "equal", "two", "zeros"])
+@pytest.mark.parametrize("lens,tail", [((8193,), 0), ((8200, 100), 8), ((9217, 16384, 12), 0), ((16384 + 32,), 32), ((16385,), 0),
+                                       ((8193, 5) * 5 + (16000,), 0), ((8193,) * 28, 0), ((8193,) * 29, 0)])
 def test_selection_of_up_to_16384_scores(lens, tail, kind):
-    """One launch behind the histogram, and the first size that takes two: lists of candidates, too many for a list, ties."""
+    """One launch behind the histogram, and the first size that takes two: lists of candidates, a tenth of the scores equal (a list of
+    ties), too many for a list.  More sequences than the small table holds; as many workgroups (9 a sequence) as one launch takes, and more."""
     from paper_2604_06746_amd import binding as B
     g = torch.Generator(device="cuda")
     g.manual_seed(sum(lens))
