@@ -695,34 +695,38 @@ __device__ inline void mid_share(const TAB& seq, int* b_out, uint32_t* blk, int*
   *j0 = (int)*blk * kMidShare;
 }
 
-// workgroups of 1024 threads on two shares: what this costs is clearing and merging a histogram per workgroup (131072 scores, the
-// kernel: 256 threads on one share 5.5 us, 1024 on one 4.9, on two 4.5, on four 4.6)
-constexpr int kHistShares = 2;
+// Workgroups of 512 threads on two shares: what this costs is clearing and merging a histogram per workgroup, and where there are many,
+// finding its sequence (one after the other, 64 x 17000 scores took 47.3 us in a graph, a sequence per lane 32.6).  Selections alone, us
+// in a graph, 256 threads on one share / 512 on one / 512 on two / 1024 on two: 131072 scores 16.5 / 15.8 / 14.8 / 14.9, 8 x 32768
+// 16.3 / 15.8 / 15.3 / 15.5, 64 x 17000 34.5 / 34.7 / 32.6 / 33.8, 8 x 262144 38.2 / 39.2 / 30.7 / 32.2.
+constexpr int kHistThreads = 512, kHistShares = 2;
 template <class TAB>
-__global__ __launch_bounds__(kWide) void topk_mid_hist_kernel(const float* __restrict__ scores, TAB seq, int keep_tail, TopkWs ws) {
+__global__ __launch_bounds__(kHistThreads) void topk_mid_hist_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
+                                                                     TopkWs ws) {
   short_kernel_priority();
-  static_assert(kMidShare == kWide, "a score of every share per thread");
+  constexpr int NT = kHistThreads, PER = kHistShares * kMidShare / NT;
   __shared__ alignas(8) uint32_t h[kFineBins];
-  int b = 0, at = (int)blockIdx.x;
-  for (; b + 1 < seq.batch; ++b) {
-    const int wgs = (seq.chunk_start[b + 1] - seq.chunk_start[b] + kHistShares - 1) / kHistShares;
-    if (at < wgs) break;
-    at -= wgs;
-  }
+  // the sequence and the number inside it, a sequence per lane
+  static_assert(kMaxBatch <= 64, "a wave holds all sequences");
+  const int lane = threadIdx.x & 63;
+  const int wgs = lane < seq.batch ? (seq.chunk_start[lane + 1] - seq.chunk_start[lane] + kHistShares - 1) / kHistShares : 0;
+  const uint32_t ends = wave_scan((uint32_t)wgs);
+  const int b = __popcll(__ballot(lane < seq.batch && ends <= blockIdx.x));
+  const int at = (int)blockIdx.x - (b ? __builtin_amdgcn_readlane((int)ends, b - 1) : 0);
   const int t = threadIdx.x, j0 = at * (kHistShares * kMidShare);
   const int m = (int)(seq.cu[b + 1] - seq.cu[b]) - keep_tail;
   const float* sc = scores + seq.cu[b];
-  float v[kHistShares];
+  float v[PER];
 #pragma unroll
-  for (int i = 0; i < kHistShares; ++i) v[i] = j0 + i * kWide + t < m ? sc[j0 + i * kWide + t] : 0.f;
+  for (int i = 0; i < PER; ++i) v[i] = j0 + i * NT + t < m ? sc[j0 + i * NT + t] : 0.f;
   const BinTiers tiers = bins_around(ws.state[b * 8 + 4]);
-  for (int i = t; i < kFineBins; i += kWide) h[i] = 0u;
+  for (int i = t; i < kFineBins; i += NT) h[i] = 0u;
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < kHistShares; ++i)
-    if (j0 + i * kWide + t < m) atomicAdd(&h[fine_bin(score_key(v[i]), tiers)], 1u);
+  for (int i = 0; i < PER; ++i)
+    if (j0 + i * NT + t < m) atomicAdd(&h[fine_bin(score_key(v[i]), tiers)], 1u);
   __syncthreads();
-  merge_bins(h, kFineBins, ws.hist + (size_t)b * 3 * kBins, kWide);
+  merge_bins(h, kFineBins, ws.hist + (size_t)b * 3 * kBins, NT);
 }
 
 // Most candidates of a sequence of `nblk` workgroups that are listed; the list lies in the words of their suffix sums.  In an
@@ -987,9 +991,9 @@ __global__ __launch_bounds__(NT) void topk_place_kernel(const float* __restrict_
 // stands before its own share of 1024, and places that.  The launch that it saves is worth 4.5 us, a thread's sixteen scores cost 2.5,
 // 32 of them more than the launch (layer steps of 32 heads on 8, window 8, us in a graph, compact + place / here: 9000 tokens 29.8 / 27.9, 16392
 // 37.1 / 34.7; with 32 scores a thread 24000 tokens 43.5 / 43.4, 32768 48.8 / 49.7).  Also beside other layers: 13 layers of 9000 to 16384
-// tokens on four streams 32 / 29 us a layer.  The workgroups' own share of the work is a sixteenth, which costs nothing while each has a CU
-// to itself and more than the launch beyond kDirectBlocks of them (selections alone, us in a graph: 8 x 16000 scores 15.9 / 14.7, 17 x 9000
-// 19.0 / 17.5, 17 x 16000 -- 272 workgroups -- 19.3 / 19.2, 32 x 12000 24.3 / 25.1, 64 x 9000 36.3 / 41.4, 64 x 16000 43.5 / 52.6).
+// tokens on four streams 24 / 22 us a layer.  A workgroup's own share of the work is a sixteenth, which costs nothing while each has a CU
+// to itself and more than the launch beyond kDirectBlocks of them (selections alone, us in a graph: 8 x 16000 scores 14.9 / 13.9, 17 x 9000
+// 16.6 / 15.0, 17 x 16000 -- 272 workgroups -- 17.3 / 17.2, 32 x 12000 20.1 / 20.7, 64 x 9000 25.3 / 30.1, 64 x 16000 30.7 / 40.0).
 constexpr int kDirectList = 4096;   // candidates that are listed; more are resolved where they are ...
 constexpr int kDirectFew = 512;     // ... and above this many they are expected to be equal (16000 scores, 3200 of them equal, 16.2 -> 14.2 us)
 template <class TAB>
@@ -1448,7 +1452,8 @@ hipError_t launch_topk(const float* scores, const SeqTable& seq_in, int keep_tai
       hipLaunchKernelGGL((topk_mid_init_kernel<T>), dim3((unsigned)seq.batch), dim3(kWide), 0, st, scores, tab, keep_tail, ws, idx_out);
       unsigned hist_wgs = 0;
       for (int b = 0; b < seq.batch; ++b) hist_wgs += (unsigned)ceil_div(seq.chunk_start[b + 1] - seq.chunk_start[b], kHistShares);
-      if (hist_wgs > 0) hipLaunchKernelGGL((topk_mid_hist_kernel<T>), dim3(hist_wgs), dim3(kWide), 0, st, scores, tab, keep_tail, ws);
+      if (hist_wgs > 0)
+        hipLaunchKernelGGL((topk_mid_hist_kernel<T>), dim3(hist_wgs), dim3(kHistThreads), 0, st, scores, tab, keep_tail, ws);
     } else if (ws.mode == kSelLong) {
       hipLaunchKernelGGL((topk_init_kernel<T>), dim3(4, seq.batch), dim3(kThreads), 0, st, tab, keep_tail, ws, idx_out);
       if (blocks > 0) hipLaunchKernelGGL((topk_hist0_kernel<T>), dim3(blocks), dim3(kThreads), 0, st, scores, tab, keep_tail, ws);

@@ -71,10 +71,12 @@ def _scores(kind, n, g):
 
 @pytest.mark.parametrize("kind", ["spread", "signed", "close", "plateau", "equal", "two", "zeros"])
 @pytest.mark.parametrize("lens,tail", [((8193,), 0), ((8200, 100), 8), ((9217, 16384, 12), 0), ((16384 + 32,), 32), ((16385,), 0),
-                                       ((8193, 5) * 5 + (16000,), 0), ((8193,) * 28, 0), ((8193,) * 29, 0)])
+                                       ((8193, 5) * 5 + (16000,), 0), ((8193,) * 28, 0), ((8193,) * 29, 0),
+                                       ((17000, 8, 9000) * 21 + (33000,), 8)])
 def test_selection_of_up_to_16384_scores(lens, tail, kind):
     """One launch behind the histogram, and the first size that takes two: lists of candidates, a tenth of the scores equal (a list of
-    ties), too many for a list.  More sequences than the small table holds; as many workgroups (9 a sequence) as one launch takes, and more."""
+    ties), too many for a list.  More sequences than the small table holds; as many workgroups (9 a sequence) as one launch takes, and more;
+    the most sequences, some of which have no workgroup, odd and even numbers of shares."""
     from paper_2604_06746_amd import binding as B
     g = torch.Generator(device="cuda")
     g.manual_seed(sum(lens))
