@@ -114,7 +114,11 @@ def make_shape(n_q_heads: int, n_kv_heads: int, head_dim: int, window: int, dtyp
 
 # What a call costs on the host is part of its time: a layer step of a few hundred tokens takes the GPU 11 us.  Pointers and streams
 # go to ctypes as plain integers (its argument types convert them), arrays of budgets and offsets straight from the sequence, and the
-# current stream's handle comes without a Stream object around it: 18.0 -> 12.0 us a step with its two launches.
+# current stream's handle comes without a Stream object around it (through a function of torch's own that a build may lack; then with
+# one): 18.0 -> 12.0 us a step with its two launches.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _host_i64(values: Sequence[int]):
     try:
         return (_i64 * len(values))(*values)
@@ -128,7 +132,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream(stream):
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

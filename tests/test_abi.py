@@ -186,6 +186,20 @@ def test_binding_raises_with_message(B):
     assert e.value.status == B.STRUCTKV_ERR_INVALID_ARG and "divide" in str(e.value)
 
 
+def test_current_stream_without_torchs_raw_getter(B, monkeypatch):
+    """The binding takes the current stream's handle from a function that torch keeps to itself; where there is none, from its Stream."""
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x5EED))
+    again = types.ModuleType("binding_again")
+    again.__file__ = B.__file__
+    exec(compile(open(B.__file__).read(), B.__file__, "exec"), again.__dict__)
+    assert again._stream(None) == 0x5EED and again._stream(types.SimpleNamespace(cuda_stream=7)) == 7 and again._stream(9) == 9
+
+
 def test_transition_scores_hand_values(B):
     # Eq. 7-9 is host arithmetic in the library: checked against values worked out by hand (see the same cases,
     # with the working, in test_oracle_pins.py), not against the oracle's implementation of the same formulas
