@@ -147,3 +147,28 @@ LONG_CHUNKS = [(40, 1, 64, [6000, 95, 96, 97, 128, 160, 161, 289], 0), (40, 1, 6
 # 224 to 416 keys (7 to 13 tiles, the last three of a chunk written directly, the others collected in LDS), their last ones ragged.
 LONG_CHUNKS_PIVOT = [(37, 1, 64, 9665), (3, 1, 64, 105236), (45, 1, 32, 13550), (45, 1, 32, 17435), (50, 1, 16, 16658), (34, 2, 16, 82703),
                      (50, 1, 8, 25019), (50, 1, 8, 98911)]
+
+
+# Layer steps whose selection copies the kept rows itself, and those that are too much for it: (query heads, KV heads, head_dim, dtype),
+# lengths, budgets, kept window, tensors, workgroups per sequence (0: the gather kernel copies), most 16-byte units of a workgroup.
+_S = (8, 2, 64, "bf16")   # 32 units a row
+STEP_COPY = [
+    (_S, (1000,), (100,), 8, 2, 4, 27 * 32),
+    (_S, (33, 1500, 64), (1, 700, 0), 8, 2, 23, 31 * 32),             # fewer rows than workgroups, a window alone
+    (_S, (2048,), (2040,), 8, 2, 64, 32 * 32),                        # everything kept
+    (_S, (8, 8, 8), (0, 0, 0), 8, 2, 1, 8 * 32),                      # nothing but the window
+    (_S, (4000, 5000), (800, 3), 32, 2, 26, 32 * 32),
+    (_S, (8192,), (6000,), 0, 2, 188, 32 * 32),                       # many workgroups, a unit a thread; no window
+    (_S, (8192 + 32,) * 3, (7000, 10, 100), 32, 2, 85, 83 * 32),      # 85 workgroups a sequence, three units a thread
+    (_S, tuple(range(200, 200 + 12 * 37, 37)), tuple(range(3, 3 + 12 * 9, 9)), 8, 2, 4, 28 * 32),   # more sequences than the small table holds
+    ((4, 1, 64, "bf16"), (2000,), (500,), 8, 1, 4, 127 * 8),          # one (tensor, head) pair: no division
+    ((6, 3, 64, "bf16"), (3000, 40), (1100, 17), 8, 2, 52, 22 * 48),  # six of them, and three
+    ((6, 3, 64, "bf16"), (3000, 40), (1100, 17), 8, 1, 26, 43 * 24),
+    ((5, 5, 128, "f32"), (1500,), (333,), 8, 2, 107, 4 * 320),        # ten, rows of 512 bytes
+    ((8, 8, 64, "bf16"), (2100,) * 8, (2000,) * 7 + (11,), 8, 2, 32, 63 * 128),   # eight units a thread: the copy's second trip
+    ((8, 8, 64, "bf16"), (2200,) * 8, (2100,) * 7 + (11,), 8, 2, 0, 0),           # more than that
+    ((2, 1, 16, "bf16"), (700,), (504,), 8, 1, 1, 512 * 2),           # the most rows of a workgroup
+    ((2, 1, 8, "bf16"), (700,), (504,), 8, 1, 1, 512),
+    ((2, 1, 8, "bf16"), (700,), (505,), 8, 1, 0, 0),                  # one more
+    ((2, 1, 24, "bf16"), (700,), (200,), 8, 1, 0, 0),                 # units of a row not a power of two
+]

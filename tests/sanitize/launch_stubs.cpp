@@ -7,6 +7,7 @@
 // the selection follow its forms by length.
 #include "../../paper_2604_06746_amd/csrc/score_schedule.h"
 
+#include <algorithm>
 #include <deque>
 
 namespace skv {
@@ -15,6 +16,7 @@ static int g_launches = 0;
 static int32_t g_last_plan[8];
 static int32_t g_last_selection[3];
 static int g_last_wide;
+static int g_last_copy[2];
 extern "C" int structkv_stub_launch_count(void) { return g_launches; }
 // RB, NW, KC, planes, stream_k, RC, grid_chunks, path of the latest scoring launch
 extern "C" void structkv_stub_last_plan(int32_t* out) { for (int i = 0; i < 8; ++i) out[i] = g_last_plan[i]; }
@@ -24,6 +26,19 @@ extern "C" int structkv_stub_last_wide(void) { return g_last_wide; }
 // of the latest fused layer step: the form its scoring prepared (-1: none), the form of its selection, whether that also
 // sums the scoring's planes
 extern "C" void structkv_stub_last_selection(int32_t* out) { for (int i = 0; i < 3; ++i) out[i] = g_last_selection[i]; }
+// of the latest layer step's selection: workgroups per sequence that copy the kept rows (0: the gather kernel does), and the most
+// 16-byte units that one of them moves
+extern "C" void structkv_stub_last_copy(int32_t* out) { for (int i = 0; i < 2; ++i) out[i] = g_last_copy[i]; }
+// the division of the copy's units by their (tensor, head) pairs: quotients that come out wrong, over all that a workgroup may see
+extern "C" int structkv_stub_copy_division_faults(int kv_heads, int tensors) {
+  alignas(16) static unsigned char rows[16];
+  CopyWork c;
+  if (!make_copy_work(rows, tensors == 2 ? rows : nullptr, 16, 16, rows, tensors == 2 ? rows : nullptr, 16, 16, kv_heads, 16, &c)) return -1;
+  int bad = c.planes != (uint32_t)(kv_heads * tensors);
+  for (uint32_t q = 0; q < (uint32_t)kCopyRows * c.planes; ++q)
+    bad += (c.recip ? (uint32_t)(((uint64_t)q * c.recip) >> 32) : q) != q / c.planes;
+  return bad;
+}
 static bool chunks_fit(const ScorePlan& p, const SeqTable& seq, int64_t total) {
   bool ok = seq.batch >= 1 && seq.batch <= kMaxBatch && seq.chunk_start[0] == 0 && seq.chunk_start[seq.batch] == p.grid_chunks;
   for (int b = 0; ok && b < seq.batch; ++b) {
@@ -227,6 +242,13 @@ hipError_t launch_topk_rest(const float*, const SeqTable& plan, int keep_tail, c
   g_last_selection[1] = ws.mode;
   g_last_selection[2] = ws.red != nullptr;
   bool ok = ws.hist && ws.mass > 0.f;
+  g_last_copy[0] = ws.copy ? ws.copy_parts : 0;
+  g_last_copy[1] = 0;
+  for (int b = 0; ws.copy && b < plan.batch; ++b) {   // what a workgroup has room for
+    const int64_t rows = ceil_div(plan.k[b] + keep_tail, ws.copy_parts), units = (rows * ws.copy->planes) << ws.copy->upr_shift;
+    ok = ok && ws.mode == kSelShort && ws.copy_parts >= 1 && rows <= kCopyRows;
+    g_last_copy[1] = std::max(g_last_copy[1], (int)units);
+  }
   for (int b = 0; ws.red && b < plan.batch; ++b)   // the selection sums the planes: at most two tokens a thread
     ok = ok && ws.mode == kSelShort && ws.red->planes <= kReduceShortPlanes && plan.cu[b + 1] - plan.cu[b] <= kReduceShortSeq && keep_tail >= 0;
   return ok ? hipSuccess : hipErrorInvalidValue;

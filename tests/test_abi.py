@@ -452,6 +452,42 @@ def test_selection_forms_of_a_layer_step(B):
         assert tuple(out) == want, lens
 
 
+def test_rows_copied_by_the_selection_or_by_the_gather_kernel(B):
+    """Which launch copies a layer step's rows, by how many workgroups per sequence, and the most units that one of them moves
+    (helpers.STEP_COPY, which the GPU tests run).  Stub build only."""
+    from helpers import STEP_COPY
+    lib = B._lib
+    if not hasattr(lib, "structkv_stub_last_copy"):
+        pytest.skip("the real library launches kernels; this runs against the stub build only")
+    i64 = ctypes.c_int64
+    fake, fake2, fake3 = (ctypes.c_void_p(1 << s) for s in (20, 21, 22))
+    for (Hq, G, d, dtype), lens, ks, tail, tensors, parts, units in STEP_COPY:
+        cu = (i64 * (len(lens) + 1))(*np.concatenate([[0], np.cumsum(lens)]).tolist())
+        shape = B.make_shape(Hq, G, d, 8, int(dtype == "bf16"), False)
+        need = B.structkv_layer_step_workspace_bytes(shape, len(lens), sum(lens))
+        rows = sum(ks) + tail * len(lens)
+        for misaligned in (0, 4):
+            dst = ctypes.c_void_p((1 << 21) + misaligned)
+            assert lib.structkv_layer_step(ctypes.byref(shape), fake, fake, fake, sum(lens) * d, d, len(lens), cu, (i64 * len(ks))(*ks), tail,
+                                           fake3, None, 0.9, 0.1, fake, None, fake, dst, dst if tensors == 2 else None, rows * d, d, fake2,
+                                           need, None) == B.STRUCTKV_OK, B.structkv_last_error()
+            out = (ctypes.c_int32 * 2)()
+            lib.structkv_stub_last_copy(out)
+            assert tuple(out) == ((0, 0) if misaligned else (parts, units)), (Hq, G, d, dtype, lens, ks, tail)
+
+
+def test_division_of_the_copied_units(B):
+    """Units by (tensor, head) pairs through a rounded reciprocal, every quotient of every row that a workgroup may hold.  Stub build only."""
+    lib = B._lib
+    if not hasattr(lib, "structkv_stub_copy_division_faults"):
+        pytest.skip("the real library launches kernels; this runs against the stub build only")
+    for G in (1, 2, 3, 5, 7, 8, 12, 31, 32, 96, 127, 255, 683, 1023, 1024):
+        for tensors in (1, 2):
+            assert lib.structkv_stub_copy_division_faults(G, tensors) == 0, (G, tensors)
+    assert lib.structkv_stub_copy_division_faults(2048, 1) == 0
+    assert lib.structkv_stub_copy_division_faults(2049, 1) == -1 and lib.structkv_stub_copy_division_faults(1025, 2) == -1   # (the gather kernel's)
+
+
 def test_longest_sequences_of_the_one_launch_scoring(B):
     """Keys of 256 bytes go through one scoring launch up to 1792 of them, where it still wins more for a caller that launches
     eagerly than it costs a captured replay; shorter keys up to 2048, fp32 up to 1024.  Stub build only."""

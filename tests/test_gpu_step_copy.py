@@ -3,42 +3,34 @@ bits, for shares of one row, none and many, K or V alone, strided and misaligned
 import pytest
 import torch
 
-pytestmark = pytest.mark.gpu
+from helpers import STEP_COPY
 
-SHORT = [
-    # lens, budgets, kept window
-    ((1000,), (100,), 8),
-    ((33, 1500, 64), (1, 700, 0), 8),            # fewer rows than workgroups, a window alone
-    ((2048,), (2040,), 8),                       # everything kept
-    ((8, 8, 8), (0, 0, 0), 8),                   # nothing but the window
-    ((4000, 5000), (800, 3), 32),
-    ((8192,), (6000,), 0),                       # many units a workgroup; no window
-    ((8192 + 32,) * 3, (7000, 10, 100), 32),     # too many rows for the selection: the gather kernel
-    (tuple(range(200, 200 + 12 * 37, 37)), tuple(range(3, 3 + 12 * 9, 9)), 8),   # more sequences than the small table holds
-]
+pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("form", ["both", "k", "v", "strided", "misaligned"])
-@pytest.mark.parametrize("lens,ks,tail", SHORT)
-def test_rows_copied_by_the_selection(lens, ks, tail, form):
+@pytest.mark.parametrize("shape,lens,ks,tail,tensors,parts,units", STEP_COPY)
+def test_rows_copied_by_the_selection(shape, lens, ks, tail, tensors, parts, units, form):
+    """(The host tests hold `parts` and `units`, of the form with that many tensors, to what the library decides.)"""
     from paper_2604_06746_amd import binding as B
     from paper_2604_06746_amd.sweep import LayerSweep
-    Hq, G, d, w = 8, 2, 64, 8
-    sw = LayerSweep(Hq, G, d, w, torch.bfloat16, lens, ks)
+    Hq, G, d, dtype = shape
+    dtype, w = (torch.bfloat16 if dtype == "bf16" else torch.float32), 8
+    sw = LayerSweep(Hq, G, d, w, dtype, lens, ks)
     g = torch.Generator(device="cuda")
     g.manual_seed(sum(lens) + tail)
-    q = torch.randn(len(lens), Hq, w, d, generator=g, device="cuda").to(torch.bfloat16)
-    k = torch.randn(G, sum(lens), d, generator=g, device="cuda").to(torch.bfloat16)
-    v = torch.randn(G, sum(lens), d, generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn(len(lens), Hq, w, d, generator=g, device="cuda").to(dtype)
+    k = torch.randn(G, sum(lens), d, generator=g, device="cuda").to(dtype)
+    v = torch.randn(G, sum(lens), d, generator=g, device="cuda").to(dtype)
     rows = [x + tail for x in ks]
     total = sum(rows)
 
     def dst():
         if form == "strided":
-            return torch.full((G, 2 * total + 3, 2 * d), -7.0, device="cuda", dtype=torch.bfloat16)[:, :total, :d]
+            return torch.full((G, 2 * total + 3, 2 * d), -7.0, device="cuda", dtype=dtype)[:, :total, :d]
         if form == "misaligned":
-            return torch.full((G * total * d + 2,), -7.0, device="cuda", dtype=torch.bfloat16)[2:].view(G, total, d)
-        return torch.full((G, total, d), -7.0, device="cuda", dtype=torch.bfloat16)
+            return torch.full((G * total * d + 2,), -7.0, device="cuda", dtype=dtype)[2:].view(G, total, d)
+        return torch.full((G, total, d), -7.0, device="cuda", dtype=dtype)
     want_k, want_v, got_k, got_v = (dst() for _ in range(4))
     cen = torch.rand(sum(lens), generator=g, device="cuda")
     cen2 = cen.clone()
