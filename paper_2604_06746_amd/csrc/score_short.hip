@@ -149,7 +149,7 @@ struct ThirdsOfRows {
 #undef SKV_MUL
     large += small;
     const float none = (large[0] - large[0]) + (large[1] - large[1]) + ((large[2] - large[2]) + (large[3] - large[3]));
-    if (__ballot(none != 0.f) != 0ull) {   // (uniform)
+    if (__builtin_expect(__ballot(none != 0.f) != 0ull, 0)) {   // (uniform)
       F::mul(acc, k, operand(row));
     } else {
       acc = large;
@@ -283,7 +283,14 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
     return causal ? n - w + row - w * (int)__umulhi((uint32_t)row, w_recip) + 1 : n;
   };
   float M[NRB], Z[NRB], E[NRB];
-  auto wave_maxima = [&]() __attribute__((always_inline)) {
+  auto row_maximum = [&](int rb) __attribute__((always_inline)) {
+    float m = sM[lg][rb * 16 + l16];   // (each row of lanes reads a quarter of the waves': the reads were what the phase took)
+#pragma unroll
+    for (int v = 4; v < kWaves; v += 4) m = fmaxf(m, sM[v + lg][rb * 16 + l16]);
+    return over_groups(m, [](float x, float y) { return fmaxf(x, y); }) * c2;
+  };
+#pragma unroll
+  for (int round = 0; round < (CUT ? 2 : 1); ++round) {
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
       const int lim = seen((rc * NRB + rb) * 16 + l16);
@@ -302,21 +309,10 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
       m = over_groups(m, [](float x, float y) { return fmaxf(x, y); });
       if (lg == 0) sM[wave][rb * 16 + l16] = m;
     }
-  };
-  auto row_maxima = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-      float m = sM[lg][rb * 16 + l16];   // (each row of lanes reads a quarter of the waves': the reads were what the phase took)
-#pragma unroll
-      for (int v = 4; v < kWaves; v += 4) m = fmaxf(m, sM[v + lg][rb * 16 + l16]);
-      M[rb] = over_groups(m, [](float x, float y) { return fmaxf(x, y); }) * c2;
-    }
-  };
-  wave_maxima();
-  __syncthreads();
-  row_maxima();
-  if constexpr (CUT)
-    if (__builtin_amdgcn_readfirstlane(again) != 0) {   // (the same for all waves)
+    __syncthreads();
+    if constexpr (CUT) {
+      M[0] = row_maximum(0);
+      if (round > 0 || __builtin_expect(__builtin_amdgcn_readfirstlane(again) == 0, 1)) break;   // (the same for all waves)
       const F qr = ThirdsOfRows::operand(q_row());
 #pragma unroll
       for (int i = 0; i < TW; ++i) {
@@ -325,12 +321,11 @@ __global__ __launch_bounds__(64 * kWaves) void score_short_kernel(
           F::mul(acc[0][i], ThirdsOfRows::operand(kg + (int64_t)min(tile0(i) + l16, n - 1) * kst + F::PIECES * lg * 4), qr);
       }
       __syncthreads();   // (the maxima have been read)
-      wave_maxima();
-      __syncthreads();
-      row_maxima();
     }
+  }
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) {
+    if constexpr (!CUT) M[rb] = row_maximum(rb);
     float z = 0.f, e = 0.f;
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
