@@ -746,7 +746,11 @@ __device__ __forceinline__ uint16_t* sub_sums(const TopkWs& ws, uint32_t workgro
 // 512 threads end sooner than 256 (layer steps of 32K tokens 48.3 -> 47.2 us, a truncation at 128K 96.2 -> 95.0; 1024 are no better).  Not
 // where there are more than 256 workgroups (554K tokens in eight sequences 478 -> 483 us), nor in the second half of a layer step by itself,
 // which runs beside other layers' scoring and gets on the chip the sooner the smaller its workgroups are (32 layers of
-// 128K tokens on four streams 5.20 ms with 256, 5.22 with 512, 5.29 with 1024).
+// 128K tokens on four streams 5.20 ms with 256, 5.22 with 512, 5.29 with 1024).  What else runs beside other work -- a selection on a side
+// stream, whole steps on streams of their own -- does not say so: with 512 threads place has 84 registers (136 with the scores of four shares in flight a wave, as with
+// 256, not of one), so that its two waves per SIMD fit where ONE workgroup of scoring has left, as the one of 256 threads does
+// (four streams of 64K-token steps, window 64, us a step in a graph: 256 threads 88.5, 512 of 136 registers 90.0, of 84 88.1; alone 72.9, 72.1,
+// 71.9 at a window of 8).
 template <int NT, class TAB>
 __global__ __launch_bounds__(NT) void topk_compact_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
                                                                 TopkWs ws) {
@@ -844,7 +848,8 @@ template <int NT, class TAB>
 __global__ __launch_bounds__(NT) void topk_place_kernel(const float* __restrict__ scores, TAB seq, int keep_tail, TopkWs ws,
                                                               int32_t* __restrict__ idx_out) {
   short_kernel_priority();
-  constexpr int kMidPer = kMidShare / NT, CPT = 4;   // candidates a thread keeps in registers; the first is requested before their number is known
+  // candidates a thread keeps in registers; the first is requested before their number is known
+  constexpr int kMidPer = kMidShare / NT, CPT = 1024 / NT;
   constexpr int kPicked = CPT * NT;   // most keys of a sub-bin that are copied together
   __shared__ ResolveLds l;
   __shared__ uint32_t tot[NT / 64], cnt[2], npick, nhold, ends[2][NT / 64];
@@ -927,7 +932,7 @@ __global__ __launch_bounds__(NT) void topk_place_kernel(const float* __restrict_
       const uint32_t nh = nhold;
       // f(key, workgroup), a wave to the scores of kAtOnce workgroups
       auto visit = [&](auto f) {
-        constexpr uint32_t kAtOnce = 4;
+        constexpr uint32_t kAtOnce = NT == 256 ? 4 : 1;
         constexpr int PER = kMidShare / 64;
         for (uint32_t i0 = wv * kAtOnce; i0 < nh; i0 += kAtOnce * (NT / 64)) {
           float y[kAtOnce][PER];
