@@ -181,9 +181,12 @@ structkv_status structkv_gather_kv(const void* k_src, const void* v_src, int64_t
  *                                      on several streams applies the recurrence itself, in layer order)
  *   structkv_select_topk(indeg_out, k_per_seq, keep_tail) -> idx_out
  *   structkv_gather_kv(k, v, idx_out) -> k_dst, v_dst   (rows_b = k_b + keep_tail; either dst may be NULL)
- * with the results of those four calls bit for bit, in eight kernel launches instead of eleven: the kernel
- * that forms the in-degree also applies the recurrence, histograms the first radix digit of the selection and
- * writes the kept window's indices (the scoring kernel before it has cleared the histograms).
+ * with the results of those four calls bit for bit, in fewer kernel launches.  By the longest searched prefix
+ * (n_b - keep_tail): up to 8192 scores the selection is one launch, which mostly copies the rows too and up to 2048
+ * tokens also forms the in-degree and applies the recurrence: two launches in all where the scoring is one, five at
+ * 8192.  Beyond, the kernel that forms the in-degree applies the recurrence, fills the
+ * selection's histogram and writes the kept window's indices: six launches up to 16384 scores (seven in large
+ * batches), seven up to 262144, eight after that.
  * v shares k's strides (kv_stride_head, kv_stride_tok) and element type; k_dst / v_dst share
  * dst_stride_head / dst_stride_tok.  Other arguments as in the four calls.
  * workspace: structkv_layer_step_workspace_bytes(shape, batch, total_tokens) bytes (scoring and selection
@@ -201,9 +204,9 @@ structkv_status structkv_layer_step(const structkv_shape* shape, const void* q_w
 /*
  * structkv_layer_step in two halves, for callers that run the layers of a prefill on several streams and must
  * apply the centrality recurrence (paper Eq. 3 / Alg. 1 line 6) in layer order BETWEEN the halves:
- *   structkv_layer_begin  : the scoring (Eq. 1, 2, 4) -> indeg_out, entropies; the first radix digit of the
- *                           selection and the kept window's indices; with centrality != NULL also the
- *                           recurrence (then this is the first four kernels of structkv_layer_step)
+ *   structkv_layer_begin  : the scoring (Eq. 1, 2, 4) -> indeg_out, entropies; beyond 8192 searched scores the
+ *                           selection's histogram and the kept window's indices; with centrality != NULL also
+ *                           the recurrence
  *   (the caller: wait for the previous layer's update, structkv_accumulate_centrality, signal)
  *   structkv_layer_finish : the rest of the selection (Eq. 13) -> idx_out, and the selected rows -> k_dst, v_dst
  * Both take the same arguments as structkv_layer_step (finish only those it uses), on the same stream, with the

@@ -218,19 +218,18 @@ void short_carve(const structkv_shape& s, int batch, int64_t total, ScorePlan* p
 // Short sequences in one scoring launch (score_short.hip) where that is one round of workgroups, at most one per CU, whose
 // registers hold the logits of 2048 (bf16) or 1024 (fp32) keys.  A workgroup reads all keys of its sequence, so the work per
 // CU grows with the length, and beyond 1024 keys more than 32 planes make the sum over them the longer part.
-// A layer step of 32 heads on 8, head_dim 128, us a call (in a graph, where launches are cheap), two passes -> one launch:
-//   window 8:  512 keys 23.9 -> 18.6 (17.1 -> 13.9), 1024 keys 23.1 -> 18.7 (17.6 -> 16.5), 1280 keys 25.0 -> 19.6 (18.2 -> 18.5),
-//              1536 keys 23.3 -> 20.5 (18.7 -> 19.8), 1792 keys 25.1 -> 21.6 (18.8 -> 20.7), 2048 keys 24.0 -> 23.0 (19.3 -> 21.9);
-//              four sequences of 1536 keys 24.7 -> 22.4 (21.2 -> 21.2), of 2048 keys 24.7 -> 24.6 (22.4 -> 23.6)
-//   window 32: 512 keys 24.1 -> 18.0 (19.1 -> 15.8), 1024 keys 24.9 -> 19.9 (19.6 -> 18.7)
-//   window 64: 1024 keys 24.9 -> 22.6 (23.1 -> 21.8); four sequences of 1024 keys 30.5 -> 25.0 (27.9 -> 23.9)
-// (Before the kernel's sums and query loads became cheaper: one launch now takes 11.5 us in a graph at 512 keys and a window of 8, 13.5 at 1024.)
-// So beyond 1280 keys of 256 bytes fewer launches win for a caller that launches each time and lose in a captured graph; the
-// line is where what they lose outweighs what they win, after 1792 keys.  Keys of 128 bytes, 8 heads on 2:
-//   window 8:  1024 keys 24.4 -> 18.4 (16.7 -> 14.2), 1536 keys 24.6 -> 18.5 (17.1 -> 15.8), 2048 keys 24.4 -> 18.7 (17.8 -> 17.3)
-//   window 64: 1024 keys 25.0 -> 18.4 (20.1 -> 15.7), 1536 keys 24.5 -> 19.4 (20.7 -> 18.5), 2048 keys 24.5 -> 21.2 (21.1 -> 20.2)
-//   fp32, 8 heads on 8, window 32: 512 keys 24.9 -> 18.8 (21.8 -> 15.4), 1024 keys 24.7 -> 20.2 (22.2 -> 19.4)
-// fp32 keys of 512 bytes, 8 heads on 2: window 8, 1024 keys 29.1 -> 27.3 (27.0 -> 26.3); window 64 30.6 -> 30.1 (28.2 -> 29.1)
+// A layer step of 32 heads on 8, head_dim 128, a tenth kept, us a call (in a graph, where launches are cheap), two passes -> one launch:
+//   window 8:  512 keys 20.6 -> 14.3 (15.9 -> 11.2), 1024 keys 20.8 -> 14.2 (16.5 -> 13.2), 1280 keys 20.5 -> 15.5 (16.5 -> 15.0),
+//              1536 keys 20.4 -> 16.6 (16.7 -> 15.9), 1792 keys 20.8 -> 17.7 (17.0 -> 17.0), 2048 keys 20.9 -> 18.4 (17.0 -> 17.6);
+//              four sequences of 1536 keys 21.7 -> 17.3 (18.4 -> 17.0), of 2048 keys 21.5 -> 19.3 (19.6 -> 19.0)
+//   window 32: 512 keys 20.8 -> 14.1 (17.4 -> 13.7), 1024 keys 21.0 -> 15.8 (17.9 -> 15.9)
+//   window 64: 1024 keys 22.5 -> 18.0 (20.9 -> 18.0); four sequences of 1024 keys 26.2 -> 19.0 (24.8 -> 19.0)
+// So keys of 256 bytes go through one launch as far as a captured graph does not lose by it, up to 1792 of them.  Keys of 128
+// bytes, 8 heads on 2:
+//   window 8:  1024 keys 20.7 -> 14.1 (15.5 -> 12.3), 1536 keys 20.4 -> 14.3 (15.7 -> 13.8), 2048 keys 20.4 -> 15.6 (16.3 -> 15.2)
+//   window 64: 1024 keys 20.8 -> 14.1 (18.2 -> 13.7), 1536 keys 20.6 -> 16.6 (18.4 -> 16.0), 2048 keys 20.5 -> 17.9 (18.7 -> 17.4)
+//   fp32, 8 heads on 8, window 32: 512 keys 21.8 -> 14.1 (20.5 -> 13.2), 1024 keys 22.2 -> 16.8 (20.8 -> 16.5)
+// fp32 keys of 512 bytes, 8 heads on 2: window 8, 1024 keys 27.3 -> 24.8 (25.8 -> 24.8); window 64 28.4 -> 27.0 (26.8 -> 27.2)
 int64_t short_keys(const structkv_shape& s) {
   if (s.dtype != STRUCTKV_DTYPE_BF16) return 1024;
   return s.head_dim == 128 ? 1792 : 2048;
@@ -772,9 +771,13 @@ structkv_status plan_layer_step(const structkv_shape* shape, const void* k, cons
 }
 
 // Workgroups per sequence where the selection's last launch also copies the kept rows; 0: the gather kernel does.
-// Short form: a unit a thread where 256 workgroups suffice for that, and up to eight; beyond them the gather kernel's many light
-// workgroups are as fast (layer steps of 32 heads on 8, window 32, us in a graph, gather launch / here: 4 x 1000 tokens, 60 % kept, 4
-// units a thread, 23.6 / 21.3; 32 x 1500, 5 %, 5 units, 68.5 / 62.1; 4 x 8000, 5 %, 7 units, 49.8 / 48.8).
+// Short form: a unit a thread where 256 workgroups suffice for that, and up to eight, beyond which rows are most of what a step moves
+// and the gather kernel's many light workgroups were expected to be as fast.  Layer steps of 32 heads on 8 (256 units a row), window 32, us in
+// a graph, gather launch / here, by units a thread:
+//   4 sequences of 8000 tokens   1.6: 48.1 / 46.7   3.9: 52.2 / 50.5   7.8: 58.6 / 58.5   (11.7: 66.4 / 65.2)
+//   16 of 4000                   1.6: 70.1 / 67.1   4.7: 75.2 / 72.3   8.0: 80.5 / 77.9   (12.8: 87.9 / 85.1)
+//   32 of 1500                   1.6: 63.5 / 58.8   4.7: 68.9 / 63.6   8.0: 74.8 / 69.3   (12.5: 83.6 / 76.4)
+// In brackets the other side of the limit, which could lie further out.  Nothing is lost beside other layers either, see topk_short_kernel.
 int copy_parts(const SeqTable& sel, const CopyWork& c, int mode, int keep_tail) {
   int64_t most = 0;
   for (int b = 0; b < sel.batch; ++b) most = std::max(most, (int64_t)sel.k[b] + keep_tail);

@@ -147,17 +147,17 @@ __device__ inline uint32_t score_key(float f) {
 #endif
 
 // How one selection call runs, by its longest searched prefix (n_b - keep_tail):
-//   short  up to kShortSeq scores: one workgroup per sequence does everything in one launch.  At 8192 scores 7.8 us
-//          against 15.3 us for the mid form's four launches (in a layer step, where two of those fall away, about
-//          even); at 16384 one workgroup needs 13.2 us.
+//   short  up to kShortSeq scores: one workgroup per sequence does everything in one launch (in a layer step several, which
+//          select for themselves and copy a share of the kept rows each).  At 8192 scores 7.9 us against 12.5 us for the mid
+//          form's three launches (in a layer step two of those fall away); at 16384 one workgroup needs 13.2 us.
 //   mid    up to kMidSeq: a histogram whose fine bins lie around the scores that matter, so that the k-th largest's bin
 //          holds few scores (the candidates) or, where the scores crowd together, few different ones; one launch lists
-//          or counts them, one resolves them and places the indices.  131072 scores: 17.7 us spread over octaves, 19.4
-//          within 0.3 % of each other, 20.0 all equal (the long form 22.6, 24.7 and 24.7); in a layer step two launches
-//          after the reduce kernel, 12.5 us against 20.6 for the long form's three.
+//          or counts them, one resolves them and places the indices (one does both for shorter sequences, see kDirectSeq).
+//          131072 scores: 14.9 us spread over octaves, 18.7 all equal (the long form 23.1 and 23.9); in a layer step two
+//          launches after the reduce kernel.
 //   long   beyond: three radix digits (11/11/10 bits), one launch each, then the placement.  Every workgroup of the mid
 //          form reads all candidates of its sequence and all counts before it, a thread each: 256 workgroups at most.
-//          At the limit 20.7 us (mid; all equal 23.3) and 25.9 us (long; 29.2).
+//          At the limit 16.4 us (mid; all equal 21.5) and 26.5 us (long; 28.6).
 enum { kSelShort = 0, kSelMid = 1, kSelLong = 2 };
 constexpr int kShortSeq = 8192;
 constexpr int kMidSeq = 262144;

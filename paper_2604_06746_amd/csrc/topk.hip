@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kThreads) void topk_write_kernel(const float* __res
 
 constexpr int kWide = 1024;        // threads of a short-form workgroup
 static_assert(kReduceShortSeq <= 2 * kWide, "a workgroup that forms the scores holds two per thread");
-constexpr int kMidShare = 1024;    // scores of a mid-form workgroup: four per thread
+constexpr int kMidShare = 1024;    // scores of a mid-form workgroup
 
 constexpr int kListed = 64;        // keys that one wave ranks directly
 
@@ -531,14 +531,15 @@ __device__ inline void place_ordered(const uint32_t (&key)[PER], int j0, int m, 
   }
 }
 
-// short form: one workgroup per sequence of at most PER x 1024 scores; also writes the kept window.
+// short form: a workgroup has all of a sequence of at most PER x 1024 scores; also writes the kept window.
 // SUM (a layer step): it first does what the reduce kernel does -- the column-sum planes of its sequence's tokens (at most
 // PER x 1024 with the window) added up in ascending order, the centrality update, the entropies' means -- and selects on the
 // scores it holds: one launch fewer (a layer step of 1K tokens is a handful of 3 us kernels: see short_plan in api.cpp).
 // COPY (a layer step): `parts` workgroups per sequence, which all select for themselves and then copy a share each of the kept
 // rows, instead of a gather launch that reads the indices again (one
-// launch fewer for the host as well).  A layer step, 32 heads on 8, head_dim 128, window 8, us a call eager (in a graph), a fifth kept:
-// 512 tokens 19.5 -> 17.0 (13.6 -> 13.0), 2048 25.2 -> 21.9 (18.6 -> 18.0), 8192 29.7 -> 29.1 (27.3 -> 27.6).
+// launch fewer for the host as well).  A layer step, 32 heads on 8, head_dim 128, window 8, a fifth kept, us a call eager (in a graph) with
+// the gather launch -> here: 512 tokens 17.0 -> 14.1 (11.9 -> 11.2), 2048 19.7 -> 18.6 (18.7 -> 18.0), 8192 29.0 -> 28.5 (26.8 -> 25.9);
+// thirteen layers on four streams, a layer in a graph: 1000 tokens 21.7 -> 18.2, 8192 29.0 -> 25.4.
 template <int PER, class TAB, bool SUM, bool COPY>
 __global__ __launch_bounds__(kWide) void topk_short_kernel(const float* __restrict__ scores, TAB seq, int keep_tail,
                                                            int32_t* __restrict__ idx_out, ReduceWork red, CopyWork copy, int parts) {
